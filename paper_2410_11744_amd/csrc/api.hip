@@ -124,6 +124,7 @@ dyspec_status dyspec_init(void)
 {
     void* scratch_address = nullptr;
     if (prepare_tree_attn() != hipSuccess || prepare_build_tree() != hipSuccess || prepare_build_threshold() != hipSuccess || prepare_verify() != hipSuccess ||
+        prepare_reorder() != hipSuccess ||
         static_scratch_address(&scratch_address) != hipSuccess)
         return DYSPEC_HIP_ERROR;
     return DYSPEC_OK;

@@ -95,6 +95,7 @@ hipError_t prepare_tree_attn();
 hipError_t prepare_build_tree();
 hipError_t prepare_build_threshold();
 hipError_t prepare_verify();
+hipError_t prepare_reorder();
 
 enum : uint32_t { KIND_PATH = 0, KIND_BUILD = 1, KIND_ACCEPT = 2, KIND_RESID = 3 };
 
