@@ -1,60 +1,70 @@
 // Greedy fixed-budget token-tree construction (Algorithm 1, Section 4.2, Appendix A.1)
 // and the ancestor bitmask of tree attention (Section 2) for gfx950.
 //
-// One 512-thread workgroup builds one sequence's tree without leaving the GPU.  The
-// paper keeps the expandable slots in a heap on the host; here the frontier (at most two
-// new slots per node) lives in LDS or in registers and the pop is a workgroup arg-max, which
-// costs less than a heap's pointer chasing at these sizes.  A draw needs the parent's residual draft
-// distribution: fp64 softmax weights summed four tokens at a time, a workgroup sum and scan
-// of those sums for the inverse CDF.  fp64 keeps every discrete decision (which slot, which
-// token) equal to an fp64 evaluation of the algorithm except at relative margins near 1e-13.
+// One workgroup builds one sequence's tree without leaving the GPU.  The paper keeps the
+// expandable slots in a heap on the host; here the frontier lives in registers or LDS and the pop
+// is an arg-max, which costs less than a heap's pointer chasing at these sizes.  A draw needs the
+// parent's residual draft distribution: fp64 softmax weights and an inverse CDF over them.
+// fp64 keeps every discrete decision (which slot, which token) equal to an fp64 evaluation of the
+// algorithm except at relative margins near 1e-13.
 //
-// With a workspace the O(vocabulary) part leaves the serial loop: draft_row_sums_kernel (one
-// workgroup per row, all rows at once) stores every row's maximum and the totals of its kMaxSeg
-// segments, and the builder (build_tree_cached_kernel) keeps the totals current in LDS and a bit
-// per drawn token in the workspace.  A draw picks the segment from the totals, makes one trip to
-// global memory (each thread fetches its four logits and its drawn-already bits of the picked
-// segment and recomputes their four weights, a 16th of a row pass) and passes two barriers.  Without a
-// workspace the builder (build_tree_kernel) recomputes the sums of the parent's row for every
-// draw; both ways take the same decisions and build the same tree.
+// With a workspace (build_tree_waves_kernel) the draws leave the pop's way.  The draws of a node
+// depend on its row, its path key and the child's rank only, not on when the node is popped, so
+// they are made ahead by other waves of the workgroup; draft_row_sums_kernel (one workgroup per row, all
+// rows at once) has stored every row's maximum and group totals before.  Without a workspace the builder (build_tree_kernel)
+// recomputes the sums of the parent's row for every draw; both ways take the same decisions
+// and build the same tree.
+#include <cstddef>
+
 #include "draft_row.h"
 #include "lane_ops.h"
+#include "wave_draw.h"
 
 namespace dyspec {
 
 constexpr int kMaxSlots = 2 * DYSPEC_MAX_BUILD_NODES + 2;
 
-// Workspace of the cached form, per row (doubles): kMaxSeg segment totals, the row maximum
-// (already divided by the temperature), and one bit per token: drawn at this position already
-// (its weight is no longer in the totals).
-constexpr int kGoneWords = DYSPEC_MAX_VOCAB / 32;
-constexpr int kRowSumDoubles = kMaxSeg + 8 + kGoneWords / 2;
+// Workspace, per row (kRowSumDoubles doubles): the totals of kSums runs of kRun tokens, the row maximum
+// (already divided by the temperature), and from kDrawnOffset on the tokens drawn at this position, two
+// bytes each in the order of the draws (their weights are no longer in the totals).
+constexpr int kRun = 128;
+constexpr int kSums = DYSPEC_MAX_VOCAB / kRun;
+constexpr int kRowSumDoubles = kMaxSeg + 8 + DYSPEC_MAX_VOCAB / 64;
+constexpr int kDrawnOffset = kSums + 2;
+static_assert((kRowSumDoubles - kDrawnOffset) * 4 >= DYSPEC_MAX_BUILD_NODES, "room for every draw a row can see");
 __host__ __device__ inline double* ws_totals(double* ws, int row) { return ws + (size_t)row * kRowSumDoubles; }
-__host__ __device__ inline double* ws_rowmax(double* ws, int row) { return ws_totals(ws, row) + kMaxSeg; }
-__host__ __device__ inline uint32_t* ws_gone(double* ws, int row) { return reinterpret_cast<uint32_t*>(ws_totals(ws, row) + kMaxSeg + 8); }
+__host__ __device__ inline double* ws_rowmax(double* ws, int row) { return ws_totals(ws, row) + kSums; }
+__host__ __device__ inline unsigned short* ws_drawn(double* ws, int row) { return reinterpret_cast<unsigned short*>(ws_totals(ws, row) + kDrawnOffset); }
 
 // Data-parallel part (the draft softmax of every node, Algorithm 1's model call output):
-// one workgroup per row writes the row's segment totals and maximum and clears its drawn bits.
+// one workgroup per row writes the row's totals and maximum.
 template <bool VEC>
 __global__ __launch_bounds__(kBlock) void draft_row_sums_kernel(const float* __restrict__ draft_logits, int V, SeqArgs sa,
                                                                 double* __restrict__ ws)
 {
     __shared__ float fred[kWaves];
-    __shared__ double red[kWaves * kMaxSeg];
     const int row = blockIdx.x;
     const int seq = find_seq(sa, row);
     const double inv_temp = 1.0 / (double)sa.temp_d[seq];
     double m, seg[kMaxSeg];
     row_segment_sums<VEC>(draft_logits + (size_t)row * V, V, inv_temp, 0ull, fred, &m, seg);
-    block_sum<double, kMaxSeg>(seg, red);
-    if (threadIdx.x < kMaxSeg) {
-        double t = 0.0;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    // half a wave holds a run of a segment: its sum ends up in all lanes of the half's second row of 16,
+    // of which lane j keeps segment j's
+    static_assert(4 * kWave == 2 * kRun && kMaxSeg == 16, "two runs per wave and segment, a lane per segment");
+    double mine = 0.0;
 #pragma unroll
-        for (int j = 0; j < kMaxSeg; ++j) if (j == (int)threadIdx.x) t = seg[j];
-        ws_totals(ws, row)[threadIdx.x] = t;
+    for (int j = 0; j < kMaxSeg; ++j) {
+        double t = seg[j];
+        t += dpp_or_zero<kDppXor1>(t);
+        t += dpp_or_zero<kDppXor2>(t);
+        t += dpp_or_zero<kDppHalfMirror>(t);
+        t += dpp_or_zero<kDppMirror>(t);
+        t += dpp_or_zero<kDppBcast15, 0xa>(t);
+        if ((lane & 15) == j) mine = t;
     }
+    if (lane & 16) ws_totals(ws, row)[(lane & 15) * (kSeg / kRun) + 2 * wave + (lane >> 5)] = mine;
     if (threadIdx.x == 0) *ws_rowmax(ws, row) = m;
-    for (int w = threadIdx.x; w < kGoneWords; w += kBlock) ws_gone(ws, row)[w] = 0u;
 }
 
 // LDS state of the form without a workspace.
@@ -209,312 +219,534 @@ __global__ __launch_bounds__(kBlock) void build_tree_kernel(
     if (tid == 0) n_built[seq] = n;
 }
 
-// The form with a workspace.  State of a row in LDS: its kMaxSeg segment totals and its maximum,
-// kRowState doubles that follow each other in the workspace as well (the workspace's copy of the
-// totals is not kept current).
+// The form with a workspace: waves with roles.
 //
-// The open slots live in registers: slot s belongs to thread s % kBlock, which keeps its value,
-// its (parent, rank) and the uniform draw of its sampling.  Every thread knows the slot being
-// drawn from, its parent p, the rank of the child to draw and the draw u.
+// Wave 0 (control) pops.  Every node has one open slot, its next draw; lane l of control keeps the best
+// slot of the nodes l, l + 64, ... in registers (the slots themselves lie in LDS), so the pop is a maximum over
+// the wave.  It takes the popped node's next draw (token, R[y], the new node's path key and first uniform) from
+// LDS, opens the new node's slot and the parent's next one.
+// Wave 1 draws from the root's row, which it keeps in LDS (wave_draw.h), up to kRing draws
+// ahead: the root is popped most often in wide trees.
+// kDrawWaves waves draw for the other nodes (node i: wave i % kDrawWaves of them), one draw ahead per node,
+// the node of the largest slot value first: totals from the workspace (a new node's were fetched before it
+// was made: its row is known), a wave scan, the picked run's 128 logits, two per lane, a wave scan.
 //
-// A draw takes two barriers.  Lanes read p's segment totals from LDS (one each) and pick the
-// segment with a 16-lane scan; every thread fetches, in one trip to global memory, its four
-// logits of that segment and the word with their drawn-already bits.  While those loads
-// are in flight each wave finds the best of its other open slots (DPP maximum and a ballot).
-// Every thread computes its four weights (drawn tokens: 0) and their sum, in the order the
-// pre-pass summed them; the sums are scanned (barrier 1).  The waves' totals tell every thread
-// which wave holds the crossing; that wave finds the thread (the owner) with a ballot, takes the
-// owner's four weights, finishes the draw (token, weight), has
-// the owner store its bits and writes the segment's new total.  Meanwhile three
-// other waves compute the path key of the new node and the draws of the two slots the draw
-// opens (functions of p and rank only) and reduce the waves' bests to the best open slot outside
-// this draw (barrier 2).  Every thread then computes the values of the two new slots, keeps them
-// if they are its own, and picks the next slot among those two and the best of the rest; single
-// lanes of different waves write the node down.
-constexpr int kRowState = kMaxSeg + 1;
-struct CachedShared {
-    int last_child[DYSPEC_MAX_BUILD_NODES];
-    int depth[DYSPEC_MAX_BUILD_NODES];
-    uint2 pk[DYSPEC_MAX_BUILD_NODES];         // path keys of the nodes
-    double wave_tot[kWaves];            // per draw: the waves' sums of the picked segment
-    int last_live[kWaves];              // last thread of each wave with weight left, -1: none
-    uint2 next_key;                     // path key of the node this draw makes
-    float next_u[2];                    // draws of the two slots it opens
-    double best_v[kWaves];              // per wave: its best open slot outside the current draw,
-    int best_i[kWaves];                 //   the slot's index,
-    int best_pr[kWaves];                //   its parent | rank << 10
-    float best_u[kWaves];               //   and its draw
-    double rest_v;                      // the best of those
-    int rest_i, rest_pr;
-    float rest_u;
-    double draw_wy;                     // the drawn token and its weight
-    int draw_y;
-};
-// LDS a workgroup may use on gfx950, less a margin; what CachedShared leaves of it holds the row states
-constexpr size_t kLdsPerWorkgroup = 160 * 1024 - 1024;
-static_assert(sizeof(CachedShared) + (size_t)DYSPEC_MAX_BUILD_NODES * kRowState * sizeof(double) <= kLdsPerWorkgroup,
-              "the row states of the largest tree fit in LDS");
-// A tree of N rows opens at most 2N - 1 slots (the root's, then two per draw): SLOTS of them per thread,
-// 1 for N <= 256, 2 for N <= 512, 4 beyond.
-constexpr int slots_per_thread(int n) { return n <= kBlock / 2 ? 1 : n <= kBlock ? 2 : 4; }
-static_assert(4 * kBlock >= 2 * DYSPEC_MAX_BUILD_NODES - 1, "four slots per thread hold the largest tree's");
-static_assert(DYSPEC_MAX_BUILD_NODES <= 1024 && DYSPEC_MAX_VOCAB <= (1 << 21), "a slot's parent and rank share one word");
+// LDS words, one writer at a time.  A node's word is, with the top bit clear, a request of control for
+// draw `rank` (low bits: the upper bits of the slot value, the order in which requests are
+// served), and with the top bit set the answer (the token; the rest of the draw lies beside it) or nothing at
+// all.  Control writes it only while the bit is set, the node's wave only while it is clear.  The root's
+// draws go through a ring; `news` tells the draw waves which requests the last pop made.  LDS operations
+// of a wave take effect in their order, so data written before a word are there for whoever has read the word.
+//
+// Every wait ends: control waits only for a requested draw, which the node's wave makes in finitely
+// many steps whatever else happens (an empty row is an answer as well); the drawing waves leave when
+// control has set `news` to kStop, which it does after at most N - 1 pops.  (Were an answer to stay out all the
+// same, control gives up after kMaxPolls looks and the tree ends there.)
+//
+// What bounds it: the number of instructions of control's pop and of wave 1's draw (a wave alone issues one in
+// eight cycles, whatever it is; an LDS read is back after 52), and for trees that open one chain of nodes the trip to
+// memory of a fresh node's first draw.  Measured against a workgroup that popped and drew in turn, two barriers a
+// draw: 512 rows of 32000 tokens 1338 -> 520 us, 128 rows 328 -> 112, 32 rows of 1000 tokens 79 -> 30; a
+// single chain of 512 nodes 1413 -> 1094 with the pass over the rows.
+constexpr int kBuildThreads = 1024;
+constexpr int kDrawWaves = 8;
+constexpr int kRing = 16;
+constexpr int kMaxPolls = 1 << 24;          // of a whole build, about a second: no build comes near, none can outlast it
+constexpr uint32_t kAnswer = 0x80000000u;
+constexpr uint32_t kStop = 0u;              // news of a pop is never 0: the new node's index is not
+static_assert(DYSPEC_MAX_BUILD_NODES <= 1024 && DYSPEC_MAX_VOCAB <= (1 << 15), "parent, rank and previous sibling share a word, rank and token too");
+static_assert((kDrawWaves & (kDrawWaves - 1)) == 0, "a node's wave by a mask");
 
-template <bool VEC, int SLOTS>
-__global__ __launch_bounds__(kBlock) void build_tree_cached_kernel(
-    const float* __restrict__ draft_logits, int V, SeqArgs sa, uint64_t seed,
-    dyspec_tree tree, float* __restrict__ est_value, uint64_t* __restrict__ anc_mask,
-    int mask_words, int* __restrict__ n_built, double* ws)
+// What LDS holds of a node.
+struct Node {
+    double r;               // its next draw, made ahead: R[y] (< 0: the row is empty),
+    unsigned long long child_key;   // path key of the node the draw makes
+    double value;           // open slot (<= 0: none)
+    unsigned long long key; // path key
+    float u;                // uniform of the next draw
+    uint32_t word;          // request or answer: kAnswer | rank << 15 | token
+    float child_u;          // uniform of the first draw of the node the draw makes
+    uint32_t opened;        // order in which the open slot was opened (2 i + 1: first child, 2 i: next sampling of the parent of node i)
+};
+constexpr uint32_t kNode = sizeof(Node), kChildKeyAt = 8, kValueAt = 16, kKeyAt = 24, kUAt = 32, kWordAt = 36, kChildUAt = 40, kOpenedAt = 44;
+static_assert(kNode == 48 && offsetof(Node, child_key) == kChildKeyAt && offsetof(Node, value) == kValueAt && offsetof(Node, key) == kKeyAt &&
+              offsetof(Node, u) == kUAt && offsetof(Node, word) == kWordAt && offsetof(Node, child_u) == kChildUAt && offsetof(Node, opened) == kOpenedAt, "");
+// Dynamic LDS of the builder: byte offsets.
+struct BuildLds {
+    static constexpr uint32_t ring = 0;                                            // the root's draws: draw r at r % kRing (r, child's, word)
+    static constexpr uint32_t root_taken = ring + kRing * kNode;
+    static constexpr uint32_t news = root_taken + 4;                               // new node | popped node << 10 | kRequest if it was asked for another draw
+    static constexpr uint32_t n_built = news + 4;
+    static constexpr uint32_t fred = n_built + 4;
+    static constexpr uint32_t gone = fred + 4 * (kBuildThreads / kWave);          // drawn tokens of the run a wave is drawing from
+    static constexpr uint32_t nodes = (gone + kDrawWaves * (kRun / 8) + 15) / 16 * 16;
+    __host__ __device__ static constexpr uint32_t row(int widest) { return nodes + kNode * widest; }
+};
+constexpr uint32_t kRequest = 1u << 20;
+constexpr size_t kLdsPerWorkgroup = 160 * 1024;
+static_assert(BuildLds::row(DYSPEC_MAX_BUILD_NODES) <= kLdsPerWorkgroup, "the node state of the largest tree fits in LDS");
+typedef uint32_t uint2v __attribute__((ext_vector_type(2)));
+typedef unsigned long long u64x2 __attribute__((ext_vector_type(2)));
+
+typedef unsigned long long u64;
+__device__ __forceinline__ u64 join_key(uint2 k) { return (u64)k.x | ((u64)k.y << 32); }
+__device__ __forceinline__ uint2 split_key(u64 k) { return make_uint2((uint32_t)k, (uint32_t)(k >> 32)); }
+__device__ __forceinline__ uint32_t uniform(uint32_t x) { return (uint32_t)__builtin_amdgcn_readfirstlane((int)x); }
+__device__ __forceinline__ u64 uniform(u64 x) { return (u64)uniform((uint32_t)x) | ((u64)uniform((uint32_t)(x >> 32)) << 32); }
+__device__ __forceinline__ int uniform(int x) { return __builtin_amdgcn_readfirstlane(x); }
+__device__ __forceinline__ double uniform(double x) { return __longlong_as_double((long long)uniform((u64)__double_as_longlong(x))); }
+template <typename T> __device__ __forceinline__ T* uniform(T* p) { return (T*)(T __attribute__((address_space(1)))*)uniform((u64)p); }      // global memory
+__device__ __forceinline__ void keep_order() { asm volatile("" ::: "memory"); }
+// What the lane publishes: the draw, then its word.
+__device__ __forceinline__ void publish(uint32_t place, double r, u64 key, float u, uint32_t word)
 {
-    __shared__ CachedShared sh;
-    extern __shared__ double row_state[];              // [N][kRowState]
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    *lds_at<double>(place) = r;
+    *lds_at<u64>(place + kChildKeyAt) = key;
+    *lds_at<float>(place + kChildUAt) = u;
+    lds_set(lds_at<uint32_t>(place + kWordAt), word);
+}
+
+// The roles are functions of their own, so that each has the scalar registers to itself; their arguments arrive
+// in vector registers and are declared uniform again.
+
+// Wave 1: the root's draws, in order, up to kRing ahead of control.
+__device__ __attribute__((noinline)) void draw_for_root(uint32_t lds_, uint32_t row_at, double inv_temp, double m, int V_, int N_, uint64_t seed_, uint32_t seq)
+{
+    const uint32_t lds = uniform(lds_);
+    const int V = uniform(V_), N = uniform(N_);
+    const u64 seed = uniform((u64)seed_);
+    const uint2 key = root_key(uniform(seq));
+    WaveRow row;
+    row.leaf = lds_at<double>(uniform(row_at));
+    row.logits = lds_at<float>(uniform(row_at) + 8 * row_leaves(V));
+    row.inv_temp = uniform(inv_temp);
+    row.m = uniform(m);
+    const int lane = threadIdx.x & 63;
+    open_wave_row(row, V);
+    float us = 0.f, child_u = 0.f;                  // of 64 ranks, one per lane: the draw's uniform, the child's first one,
+    u64 child = 0;                                  // its key
+    for (int rank = 0; rank < N - 1; ++rank) {
+        if ((rank & 63) == 0) {
+            const uint2 ck = child_key(seed, key, (uint32_t)(rank + lane));
+            us = u01(seed, key, (uint32_t)(rank + lane), KIND_BUILD);
+            child_u = u01(seed, ck, 0u, KIND_BUILD);
+            child = join_key(ck);
+        }
+        uint32_t news = lds_now(lds_at<uint32_t>(lds + BuildLds::news));
+        uint32_t taken = lds_now(lds_at<uint32_t>(lds + BuildLds::root_taken));
+        Drawn d;
+        const bool drawn = draw_wave_row(row, (double)readlane_f32(us, rank & 63), &d);
+        const double R = drawn ? d.wy / d.W : -1.0;
+        for (;;) {
+            if (uniform(news) == kStop) return;
+            if (rank - (int)uniform(taken) < kRing) break;
+            __builtin_amdgcn_s_sleep(1);
+            news = lds_now(lds_at<uint32_t>(lds + BuildLds::news));
+            taken = lds_now(lds_at<uint32_t>(lds + BuildLds::root_taken));
+        }
+        // (lane rank % 64 has the child's key at hand)
+        if (lane == (rank & 63))
+            publish(lds + BuildLds::ring + (uint32_t)(rank % kRing) * kNode, R, child, child_u, kAnswer | ((uint32_t)rank << 15) | (uint32_t)(drawn ? d.y : 0));
+        if (!drawn) return;
+    }
+}
+
+// A draw wave's copy of a node's totals (lane l: totals 4 l .. 4 l + 3) and row maximum.
+struct HeldRow {
+    int node;               // -1: none
+    double tot[4], m;
+};
+__device__ __forceinline__ void fetch_row(double* ws, int base, int i, HeldRow& h)
+{
+    const double* const t = ws_totals(ws, base + i) + 4 * (threadIdx.x & 63);
+    h.node = i;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) h.tot[k] = t[k];
+    h.m = *ws_rowmax(ws, base + i);
+}
+
+// One draw for node i of a sequence by a wave, the node's row in global memory: what is left of its
+// totals lies in the workspace (totals 4 l .. 4 l + 3 are read and written by lane l), as do the tokens drawn
+// before (entry r by lane r % 64); this wave alone draws for the node.
+template <bool VEC>
+__device__ __forceinline__ void draw_for_node(uint32_t place, uint32_t gone, const float* __restrict__ row, int V,
+                                              double inv_temp, uint64_t seed, double* ws, int ws_row, HeldRow& h, int rank)
+{
+    const int lane = threadIdx.x & 63;
+    const double u = (double)*lds_at<float>(place + kUAt);
+    const u64 key_word = *lds_at<u64>(place + kKeyAt);
+    // ---- the run: the lane of the crossing, then one of its four totals (every lane walks its own)
+    const double t01 = h.tot[0] + h.tot[1], four = t01 + (h.tot[2] + h.tot[3]);
+    const double cum = wave_scan_dpp(four);
+    const double W = readlane_f64(cum, 63);
+    if (!(W > 0.0)) {                               // nothing left to sample under the node
+        if (lane == 0) publish(place, -1.0, 0ull, 0.f, kAnswer);
+        return;
+    }
+    const double target = u * W;
+    const int gl = pick_lane(ballot(four > 0.0) & ballot(cum > target), ballot(four > 0.0));
+    const double start = scan_at(cum, gl - 1);
+    double run_start = start;
+    int k = -1;
+    {
+        double run = start;
+        int last = 0;
+        double last_start = start;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const double after = run + h.tot[e];
+            if (h.tot[e] > 0.0) { last = e; last_start = run; }
+            if (k < 0 && h.tot[e] > 0.0 && after > target) { k = e; run_start = run; }
+            run = after;
+        }
+        if (k < 0) { k = last; run_start = last_start; }            // rounding at the top
+    }
+    k = __builtin_amdgcn_readlane(k, gl);
+    run_start = readlane_f64(run_start, gl);
+    const int run0 = (4 * gl + k) * kRun;
+    const int tok0 = run0 + 2 * lane;               // this lane's two tokens of the run
+    float x[2];
+    if constexpr (VEC) {
+        const float2 v = tok0 < V ? *reinterpret_cast<const float2*>(row + tok0) : make_float2(-INFINITY, -INFINITY);
+        x[0] = v.x; x[1] = v.y;
+    } else {
+        x[0] = tok0 < V ? row[tok0] : -INFINITY;
+        x[1] = tok0 + 1 < V ? row[tok0 + 1] : -INFINITY;
+    }
+    unsigned short* const drawn = ws_drawn(ws, ws_row);
+    uint32_t out = 0u;                              // bit e: token tok0 + e was drawn here before
+    if (rank > 0) {
+        if (lane < kRun / 32) lds_set(lds_at<uint32_t>(gone + 4 * lane), 0u);
+        for (int c = lane; c < rank; c += kWave) {
+            const int t = drawn[c];
+            if (t / kRun * kRun == run0)
+                __hip_atomic_fetch_or(lds_at<uint32_t>(gone + 4 * (t % kRun / 32)), 1u << (t % 32), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        }
+        out = lds_now(lds_at<uint32_t>(gone + 4 * (lane / 16))) >> (2 * (lane & 15));
+    }
+    // ---- while the logits are on their way: lane 0 the key of the node this draw makes, lane 1 the
+    //      uniform of this node's next draw; then the first uniform of the new node
+    const uint2 key = split_key(key_word);
+    const uint4 blk = philox4x32_10(make_uint4(key.x, key.y, (uint32_t)rank + (lane & 1), (lane & 1) ? KIND_BUILD : KIND_PATH), seed_key(seed));
+    const uint2 child = make_uint2((uint32_t)__builtin_amdgcn_readlane((int)blk.x, 0), (uint32_t)__builtin_amdgcn_readlane((int)blk.y, 0));
+    const float next_u = (float)(blk.x >> 8) * (1.0f / 16777216.0f);                // lane 1's counts
+    const float child_u = u01(seed, child, 0u, KIND_BUILD);
+    // ---- the token: as above among the run's 128
+    double z[2], w[2];
+#pragma unroll
+    for (int e = 0; e < 2; ++e) z[e] = fma((double)x[e], inv_temp, -h.m);
+    exp_nonpos_xn<2>(z, w);
+    if (out & 1u) w[0] = 0.0;
+    if (out & 2u) w[1] = 0.0;
+    const double mine = w[0] + w[1];
+    const double inc = wave_scan_dpp(mine);
+    const int ol = pick_lane(ballot(mine > 0.0) & ballot(run_start + inc > target), ballot(mine > 0.0));
+    const double mid = run_start + scan_at(inc, ol - 1) + w[0];     // (of interest in lane ol)
+    const int second = (w[0] > 0.0 && (mid > target || !(w[1] > 0.0))) ? 0 : 1;
+    const int e = __builtin_amdgcn_readlane(second, ol);
+    const int y = run0 + 2 * ol + e;
+    const double wy = readlane_f64(e ? w[1] : w[0], ol);
+    if (lane == 1) *lds_at<float>(place + kUAt) = next_u;
+    if (lane == 0) publish(place, wy / W, join_key(child), child_u, kAnswer | ((uint32_t)rank << 15) | (uint32_t)y);
+    // what is left of the run
+    const double left = wave_sum_dpp(lane == ol ? (e ? w[0] : w[1]) : mine);
+    if (lane == gl) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) if (q == k) h.tot[q] = left;
+        ws_totals(ws, ws_row)[4 * lane + k] = left;
+    }
+    if (lane == (rank & 63)) drawn[rank] = (unsigned short)y;
+}
+
+// Draw wave `mine`: serves the requests of its nodes, the largest slot value first, until told to stop.
+template <bool VEC>
+__device__ __attribute__((noinline)) void draw_for_nodes(uint32_t lds_, int mine_, const float* draft_logits_, int V_,
+                                                         double inv_temp_, uint64_t seed_, double* ws_, int base_, int N_)
+{
+    const uint32_t lds = uniform(lds_);
+    const int mine = uniform(mine_), V = uniform(V_), base = uniform(base_), N = uniform(N_);
+    const float* __restrict__ const draft_logits = uniform(draft_logits_);
+    const double inv_temp = uniform(inv_temp_);
+    const u64 seed = uniform((u64)seed_);
+    double* const ws = uniform(ws_);
+    const int lane = threadIdx.x & 63;
+    const uint32_t nodes = lds + BuildLds::nodes, gone = lds + BuildLds::gone + mine * (kRun / 8);
+    HeldRow held, ahead;                            // the row drawn from last; the next new node's
+    held.node = -1;
+    ahead.node = -1;
+    int next_new = mine;
+    uint32_t seen = 1u << 31;                       // the news last looked at (none yet)
+    bool look = mine == 0;                          // requests may be open (node 0's, at the start)
+    for (;;) {
+        if (ahead.node < next_new && next_new < N) fetch_row(ws, base, next_new, ahead);
+        int i = -1, rank = 0;
+        if (look) {
+            // the best request of each lane's nodes, then of the wave
+            int best = 0, node = 0;
+#pragma unroll
+            for (int s = 0; s < DYSPEC_MAX_BUILD_NODES / (kDrawWaves * kWave); ++s) {
+                const int q = mine + kDrawWaves * (lane + s * kWave);
+                if (q < N) {
+                    const uint32_t w = lds_now(lds_at<uint32_t>(nodes + kNode * q + kWordAt));
+                    const int p = (w & kAnswer) ? 0 : (int)(w & 0x7fffu) + 1;
+                    if (p > best) { best = p; node = q | (int)(w >> 15) << 16; }
+                }
+            }
+            const int top = wave_max_dpp_int(best);
+            if (top > 0) {
+                const int nr = __builtin_amdgcn_readlane(node, __builtin_ctzll(ballot(best == top)));
+                i = nr & 0xffff;
+                rank = nr >> 16;
+            }
+        }
+        if (i < 0) {                                // nothing to do: wait for news
+            uint32_t m;
+            while ((m = uniform(lds_now(lds_at<uint32_t>(lds + BuildLds::news)))) == seen) __builtin_amdgcn_s_sleep(1);
+            if (m == kStop) return;
+            // the requests of one pop, if it is the one after the last seen; else look at all
+            const int a = (int)(m & 1023u), p = (int)(m >> 10) & 1023;
+            const bool a_mine = (a & (kDrawWaves - 1)) == mine, p_mine = (m & kRequest) && (p & (kDrawWaves - 1)) == mine;
+            look = a != (int)(seen & 1023u) + 1 || (a_mine && p_mine);
+            seen = m;
+            if (look || !(a_mine || p_mine)) continue;
+            look = true;                            // ... after it has been served
+            i = a_mine ? a : p;
+            const uint32_t w = uniform(lds_now(lds_at<uint32_t>(nodes + kNode * i + kWordAt)));
+            if (w & kAnswer) continue;              // served already
+            rank = (int)(w >> 15);
+        }
+        if (held.node != i) {
+            if (ahead.node == i) held = ahead;
+            else fetch_row(ws, base, i, held);
+        }
+        if (i >= next_new) next_new = i + kDrawWaves;
+        draw_for_node<VEC>(nodes + kNode * i, gone, draft_logits + (size_t)(base + i) * V, V, inv_temp, seed, ws, base + i, held, rank);
+        if (uniform(lds_now(lds_at<uint32_t>(lds + BuildLds::news))) == kStop) return;
+    }
+}
+
+// Among the lanes of `cand` (of equal slot values) those of the slot opened first.
+__device__ __forceinline__ u64 opened_first(u64 cand, uint32_t opened_at)
+{
+    int first = 0;
+    if ((cand >> (threadIdx.x & 63)) & 1u) first = 0xffff - (int)lds_now(lds_at<unsigned short>(opened_at));
+    return cand & ballot(first == wave_max_dpp_int(first));
+}
+// Largest of the upper words over rows of 16 lanes (every lane of a row gets its row's).
+__device__ __forceinline__ int row_max(int x)
+{
+    x = max(x, dpp_or_zero<kDppXor1>(x));
+    x = max(x, dpp_or_zero<kDppXor2>(x));
+    x = max(x, dpp_or_zero<kDppHalfMirror>(x));
+    return max(x, dpp_or_zero<kDppMirror>(x));
+}
+
+// Wave 0: pops and appends.  Returns the number of rows built.  Row i's parent | rank << 10 | previous
+// sibling << 20 goes to `parent` for the time being.
+__device__ __attribute__((noinline)) int pop_nodes(uint32_t lds_, int root_ring_, int N_, int* parent_, int* token_, float* est_value_)
+{
+    const uint32_t lds = uniform(lds_), nodes = lds + BuildLds::nodes;
+    const bool root_ring = uniform(root_ring_) != 0;
+    const int N = uniform(N_);
+    int *const parent = uniform(parent_), *const token = uniform(token_);
+    float* const est_value = uniform(est_value_);
+    const int lane = threadIdx.x & 63;
+    double best_v = lane == 0 ? 1.0 : -1.0;         // the best open slot of the nodes lane, lane + 64, ...; <= 0: none
+    int best_i = lane;
+    int n = 1, root_rank = 0, polls = kMaxPolls;
+    uint32_t place_n = nodes + kNode;               // LDS of node n
+    int tokens = -1, froms = 0;                     // of the last 64 rows, row i in lane i % 64; written out together
+    float values = 1.0f;
+    while (n < N) {
+        // ---- the largest value: by its upper word first (positive doubles order like integers)
+        const int hi = __double2hiint(best_v);
+        const int rows_hi = row_max(hi);
+        const int top = max(max(__builtin_amdgcn_readlane(rows_hi, 0), __builtin_amdgcn_readlane(rows_hi, 16)),
+                            max(__builtin_amdgcn_readlane(rows_hi, 32), __builtin_amdgcn_readlane(rows_hi, 48)));
+        u64 cand = ballot(hi == top);
+        if (cand & (cand - 1)) {                    // the lower word; equal values: the slot opened first
+            cand = ballot(best_v == wave_max_dpp(hi == top ? best_v : -1.0));
+            if ((cand & (cand - 1)) && uniform(top) >= 0) cand = opened_first(cand, nodes + kNode * best_i + kOpenedAt);
+        }
+        const int lp = __builtin_ctzll(cand);
+        const int p = __builtin_amdgcn_readlane(best_i, lp);
+        const double v = readlane_f64(best_v, lp);
+        const int v_hi = __double2hiint(v);
+        if (v_hi <= 0 && !(v > 0.0)) break;         // no slot is open
+        // ---- the other slots of p's lane (lanes 0..15: nodes lp, lp + 64, ...)
+        const int q = lp + kWave * (lane & 15);
+        double other = -1.0;
+        if (q < N && q != p) other = *lds_at<double>(nodes + kNode * q + kValueAt);
+        // ---- the node's next draw
+        const bool from_ring = root_ring && p == 0;
+        const uint32_t place_p = nodes + kNode * (uint32_t)p;
+        const uint32_t place = from_ring ? lds + BuildLds::ring + kNode * (uint32_t)(root_rank % kRing) : place_p;
+        // the bits of the word that tell: the answer's, in the ring the draw's rank as well
+        const uint32_t mask = from_ring ? kAnswer | (1023u << 15) : kAnswer, want = from_ring ? kAnswer | (uint32_t)root_rank << 15 : kAnswer;
+        uint32_t w = uniform(lds_now(lds_at<uint32_t>(place + kWordAt)));
+        while ((w & mask) != want && --polls > 0) w = uniform(lds_now(lds_at<uint32_t>(place + kWordAt)));
+        const double R = *lds_at<double>(place);
+        const u64 child = *lds_at<u64>(place + kChildKeyAt);
+        const uint32_t child_u = *lds_at<uint32_t>(place + kChildUAt);
+        const uint32_t o = *lds_at<uint32_t>(place_p + kOpenedAt);
+        if (uniform(__double2hiint(R)) < 0 || polls <= 0) break;    // nothing left to sample under p
+        // ---- node n = child number `rank` of p, its slot and p's next one (p's is opened first)
+        const double v0 = v * R, v1 = v * (1.0 - R);
+        const uint32_t rank = (w >> 15) & 1023u;
+        if (lane == 0) {
+            *lds_at<double>(place_n + kValueAt) = v0;
+            *lds_at<u64>(place_n + kKeyAt) = child;
+            keep_order();
+            *lds_at<uint2v>(place_n + kUAt) = uint2v{ child_u, (uint32_t)__double2hiint(v0) >> 16 };       // uniform, and word: request of draw 0
+            *lds_at<double>(place_p + kValueAt) = v1;
+            *lds_at<uint32_t>(place_p + kOpenedAt) = 2u * (uint32_t)n;
+            keep_order();
+            if (from_ring) lds_set(lds_at<uint32_t>(lds + BuildLds::root_taken), rank + 1u);
+            else lds_set(lds_at<uint32_t>(place_p + kWordAt), ((rank + 1u) << 15) | ((uint32_t)__double2hiint(v1) >> 16));
+            lds_set(lds_at<uint32_t>(lds + BuildLds::news), (uint32_t)n | ((uint32_t)p << 10) | (from_ring ? 0u : kRequest));
+        }
+        if (from_ring) root_rank = (int)rank + 1;
+        // ---- the best of p's lane again, then the new node's
+        const int other_hi = __double2hiint(other);
+        const int other_top = uniform(row_max(other_hi));
+        u64 same = ballot(other_hi == other_top) & 0xffffull;
+        if ((same & (same - 1)) && other_top >= 0) {
+            const double ov = wave_max_dpp(other);
+            same = ballot(other == ov) & 0xffffull;
+            if ((same & (same - 1)) && readlane_f64(ov, 0) > 0.0) same = opened_first(same, nodes + kNode * q + kOpenedAt);
+        }
+        const int ok = __builtin_ctzll(same);
+        const double ov = readlane_f64(other, ok);
+        const bool p_best = v1 > ov;                // equal: the other one was opened before
+        if (lane == lp) { best_v = p_best ? v1 : ov; best_i = p_best ? p : lp + kWave * ok; }
+        if (lane == (n & 63)) {
+            if (v0 > best_v) { best_v = v0; best_i = n; }
+            tokens = (int)(w & 0x7fffu);
+            values = (float)v;
+            froms = (int)((uint32_t)p | (rank << 10) | ((o >> 1) << 20));
+        }
+        ++n;
+        place_n += kNode;
+        if ((n & 63) == 0) {                        // rows n - 64 .. n - 1 are complete
+            token[n - kWave + lane] = tokens;
+            est_value[n - kWave + lane] = values;
+            parent[n - kWave + lane] = froms;
+        }
+    }
+    if ((n & 63) > lane) {
+        token[(n & ~63) + lane] = tokens;
+        est_value[(n & ~63) + lane] = values;
+        parent[(n & ~63) + lane] = froms;
+    }
+    return n;
+}
+
+template <bool VEC>
+__global__ __launch_bounds__(kBuildThreads) void build_tree_waves_kernel(
+    const float* __restrict__ draft_logits, int V, SeqArgs sa, uint64_t seed,
+    dyspec_tree tree, float* est_value, uint64_t* __restrict__ anc_mask,
+    int mask_words, int* __restrict__ n_built, double* ws, int widest, int root_ring)
+{
+    extern __shared__ __attribute__((aligned(16))) unsigned char dyn[];
+    const uint32_t lds = lds_base(dyn);
+    const uint32_t nodes = lds + BuildLds::nodes, row_at = lds + BuildLds::row(widest);
+    const int tid = threadIdx.x;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int seq = blockIdx.x;
     const int base = sa.node_off[seq];
     const int N = sa.node_off[seq + 1] - base;
     const double inv_temp = 1.0 / (double)sa.temp_d[seq];
-    for (int x = tid; x < N * kRowState; x += kBlock)
-        row_state[x] = ws_totals(ws, base + x / kRowState)[x % kRowState];
-    init_tree_rows(base, N, tree, est_value, anc_mask, mask_words);
-    for (int i = tid; i < N; i += kBlock) { sh.last_child[i] = -1; sh.depth[i] = 0; }
-    const uint2 key_root = root_key((uint32_t)seq);
-    const float u_root = u01(seed, key_root, 0u, KIND_BUILD);
-    if (tid == 0) sh.pk[0] = key_root;
+    const uint2 key = root_key((uint32_t)seq);
+    for (int i = tid; i < N; i += kBuildThreads) {
+        const uint32_t place = nodes + kNode * i;
+        *lds_at<double>(place + kValueAt) = i == 0 ? 1.0 : -1.0;
+        *lds_at<uint32_t>(place + kWordAt) = (i == 0 && !root_ring) ? 0x3ff0u : kAnswer;           // a request for draw 0, or nothing
+        *lds_at<uint32_t>(place + kOpenedAt) = 2u * (uint32_t)i + 1u;
+    }
+    if (tid < kRing) *lds_at<uint32_t>(lds + BuildLds::ring + kNode * tid + kWordAt) = 0u;
+    if (tid == 0) {
+        *lds_at<u64>(nodes + kKeyAt) = join_key(key);
+        *lds_at<float>(nodes + kUAt) = u01(seed, key, 0u, KIND_BUILD);
+        *lds_at<uint32_t>(lds + BuildLds::root_taken) = 0u;
+        *lds_at<uint32_t>(lds + BuildLds::news) = 1u << 31;
+    }
+    double m = 0.0;
+    if (root_ring && N > 1)
+        m = load_row_lds<kBuildThreads, VEC>(draft_logits + (size_t)base * V, V, inv_temp, lds_at<double>(row_at),
+                                             lds_at<float>(row_at + 8 * row_leaves(V)), reinterpret_cast<float*>(dyn + BuildLds::fred));
     __syncthreads();
-
-    // this thread's slots tid, tid + kBlock, ...: value (< 0: closed), parent | rank << 10, draw
-    double my_v[SLOTS];
-    int my_pr[SLOTS];
-    float my_u[SLOTS];
-#pragma unroll
-    for (int k = 0; k < SLOTS; ++k) { my_v[k] = -1.0; my_pr[k] = 0; my_u[k] = 0.f; }
-    if (tid == 0) { my_v[0] = 1.0; my_u[0] = u_root; }              // the root's slot
-    auto set_slot = [&](int s, double v, int pr, float u) {
-        if (tid == s % kBlock) {
-#pragma unroll
-            for (int k = 0; k < SLOTS; ++k)
-                if (k == s / kBlock) { my_v[k] = v; my_pr[k] = pr; my_u[k] = u; }
+    // waves w and w + 4 share a SIMD: control and the root's wave have one each to themselves
+    if (wave == 0) {
+        __builtin_amdgcn_s_setprio(3);
+        const int n = pop_nodes(lds, root_ring, N, tree.parent + base, tree.token + base, est_value + base);
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");            // the rows are read back below
+        if (tid == 0) {
+            *lds_at<int>(lds + BuildLds::n_built) = n;
+            lds_set(lds_at<uint32_t>(lds + BuildLds::news), kStop);
         }
-    };
-
-    int n = 1, n_slots = 1;
-    // the slot to draw from (known to every thread): the root's at first
-    int pick = 0, p = 0, rank = 0;
-    double v = 1.0, u = (double)u_root;
-    while (n < N) {
-        // the parent's mask word, needed when the node is appended: on its way during the draw
-        const int mtid = tid - 4 * kWave;              // a wave that writes nothing else down
-        uint64_t up = 0ull;
-        if (mtid >= 0 && mtid < mask_words) up = anc_mask[(size_t)(base + p) * mask_words + mtid];
-
-        // ---- draw the token from the residual draft distribution of p
-        const float* __restrict__ row = draft_logits + (size_t)(base + p) * V;
-        // (ws is written by this kernel and not declared restrict or const, so these are
-        //  ordinary vector loads and stores; a bit word or a mask word is only ever re-read
-        //  by the wave that wrote it)
-        const double my_tot = row_state[p * kRowState + (lane & 15)];
-        const double m = row_state[p * kRowState + kMaxSeg];
-        const SegPick pk = pick_segment_lanes(my_tot, u);
-        const double W = pk.W;
-        if (!(W > 0.0)) break;                         // nothing left to sample under p
-        const int tok_mine = pk.js * kSeg + 4 * tid;   // this thread's four tokens of the segment
-        uint32_t* const gone_word = ws_gone(ws, base + p) + tok_mine / 32;
-        const uint32_t gone = *gone_word;
-        float lg[4];
-        if constexpr (VEC) {
-            const float4 x = tok_mine < V ? *reinterpret_cast<const float4*>(row + tok_mine) : make_float4(0.f, 0.f, 0.f, 0.f);
-            lg[0] = x.x; lg[1] = x.y; lg[2] = x.z; lg[3] = x.w;
-        } else {
-#pragma unroll
-            for (int e = 0; e < 4; ++e) lg[e] = tok_mine + e < V ? row[tok_mine + e] : 0.f;
+    } else if (wave == 1) {
+        __builtin_amdgcn_s_setprio(2);
+        if (root_ring && N > 1) draw_for_root(lds, row_at, inv_temp, m, V, N, seed, (uint32_t)seq);
+    } else if (wave & 2) {
+        draw_for_nodes<VEC>(lds, (wave >> 2) * 2 + (wave & 1), draft_logits, V, inv_temp, seed, ws, base, N);
+    }
+    __builtin_amdgcn_s_setprio(0);
+    __syncthreads();
+    // ---- the tree is known: links, depths and masks, all rows at once
+    const int n = *lds_at<int>(lds + BuildLds::n_built);
+    lds_t<int>* const first = lds_at<int>(nodes);             // the nodes' place is free now
+    lds_t<int>* const next = first + widest;
+    lds_t<uint32_t>* const from = lds_at<uint32_t>(nodes + 8 * widest);
+    for (int i = tid; i < N; i += kBuildThreads) {
+        first[i] = -1;
+        next[i] = -1;
+        from[i] = (i > 0 && i < n) ? (uint32_t)tree.parent[base + i] : 0u;
+    }
+    __syncthreads();
+    for (int i = tid; i < n; i += kBuildThreads)
+        if (i > 0) {
+            const uint32_t f = from[i];
+            if ((f >> 10) & 1023u) next[f >> 20] = i; else first[f & 1023u] = i;
         }
-        // ---- while the loads are on their way: 1 / W for the slot values, and the best of this
-        //      wave's open slots other than the one being drawn from (for the next pop)
-        const double inv_W = 1.0 / W;
-        {
-            double bv = -1.0; int bi = 0x7fffffff, bpr = 0; float bu = 0.f;
-#pragma unroll
-            for (int k = 0; k < SLOTS; ++k)
-                if (my_v[k] > bv && tid + k * kBlock != pick) { bv = my_v[k]; bi = tid + k * kBlock; bpr = my_pr[k]; bu = my_u[k]; }
-            const double wv = wave_max_dpp(bv);        // largest value of the wave
-            int wl;                                    // (a wave without an open slot: every lane holds -1, any will do)
-            const int wi = first_of_equals(wv > 0.0 ? __ballot(bv == wv) : 1ull, bi, &wl);
-            const int wpr = __builtin_amdgcn_readlane(bpr, wl);
-            const float wu = readlane_f32(bu, wl);
-            if (lane == 0) { sh.best_v[wave] = wv; sh.best_i[wave] = wi; sh.best_pr[wave] = wpr; sh.best_u[wave] = wu; }
+    __syncthreads();
+    for (int i = tid; i < N; i += kBuildThreads) {
+        const bool built = i > 0 && i < n;
+        const uint32_t f = from[i];
+        tree.parent[base + i] = built ? (int)(f & 1023u) : -1;
+        tree.sib_rank[base + i] = (int)((f >> 10) & 1023u);
+        tree.first_child[base + i] = first[i];
+        tree.next_sibling[base + i] = next[i];
+        if (i >= n) {
+            tree.token[base + i] = -1;
+            est_value[base + i] = 0.0f;
         }
-        // ---- this thread's four weights of the segment (a drawn token has none) and their sum,
-        //      associated as the pre-pass did: the totals in LDS are sums of exactly these
-        double w4[4];
-        {
-            double z[4];
-#pragma unroll
-            for (int e = 0; e < 4; ++e) z[e] = fma((double)lg[e], inv_temp, -m);
-            exp_nonpos_x4(z, w4);
-#pragma unroll
-            for (int e = 0; e < 4; ++e)
-                if (tok_mine + e >= V || ((gone >> (tok_mine % 32 + e)) & 1u)) w4[e] = 0.0;
+        // own bit and the ancestors', which are smaller and smaller: a word at a time
+        uint64_t* const mrow = anc_mask + (size_t)(base + i) * mask_words;
+        int word = i >> 6, depth = 0;
+        for (int w = mask_words - 1; w > word; --w) mrow[w] = 0ull;
+        uint64_t bits = 1ull << (i & 63);
+        for (int a = i; built && a > 0; ++depth) {
+            a = (int)(from[a] & 1023u);
+            for (; (a >> 6) != word; --word) { mrow[word] = bits; bits = 0ull; }
+            bits |= 1ull << (a & 63);
         }
-        const double mine = (w4[0] + w4[1]) + (w4[2] + w4[3]);
-        // ---- inclusive scan of the 512 sums in thread order
-        const double inc = wave_scan_dpp(mine);
-        if (lane == kWave - 1) sh.wave_tot[wave] = inc;
-        __syncthreads();                               // barrier 1 of 2
-        // the waves' totals, one per lane (lanes 0..7 of every row of 16), scanned like the totals
-        const double wt = (lane & 8) ? 0.0 : sh.wave_tot[lane & 7];
-        double wc = wt;
-        wc += dpp_or_zero<0x111>(wc);
-        wc += dpp_or_zero<0x112>(wc);
-        wc += dpp_or_zero<0x114>(wc);
-        const double before = readlane_f64(dpp_or_zero<0x111>(wc), __builtin_amdgcn_readfirstlane(wave));
-        // first wave whose running total is past u * W
-        const uint32_t past = (uint32_t)__ballot(pk.cum_js + wc > pk.target) & 0xffu;
-        int kw = past ? __builtin_ctz(past) : -1;
-        const double incl = before + inc;
-        const unsigned long long live = __ballot(mine > 0.0);
-        int fixed_owner = -1;
-        if (kw < 0) {
-            // rounding at the very top: the last thread with weight left (the same in every thread)
-            if (lane == 0) sh.last_live[wave] = live ? wave * kWave + 63 - __builtin_clzll(live) : -1;
-            __syncthreads();
-#pragma unroll
-            for (int k = 0; k < kWaves; ++k) if (sh.last_live[k] >= 0) fixed_owner = sh.last_live[k];
-            if (fixed_owner < 0) break;                // nothing left to sample under p
-            kw = fixed_owner / kWave;
-        }
-        // ---- three waves that do not hold the crossing: the path key of the node this draw makes
-        //      and the uniform draws of the two slots it opens (functions of p and rank only); the
-        //      best open slot outside this draw (the winner among the waves' bests)
-        if (wave == ((kw + 1) & 7) && lane == 0) sh.next_u[0] = u01(seed, sh.pk[p], (uint32_t)rank + 1u, KIND_BUILD);
-        if (wave == ((kw + 2) & 7) && lane == 0) {
-            const uint2 key_i = child_key(seed, sh.pk[p], (uint32_t)rank);
-            sh.next_key = key_i;
-            sh.next_u[1] = u01(seed, key_i, 0u, KIND_BUILD);
-        }
-        if (wave == ((kw + 3) & 7)) {
-            const double cv = sh.best_v[lane & 7];     // lane l looks at wave l % 8
-            const int ci = sh.best_i[lane & 7], cpr = sh.best_pr[lane & 7];
-            const float cu = sh.best_u[lane & 7];
-            double rv = cv;
-            rv = fmax(rv, dpp_or_zero<kDppXor1>(rv));
-            rv = fmax(rv, dpp_or_zero<kDppXor2>(rv));
-            rv = fmax(rv, dpp_or_zero<kDppHalfMirror>(rv));
-            rv = readlane_f64(rv, 0);
-            int el;
-            const int ri = first_of_equals(rv > 0.0 ? __ballot(cv == rv) & 0xffull : 1ull, ci, &el);
-            const int rpr = __builtin_amdgcn_readlane(cpr, el);
-            const float ru = readlane_f32(cu, el);
-            if (lane == 0) { sh.rest_v = rv; sh.rest_i = ri; sh.rest_pr = rpr; sh.rest_u = ru; }
-        }
-        if (wave == kw) {
-            // the wave's total is positive (it moved the running sum past the target), so a thread
-            // with weight exists; after the first one past the target, else (the scan's rounding
-            // can put the crossing on a thread without weight) the last one with weight
-            const unsigned long long hit = __ballot(mine > 0.0 && pk.cum_js + incl > pk.target);
-            const int ol = fixed_owner >= 0 ? fixed_owner % kWave : hit ? __builtin_ctzll(hit) : 63 - __builtin_clzll(live);
-            const int tok0 = pk.js * kSeg + 4 * (kw * kWave + ol);
-            // every lane of the wave finishes the draw with the owner's four weights: the token
-            // among the four, what is left of their sum
-            const double w4v[4] = { readlane_f64(w4[0], ol), readlane_f64(w4[1], ol), readlane_f64(w4[2], ol), readlane_f64(w4[3], ol) };
-            double run = readlane_f64(pk.cum_js + (incl - mine), ol), wy = 0.0, wlast = 0.0;
-            int y = -1, ylast = -1;
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                run += w4v[e];
-                if (w4v[e] > 0.0) { ylast = tok0 + e; wlast = w4v[e]; }
-                if (y < 0 && w4v[e] > 0.0 && run > pk.target) { y = tok0 + e; wy = w4v[e]; }
-            }
-            if (y < 0) { y = ylast; wy = wlast; }
-            if (lane == 0) { sh.draw_y = y; sh.draw_wy = wy; }
-            if (y >= 0) {
-                // the sum that held y and the total of its segment lose y's weight
-                const int ey = y - tok0;
-                const double left = ((ey == 0 ? 0.0 : w4v[0]) + (ey == 1 ? 0.0 : w4v[1])) + ((ey == 2 ? 0.0 : w4v[2]) + (ey == 3 ? 0.0 : w4v[3]));
-                if (lane == ol) *gone_word = gone | (1u << (tok0 % 32 + ey));
-                const double wsum = wave_sum_dpp(lane == ol ? left : mine);     // the wave's sums again, the owner's replaced
-                double t = (lane & 15) == kw ? wsum : wt;                       // lanes 0..7: the waves' totals now
-                t += dpp_or_zero<kDppXor1>(t);
-                t += dpp_or_zero<kDppXor2>(t);
-                t += dpp_or_zero<kDppHalfMirror>(t);
-                if (lane == 0) row_state[p * kRowState + pk.js] = t;
-            }
-        }
-        __syncthreads();                               // barrier 2 of 2
-        const int y = sh.draw_y;
-        const double wy = sh.draw_wy;
-        const float u_a = sh.next_u[0], u_b = sh.next_u[1];
-        double nv = sh.rest_v; int ni = sh.rest_i, npr = sh.rest_pr; float nu = sh.rest_u;
-        if (y < 0) break;                              // nothing left to sample under p
-        // ---- node n: close the slot, open its two slots
-        const int i = n;
-        // R[y] = wy / W: with the correctly rounded 1 / W at hand, a product and one correction step
-        // give the correctly rounded quotient; the last token of a row has R[y] = 1 exactly
-        double Ry = wy * inv_W;
-        Ry = fma(fma(-W, Ry, wy), inv_W, Ry);
-        if (wy == W) Ry = 1.0;
-        const double v0 = v * Ry, v1 = v * (1.0 - Ry);
-        set_slot(pick, -1.0, 0, 0.f);
-        // ---- the node is written down by single lanes of waves with nothing else to store
-        if (tid == 0) {                                // links
-            const int prev = sh.last_child[p];
-            if (prev < 0) tree.first_child[base + p] = i; else tree.next_sibling[base + prev] = i;
-            sh.last_child[p] = i;
-            sh.pk[i] = sh.next_key;
-        }
-        if (tid == 3 * kWave) {                        // the node's own row
-            const int dep = sh.depth[p] + 1;
-            sh.depth[i] = dep;
-            tree.parent[base + i] = p; tree.token[base + i] = y; tree.sib_rank[base + i] = rank;
-            tree.depth[base + i] = dep;
-            est_value[base + i] = (float)v;
-        }
-        if (mtid >= 0 && mtid < mask_words)
-            anc_mask[(size_t)(base + i) * mask_words + mtid] = up | ((mtid == i / 64) ? (1ull << (i % 64)) : 0ull);
-        ++n;
-        // ---- the two new slots, and the next pop: the best slot outside this draw or one of the
-        //      new ones (largest value, earliest-opened on ties: the new ones are the latest)
-        if (v1 > 0.0) {                                // next sampling at this position
-            const int pr_a = p | ((rank + 1) << 10);
-            if (v1 > nv) { nv = v1; ni = n_slots; npr = pr_a; nu = u_a; }
-            set_slot(n_slots++, v1, pr_a, u_a);
-        }
-        if (v0 > 0.0) {                                // first child of the new node
-            if (v0 > nv) { nv = v0; ni = n_slots; npr = i; nu = u_b; }
-            set_slot(n_slots++, v0, i, u_b);
-        }
-        if (!(nv > 0.0)) break;                        // frontier is empty
-        pick = ni; p = npr & 1023; rank = npr >> 10; v = nv; u = (double)nu;
+        for (; word >= 0; --word) { mrow[word] = bits; bits = 0ull; }
+        tree.depth[base + i] = depth;
     }
     if (tid == 0) n_built[seq] = n;
 }
 
-// the cached builder keeps kRowState doubles per row in dynamic LDS: raised to the largest tree once
+// The root's row is kept in LDS where it fits beside the node state (32000 tokens: up to 558 rows,
+// 32768: up to 491); else the root's draws are made like every other node's.
+static size_t build_lds_bytes(int V, int widest, bool root_ring) { return BuildLds::row(widest) + (root_ring ? row_lds_bytes(V) : 0); }
+
+// the builder takes up to a whole CU's LDS: the kernels' limit is raised once
 hipError_t prepare_build_tree()
 {
-    static std::atomic<unsigned long long> done[6] = { {0}, {0}, {0}, {0}, {0}, {0} };
-    constexpr int bytes = DYSPEC_MAX_BUILD_NODES * kRowState * (int)sizeof(double);
-    const void* const kernels[6] = {
-        reinterpret_cast<const void*>(&build_tree_cached_kernel<true, 1>), reinterpret_cast<const void*>(&build_tree_cached_kernel<true, 2>),
-        reinterpret_cast<const void*>(&build_tree_cached_kernel<true, 4>), reinterpret_cast<const void*>(&build_tree_cached_kernel<false, 1>),
-        reinterpret_cast<const void*>(&build_tree_cached_kernel<false, 2>), reinterpret_cast<const void*>(&build_tree_cached_kernel<false, 4>) };
-    for (int k = 0; k < 6; ++k) {
-        const hipError_t e = raise_dynamic_lds_once(kernels[k], bytes, done[k]);
-        if (e != hipSuccess) return e;
-    }
-    return hipSuccess;
-}
-
-template <bool VEC>
-static void launch_cached(int slots, int n_seq, size_t dyn_bytes, hipStream_t stream, const float* draft_logits, int V, const SeqArgs& sa,
-                          uint64_t seed, const dyspec_tree& tree, float* est_value, uint64_t* anc_mask, int mask_words, int* n_built,
-                          double* ws)
-{
-    if (slots == 1)
-        build_tree_cached_kernel<VEC, 1><<<n_seq, kBlock, dyn_bytes, stream>>>(draft_logits, V, sa, seed, tree, est_value, anc_mask, mask_words, n_built, ws);
-    else if (slots == 2)
-        build_tree_cached_kernel<VEC, 2><<<n_seq, kBlock, dyn_bytes, stream>>>(draft_logits, V, sa, seed, tree, est_value, anc_mask, mask_words, n_built, ws);
-    else
-        build_tree_cached_kernel<VEC, 4><<<n_seq, kBlock, dyn_bytes, stream>>>(draft_logits, V, sa, seed, tree, est_value, anc_mask, mask_words, n_built, ws);
+    static std::atomic<unsigned long long> done_vec{0}, done_scalar{0};
+    const hipError_t e = raise_dynamic_lds_once(reinterpret_cast<const void*>(&build_tree_waves_kernel<true>), (int)kLdsPerWorkgroup, done_vec);
+    if (e != hipSuccess) return e;
+    return raise_dynamic_lds_once(reinterpret_cast<const void*>(&build_tree_waves_kernel<false>), (int)kLdsPerWorkgroup, done_scalar);
 }
 
 size_t build_tree_workspace_bytes(int total_rows) { return (size_t)total_rows * kRowSumDoubles * sizeof(double); }
@@ -529,17 +761,18 @@ hipError_t launch_build_tree(const float* draft_logits, int V, const SeqArgs& sa
     if (cached) {
         int widest = 0;
         for (int s = 0; s < sa.n_seq; ++s) widest = max(widest, sa.node_off[s + 1] - sa.node_off[s]);
-        const size_t dyn_bytes = (size_t)widest * kRowState * sizeof(double);
+        const int root_ring = build_lds_bytes(V, widest, true) <= kLdsPerWorkgroup;
+        const size_t lds_bytes = build_lds_bytes(V, widest, root_ring);
         const hipError_t ea = prepare_build_tree();
         if (ea != hipSuccess) return ea;
         if (V % 4 == 0) {
             draft_row_sums_kernel<true><<<rows, kBlock, 0, stream>>>(draft_logits, V, sa, ws);
-            launch_cached<true>(slots_per_thread(widest), sa.n_seq, dyn_bytes, stream, draft_logits, V, sa, seed, tree, est_value, anc_mask,
-                                mask_words, n_built, ws);
+            build_tree_waves_kernel<true><<<sa.n_seq, kBuildThreads, lds_bytes, stream>>>(
+                draft_logits, V, sa, seed, tree, est_value, anc_mask, mask_words, n_built, ws, widest, root_ring);
         } else {
             draft_row_sums_kernel<false><<<rows, kBlock, 0, stream>>>(draft_logits, V, sa, ws);
-            launch_cached<false>(slots_per_thread(widest), sa.n_seq, dyn_bytes, stream, draft_logits, V, sa, seed, tree, est_value, anc_mask,
-                                 mask_words, n_built, ws);
+            build_tree_waves_kernel<false><<<sa.n_seq, kBuildThreads, lds_bytes, stream>>>(
+                draft_logits, V, sa, seed, tree, est_value, anc_mask, mask_words, n_built, ws, widest, root_ring);
         }
     } else if (V % 4 == 0) {
         build_tree_kernel<true><<<sa.n_seq, kBlock, 0, stream>>>(draft_logits, V, sa, seed, tree, est_value,

@@ -5,6 +5,29 @@
 
 namespace dyspec {
 
+// LDS by its own address space: 32-bit addresses and ds instructions also where a generic pointer would
+// leave the compiler in doubt.
+template <typename T> using lds_t = T __attribute__((address_space(3)));
+template <typename T> __device__ __forceinline__ lds_t<T>* lds_at(uint32_t byte_address) { return (lds_t<T>*)byte_address; }
+__device__ __forceinline__ uint32_t lds_base(const void* p) { return (uint32_t)(size_t)(lds_t<const void>*)p; }
+// A word shared by waves that do not meet at a barrier: read and written as it stands, in program
+// order.  (The LDS operations of a wave take effect in the order they are issued; relaxed atomics keep the
+// compiler from caching or splitting them, the empty asm from moving other accesses across.)
+template <typename T> __device__ __forceinline__ T lds_now(lds_t<T>* p)
+{
+    asm volatile("" ::: "memory");
+    const T v = __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    asm volatile("" ::: "memory");
+    return v;
+}
+template <typename T> __device__ __forceinline__ void lds_set(lds_t<T>* p, T v)
+{
+    asm volatile("" ::: "memory");
+    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    asm volatile("" ::: "memory");
+}
+__device__ __forceinline__ unsigned long long ballot(bool b) { return __builtin_amdgcn_ballot_w64(b); }
+
 // Cross-lane moves of the vector ALU (DPP) for the serial builder's reductions and scan; a
 // shuffle would go through the LDS crossbar and wait for it at every step.
 constexpr int kDppXor1 = 0xB1;          // quad_perm [1,0,3,2]
@@ -16,7 +39,7 @@ constexpr int kDppBcast31 = 0x143;      // lane 31 to rows 2 and 3
 template <int CTRL, int ROW_MASK = 0xf>
 __device__ __forceinline__ int dpp_or_zero(int x)   // the picked lane's x; 0 where there is none or the row is masked off
 {
-    return __builtin_amdgcn_update_dpp(0, x, CTRL, ROW_MASK, 0xf, false);
+    return __builtin_amdgcn_update_dpp(0, x, CTRL, ROW_MASK, 0xf, ROW_MASK == 0xf);     // (no source lane: 0 either way)
 }
 template <int CTRL, int ROW_MASK = 0xf>
 __device__ __forceinline__ double dpp_or_zero(double x)
@@ -35,6 +58,16 @@ __device__ __forceinline__ double wave_max_dpp(double x)
     for (int k = 0; k < 4; ++k)
         r[k] = __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(x), 16 * k), __builtin_amdgcn_readlane(__double2loint(x), 16 * k));
     return fmax(fmax(r[0], r[1]), fmax(r[2], r[3]));
+}
+// The same for non-negative integers.
+__device__ __forceinline__ int wave_max_dpp_int(int x)
+{
+    x = max(x, dpp_or_zero<kDppXor1>(x));
+    x = max(x, dpp_or_zero<kDppXor2>(x));
+    x = max(x, dpp_or_zero<kDppHalfMirror>(x));
+    x = max(x, dpp_or_zero<kDppMirror>(x));
+    return max(max(__builtin_amdgcn_readlane(x, 0), __builtin_amdgcn_readlane(x, 16)),
+               max(__builtin_amdgcn_readlane(x, 32), __builtin_amdgcn_readlane(x, 48)));
 }
 // Sum over the wave, the same in every lane.
 __device__ __forceinline__ double wave_sum_dpp(double x)
@@ -68,19 +101,6 @@ __device__ __forceinline__ double readlane_f64(double x, int l)
 __device__ __forceinline__ float readlane_f32(float x, int l)
 {
     return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), l));
-}
-// Among the lanes of `lanes` (a ballot, not empty) the one with the smallest idx; idx of that lane.
-__device__ __forceinline__ int first_of_equals(unsigned long long lanes, int idx, int* lane_out)
-{
-    int l = __builtin_ctzll(lanes);
-    int best = __builtin_amdgcn_readlane(idx, l);
-    for (unsigned long long rest = lanes & (lanes - 1); rest; rest &= rest - 1) {    // ties only
-        const int l2 = __builtin_ctzll(rest);
-        const int i2 = __builtin_amdgcn_readlane(idx, l2);
-        if (i2 < best) { best = i2; l = l2; }
-    }
-    *lane_out = l;
-    return best;
 }
 // The segment pick of pick_segment() with total j in lanes j, j + 16, ... (t: this lane's
 // total): an inclusive scan over each row of 16 lanes, a ballot for the first segment with
