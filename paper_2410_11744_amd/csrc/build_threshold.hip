@@ -3,10 +3,9 @@
 // The tree grows level by level.  Within a level the nodes are independent: every node whose
 // estimated value is at or above the threshold draws children from its own draft row, without
 // replacement, for as long as the value of the next draw stays at or above the threshold.
-// That is the data-parallel form of the builder: one 512-thread workgroup per node of the
-// level (threshold_expand_kernel), all of them at once, each keeping its row's 4-token
-// weight sums in registers so that a draw costs a segment pick, one workgroup scan and the
-// update of one sum -- the arithmetic of the greedy builder, draw for draw.  Nodes are
+// That is the data-parallel form of the builder: one workgroup per node of the level
+// (threshold_expand_kernel), all of them at once, each with its row in LDS, from which one
+// wave makes the node's draws (wave_draw.h, as the greedy builder draws from the root).  Nodes are
 // numbered in creation order (level by level, parents in order, children in sampling order),
 // which a workgroup cannot know while its neighbours are still drawing, so children go to a
 // per-level pool first and threshold_commit_kernel (one workgroup per sequence) scans the
@@ -15,6 +14,7 @@
 // grid and ends the loop.  Draft row of a node = its row index, as for Algorithm 1.
 #include "draft_row.h"
 #include "lane_ops.h"
+#include "wave_draw.h"
 
 namespace dyspec {
 
@@ -98,35 +98,24 @@ __global__ __launch_bounds__(256) void threshold_init_kernel(SeqArgs sa, dyspec_
     }
 }
 
-struct ExpandShared {
-    double red[kWaves * kMaxSeg];       // workgroup sums at set-up
-    double wave_tot[kWaves];            // per draw: the waves' sums of the picked segment
-    double wy, old_sum, new_sum;        // per draw: the drawn token's weight, its thread's sum before and after
-    int y, owner;                       // the drawn token, the thread that held it
-    int last_live[kWaves];              // last thread of each wave with weight left, -1: none
-    float fred[kWaves];
-    float u_draw[DYSPEC_MAX_BUILD_NODES];     // the uniform draws of this node's samplings, by child rank
-};
-
-// One workgroup per node of the current level: blockIdx.x = position in the level.  The node's
-// row of logits and a drawn-already bitmap live in LDS (dynamic: 4 bytes per token, 1 bit per
-// token), the threads' 4-token weight sums in registers, segment total j in lanes j, j + 16, ...
-// A draw is: segment pick (a 16-lane scan), a scan of the 512 sums of that segment (DPP, one
-// barrier); the waves' totals tell every thread which wave holds the crossing; that wave finds
-// the owning thread with a ballot, computes its four weights in four lanes and finishes the draw
-// (one barrier); every thread then updates its copy of the totals.  The uniform draws of all
-// samplings of the node (functions of its path key and the child rank) are made at set-up.
+// One workgroup per node of the current level: blockIdx.x = position in the level.  All waves bring
+// the node's row into LDS (logits, leaf sums); then the first one draws and the others leave.
+// Bound by the instructions of a draw (a lone wave issues one in eight cycles, about 170 of them): 0.6 us each,
+// against 1.5 us when the whole workgroup made every draw, with two barriers and eight waves doing every
+// scan: the 384-row tree of the Zipf table (383 draws under the root) 587 -> 235 us.  A second wave that takes
+// over the division and the writing through a ring of draws in LDS makes it 256: keeping the ring costs the
+// drawing wave more instructions than it saves.
+constexpr int kExpandThreads = 1024;
 template <bool VEC>
-__global__ __launch_bounds__(kBlock) void threshold_expand_kernel(const float* __restrict__ draft_logits, int V, SeqArgs sa,
-                                                                  ThresholdArgs ta, uint64_t seed, ThresholdWs w)
+__global__ __launch_bounds__(kExpandThreads) void threshold_expand_kernel(const float* __restrict__ draft_logits, int V, SeqArgs sa,
+                                                                          ThresholdArgs ta, uint64_t seed, ThresholdWs w)
 {
     extern __shared__ __attribute__((aligned(16))) unsigned char dyn[];
-    __shared__ ExpandShared sh;
+    __shared__ float fred[kExpandThreads / kWave];
     const int tid = threadIdx.x, lane = tid & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int seq = blockIdx.y;
     const int base = sa.node_off[seq];
-    const int lvl_begin = w.state[4 * seq + 0], lvl_end = w.state[4 * seq + 1], left = w.state[4 * seq + 2];
+    const int lvl_begin = uniform(w.state[4 * seq + 0]), lvl_end = uniform(w.state[4 * seq + 1]), left = uniform(w.state[4 * seq + 2]);
     const int f = blockIdx.x;
     const int p = lvl_begin + f;
     if (p >= lvl_end) return;                           // uniform over the workgroup
@@ -136,111 +125,35 @@ __global__ __launch_bounds__(kBlock) void threshold_expand_kernel(const float* _
         if (tid == 0) w.counts[base + p] = 0;
         return;
     }
-    const double inv_temp = 1.0 / (double)sa.temp_d[seq];
-    const float* __restrict__ row = draft_logits + (size_t)(base + p) * V;
-    const uint2 pk_p = w.pk[base + p];
+    WaveRow row;
+    row.leaf = lds_at<double>(lds_base(dyn));
+    row.logits = lds_at<float>(lds_base(dyn) + 8 * row_leaves(V));
+    row.inv_temp = 1.0 / (double)sa.temp_d[seq];
+    row.m = load_row_lds<kExpandThreads, VEC>(draft_logits + (size_t)(base + p) * V, V, row.inv_temp, row.leaf, row.logits, fred);
+    if (tid >= kWave) return;
+    open_wave_row(row, V);
+    const uint2 pk = w.pk[base + p];
     const size_t pool0 = (size_t)w.pool_off[seq] + (size_t)f * left;
-    const int Vpad = (V + 31) & ~31;
-    float* const row_lds = reinterpret_cast<float*>(dyn);
-    uint32_t* const gone = reinterpret_cast<uint32_t*>(dyn + (size_t)Vpad * 4);
-    for (int i = tid; i < Vpad; i += kBlock) row_lds[i] = (i < V) ? row[i] : -INFINITY;
-    for (int i = tid; i < Vpad / 32; i += kBlock) gone[i] = 0u;
-
-    for (int c = tid; c < left; c += kBlock) sh.u_draw[c] = u01(seed, pk_p, (uint32_t)c, KIND_BUILD);
-
-    double m, seg[kMaxSeg], tot[kMaxSeg];
-    row_segment_sums<VEC>(row, V, inv_temp, 0ull, sh.fred, &m, seg);
-#pragma unroll
-    for (int j = 0; j < kMaxSeg; ++j) tot[j] = seg[j];
-    block_sum<double, kMaxSeg>(tot, sh.red);
-    double my_tot = 0.0;                                // total of segment lane % 16
-#pragma unroll
-    for (int j = 0; j < kMaxSeg; ++j) if (j == (lane & 15)) my_tot = tot[j];
-    __syncthreads();                                    // the row, the bitmap and the draws are in LDS for everyone
-
-    int count = 0;
-    while (v >= t && count < left) {
-        const double u = (double)sh.u_draw[count];
-        const SegPick pk = pick_segment_lanes(my_tot, u);
-        if (!(pk.W > 0.0)) break;                       // nothing left to sample under p
-        double mine = 0.0;
-#pragma unroll
-        for (int j = 0; j < kMaxSeg; ++j) if (j == pk.js) mine = seg[j];
-        // ---- inclusive scan of the sums of segment js in thread order
-        const double inc = wave_scan_dpp(mine);
-        if (lane == kWave - 1) sh.wave_tot[wave] = inc;
-        __syncthreads();
-        // the waves' totals, one per lane (lanes 0..7 of every row of 16), scanned the same way
-        const double wt = (lane & 8) ? 0.0 : sh.wave_tot[lane & 7];
-        double wc = wt;
-        wc += dpp_or_zero<0x111>(wc);
-        wc += dpp_or_zero<0x112>(wc);
-        wc += dpp_or_zero<0x114>(wc);
-        const double before = readlane_f64(dpp_or_zero<0x111>(wc), wave);
-        const uint32_t past = (uint32_t)__ballot(pk.cum_js + wc > pk.target) & 0xffu;
-        int kw = past ? __builtin_ctz(past) : -1;       // first wave whose running total is past u * W
-        const double incl = before + inc;
-        const unsigned long long live = __ballot(mine > 0.0);
-        int fixed_owner = -1;
-        if (kw < 0) {
-            // rounding at the very top: the last thread with weight left (the same in every thread)
-            if (lane == 0) sh.last_live[wave] = live ? wave * kWave + 63 - __builtin_clzll(live) : -1;
-            __syncthreads();
-#pragma unroll
-            for (int k = 0; k < kWaves; ++k) if (sh.last_live[k] >= 0) fixed_owner = sh.last_live[k];
-            if (fixed_owner < 0) break;                 // the totals held rounding dust only
-            kw = fixed_owner / kWave;
-        }
-        if (wave == kw) {
-            // the wave's total is positive, so a thread with weight exists: the first one past the
-            // target, else (the scan's rounding) the last one with weight
-            const unsigned long long hit = __ballot(mine > 0.0 && pk.cum_js + incl > pk.target);
-            const int ol = fixed_owner >= 0 ? fixed_owner % kWave : hit ? __builtin_ctzll(hit) : 63 - __builtin_clzll(live);
-            const int tok0 = pk.js * kSeg + 4 * (kw * kWave + ol);      // first of the owner's four tokens
-            double wgt = 0.0;                           // lanes 0..3: one weight each
-            if (lane < 4) {
-                const int idx = tok0 + lane;
-                const bool there = idx < V && !((gone[idx >> 5] >> (idx & 31)) & 1u);
-                if (there) wgt = token_weight(row_lds[idx], inv_temp, m);
-            }
-            const double w4v[4] = { readlane_f64(wgt, 0), readlane_f64(wgt, 1), readlane_f64(wgt, 2), readlane_f64(wgt, 3) };
-            double run = readlane_f64(pk.cum_js + (incl - mine), ol), wy = 0.0, wlast = 0.0;
-            int y = -1, ylast = -1;
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                run += w4v[e];
-                if (w4v[e] > 0.0) { ylast = tok0 + e; wlast = w4v[e]; }
-                if (y < 0 && w4v[e] > 0.0 && run > pk.target) { y = tok0 + e; wy = w4v[e]; }
-            }
-            if (y < 0) { y = ylast; wy = wlast; }
-            const int ey = y - tok0;
-            if (lane == 0) {
-                sh.y = y; sh.wy = wy; sh.owner = kw * kWave + ol;
-                sh.old_sum = (w4v[0] + w4v[1]) + (w4v[2] + w4v[3]);
-                sh.new_sum = ((ey == 0 ? 0.0 : w4v[0]) + (ey == 1 ? 0.0 : w4v[1])) + ((ey == 2 ? 0.0 : w4v[2]) + (ey == 3 ? 0.0 : w4v[3]));
-            }
-        }
-        __syncthreads();
-        // ---- every thread updates its copy of the state
-        const int y = sh.y;
-        if (y < 0) break;
-        const double wy = sh.wy, old_sum = sh.old_sum, new_sum = sh.new_sum;
-        if (tid == sh.owner) {
-#pragma unroll
-            for (int j = 0; j < kMaxSeg; ++j) if (j == pk.js) seg[j] = new_sum;
-        }
-        if ((lane & 15) == pk.js) my_tot = (my_tot - old_sum) + new_sum;
-        const double dy = wy / pk.W;
-        if (tid == 0) {
-            gone[y >> 5] |= 1u << (y & 31);             // read again one barrier from here at the earliest
-            w.pool_token[pool0 + count] = y;
-            w.pool_v[pool0 + count] = v;
-            w.pool_v0[pool0 + count] = v * dy;
-        }
+    // draws count - 64 .. count - 1 wait in the lanes to be written out together, draw c in lane c % 64
+    float us = 0.f;                                     // the uniforms of 64 samplings, one per lane
+    int token = 0, count = 0;
+    double value = 0.0, own = 0.0;
+    auto flush = [&](int first) {                       // draws first .. count - 1
+        const int c = first + lane;
+        if (c < count) { w.pool_token[pool0 + c] = token; w.pool_v[pool0 + c] = value; w.pool_v0[pool0 + c] = own; }
+    };
+    while (count < left && ballot(v >= t)) {
+        if ((count & 63) == 0) us = u01(seed, pk, (uint32_t)(count + lane), KIND_BUILD);
+        Drawn d;
+        if (!draw_wave_row(row, (double)readlane_f32(us, count & 63), &d)) break;       // nothing left to sample under p
+        const double dy = d.wy / d.W;
+        if (lane == (count & 63)) { token = d.y; value = v; own = v * dy; }
         v = v * (1.0 - dy);
         ++count;
+        if ((count & 63) == 0) flush(count - kWave);
     }
-    if (tid == 0) w.counts[base + p] = count;
+    flush(count & ~63);
+    if (lane == 0) w.counts[base + p] = count;
 }
 
 struct CommitShared {
@@ -307,12 +220,11 @@ __global__ __launch_bounds__(kBlock) void threshold_commit_kernel(SeqArgs sa, ui
     }
 }
 
-// the expanding workgroups keep a row of logits and a token bitmap in dynamic LDS: raised to the
-// largest vocabulary once
+// the expanding workgroups keep a row in dynamic LDS: raised to the largest vocabulary once
 hipError_t prepare_build_threshold()
 {
     static std::atomic<unsigned long long> done_vec{0}, done_scalar{0};
-    constexpr int bytes = DYSPEC_MAX_VOCAB * 4 + DYSPEC_MAX_VOCAB / 8;
+    constexpr int bytes = (int)row_lds_bytes(DYSPEC_MAX_VOCAB);
     hipError_t e = raise_dynamic_lds_once(reinterpret_cast<const void*>(&threshold_expand_kernel<true>), bytes, done_vec);
     if (e != hipSuccess) return e;
     return raise_dynamic_lds_once(reinterpret_cast<const void*>(&threshold_expand_kernel<false>), bytes, done_scalar);
@@ -325,9 +237,7 @@ hipError_t launch_build_threshold(const float* draft_logits, int V, const SeqArg
     const ThresholdWs w = carve(workspace, sa);
     ThresholdArgs ta;
     for (int s = 0; s < sa.n_seq; ++s) ta.t[s] = threshold[s];
-    // the expanding workgroups keep their row (4 bytes per token) and a bitmap (1 bit per token) in LDS
-    const int Vpad = (V + 31) & ~31;
-    const size_t dyn_bytes = (size_t)Vpad * 4 + Vpad / 8;
+    const size_t dyn_bytes = row_lds_bytes(V);
     const hipError_t ea = prepare_build_threshold();
     if (ea != hipSuccess) return ea;
     threshold_init_kernel<<<sa.n_seq, 256, 0, stream>>>(sa, tree, est_value, anc_mask, mask_words, n_built, w);
@@ -342,9 +252,9 @@ hipError_t launch_build_threshold(const float* draft_logits, int V, const SeqArg
     // a level adds at least one row or ends the loop, so this runs at most max N times
     while (frontier > 0) {
         if (V % 4 == 0)
-            threshold_expand_kernel<true><<<dim3(frontier, sa.n_seq), kBlock, dyn_bytes, stream>>>(draft_logits, V, sa, ta, seed, w);
+            threshold_expand_kernel<true><<<dim3(frontier, sa.n_seq), kExpandThreads, dyn_bytes, stream>>>(draft_logits, V, sa, ta, seed, w);
         else
-            threshold_expand_kernel<false><<<dim3(frontier, sa.n_seq), kBlock, dyn_bytes, stream>>>(draft_logits, V, sa, ta, seed, w);
+            threshold_expand_kernel<false><<<dim3(frontier, sa.n_seq), kExpandThreads, dyn_bytes, stream>>>(draft_logits, V, sa, ta, seed, w);
         threshold_commit_kernel<<<sa.n_seq, kBlock, 0, stream>>>(sa, seed, tree, est_value, anc_mask, mask_words, n_built, w);
         hipError_t e = hipMemcpyAsync(state, w.state, sizeof(int) * 4 * sa.n_seq, hipMemcpyDeviceToHost, stream);
         if (e != hipSuccess) return e;

@@ -288,14 +288,8 @@ static_assert(BuildLds::row(DYSPEC_MAX_BUILD_NODES) <= kLdsPerWorkgroup, "the no
 typedef uint32_t uint2v __attribute__((ext_vector_type(2)));
 typedef unsigned long long u64x2 __attribute__((ext_vector_type(2)));
 
-typedef unsigned long long u64;
 __device__ __forceinline__ u64 join_key(uint2 k) { return (u64)k.x | ((u64)k.y << 32); }
 __device__ __forceinline__ uint2 split_key(u64 k) { return make_uint2((uint32_t)k, (uint32_t)(k >> 32)); }
-__device__ __forceinline__ uint32_t uniform(uint32_t x) { return (uint32_t)__builtin_amdgcn_readfirstlane((int)x); }
-__device__ __forceinline__ u64 uniform(u64 x) { return (u64)uniform((uint32_t)x) | ((u64)uniform((uint32_t)(x >> 32)) << 32); }
-__device__ __forceinline__ int uniform(int x) { return __builtin_amdgcn_readfirstlane(x); }
-__device__ __forceinline__ double uniform(double x) { return __longlong_as_double((long long)uniform((u64)__double_as_longlong(x))); }
-template <typename T> __device__ __forceinline__ T* uniform(T* p) { return (T*)(T __attribute__((address_space(1)))*)uniform((u64)p); }      // global memory
 __device__ __forceinline__ void keep_order() { asm volatile("" ::: "memory"); }
 // What the lane publishes: the draw, then its word.
 __device__ __forceinline__ void publish(uint32_t place, double r, u64 key, float u, uint32_t word)

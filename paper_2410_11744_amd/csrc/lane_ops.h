@@ -1,5 +1,5 @@
 // Cross-lane helpers of the serial tree builders: DPP moves, lane reads, wave-wide maximum, sum
-// and scan in fp64, and the segment pick with the totals spread over lanes.
+// and scan in fp64.
 #pragma once
 #include "vocab_common.h"
 
@@ -26,7 +26,15 @@ template <typename T> __device__ __forceinline__ void lds_set(lds_t<T>* p, T v)
     __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
     asm volatile("" ::: "memory");
 }
-__device__ __forceinline__ unsigned long long ballot(bool b) { return __builtin_amdgcn_ballot_w64(b); }
+typedef unsigned long long u64;
+__device__ __forceinline__ u64 ballot(bool b) { return __builtin_amdgcn_ballot_w64(b); }
+
+// A value known to be the same in every lane, declared so (scalar registers, scalar branches).
+__device__ __forceinline__ uint32_t uniform(uint32_t x) { return (uint32_t)__builtin_amdgcn_readfirstlane((int)x); }
+__device__ __forceinline__ u64 uniform(u64 x) { return (u64)uniform((uint32_t)x) | ((u64)uniform((uint32_t)(x >> 32)) << 32); }
+__device__ __forceinline__ int uniform(int x) { return __builtin_amdgcn_readfirstlane(x); }
+__device__ __forceinline__ double uniform(double x) { return __longlong_as_double((long long)uniform((u64)__double_as_longlong(x))); }
+template <typename T> __device__ __forceinline__ T* uniform(T* p) { return (T*)(T __attribute__((address_space(1)))*)uniform((u64)p); }      // global memory
 
 // Cross-lane moves of the vector ALU (DPP) for the serial builder's reductions and scan; a
 // shuffle would go through the LDS crossbar and wait for it at every step.
@@ -102,25 +110,4 @@ __device__ __forceinline__ float readlane_f32(float x, int l)
 {
     return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), l));
 }
-// The segment pick of pick_segment() with total j in lanes j, j + 16, ... (t: this lane's
-// total): an inclusive scan over each row of 16 lanes, a ballot for the first segment with
-// weight whose running sum is past u * W, the last segment with weight if rounding leaves none.
-__device__ __forceinline__ SegPick pick_segment_lanes(double t, double u)
-{
-    double c = t;
-    c += dpp_or_zero<0x111>(c);
-    c += dpp_or_zero<0x112>(c);
-    c += dpp_or_zero<0x114>(c);
-    c += dpp_or_zero<0x118>(c);
-    SegPick pk;
-    pk.W = readlane_f64(c, 15);
-    pk.target = u * pk.W;
-    const uint32_t hit = (uint32_t)__ballot(t > 0.0 && c > pk.target) & 0xffffu;
-    const uint32_t live = (uint32_t)__ballot(t > 0.0) & 0xffffu;
-    pk.js = hit ? __builtin_ctz(hit) : live ? 31 - __builtin_clz(live) : 0;
-    pk.cum_js = readlane_f64(c - t, pk.js);
-    return pk;
-}
-
-
 }  // namespace dyspec

@@ -49,8 +49,6 @@ __device__ __forceinline__ double scan32_dpp(double x)
 }
 // the lane's value at position i of a scan, 0 for i = -1
 __device__ __forceinline__ double scan_at(double x, int i) { const double v = readlane_f64(x, i & 63); return i < 0 ? 0.0 : v; }
-// the scan of the reversed copy at a lane; 0 where nothing lies behind
-__device__ __forceinline__ double sum_after(double x, int l, bool any) { const double v = readlane_f64(x, l); return any ? v : 0.0; }
 
 // Brings a row into LDS with NT threads: logits, leaf sums; the row maximum over T is returned to
 // every thread.  `fred`: NT / 64 floats.  Ends with a barrier.
@@ -125,7 +123,7 @@ __device__ __forceinline__ void open_wave_row(WaveRow& r, int V)
 struct Drawn { int y; double wy, W; };
 
 // First lane of `hit`, or the last one of `live` (not empty) where rounding left no hit.
-__device__ __forceinline__ int pick_lane(unsigned long long hit, unsigned long long live)
+__device__ __forceinline__ int pick_lane(u64 hit, u64 live)
 {
     return hit ? __builtin_ctzll(hit) : 63 - __builtin_clzll(live);
 }
@@ -138,26 +136,30 @@ __device__ __forceinline__ bool draw_wave_row(WaveRow& r, double u, Drawn* d)
     const double W = readlane_f64(r.cum, 63);
     if (!(W > 0.0)) return false;
     const double target = u * W;
-    const int g = pick_lane(ballot(r.tot > 0.0) & ballot(r.cum > target), ballot(r.tot > 0.0));
+    const u64 live_g = ballot(r.tot > 0.0);
+    const int g = pick_lane(live_g & ballot(r.cum > target), live_g);
     // lanes 0..15 (and 32..47) hold the group's leaves, lanes 16..31 (48..63) the same in reverse order
     const double b = r.leaf[g * kGroupLeaves + ((lane & 15) ^ ((lane & 16) ? 15 : 0))];
     const double below_g = scan_at(r.cum, g - 1);
     const double cb = scan16_dpp(b);
-    const int l = pick_lane(ballot(b > 0.0) & ballot(below_g + cb > target) & 0xffffull, ballot(b > 0.0) & 0xffffull);
+    const double eb = dpp_or_zero<0x111>(cb);               // what lies before each leaf (row_shr:1; 0 at the start of a row)
+    const u64 live_l = ballot(b > 0.0) & 0xffffull;
+    const int l = pick_lane(live_l & ballot(below_g + cb > target), live_l);
     // lanes 0..31: the leaf's tokens, lanes 32..63: the same in reverse order
     const int leaf0 = (g * kGroupLeaves + l) * kLeafTokens;
     const float x = r.logits[leaf0 + ((lane & 31) ^ ((lane & 32) ? 31 : 0))];
-    const double below_l = below_g + scan_at(cb, l - 1);
-    const double leaves_before = scan_at(cb, l - 1), leaves_after = sum_after(cb, 30 - l, l < 15);
+    const double leaves_before = readlane_f64(eb, l), leaves_after = readlane_f64(eb, 31 - l);
+    const double below_l = below_g + leaves_before;
     const double rest = wave_scan_dpp(lane == g ? 0.0 : r.tot);        // scan of the groups without this one
     double z[1] = { fma((double)x, r.inv_temp, -r.m) }, w[1];
     exp_nonpos_xn<1>(z, w);
     const double cw = scan32_dpp(w[0]);
-    const int e = pick_lane(ballot(w[0] > 0.0) & ballot(below_l + cw > target) & 0xffffffffull, ballot(w[0] > 0.0) & 0xffffffffull);
+    const u64 live_e = ballot(w[0] > 0.0) & 0xffffffffull;
+    const int e = pick_lane(live_e & ballot(below_l + cw > target), live_e);
     d->y = leaf0 + e;
     d->wy = readlane_f64(w[0], e);
     d->W = W;
-    const double left = scan_at(cw, e - 1) + sum_after(cw, 62 - e, e < 31);
+    const double left = scan_at(cw, e - 1) + (e < 31 ? readlane_f64(cw, 62 - e) : 0.0);
     const double t = (leaves_before + left) + leaves_after;
     r.cum = rest + (lane >= g ? t : 0.0);
     if (lane == g) r.tot = t;
