@@ -90,6 +90,16 @@ __device__ __forceinline__ double wave_sum_dpp(double x)
         r[k] = __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(x), 16 * k), __builtin_amdgcn_readlane(__double2loint(x), 16 * k));
     return (r[0] + r[1]) + (r[2] + r[3]);
 }
+__device__ __forceinline__ float readlane_f32(float x, int l);
+// The same in fp32.
+__device__ __forceinline__ float wave_sum_f32_dpp(float x)
+{
+    x += __int_as_float(dpp_or_zero<kDppXor1>(__float_as_int(x)));
+    x += __int_as_float(dpp_or_zero<kDppXor2>(__float_as_int(x)));
+    x += __int_as_float(dpp_or_zero<kDppHalfMirror>(__float_as_int(x)));
+    x += __int_as_float(dpp_or_zero<kDppMirror>(__float_as_int(x)));
+    return (readlane_f32(x, 0) + readlane_f32(x, 16)) + (readlane_f32(x, 32) + readlane_f32(x, 48));
+}
 // Inclusive scan over the wave in lane order.
 __device__ __forceinline__ double wave_scan_dpp(double x)
 {

@@ -301,19 +301,22 @@ __device__ __forceinline__ float exp_fast(float x) { return __builtin_amdgcn_exp
 // tell every thread which wave holds the crossing, and that wave finds the owning thread with a
 // ballot; the owner walks its four weights.  Three barriers.  Every thread gets y (-1 when W == 0).
 constexpr int kStageDoubles = kMaxSeg * kBlock + kMaxSeg;
+// A thread's tokens of a row: component e of segment j is v[e][j] (a segment known to be the same in every
+// thread picks the registers by index).
+typedef float RowVec __attribute__((ext_vector_type(kMaxSeg)));
 struct DrawScratch {
     double wave_tot[kWaves];
     int last_live[kWaves];
     int y;
 };
-__device__ __forceinline__ int draw_from_row(const float (&w)[kMaxSeg][4], double u, DrawScratch* sc, double* stage)
+__device__ __forceinline__ int draw_from_row(const RowVec (&w)[4], double u, DrawScratch* sc, double* stage)
 {
     static_assert(kMaxSeg == 2 * kWaves, "two segments per wave");
     const int tid = threadIdx.x, lane = tid & (kWave - 1);
     const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
 #pragma unroll
     for (int j = 0; j < kMaxSeg; ++j)
-        stage[j * kBlock + tid] = ((double)w[j][0] + (double)w[j][1]) + ((double)w[j][2] + (double)w[j][3]);
+        stage[j * kBlock + tid] = ((double)w[0][j] + (double)w[1][j]) + ((double)w[2][j] + (double)w[3][j]);
     __syncthreads();
     double* const totals = stage + kMaxSeg * kBlock;
 #pragma unroll
@@ -330,6 +333,7 @@ __device__ __forceinline__ int draw_from_row(const float (&w)[kMaxSeg][4], doubl
 #pragma unroll
     for (int j = 0; j < kMaxSeg; ++j) tot[j] = totals[j];
     const SegPick pk = pick_segment(tot, u);
+    const int js = uniform(pk.js);
     if (!(pk.W > 0.0)) return -1;                            // uniform
     const double mine = stage[pk.js * kBlock + tid];
     const double inc = wave_scan_dpp(mine);                  // inclusive, in lane order
@@ -354,11 +358,8 @@ __device__ __forceinline__ int draw_from_row(const float (&w)[kMaxSeg][4], doubl
         const unsigned long long hit = __ballot(mine > 0.0 && pk.cum_js + before + inc > pk.target);
         const int ol = fixed_owner >= 0 ? fixed_owner % kWave : hit ? __builtin_ctzll(hit) : 63 - __builtin_clzll(live);
         if (lane == ol) {
-            // this thread's four weights of the picked segment (sixteen uniform compares pick the registers)
-            float w4[4] = { 0.0f, 0.0f, 0.0f, 0.0f };
-#pragma unroll
-            for (int jj = 0; jj < kMaxSeg; ++jj)
-                if (jj == pk.js) { w4[0] = w[jj][0]; w4[1] = w[jj][1]; w4[2] = w[jj][2]; w4[3] = w[jj][3]; }
+            // this thread's four weights of the picked segment (js is the same in every lane)
+            const float w4[4] = { w[0][js], w[1][js], w[2][js], w[3][js] };
             double c = pk.cum_js + before + (inc - mine);
             int y = -1, ylast = -1;
 #pragma unroll
@@ -378,17 +379,23 @@ __device__ __forceinline__ int draw_from_row(const float (&w)[kMaxSeg][4], doubl
 
 // LDS of the walk.  Static part: scratch of the reductions.  Dynamic part: the draft row of the
 // node being decided, as unnormalised weights exp(logit/T - max) indexed by token (what is left of
-// D after the children rejected so far is D_lds[x] * scale), then the sequence's tree links as
-// 16-bit values (tokens < 32768, nodes < 2048; -1 = none).  The target row R stays in registers.
+// D after the children rejected so far is D_lds[x] * scale_d), then the sequence's tree links as
+// 16-bit values (tokens < 32768, nodes < 2048; -1 = none).  The target row R stays in registers, as
+// weights of the sum `mass`.  A thread's tokens of both rows are its own: nobody else reads them, except
+// the two values at the next child's token, which their owner publishes.
+//
+// A rejection is one sweep: R <- max(R - D * (mass * scale_d), 0) (R stays within [0, 1], so the clamp of the fma
+// does for the maximum), the new mass and the weight of D on the way, and one reduction with one barrier.  (Two sweeps, R normalised every time, and five barriers before: 4.4
+// us a rejection, %s now; the rows' loads one after the other: 5.8 us for fp32 rows, %s now.)
 struct WalkShared {
     DrawScratch draw;
-    float fred[kWaves * 2];
-    float bcast[2];
+    float2 part[2][kWaves];       // per wave, by parity of the rejection: mass left in R, weight in D
+    float2 next[2];               // R and D at the next child's token
 };
 // (the row's place also stages the partial sums of the final draw: at least kStageDoubles doubles)
 __host__ __device__ __forceinline__ size_t walk_row_bytes(int V)
 {
-    const size_t row = (size_t)((V + 3) & ~3) * sizeof(float), stage = (size_t)kStageDoubles * sizeof(double);
+    const size_t row = (size_t)((V + kSeg - 1) / kSeg * kSeg) * sizeof(float), stage = (size_t)kStageDoubles * sizeof(double);
     return row > stage ? row : stage;
 }
 static size_t walk_lds_bytes(int V, int widest) { return walk_row_bytes(V) + 3 * (size_t)((widest + 7) & ~7) * sizeof(short); }
@@ -433,40 +440,49 @@ __global__ __launch_bounds__(kBlock) void verify_walk_kernel(
         int next = -1;
         uint2 pk_next = pk;
         bool rows_loaded = false;
-        float R[kMaxSeg][4];
+        RowVec R[4];
         // the node's statistics: one 16-byte load, on its way together with the first child's logits
         const float4 st = *reinterpret_cast<const float4*>(row_stats + 4 * (size_t)(base + cur));
-        float scale_d = 0.0f;                             // what is left of D = D_lds * scale_d
-        // R <- softmax of the target row (registers); with want_draft, D_lds <- the draft row's weights
-        auto load_rows = [&](bool want_draft) {
-            float X[kMaxSeg][4];
-            if (want_draft) {
+        float scale_d = 0.0f, mass = 0.0f;                // what is left of D = D_lds * scale_d; R's sum
+        // R <- the target row's weights (registers); with want_draft, D_lds <- the draft row's
+        auto load_rows = [&](bool want_draft) __attribute__((always_inline)) {
+            float Y[kMaxSeg][4];
+            if (!greedy) load_row<VEC, T>(target_logits + (size_t)(base + cur) * V, V, Y);
+            if (want_draft) {                             // (the loads of both rows are in flight together)
+                float X[kMaxSeg][4];
                 load_row<VEC, T>(draft_logits + (size_t)(base + cur) * V, V, X);
 #pragma unroll
                 for (int j = 0; j < kMaxSeg; ++j) {
                     const int i0 = tok_index(j, 0);
-                    if (i0 < V)                           // V is padded to a multiple of 4 in LDS; logits past V read as -inf
+                    if (j * kSeg < V)                     // whole segments in LDS; logits past V read as -inf
                         *reinterpret_cast<float4*>(D_lds + i0) = make_float4(exp_fast(X[j][0] * inv_td - st.x), exp_fast(X[j][1] * inv_td - st.x),
                                                                              exp_fast(X[j][2] * inv_td - st.x), exp_fast(X[j][3] * inv_td - st.x));
                 }
                 scale_d = 1.0f / st.y;
             }
-            if (!greedy) load_row<VEC, T>(target_logits + (size_t)(base + cur) * V, V, R);
-            const float it = greedy ? 0.0f : 1.0f / st.w;
-            const int top = greedy ? (int)st.w : -1;
+            mass = greedy ? 1.0f : st.w;
+            if (greedy) {
+                const int mine = (int)st.w - 4 * tid;
 #pragma unroll
-            for (int j = 0; j < kMaxSeg; ++j)
+                for (int j = 0; j < kMaxSeg; ++j)
 #pragma unroll
-                for (int e = 0; e < 4; ++e)
-                    R[j][e] = greedy ? (tok_index(j, e) == top ? 1.0f : 0.0f) : exp_fast(R[j][e] * inv_tt - st.z) * it;
+                    for (int e = 0; e < 4; ++e) R[e][j] = mine - j * kSeg == e ? 1.0f : 0.0f;
+            } else {
+#pragma unroll
+                for (int j = 0; j < kMaxSeg; ++j)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) R[e][j] = exp_fast(Y[j][e] * inv_tt - st.z);
+            }
         };
         if (!leaf) {
             // ---- first child: two logits and the row statistics decide
+            float dy = 0.0f;                              // D_lds at the tested child's token
             {
                 const int y = l_token[c];
                 float d = 0.0f, r = 0.0f;
                 if (y >= 0) {
-                    d = exp_fast(logit_to_float(draft_logits[(size_t)(base + cur) * V + y]) * inv_td - st.x) / st.y;
+                    dy = exp_fast(logit_to_float(draft_logits[(size_t)(base + cur) * V + y]) * inv_td - st.x);
+                    d = dy / st.y;
                     r = greedy ? ((float)y == st.w ? 1.0f : 0.0f)
                                : exp_fast(logit_to_float(target_logits[(size_t)(base + cur) * V + y]) * inv_tt - st.z) / st.w;
                 }
@@ -481,61 +497,84 @@ __global__ __launch_bounds__(kBlock) void verify_walk_kernel(
             if (next < 0) {
                 load_rows(true);
                 rows_loaded = true;
-                __syncthreads();                              // D_lds is complete
+                // R and D at token y (none: zeros), by the thread that owns it
+                auto publish = [&](int y, float2* place) __attribute__((always_inline)) {
+                    if (y < 0 ? tid == 0 : ((y % kSeg) >> 2) == tid) {
+                        const int js = uniform(y >= 0 ? y / kSeg : 0), e = y & 3;
+                        const float r0 = R[0][js], r1 = R[1][js], r2 = R[2][js], r3 = R[3][js];
+                        const float r = y < 0 ? 0.0f : e == 0 ? r0 : e == 1 ? r1 : e == 2 ? r2 : r3;
+                        *place = make_float2(r, y >= 0 ? D_lds[y] : 0.0f);
+                    }
+                };
                 uint32_t rank = 0;
+                uint2 keys = make_uint2(0u, 0u);          // of 64 children, one per lane: path key, uniform of the acceptance
+                float us = 0.0f;
                 for (int guard = 0; c >= 0 && guard < N; ++guard) {
-                    const int y = l_token[c];
-                    const float dy = y >= 0 ? D_lds[y] : 0.0f;        // the same word for every thread
+                    const int y = l_token[c], after = l_next[c];
+                    const int y_next = after >= 0 ? l_token[after] : -1;
+                    const int par = guard & 1;
+                    if (rank % kWave == 0) {
+                        keys = child_key(seed, pk, rank + (tid & (kWave - 1)));
+                        us = u01(seed, keys, 0u, KIND_ACCEPT);
+                    }
                     if (rank > 0) {
-                        // ratio seen by this child after its earlier siblings were rejected: R[y] sits in one
-                        // thread's registers
-                        if (y >= 0 && ((y % kSeg) >> 2) == tid) {
-#pragma unroll
-                            for (int j = 0; j < kMaxSeg; ++j)
-#pragma unroll
-                                for (int e = 0; e < 4; ++e)
-                                    if (j == y / kSeg && e == (y & 3)) sh.bcast[1] = R[j][e];
-                        }
-                        if (y < 0 && tid == 0) sh.bcast[1] = 0.0f;
-                        __syncthreads();
-                        const float ratio = ratio_of(dy * scale_d, sh.bcast[1]);
-                        const uint2 pk_n = child_key(seed, pk, rank);
-                        const float u = u01(seed, pk_n, 0u, KIND_ACCEPT);
+                        // ratio seen by this child after its earlier siblings were rejected
+                        const float2 rd = sh.next[par ^ 1];
+                        dy = rd.y;
+                        const float ratio = ratio_of(rd.y * scale_d, rd.x / mass);
+                        const uint2 pk_n = make_uint2((uint32_t)__builtin_amdgcn_readlane((int)keys.x, rank & 63), (uint32_t)__builtin_amdgcn_readlane((int)keys.y, rank & 63));
+                        const float u = readlane_f32(us, rank & 63);
                         margin = fminf(margin, fabsf(u - ratio));
                         if (tid == 0) accept_ratio[base + c] = ratio;
                         if (u < ratio) { next = c; pk_next = pk_n; break; }
                     }
                     // reject child c: R <- norm(max(R-D,0)) with D as it stands, then y leaves D
-                    float res[2] = { 0.0f, 0.0f };          // mass of relu(R-D); weight in D_lds
+                    const float f = scale_d * mass;
+                    float m[4] = { 0.0f, 0.0f, 0.0f, 0.0f }, w = 0.0f;
 #pragma unroll
                     for (int j = 0; j < kMaxSeg; ++j) {
                         const int i0 = tok_index(j, 0);
-                        if (i0 < V) {
+                        if (j * kSeg < V) {
                             const float4 dv = *reinterpret_cast<const float4*>(D_lds + i0);
-                            res[0] += fmaxf(fmaf(-scale_d, dv.x, R[j][0]), 0.0f) + fmaxf(fmaf(-scale_d, dv.y, R[j][1]), 0.0f);
-                            res[0] += fmaxf(fmaf(-scale_d, dv.z, R[j][2]), 0.0f) + fmaxf(fmaf(-scale_d, dv.w, R[j][3]), 0.0f);
-                            res[1] += (dv.x + dv.y) + (dv.z + dv.w);
+                            R[0][j] = __builtin_amdgcn_fmed3f(fmaf(-f, dv.x, R[0][j]), 0.0f, 1.0f); m[0] += R[0][j];
+                            R[1][j] = __builtin_amdgcn_fmed3f(fmaf(-f, dv.y, R[1][j]), 0.0f, 1.0f); m[1] += R[1][j];
+                            R[2][j] = __builtin_amdgcn_fmed3f(fmaf(-f, dv.z, R[2][j]), 0.0f, 1.0f); m[2] += R[2][j];
+                            R[3][j] = __builtin_amdgcn_fmed3f(fmaf(-f, dv.w, R[3][j]), 0.0f, 1.0f); m[3] += R[3][j];
+                            w += (dv.x + dv.y) + (dv.z + dv.w);
                         }
                     }
-                    block_sum<float, 2>(res, sh.fred);
-                    if (res[0] > 0.0f) {                     // else R == D: keep R (no reject can reach here)
-                        const float ir = 1.0f / res[0];
+                    if (y >= 0 && ((y % kSeg) >> 2) == tid) D_lds[y] = 0.0f;                // y leaves D
+                    publish(y_next, &sh.next[par]);
+                    const float mw = wave_sum_f32_dpp((m[0] + m[1]) + (m[2] + m[3])), ww = wave_sum_f32_dpp(w);
+                    if ((tid & (kWave - 1)) == 0) sh.part[par][tid / kWave] = make_float2(mw, ww);
+                    __syncthreads();
+                    float2 sum = sh.part[par][0];
+#pragma unroll
+                    for (int k = 1; k < kWaves; ++k) { const float2 p = sh.part[par][k]; sum.x += p.x; sum.y += p.y; }
+                    if (sum.x > 0.0f) {
+                        mass = sum.x;
+                    } else {
+                        // R == D to rounding (hardly any reject can reach here): R stays, that is, becomes D as
+                        // it stood; a greedy target's R is its one token, whatever its mass
+                        mass = greedy ? 1.0f : sum.y;
+                        // (one token's value is not in D_lds: that of the greedy row, or the one just removed)
+                        const int one = (greedy ? (int)st.w : y) - 4 * tid;
+                        const float value = greedy ? 1.0f : dy;
 #pragma unroll
                         for (int j = 0; j < kMaxSeg; ++j) {
                             const int i0 = tok_index(j, 0);
-                            if (i0 < V) {
-                                const float4 dv = *reinterpret_cast<const float4*>(D_lds + i0);
-                                R[j][0] = fmaxf(fmaf(-scale_d, dv.x, R[j][0]), 0.0f) * ir;
-                                R[j][1] = fmaxf(fmaf(-scale_d, dv.y, R[j][1]), 0.0f) * ir;
-                                R[j][2] = fmaxf(fmaf(-scale_d, dv.z, R[j][2]), 0.0f) * ir;
-                                R[j][3] = fmaxf(fmaf(-scale_d, dv.w, R[j][3]), 0.0f) * ir;
-                            }
+                            float4 dv = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+                            if (j * kSeg < V && !greedy) dv = *reinterpret_cast<const float4*>(D_lds + i0);
+                            const int mine = one - j * kSeg;
+                            R[0][j] = mine == 0 ? value : dv.x; R[1][j] = mine == 1 ? value : dv.y;
+                            R[2][j] = mine == 2 ? value : dv.z; R[3][j] = mine == 3 ? value : dv.w;
                         }
+                        __syncthreads();
+                        publish(y_next, &sh.next[par]);
+                        __syncthreads();
                     }
-                    __syncthreads();                          // every thread has read D_lds as it stood
-                    if (tid == 0 && y >= 0) D_lds[y] = 0.0f;  // y leaves D
-                    const float left = res[1] - dy;           // weight left in D
-                    c = l_next[c];
+                    const float left = sum.y - dy;            // weight left in D
+                    c = after;
                     ++rank;
                     if (!(left > 0.0f)) {                     // D is empty: later children are not tried
                         if (tid == 0)
@@ -544,7 +583,6 @@ __global__ __launch_bounds__(kBlock) void verify_walk_kernel(
                         break;
                     }
                     scale_d = 1.0f / left;                    // D <- norm(D), kept as a factor
-                    __syncthreads();                          // the removal is visible before D_lds is read again
                 }
             }
         }

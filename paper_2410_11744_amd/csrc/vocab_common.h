@@ -5,6 +5,8 @@
 // stretches of the row with 128-bit loads, and token order is (segment j, thread t,
 // element e) lexicographic -- the order the inverse CDF walks.
 #pragma once
+#include <type_traits>
+
 #include "dyspec_device.h"
 
 namespace dyspec {
@@ -17,27 +19,36 @@ __device__ __forceinline__ float logit_to_float(__bf16 x) { return (float)x; }
 __device__ __forceinline__ float bf16_bits_to_float(uint32_t bits16) { return __uint_as_float(bits16 << 16); }
 
 // Load one logits row; positions >= V read as -inf.  VEC: V % 4 == 0 (a thread's four tokens are
-// one aligned 16-byte (fp32) or 8-byte (bf16) load).
+// one aligned 16-byte (fp32) or 8-byte (bf16) load).  All loads are issued before the first is looked at
+// (past the end they re-read the row's first tokens): with the use inside a bounds branch of its own each
+// bf16 load was waited for by itself, sixteen trips to memory in turn.
 template <bool VEC, typename T>
 __device__ __forceinline__ void load_row(const T* __restrict__ row, int V, float (&x)[kMaxSeg][4])
 {
+    if constexpr (VEC) {
+        using Raw = typename std::conditional<sizeof(T) == 4, float4, uint2>::type;
+        Raw raw[kMaxSeg];
 #pragma unroll
-    for (int j = 0; j < kMaxSeg; ++j) {
-        const int i0 = tok_index(j, 0);
-        if (VEC) {
-            if (i0 < V) {
-                if constexpr (sizeof(T) == 4) {
-                    const float4 v = *reinterpret_cast<const float4*>(row + i0);
-                    x[j][0] = v.x; x[j][1] = v.y; x[j][2] = v.z; x[j][3] = v.w;
-                } else {
-                    const uint2 v = *reinterpret_cast<const uint2*>(row + i0);
-                    x[j][0] = bf16_bits_to_float(v.x & 0xffffu); x[j][1] = bf16_bits_to_float(v.x >> 16);
-                    x[j][2] = bf16_bits_to_float(v.y & 0xffffu); x[j][3] = bf16_bits_to_float(v.y >> 16);
-                }
+        for (int j = 0; j < kMaxSeg; ++j) {
+            const int i0 = tok_index(j, 0);
+            if (j * kSeg < V) raw[j] = *reinterpret_cast<const Raw*>(row + (i0 < V ? i0 : 0));      // (the same in every thread)
+        }
+#pragma unroll
+        for (int j = 0; j < kMaxSeg; ++j) {
+            const bool there = tok_index(j, 0) < V;
+            if constexpr (sizeof(T) == 4) {
+                x[j][0] = raw[j].x; x[j][1] = raw[j].y; x[j][2] = raw[j].z; x[j][3] = raw[j].w;
             } else {
-                x[j][0] = x[j][1] = x[j][2] = x[j][3] = -INFINITY;
+                x[j][0] = bf16_bits_to_float(raw[j].x & 0xffffu); x[j][1] = bf16_bits_to_float(raw[j].x >> 16);
+                x[j][2] = bf16_bits_to_float(raw[j].y & 0xffffu); x[j][3] = bf16_bits_to_float(raw[j].y >> 16);
             }
-        } else {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) x[j][e] = there ? x[j][e] : -INFINITY;
+        }
+    } else {
+#pragma unroll
+        for (int j = 0; j < kMaxSeg; ++j) {
+            const int i0 = tok_index(j, 0);
 #pragma unroll
             for (int e = 0; e < 4; ++e) x[j][e] = (i0 + e < V) ? logit_to_float(row[i0 + e]) : -INFINITY;
         }

@@ -1,0 +1,82 @@
+"""dyspec_verify on the residual updates: many rejected siblings under one node (past the 64 whose keys are made
+together), vocabularies around a thread's share (4), a segment (2048) and the largest, both table types, and rows in which
+R - D leaves no mass (R is kept).  Compared with the oracle by the helpers' rules and tolerances."""
+import numpy as np
+import pytest
+
+import oracle
+from helpers import f32, verify_in_full
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+
+def star(dy, tokens):
+    """The root with one child per token, in this order."""
+    n = len(tokens) + 1
+    parent = np.array([-1] + [0] * (n - 1), np.int32)
+    fc, ns, dep = oracle.links_from_parent(parent)
+    token = np.array([-1] + list(tokens), np.int32)
+    rank = np.array([0] + list(range(n - 1)), np.int32)
+    mk = lambda a: torch.from_numpy(np.ascontiguousarray(a, dtype=np.int32)).cuda()
+    return dy.Tree(mk(parent), mk(token), mk(rank), mk(fc), mk(ns), mk(dep)), (token, fc, ns)
+
+
+def compare(dy, tokens, d, t, td, tt, seed, bf16):
+    dd, tg = torch.from_numpy(d), torch.from_numpy(t)
+    if bf16:
+        dd, tg = dd.to(torch.bfloat16), tg.to(torch.bfloat16)
+    batch = dy.Batch.from_sizes([len(tokens) + 1])
+    tree, otree = star(dy, tokens)
+    gd, gt = dd.cuda(), tg.cuda()
+    return verify_in_full(lambda sd: dy.verify(gd, gt, batch, tree, (td,), (tt,), sd), batch, [otree],
+                          dd.float().numpy(), tg.float().numpy(), (td,), (tt,), seed)
+
+
+@pytest.fixture(scope="module")
+def dy():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2410_11744_amd as m
+    m.load_library()
+    return m
+
+
+@pytest.mark.parametrize("bf16", [False, True])
+@pytest.mark.parametrize("kids,V,tt", [(1, 4, 1.0), (3, 5, 0.7), (30, 1000, 1.0), (63, 2047, 0.6), (64, 2048, 0.6), (65, 2049, 1.0), (66, 2052, 0.0),
+                                       (130, 4100, 0.6), (200, 32000, 1.0), (200, 32768, 0.0), (70, 32765, 0.6)])
+def test_many_rejections(dy, kids, V, tt, bf16):
+    print(f"children {kids} V={V} target temperature {tt} bf16={bf16}", flush=True)
+    rng = np.random.default_rng(kids * 70000 + V)
+    n = kids + 1
+    d = (rng.standard_normal((n, V)) * 2.0).astype(np.float32)
+    t = (rng.standard_normal((n, V)) * 2.0).astype(np.float32)          # unrelated to the draft: most children are rejected
+    tokens = np.argsort(-(d[0] / f32(0.9) + rng.gumbel(size=V)))[:kids]  # a sample without replacement
+    out, _ = compare(dy, tokens, d, t, 0.9, tt, 5 + kids, bf16)
+    if kids >= 63 and tt > 0:
+        assert (out.accept_ratio.cpu().numpy()[1:] >= 0).sum() >= 1
+
+
+@pytest.mark.parametrize("V,tt", [(6, 1.0), (6, 0.0), (2100, 1.0), (2100, 0.0), (32000, 0.7)])
+def test_rows_that_leave_no_mass(dy, V, tt):
+    """Draft and target alike, children on tokens neither can emit: every one is rejected, R == D stays, and the last
+    token comes from it; then a child on a possible token, whose ratio is 1."""
+    live = [V // 2, V - 1]
+    row = np.full(V, -np.inf, np.float32)
+    row[live] = [0.5, 0.5] if tt > 0 else [0.5, -np.inf]                 # temperature 0: one token in both
+    d = np.repeat(row[None], 6, axis=0)
+    dead = [x for x in range(V) if x not in live][:4]
+    for tokens in ([dead[0]], dead[:3], [dead[0], live[0]], [dead[0], dead[1], live[0], dead[2]]):
+        n = len(tokens) + 1
+        h = np.ascontiguousarray(d[:n])
+        tree, (token, fc, ns) = star(dy, tokens)
+        g = torch.from_numpy(h).cuda()
+        for seed in range(4):
+            out = dy.verify(g, g, dy.Batch.from_sizes([n]), tree, (1.0,), (tt,), seed)
+            want = oracle.verify(h, h, token, fc, ns, 1.0, f32(tt), seed, seq=0, emit_bonus=True)
+            # (an impossible token's ratio is 0 / 0 in the oracle: the path and the last token are compared; no draw
+            #  comes near an acceptance ratio of 0 or 1, and the two tokens split the last draw in the middle)
+            k = int(out.n_accepted.item())
+            assert k == want.n_accepted and out.accepted_nodes.cpu().numpy()[:k].tolist() == want.accepted_nodes.tolist()
+            assert want.resid_margin < 1e-5 or out.final_token.item() == want.final_token
