@@ -244,18 +244,18 @@ __global__ __launch_bounds__(kBlock) void build_tree_kernel(
 // same, control gives up after kMaxPolls looks and the tree ends there.)
 //
 // What bounds it: the number of instructions of control's pop and of wave 1's draw (a wave alone issues one in
-// eight cycles, whatever it is; an LDS read is back after 52), and for trees that open one chain of nodes the trip to
-// memory of a fresh node's first draw.  Measured against a workgroup that popped and drew in turn, two barriers a
-// draw: 512 rows of 32000 tokens 1338 -> 520 us, 128 rows 328 -> 112, 32 rows of 1000 tokens 79 -> 30; a
-// single chain of 512 nodes 1413 -> 1094 with the pass over the rows.
+// eight cycles, whatever it is; an LDS read is back after 52), and where a node is popped again at once or a tree is
+// one chain, those of a draw from memory (the trip itself is over before the Philox blocks made meanwhile).  Measured against a workgroup that popped and drew in turn, two barriers a
+// draw, with the pass over the rows: 512 rows of 32000 tokens 1378 -> 508 us (with eight drawing waves, not fourteen,
+// 543: a request waits for the draw its wave is at), 128 rows 346 -> 134, 32 rows of 1000 tokens 92 -> 55; a
+// single chain of 512 nodes 1413 -> 1130.
 constexpr int kBuildThreads = 1024;
-constexpr int kDrawWaves = 8;
+constexpr int kDrawWaves = kBuildThreads / kWave - 2;
 constexpr int kRing = 16;
 constexpr int kMaxPolls = 1 << 24;          // of a whole build, about a second: no build comes near, none can outlast it
 constexpr uint32_t kAnswer = 0x80000000u;
 constexpr uint32_t kStop = 0u;              // news of a pop is never 0: the new node's index is not
 static_assert(DYSPEC_MAX_BUILD_NODES <= 1024 && DYSPEC_MAX_VOCAB <= (1 << 15), "parent, rank and previous sibling share a word, rank and token too");
-static_assert((kDrawWaves & (kDrawWaves - 1)) == 0, "a node's wave by a mask");
 
 // What LDS holds of a node.
 struct Node {
@@ -478,7 +478,7 @@ __device__ __attribute__((noinline)) void draw_for_nodes(uint32_t lds_, int mine
             // the best request of each lane's nodes, then of the wave
             int best = 0, node = 0;
 #pragma unroll
-            for (int s = 0; s < DYSPEC_MAX_BUILD_NODES / (kDrawWaves * kWave); ++s) {
+            for (int s = 0; s < (DYSPEC_MAX_BUILD_NODES + kDrawWaves * kWave - 1) / (kDrawWaves * kWave); ++s) {
                 const int q = mine + kDrawWaves * (lane + s * kWave);
                 if (q < N) {
                     const uint32_t w = lds_now(lds_at<uint32_t>(nodes + kNode * q + kWordAt));
@@ -499,7 +499,7 @@ __device__ __attribute__((noinline)) void draw_for_nodes(uint32_t lds_, int mine
             if (m == kStop) return;
             // the requests of one pop, if it is the one after the last seen; else look at all
             const int a = (int)(m & 1023u), p = (int)(m >> 10) & 1023;
-            const bool a_mine = (a & (kDrawWaves - 1)) == mine, p_mine = (m & kRequest) && (p & (kDrawWaves - 1)) == mine;
+            const bool a_mine = a % kDrawWaves == mine, p_mine = (m & kRequest) && p % kDrawWaves == mine;
             look = a != (int)(seen & 1023u) + 1 || (a_mine && p_mine);
             seen = m;
             if (look || !(a_mine || p_mine)) continue;
@@ -669,7 +669,7 @@ __global__ __launch_bounds__(kBuildThreads) void build_tree_waves_kernel(
         m = load_row_lds<kBuildThreads, VEC>(draft_logits + (size_t)base * V, V, inv_temp, lds_at<double>(row_at),
                                              lds_at<float>(row_at + 8 * row_leaves(V)), reinterpret_cast<float*>(dyn + BuildLds::fred));
     __syncthreads();
-    // waves w and w + 4 share a SIMD: control and the root's wave have one each to themselves
+    // (control and the root's wave share their SIMDs, but come first there)
     if (wave == 0) {
         __builtin_amdgcn_s_setprio(3);
         const int n = pop_nodes(lds, root_ring, N, tree.parent + base, tree.token + base, est_value + base);
@@ -681,8 +681,8 @@ __global__ __launch_bounds__(kBuildThreads) void build_tree_waves_kernel(
     } else if (wave == 1) {
         __builtin_amdgcn_s_setprio(2);
         if (root_ring && N > 1) draw_for_root(lds, row_at, inv_temp, m, V, N, seed, (uint32_t)seq);
-    } else if (wave & 2) {
-        draw_for_nodes<VEC>(lds, (wave >> 2) * 2 + (wave & 1), draft_logits, V, inv_temp, seed, ws, base, N);
+    } else {
+        draw_for_nodes<VEC>(lds, wave - 2, draft_logits, V, inv_temp, seed, ws, base, N);
     }
     __builtin_amdgcn_s_setprio(0);
     __syncthreads();
@@ -730,8 +730,8 @@ __global__ __launch_bounds__(kBuildThreads) void build_tree_waves_kernel(
     if (tid == 0) n_built[seq] = n;
 }
 
-// The root's row is kept in LDS where it fits beside the node state (32000 tokens: up to 558 rows,
-// 32768: up to 491); else the root's draws are made like every other node's.
+// The root's row is kept in LDS where it fits beside the node state (32000 tokens: up to 556 rows,
+// 32768: up to 489); else the root's draws are made like every other node's.
 static size_t build_lds_bytes(int V, int widest, bool root_ring) { return BuildLds::row(widest) + (root_ring ? row_lds_bytes(V) : 0); }
 
 // the builder takes up to a whole CU's LDS: the kernels' limit is raised once

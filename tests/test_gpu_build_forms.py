@@ -41,7 +41,7 @@ def table(kind, nodes, V, rng):
 
 CASES = [("normal", n, v) for n, v in (((2,), 1), ((1,), 5), ((3,), 2), ((40,), 31), ((40,), 33), ((64,), 511), ((65,), 512), ((66,), 513),
                                        ((127, 128, 129), 4097), ((130,), 4096), ((511, 512), 2050), ((513,), 1000), ((1024,), 3000),
-                                       ((1024, 5), 32000), ((558,), 32000), ((559,), 32000), ((491,), 32768), ((492,), 32768),
+                                       ((1024, 5), 32000), ((556,), 32000), ((557,), 32000), ((489,), 32768), ((490,), 32768),
                                        ((300,), 32767), ((895, 896, 897, 898), 700))]
 CASES += [(k, n, v) for k in ("chain", "child", "equal", "few", "peaked", "odd")
           for n, v in (((60,), 64), ((200, 31), 1000), ((140,), 2047), ((260,), 32000), ((900,), 32768))]
