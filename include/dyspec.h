@@ -6,7 +6,8 @@
  * Conventions shared by every entry point
  *  - Pointers marked DEVICE address HBM of the current HIP device; pointers marked HOST
  *    address ordinary host memory that is read before the call returns.  The caller owns
- *    every buffer; the library allocates nothing and keeps no state between calls.
+ *    every buffer; the library allocates no device memory and keeps no state between calls
+ *    (dyspec_build_tree_threshold shares 8 KB of pinned host memory among the calls in progress).
  *  - Work is enqueued on `hip_stream` (a hipStream_t passed as void*, NULL = default
  *    stream); calls return without synchronising.  Two calls that write the same buffers
  *    race unless ordered by the stream.  Apart from dyspec_build_tree_threshold (which
@@ -94,7 +95,7 @@ const char* dyspec_status_string(dyspec_status s);
  * kernels, raises their dynamic-LDS limits, takes the address of the static scratch array.
  * Every entry point does what it needs of this at its first use; calling dyspec_init first
  * moves those few milliseconds out of the first calls of a latency-sensitive loop.  Launches
- * nothing, allocates nothing; idempotent and safe to call from several threads.
+ * nothing, allocates only those 8 KB of host memory; idempotent and safe to call from several threads.
  */
 dyspec_status dyspec_init(void);
 

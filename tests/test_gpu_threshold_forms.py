@@ -5,6 +5,8 @@ around a leaf (32 tokens), a group (512) and a sweep of the workgroup (4096), dr
 Values: a value is a product of factors 1 - R, each computed with an absolute error of 2^-53 (rounding of R and of the
 difference).  No factor is below the value, so with values >= t the relative error is below 100 x 2^-52 / t where R comes
 close to 1: 2e-7 for the peaked table at t = 1e-7, inside the comparison's 1e-6 (at t = 1e-12 it would not be)."""
+import threading
+
 import numpy as np
 import pytest
 
@@ -41,3 +43,67 @@ def test_against_the_oracle(kind, cap, V, t):
         if compare_threshold_trees(built, batch, x, (0.8,), (t,), seed) == 1:
             return
     raise AssertionError("no table in 8 had all margins above 1e-9")
+
+
+@pytest.mark.parametrize("threads", [1, 8, 24])
+def test_calls_at_the_same_time(threads):
+    """Each thread on a stream of its own, trees of different depths: every call gets the levels of its own tree,
+    also where more calls run than the library has host memory for (8)."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2410_11744_amd as dy
+    sizes, temps, times = ([16, 200], [1], [64, 3, 500], [400]), (0.8,), 12
+    x = torch.from_numpy(np.random.default_rng(5).standard_normal((700, 1000)).astype(np.float32) * 3).cuda()
+    jobs = []
+    for k in range(threads):
+        batch = dy.Batch.from_sizes(sizes[k % 4])
+        jobs.append((x[k:k + batch.total_nodes].clone(), batch, (0.004, 0.05, 0.3)[k % 3], 70 + k))
+
+    def build(job):
+        d, batch, t, seed = job
+        built, levels = dy.build_tree_threshold(d, batch, temps * batch.n_seq, t, seed)
+        return levels, built.n_built.cpu().tolist(), built.tree.token.cpu().tolist(), built.tree.parent.cpu().tolist()
+
+    want = [build(j) for j in jobs]
+    wrong = []
+
+    def work(k):
+        try:
+            with torch.cuda.stream(torch.cuda.Stream()):
+                for _ in range(times):
+                    if build(jobs[k]) != want[k]:
+                        wrong.append(k)
+        except Exception as e:          # reported by the main thread
+            wrong.append(repr(e))
+
+    torch.cuda.synchronize()
+    pool = [threading.Thread(target=work, args=(k,)) for k in range(threads)]
+    for t in pool:
+        t.start()
+    for t in pool:
+        t.join()
+    assert not wrong
+    torch.cuda.synchronize()
+
+
+def test_refused_under_capture():
+    """The call waits for its levels: on a capturing stream it returns an error, having launched nothing, and the
+    capture goes on."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2410_11744_amd as dy
+    batch = dy.Batch.from_sizes([32])
+    x = torch.from_numpy(np.random.default_rng(6).standard_normal((32, 500)).astype(np.float32) * 3).cuda()
+    want = dy.build_tree_threshold(x, batch, (0.8,), 0.05, 3)[0].tree.token.clone()
+    y = torch.zeros(32, device="cuda")
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        with pytest.raises(dy.DyspecError):
+            dy.build_tree_threshold(x, batch, (0.8,), 0.05, 3)
+        y += 1.0
+    for k in range(3):
+        graph.replay()
+        torch.cuda.synchronize()
+        assert y.eq(k + 1.0).all()
+        assert torch.equal(dy.build_tree_threshold(x, batch, (0.8,), 0.05, 3)[0].tree.token, want)
