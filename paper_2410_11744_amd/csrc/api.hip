@@ -96,7 +96,7 @@ int32_t dyspec_mask_words(const dyspec_batch* batch)
 size_t dyspec_workspace_bytes(int32_t which, const dyspec_batch* batch, int32_t, int32_t n_q_heads, int32_t n_kv_heads,
                               int32_t head_dim)
 {
-    // the tree builder keeps the rows' segment sums there; tree attention its partial results
+    // the tree builder keeps the rows' run totals and drawn tokens there; tree attention its partial results
     // when it splits the prefix over several workgroups; verification needs none
     SeqArgs sa;
     if (which == DYSPEC_WS_BUILD_TREE)

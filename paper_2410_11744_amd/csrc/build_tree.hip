@@ -245,8 +245,8 @@ __global__ __launch_bounds__(kBlock) void build_tree_kernel(
 //
 // What bounds it: the number of instructions of control's pop and of wave 1's draw (a wave alone issues one in
 // eight cycles, whatever it is; an LDS read is back after 52), and where a node is popped again at once or a tree is
-// one chain, those of a draw from memory (the trip itself is over before the Philox blocks made meanwhile).  Measured against a workgroup that popped and drew in turn, two barriers a
-// draw, with the pass over the rows: 512 rows of 32000 tokens 1378 -> 508 us (with eight drawing waves, not fourteen,
+// one chain, those of a draw from memory (the trip itself is over before the Philox blocks made meanwhile).
+// Measured against a workgroup that popped and drew in turn, two barriers a draw, with the pass over the rows: 512 rows of 32000 tokens 1378 -> 508 us (with eight drawing waves, not fourteen,
 // 543: a request waits for the draw its wave is at), 128 rows 346 -> 134, 32 rows of 1000 tokens 92 -> 55; a
 // single chain of 512 nodes 1413 -> 1130.
 constexpr int kBuildThreads = 1024;

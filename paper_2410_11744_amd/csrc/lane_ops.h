@@ -1,5 +1,5 @@
-// Cross-lane helpers of the serial tree builders: DPP moves, lane reads, wave-wide maximum, sum
-// and scan in fp64.
+// Cross-lane helpers of the tree builders and the verification walk: DPP moves, lane reads, wave-wide maximum, sum
+// and scan; LDS accesses between waves that do not meet at a barrier.
 #pragma once
 #include "vocab_common.h"
 

@@ -531,8 +531,20 @@ __global__ __launch_bounds__(kBlock) void verify_walk_kernel(
                         if (tid == 0) accept_ratio[base + c] = ratio;
                         if (u < ratio) { next = c; pk_next = pk_n; break; }
                     }
-                    // reject child c: R <- norm(max(R-D,0)) with D as it stands, then y leaves D
+                    // reject child c: R <- norm(max(R-D,0)) with D as it stands, then y leaves D.  (The owner of
+                    // y does so for y first: what is left of D is summed without y, where a sum with y less
+                    // its weight would lose what y outweighs.)
                     const float f = scale_d * mass;
+                    if (y >= 0 && ((y % kSeg) >> 2) == tid) {
+                        const int js = uniform(y / kSeg), e = y & 3;
+                        const float dv = D_lds[y];
+                        D_lds[y] = 0.0f;
+#pragma unroll
+                        for (int k = 0; k < 4; ++k) {
+                            const float r = R[k][js];
+                            R[k][js] = e == k ? __builtin_amdgcn_fmed3f(fmaf(-f, dv, r), 0.0f, 1.0f) : r;
+                        }
+                    }
                     float m[4] = { 0.0f, 0.0f, 0.0f, 0.0f }, w = 0.0f;
 #pragma unroll
                     for (int j = 0; j < kMaxSeg; ++j) {
@@ -546,7 +558,6 @@ __global__ __launch_bounds__(kBlock) void verify_walk_kernel(
                             w += (dv.x + dv.y) + (dv.z + dv.w);
                         }
                     }
-                    if (y >= 0 && ((y % kSeg) >> 2) == tid) D_lds[y] = 0.0f;                // y leaves D
                     publish(y_next, &sh.next[par]);
                     const float mw = wave_sum_f32_dpp((m[0] + m[1]) + (m[2] + m[3])), ww = wave_sum_f32_dpp(w);
                     if ((tid & (kWave - 1)) == 0) sh.part[par][tid / kWave] = make_float2(mw, ww);
@@ -559,7 +570,7 @@ __global__ __launch_bounds__(kBlock) void verify_walk_kernel(
                     } else {
                         // R == D to rounding (hardly any reject can reach here): R stays, that is, becomes D as
                         // it stood; a greedy target's R is its one token, whatever its mass
-                        mass = greedy ? 1.0f : sum.y;
+                        mass = greedy ? 1.0f : sum.y + dy;
                         // (one token's value is not in D_lds: that of the greedy row, or the one just removed)
                         const int one = (greedy ? (int)st.w : y) - 4 * tid;
                         const float value = greedy ? 1.0f : dy;
@@ -576,7 +587,7 @@ __global__ __launch_bounds__(kBlock) void verify_walk_kernel(
                         publish(y_next, &sh.next[par]);
                         __syncthreads();
                     }
-                    const float left = sum.y - dy;            // weight left in D
+                    const float left = sum.y;                 // weight left in D
                     c = after;
                     ++rank;
                     if (!(left > 0.0f)) {                     // D is empty: later children are not tried

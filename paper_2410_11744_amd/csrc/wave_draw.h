@@ -5,8 +5,8 @@
 // CDF through the three levels: the wave compares its inclusive scan of the group totals with u * W, scans
 // the picked group's leaves, turns the picked leaf's logits into weights and scans those.  Nothing
 // but the wave's own instructions lies between two draws: no barrier, no trip to global memory.
-// Bound by the latency of that chain (two LDS reads, nine dependent DPP additions in fp64, one fp64
-// exponential).
+// Bound by the number of instructions, about 170 a draw: a wave alone issues one in eight cycles, dependent or not
+// (0.6 us a draw in the threshold builder; a workgroup of eight waves with two barriers a draw took 1.5).
 //
 // The sums are never updated by subtraction: the drawn token's leaf, its group and the scan of the
 // groups are each made of what is left (sum before + sum after the gap), so they are zero exactly

@@ -80,3 +80,29 @@ def test_rows_that_leave_no_mass(dy, V, tt):
             k = int(out.n_accepted.item())
             assert k == want.n_accepted and out.accepted_nodes.cpu().numpy()[:k].tolist() == want.accepted_nodes.tolist()
             assert want.resid_margin < 1e-5 or out.final_token.item() == want.final_token
+
+
+@pytest.mark.parametrize("bf16", [False, True])
+@pytest.mark.parametrize("V,rest", [(40, 1e-3), (40, 1e-5), (3000, 1e-4), (3001, 1e-6), (32000, 1e-5), (32765, 1e-6)])
+def test_ratio_behind_a_sibling_that_outweighs_the_rest(dy, V, rest, bf16):
+    """The first child's token holds all but `rest` of the draft row and is impossible for the target: rejected. The
+    second child's ratio divides by what is left of the draft row, against 64 bits.  Bound: weights exp(x) with
+    |x| <= 27 carry 2^-24 (3 |x| + 2) = 5e-6 each, in the row sums as well; sums of at most 64 terms in a row
+    another 4e-6 each, for draft and target: 3e-5 in all."""
+    rng = np.random.default_rng(V + int(1 / rest))
+    d = rng.standard_normal((3, V)).astype(np.float32)
+    t = rng.standard_normal((3, V)).astype(np.float32)
+    y1, y2 = V // 3, V - 2
+    d[0, y1] = np.log(np.exp(np.delete(d[0], y1).astype(np.float64)).sum() / rest)
+    t[0, y1] = -60.0
+    t[0, y2] = 8.0                                                      # R - D keeps it nearly whole
+    gd, gt = torch.from_numpy(d), torch.from_numpy(t)
+    if bf16:
+        gd, gt = gd.to(torch.bfloat16), gt.to(torch.bfloat16)
+    tree, _ = star(dy, [y1, y2])
+    out = dy.verify(gd.cuda(), gt.cuda(), dy.Batch.from_sizes([3]), tree, (1.0,), (1.0,), 11)
+    p, q = (np.exp(x.double().numpy()[0]) for x in (gd, gt))
+    p, q = p / p.sum(), q / q.sum()
+    r = np.maximum(q - p, 0.0)
+    left = np.delete(p, y1).sum()
+    np.testing.assert_allclose(out.accept_ratio.cpu().numpy()[2], r[y2] / r.sum() / (p[y2] / left), rtol=3e-5)
