@@ -390,6 +390,8 @@ __device__ __forceinline__ int draw_from_row(const RowVec (&w)[4], double u, Dra
 // before: 4.4 us each, 2.0 now (32000 tokens).  Both rows' loads are in flight together and every load is issued
 // before the first is used: a node's rows 5.8 -> 5.3 us in fp32, 12.9 -> 5.4 in bf16.
 // Verification of the ragged batch of eight 143 -> 105 us.
+// (R's sum shrinks with every rejection; below kSmallMass the weights are brought back to a sum of 1.)
+constexpr float kSmallMass = 9.5367431640625e-7f;     // 2^-20: weights of 1e-32 of the sum are still normal numbers
 struct WalkShared {
     DrawScratch draw;
     float2 part[2][kWaves];       // per wave, by parity of the rejection: mass left in R, weight in D
@@ -565,23 +567,33 @@ __global__ __launch_bounds__(kBlock) void verify_walk_kernel(
                     float2 sum = sh.part[par][0];
 #pragma unroll
                     for (int k = 1; k < kWaves; ++k) { const float2 p = sh.part[par][k]; sum.x += p.x; sum.y += p.y; }
-                    if (sum.x > 0.0f) {
+                    if (sum.x >= kSmallMass) {
                         mass = sum.x;
                     } else {
-                        // R == D to rounding (hardly any reject can reach here): R stays, that is, becomes D as
-                        // it stood; a greedy target's R is its one token, whatever its mass
-                        mass = greedy ? 1.0f : sum.y + dy;
-                        // (one token's value is not in D_lds: that of the greedy row, or the one just removed)
-                        const int one = (greedy ? (int)st.w : y) - 4 * tid;
-                        const float value = greedy ? 1.0f : dy;
+                        if (sum.x > 0.0f) {
+                            // R's weights are scaled up again long before the smallest of them are lost
+                            const float up = 1.0f / sum.x;
+                            mass = 1.0f;
 #pragma unroll
-                        for (int j = 0; j < kMaxSeg; ++j) {
-                            const int i0 = tok_index(j, 0);
-                            float4 dv = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-                            if (j * kSeg < V && !greedy) dv = *reinterpret_cast<const float4*>(D_lds + i0);
-                            const int mine = one - j * kSeg;
-                            R[0][j] = mine == 0 ? value : dv.x; R[1][j] = mine == 1 ? value : dv.y;
-                            R[2][j] = mine == 2 ? value : dv.z; R[3][j] = mine == 3 ? value : dv.w;
+                            for (int j = 0; j < kMaxSeg; ++j)
+#pragma unroll
+                                for (int e = 0; e < 4; ++e) R[e][j] = fminf(R[e][j] * up, 1.0f);
+                        } else {
+                            // R == D to rounding (hardly any reject can reach here): R stays, that is, becomes D as
+                            // it stood; a greedy target's R is its one token, whatever its mass
+                            mass = greedy ? 1.0f : sum.y + dy;
+                            // (one token's value is not in D_lds: that of the greedy row, or the one just removed)
+                            const int one = (greedy ? (int)st.w : y) - 4 * tid;
+                            const float value = greedy ? 1.0f : dy;
+#pragma unroll
+                            for (int j = 0; j < kMaxSeg; ++j) {
+                                const int i0 = tok_index(j, 0);
+                                float4 dv = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+                                if (j * kSeg < V && !greedy) dv = *reinterpret_cast<const float4*>(D_lds + i0);
+                                const int mine = one - j * kSeg;
+                                R[0][j] = mine == 0 ? value : dv.x; R[1][j] = mine == 1 ? value : dv.y;
+                                R[2][j] = mine == 2 ? value : dv.z; R[3][j] = mine == 3 ? value : dv.w;
+                            }
                         }
                         __syncthreads();
                         publish(y_next, &sh.next[par]);

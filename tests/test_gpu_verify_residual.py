@@ -106,3 +106,19 @@ def test_ratio_behind_a_sibling_that_outweighs_the_rest(dy, V, rest, bf16):
     r = np.maximum(q - p, 0.0)
     left = np.delete(p, y1).sum()
     np.testing.assert_allclose(out.accept_ratio.cpu().numpy()[2], r[y2] / r.sum() / (p[y2] / left), rtol=3e-5)
+
+
+@pytest.mark.parametrize("kids,V,tt", [(20, 50, 1.0), (300, 1000, 1.0), (300, 1000, 0.0), (700, 32000, 0.8)])
+def test_mass_that_shrinks_with_every_rejection(dy, kids, V, tt):
+    """What is left of the target lies on one token, which holds most of the draft row and is no child: each rejection
+    takes more than half of its weight (2^-700 in all), and the last token is still that one."""
+    rng = np.random.default_rng(kids + V)
+    d = (rng.standard_normal((kids + 1, V)) * 0.5).astype(np.float32)
+    t = d.copy()
+    top = V // 2
+    d[0, top] = np.log(2.0 * np.exp(np.delete(d[0], top).astype(np.float64)).sum())
+    t[0] = d[0]
+    t[0, top] += 3.0
+    tokens = np.array([x for x in rng.permutation(V) if x != top][:kids])
+    out, _ = compare(dy, tokens, d, t, 1.0, tt, 3, False)
+    assert out.n_accepted.item() == 0 and out.final_token.item() == top
