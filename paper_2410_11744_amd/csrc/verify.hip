@@ -572,12 +572,13 @@ __global__ __launch_bounds__(kBlock) void verify_walk_kernel(
                     } else {
                         if (sum.x > 0.0f) {
                             // R's weights are scaled up again long before the smallest of them are lost
-                            const float up = 1.0f / sum.x;
+                            // (in two steps: the sum's reciprocal alone may be past the range)
+                            const float lift = sum.x < 0x1p-100f ? 0x1p100f : 1.0f, up = 1.0f / (sum.x * lift);
                             mass = 1.0f;
 #pragma unroll
                             for (int j = 0; j < kMaxSeg; ++j)
 #pragma unroll
-                                for (int e = 0; e < 4; ++e) R[e][j] = fminf(R[e][j] * up, 1.0f);
+                                for (int e = 0; e < 4; ++e) R[e][j] = fminf(R[e][j] * lift * up, 1.0f);
                         } else {
                             // R == D to rounding (hardly any reject can reach here): R stays, that is, becomes D as
                             // it stood; a greedy target's R is its one token, whatever its mass

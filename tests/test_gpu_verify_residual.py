@@ -122,3 +122,19 @@ def test_mass_that_shrinks_with_every_rejection(dy, kids, V, tt):
     tokens = np.array([x for x in rng.permutation(V) if x != top][:kids])
     out, _ = compare(dy, tokens, d, t, 1.0, tt, 3, False)
     assert out.n_accepted.item() == 0 and out.final_token.item() == top
+
+
+@pytest.mark.parametrize("low", [-40.0, -60.0, -86.0])
+def test_what_is_left_weighs_next_to_nothing(dy, low):
+    """Draft and target alike but for one token of weight exp(low) that only the target has: after a rejected child it is
+    all that is left, however small."""
+    V, a, b = 2100, 7, 2099
+    d = np.full((4, V), -np.inf, np.float32)
+    d[:, a] = 0.0
+    t = d.copy()
+    t[:, b] = low
+    for tokens in ([3], [3, 2051], [3, 2051, 4]):
+        n = len(tokens) + 1
+        tree, _ = star(dy, tokens)
+        out = dy.verify(torch.from_numpy(d[:n].copy()).cuda(), torch.from_numpy(t[:n].copy()).cuda(), dy.Batch.from_sizes([n]), tree, (1.0,), (1.0,), 1)
+        assert out.n_accepted.item() == 0 and out.final_token.item() == b
