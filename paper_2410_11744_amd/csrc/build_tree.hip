@@ -18,6 +18,7 @@
 
 #include "draft_row.h"
 #include "lane_ops.h"
+#include "row_copies.h"
 #include "wave_draw.h"
 
 namespace dyspec {
@@ -434,7 +435,12 @@ __device__ __forceinline__ void draw_for_node(uint32_t place, uint32_t gone, con
     if (out & 2u) w[1] = 0.0;
     const double mine = w[0] + w[1];
     const double inc = wave_scan_dpp(mine);
-    const int ol = pick_lane(ballot(mine > 0.0) & ballot(run_start + inc > target), ballot(mine > 0.0));
+    const u64 live = ballot(mine > 0.0);
+    if (!live) {                                    // (the run's total says otherwise: not while totals and logits belong together)
+        if (lane == 0) publish(place, -1.0, 0ull, 0.f, kAnswer);
+        return;
+    }
+    const int ol = pick_lane(live & ballot(run_start + inc > target), live);
     const double mid = run_start + scan_at(inc, ol - 1) + w[0];     // (of interest in lane ol)
     const int second = (w[0] > 0.0 && (mid > target || !(w[1] > 0.0))) ? 0 : 1;
     const int e = __builtin_amdgcn_readlane(second, ol);
@@ -465,14 +471,13 @@ __device__ __attribute__((noinline)) void draw_for_nodes(uint32_t lds_, int mine
     double* const ws = uniform(ws_);
     const int lane = threadIdx.x & 63;
     const uint32_t nodes = lds + BuildLds::nodes, gone = lds + BuildLds::gone + mine * (kRun / 8);
-    HeldRow held, ahead;                            // the row drawn from last; the next new node's
-    held.node = -1;
-    ahead.node = -1;
-    int next_new = mine;
+    RowCopies<HeldRow> rows;
+    rows.open(mine);
+    const auto fetch = [&](int i, HeldRow& h) __attribute__((always_inline)) { fetch_row(ws, base, i, h); };
     uint32_t seen = 1u << 31;                       // the news last looked at (none yet)
     bool look = mine == 0;                          // requests may be open (node 0's, at the start)
     for (;;) {
-        if (ahead.node < next_new && next_new < N) fetch_row(ws, base, next_new, ahead);
+        rows.look_ahead(N, fetch);
         int i = -1, rank = 0;
         if (look) {
             // the best request of each lane's nodes, then of the wave
@@ -509,12 +514,8 @@ __device__ __attribute__((noinline)) void draw_for_nodes(uint32_t lds_, int mine
             if (w & kAnswer) continue;              // served already
             rank = (int)(w >> 15);
         }
-        if (held.node != i) {
-            if (ahead.node == i) held = ahead;
-            else fetch_row(ws, base, i, held);
-        }
-        if (i >= next_new) next_new = i + kDrawWaves;
-        draw_for_node<VEC>(nodes + kNode * i, gone, draft_logits + (size_t)(base + i) * V, V, inv_temp, seed, ws, base + i, held, rank);
+        rows.hold(i, kDrawWaves, fetch);
+        draw_for_node<VEC>(nodes + kNode * i, gone, draft_logits + (size_t)(base + i) * V, V, inv_temp, seed, ws, base + i, rows.held, rank);
         if (uniform(lds_now(lds_at<uint32_t>(lds + BuildLds::news))) == kStop) return;
     }
 }
