@@ -536,7 +536,16 @@ __global__ __launch_bounds__(kBlock) void verify_walk_kernel(
                     // reject child c: R <- norm(max(R-D,0)) with D as it stands, then y leaves D.  (The owner of
                     // y does so for y first: what is left of D is summed without y, where a sum with y less
                     // its weight would lose what y outweighs.)
-                    const float f = scale_d * mass;
+                    float f = scale_d * mass;
+                    if (f == INFINITY) {                      // what is left of D weighs next to nothing: R's weights come down to shares first
+                        const float down = 1.0f / mass;
+#pragma unroll
+                        for (int j = 0; j < kMaxSeg; ++j)
+#pragma unroll
+                            for (int e = 0; e < 4; ++e) R[e][j] *= down;
+                        mass = 1.0f;
+                        f = scale_d;                          // at most 2^126, as D's weights are normal numbers
+                    }
                     if (y >= 0 && ((y % kSeg) >> 2) == tid) {
                         const int js = uniform(y / kSeg), e = y & 3;
                         const float dv = D_lds[y];

@@ -138,3 +138,28 @@ def test_what_is_left_weighs_next_to_nothing(dy, low):
         tree, _ = star(dy, tokens)
         out = dy.verify(torch.from_numpy(d[:n].copy()).cuda(), torch.from_numpy(t[:n].copy()).cuda(), dy.Batch.from_sizes([n]), tree, (1.0,), (1.0,), 1)
         assert out.n_accepted.item() == 0 and out.final_token.item() == b
+
+
+@pytest.mark.parametrize("bf16", [False, True])
+@pytest.mark.parametrize("V", [2100, 2101, 32000, 32768])
+def test_draft_rest_far_below_the_first_child(dy, V, bf16):
+    """The draft row lies on a few tokens, 84 nats and more apart, all of them children; the target is flat: all children
+    are rejected and the last token is one of the others.  (A factor that turns the draft's weights into shares of a
+    target row of weight V is past the range of fp32 here.)"""
+    tokens = [V // 3, 5, V - 1]
+    d, t = np.full((4, V), -np.inf, np.float32), np.zeros((4, V), np.float32)
+    d[:, tokens[0]], d[:, tokens[1]], d[:, tokens[2]] = 0.0, -84.0, -87.0
+    tree, (token, fc, ns) = star(dy, tokens)
+    gd, gt = torch.from_numpy(d), torch.from_numpy(t)
+    if bf16:
+        gd, gt = gd.to(torch.bfloat16), gt.to(torch.bfloat16)
+    gd, gt = gd.cuda(), gt.cuda()
+    want = oracle.accept_ratio_all(d, t, token, fc, ns, 1.0, 1.0)
+    last = set()
+    for seed in range(16):
+        out = dy.verify(gd, gt, dy.Batch.from_sizes([4]), tree, (1.0,), (1.0,), seed)
+        # weights exp(x) with |x| <= 87 carry 2^-24 (3 |x| + 2) = 1.6e-5, twice in a ratio
+        np.testing.assert_allclose(out.accept_ratio.cpu().numpy(), want, rtol=5e-5, atol=1e-12)
+        assert out.n_accepted.item() == 0
+        last.add(out.final_token.item())
+    assert not last & set(tokens) and len(last) > 8
