@@ -576,10 +576,16 @@ __global__ __launch_bounds__(kBlock) void verify_walk_kernel(
                     float2 sum = sh.part[par][0];
 #pragma unroll
                     for (int k = 1; k < kWaves; ++k) { const float2 p = sh.part[par][k]; sum.x += p.x; sum.y += p.y; }
+                    // a draft row that is no distribution (no weight at all, or NaN among it) empties at once
+                    const bool no_draft = !(sum.y + dy > 0.0f);
                     if (sum.x >= kSmallMass) {
                         mass = sum.x;
                     } else {
-                        if (sum.x > 0.0f) {
+                        if (!(sum.x > 0.0f) && no_draft) {
+                            rows_loaded = false;              // the last token comes from the target row as it is
+                        } else if (!(sum.x > 0.0f) && !greedy && !(mass > 0.0f && fabsf(st.z) < INFINITY)) {
+                            // a target row that is no distribution: every child is rejected, no last token
+                        } else if (sum.x > 0.0f) {
                             // R's weights are scaled up again long before the smallest of them are lost
                             // (in two steps: the sum's reciprocal alone may be past the range)
                             const float lift = sum.x < 0x1p-100f ? 0x1p100f : 1.0f, up = 1.0f / (sum.x * lift);
@@ -612,7 +618,7 @@ __global__ __launch_bounds__(kBlock) void verify_walk_kernel(
                     const float left = sum.y;                 // weight left in D
                     c = after;
                     ++rank;
-                    if (!(left > 0.0f)) {                     // D is empty: later children are not tried
+                    if (!(left > 0.0f) || no_draft) {         // D is empty: later children are not tried
                         if (tid == 0)
                             for (int k = 0, cc = c; cc >= 0 && k < N; ++k, cc = l_next[cc])
                                 accept_ratio[base + cc] = -1.0f;

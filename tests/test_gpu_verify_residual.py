@@ -163,3 +163,47 @@ def test_draft_rest_far_below_the_first_child(dy, V, bf16):
         assert out.n_accepted.item() == 0
         last.add(out.final_token.item())
     assert not last & set(tokens) and len(last) > 8
+
+
+def spoilt(kind, rows, V, at, rng):
+    x = (rng.standard_normal((rows, V)) * 2.0).astype(np.float32)
+    if kind == "all -inf":
+        x[:] = -np.inf
+    elif kind == "one nan":
+        x[:, at] = np.nan
+    elif kind == "all nan":
+        x[:] = np.nan
+    elif kind == "one inf":
+        x[:, at] = np.inf
+    return x
+
+
+@pytest.mark.parametrize("bf16", [False, True])
+@pytest.mark.parametrize("draft,target,tt", [("fine", "all -inf", 1.0), ("fine", "one nan", 1.0), ("fine", "all nan", 1.0), ("fine", "one inf", 1.0),
+                                             ("all -inf", "fine", 1.0), ("one nan", "fine", 1.0), ("all nan", "fine", 1.0), ("one inf", "fine", 1.0),
+                                             ("one nan", "one nan", 1.0), ("all -inf", "all -inf", 1.0),
+                                             ("all -inf", "fine", 0.0), ("one nan", "fine", 0.0), ("one inf", "fine", 0.0)])
+def test_rows_that_are_no_distribution(dy, draft, target, tt, bf16):
+    """Against the oracle: under such a target row no child is accepted and there is no last token; after a draft row like
+    that the first child's rejection ends the scan, and the last token comes from the target row as it is.  (The
+    children are impossible for the target, so the first one is rejected.)"""
+    rng = np.random.default_rng(len(draft) * 100 + len(target))
+    last_tokens = 0
+    for V in (5, 2101, 4096):
+        for tokens in ([V // 2], [0, V - 1, 1, V // 2], [V // 2, V // 2 - 1, 0]):
+            n = len(tokens) + 1
+            d, t = spoilt(draft, n, V, V // 2, rng), spoilt(target, n, V, V // 2 + 1, rng)
+            if target != "all nan":
+                t[:, tokens] = -np.inf
+            dd, tg = torch.from_numpy(d), torch.from_numpy(t)
+            if bf16:
+                dd, tg = dd.to(torch.bfloat16), tg.to(torch.bfloat16)
+            tree, (token, fc, ns) = star(dy, tokens)
+            for seed in range(4):
+                out = dy.verify(dd.cuda(), tg.cuda(), dy.Batch.from_sizes([n]), tree, (1.0,), (tt,), seed)
+                want = oracle.verify(dd.float().numpy(), tg.float().numpy(), token, fc, ns, 1.0, tt, seed, seq=0, emit_bonus=True)
+                assert out.n_accepted.item() == want.n_accepted == 0
+                if want.final_token < 0 or want.resid_margin >= 1e-5:
+                    assert out.final_token.item() == want.final_token
+                    last_tokens += 1
+    assert last_tokens >= 24
