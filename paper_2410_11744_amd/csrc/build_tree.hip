@@ -580,11 +580,17 @@ __device__ __attribute__((noinline)) int pop_nodes(uint32_t lds_, int root_ring_
         const uint32_t mask = from_ring ? kAnswer | (1023u << 15) : kAnswer, want = from_ring ? kAnswer | (uint32_t)root_rank << 15 : kAnswer;
         uint32_t w = uniform(lds_now(lds_at<uint32_t>(place + kWordAt)));
         while ((w & mask) != want && --polls > 0) w = uniform(lds_now(lds_at<uint32_t>(place + kWordAt)));
-        const double R = *lds_at<double>(place);
+        double R = *lds_at<double>(place);
         const u64 child = *lds_at<u64>(place + kChildKeyAt);
         const uint32_t child_u = *lds_at<uint32_t>(place + kChildUAt);
         const uint32_t o = *lds_at<uint32_t>(place_p + kOpenedAt);
-        if (uniform(__double2hiint(R)) < 0 || polls <= 0) break;    // nothing left to sample under p
+        const int R_hi = uniform(__double2hiint(R));
+        if (R_hi < 0 || polls <= 0) {
+            if (polls <= 0 || R_hi == (int)0xbff00000u) break;      // (-1) nothing left to sample under p
+            // the quotient of two infinite weights, a NaN with its sign bit set: the token holds all that is left, at a
+            // temperature so small that the row's maximum over it is rounded by more than the range of exp
+            R = 1.0;
+        }
         // ---- node n = child number `rank` of p, its slot and p's next one (p's is opened first)
         const double v0 = v * R, v1 = v * (1.0 - R);
         const uint32_t rank = (w >> 15) & 1023u;

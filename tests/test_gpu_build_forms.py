@@ -66,3 +66,25 @@ def test_same_tree_as_without_a_workspace(kind, nodes, V):
         assert torch.equal(getattr(a.tree, name), getattr(b.tree, name)), name
     assert torch.equal(a.anc_mask, b.anc_mask)
     assert torch.equal(a.est_value, b.est_value)
+
+
+@pytest.mark.parametrize("nodes,V", [((8,), 5), ((40, 20), 1000), ((64,), 2047), ((600,), 32000)])
+def test_temperature_so_small_that_the_maximum_over_it_is_rounded(nodes, V):
+    """The largest logit is 20 everywhere: 20 / 1e-20 is rounded down by 65536, its weight is infinite, and it is still
+    all that there is: one chain of those tokens, as in the oracle, where 20 / 1e-20 less itself is 0."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2410_11744_amd as dy
+    from helpers import oracle_trees
+    rng = np.random.default_rng(V)
+    x = normal(rng, sum(nodes), V)
+    x = np.minimum(x, 19.0).astype(np.float32)
+    x[np.arange(len(x)), rng.integers(0, V, len(x))] = 20.0
+    batch = dy.Batch.from_sizes(nodes)
+    a = dy.build_tree(torch.from_numpy(x).cuda(), batch, [1e-20] * len(nodes), 3)
+    for s, t in enumerate(oracle_trees(x, nodes, [1e-20] * len(nodes), 3)):
+        rows = slice(int(batch.node_offset[s]), int(batch.node_offset[s + 1]))
+        assert a.n_built[s].item() == t.n_built == nodes[s]
+        for name in ("parent", "token", "sib_rank", "first_child", "next_sibling", "depth"):
+            np.testing.assert_array_equal(getattr(a.tree, name).cpu().numpy()[rows], getattr(t, name), err_msg=name)
+        np.testing.assert_array_equal(a.est_value.cpu().numpy()[rows], t.est_value.astype(np.float32))
