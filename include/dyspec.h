@@ -123,6 +123,8 @@ dyspec_status dyspec_init(void);
  *                 ancestor of local node j or i == j
  *   n_built       DEVICE [n_seq]: rows actually built (< N only if no slot of positive
  *                 value is left); later rows keep parent = token = -1 and their own mask bit
+ *                 -1: the builder waited for a draw in vain and gave up (a fault of the library
+ *                 or the device, not of the tables; the rows it had built stand)
  *   workspace     DEVICE, dyspec_workspace_bytes(DYSPEC_WS_BUILD_TREE, ...) bytes, 8-byte
  *                 aligned, contents overwritten (about 4.2 KB per row): every row's
  *                 maximum and the totals of its 16 vocabulary segments, computed for all

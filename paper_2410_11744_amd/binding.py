@@ -227,7 +227,7 @@ class BuiltTrees:
     tree: Tree
     est_value: "torch.Tensor"      # fp32 [sum N]
     anc_mask: "torch.Tensor"       # int64 view of u64 [sum N, mask_words]
-    n_built: "torch.Tensor"        # int32 [n_seq]
+    n_built: "torch.Tensor"        # int32 [n_seq]; -1: the builder gave up waiting for a draw
 
 
 def build_tree(draft_logits, batch: Batch, draft_temp, seed: int, stream=None, use_workspace: bool = True) -> BuiltTrees:

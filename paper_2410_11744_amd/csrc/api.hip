@@ -143,10 +143,12 @@ const char* dyspec_status_string(dyspec_status s)
     }
 }
 
-dyspec_status dyspec_build_tree(const float* draft_logits, int32_t vocab, const dyspec_batch* batch,
-                                const float* draft_temp, uint64_t seed, const dyspec_tree* tree,
-                                float* est_value, uint64_t* anc_mask, int32_t* n_built,
-                                void* workspace, size_t workspace_bytes, void* hip_stream)
+// dyspec_build_tree with another bound on the builder's looks for draws (0: it gives up at the first one, which is how
+// the tests see that a build that gave up says so).  Exported, but no part of the interface.
+dyspec_status dyspec_build_tree_bounded(const float* draft_logits, int32_t vocab, const dyspec_batch* batch,
+                                        const float* draft_temp, uint64_t seed, const dyspec_tree* tree,
+                                        float* est_value, uint64_t* anc_mask, int32_t* n_built,
+                                        void* workspace, size_t workspace_bytes, int32_t max_polls, void* hip_stream)
 {
     SeqArgs sa;
     const dyspec_status st = check_batch(batch, false, &sa, DYSPEC_MAX_BUILD_NODES);
@@ -162,9 +164,18 @@ dyspec_status dyspec_build_tree(const float* draft_logits, int32_t vocab, const 
         sa.temp_d[s] = draft_temp[s];
     }
     const hipError_t e = launch_build_tree(draft_logits, vocab, sa, seed, *tree, est_value, anc_mask,
-                                           mask_words_of(batch), n_built, workspace, workspace_bytes,
+                                           mask_words_of(batch), n_built, workspace, workspace_bytes, max_polls,
                                            static_cast<hipStream_t>(hip_stream));
     return e == hipSuccess ? DYSPEC_OK : DYSPEC_HIP_ERROR;
+}
+
+dyspec_status dyspec_build_tree(const float* draft_logits, int32_t vocab, const dyspec_batch* batch,
+                                const float* draft_temp, uint64_t seed, const dyspec_tree* tree,
+                                float* est_value, uint64_t* anc_mask, int32_t* n_built,
+                                void* workspace, size_t workspace_bytes, void* hip_stream)
+{
+    return dyspec_build_tree_bounded(draft_logits, vocab, batch, draft_temp, seed, tree, est_value, anc_mask, n_built,
+                                     workspace, workspace_bytes, kBuildPolls, hip_stream);
 }
 
 size_t dyspec_build_tree_threshold_workspace_bytes(const dyspec_batch* batch)

@@ -242,7 +242,7 @@ __global__ __launch_bounds__(kBlock) void build_tree_kernel(
 // Every wait ends: control waits only for a requested draw, which the node's wave makes in finitely
 // many steps whatever else happens (an empty row is an answer as well); the drawing waves leave when
 // control has set `news` to kStop, which it does after at most N - 1 pops.  (Were an answer to stay out all the
-// same, control gives up after kMaxPolls looks and the tree ends there.)
+// same, control gives up after kBuildPolls looks: the tree ends there, and n_built says so.)
 //
 // What bounds it: the number of instructions of control's pop and of wave 1's draw (a wave alone issues one in
 // eight cycles, whatever it is; an LDS read is back after 52), and where a node is popped again at once or a tree is
@@ -253,7 +253,6 @@ __global__ __launch_bounds__(kBlock) void build_tree_kernel(
 constexpr int kBuildThreads = 1024;
 constexpr int kDrawWaves = kBuildThreads / kWave - 2;
 constexpr int kRing = 16;
-constexpr int kMaxPolls = 1 << 24;          // of a whole build, about a second: no build comes near, none can outlast it
 constexpr uint32_t kAnswer = 0x80000000u;
 constexpr uint32_t kStop = 0u;              // news of a pop is never 0: the new node's index is not
 static_assert(DYSPEC_MAX_BUILD_NODES <= 1024 && DYSPEC_MAX_VOCAB <= (1 << 15), "parent, rank and previous sibling share a word, rank and token too");
@@ -536,9 +535,9 @@ __device__ __forceinline__ int row_max(int x)
     return max(x, dpp_or_zero<kDppMirror>(x));
 }
 
-// Wave 0: pops and appends.  Returns the number of rows built.  Row i's parent | rank << 10 | previous
+// Wave 0: pops and appends.  Returns the number of rows built, its complement if a draw stayed out.  Row i's parent | rank << 10 | previous
 // sibling << 20 goes to `parent` for the time being.
-__device__ __attribute__((noinline)) int pop_nodes(uint32_t lds_, int root_ring_, int N_, int* parent_, int* token_, float* est_value_)
+__device__ __attribute__((noinline)) int pop_nodes(uint32_t lds_, int root_ring_, int N_, int max_polls_, int* parent_, int* token_, float* est_value_)
 {
     const uint32_t lds = uniform(lds_), nodes = lds + BuildLds::nodes;
     const bool root_ring = uniform(root_ring_) != 0;
@@ -548,7 +547,8 @@ __device__ __attribute__((noinline)) int pop_nodes(uint32_t lds_, int root_ring_
     const int lane = threadIdx.x & 63;
     double best_v = lane == 0 ? 1.0 : -1.0;         // the best open slot of the nodes lane, lane + 64, ...; <= 0: none
     int best_i = lane;
-    int n = 1, root_rank = 0, polls = kMaxPolls;
+    int n = 1, root_rank = 0, polls = uniform(max_polls_);
+    bool lost = false;
     uint32_t place_n = nodes + kNode;               // LDS of node n
     int tokens = -1, froms = 0;                     // of the last 64 rows, row i in lane i % 64; written out together
     float values = 1.0f;
@@ -586,7 +586,8 @@ __device__ __attribute__((noinline)) int pop_nodes(uint32_t lds_, int root_ring_
         const uint32_t o = *lds_at<uint32_t>(place_p + kOpenedAt);
         const int R_hi = uniform(__double2hiint(R));
         if (R_hi < 0 || polls <= 0) {
-            if (polls <= 0 || R_hi == (int)0xbff00000u) break;      // (-1) nothing left to sample under p
+            lost = polls <= 0;
+            if (lost || R_hi == (int)0xbff00000u) break;            // (-1) nothing left to sample under p
             // the quotient of two infinite weights, a NaN with its sign bit set: the token holds all that is left, at a
             // temperature so small that the row's maximum over it is rounded by more than the range of exp
             R = 1.0;
@@ -639,14 +640,14 @@ __device__ __attribute__((noinline)) int pop_nodes(uint32_t lds_, int root_ring_
         est_value[(n & ~63) + lane] = values;
         parent[(n & ~63) + lane] = froms;
     }
-    return n;
+    return lost ? ~n : n;
 }
 
 template <bool VEC>
 __global__ __launch_bounds__(kBuildThreads) void build_tree_waves_kernel(
     const float* __restrict__ draft_logits, int V, SeqArgs sa, uint64_t seed,
     dyspec_tree tree, float* est_value, uint64_t* __restrict__ anc_mask,
-    int mask_words, int* __restrict__ n_built, double* ws, int widest, int root_ring)
+    int mask_words, int* __restrict__ n_built, double* ws, int widest, int root_ring, int max_polls)
 {
     extern __shared__ __attribute__((aligned(16))) unsigned char dyn[];
     const uint32_t lds = lds_base(dyn);
@@ -679,7 +680,7 @@ __global__ __launch_bounds__(kBuildThreads) void build_tree_waves_kernel(
     // (control and the root's wave share their SIMDs, but come first there)
     if (wave == 0) {
         __builtin_amdgcn_s_setprio(3);
-        const int n = pop_nodes(lds, root_ring, N, tree.parent + base, tree.token + base, est_value + base);
+        const int n = pop_nodes(lds, root_ring, N, max_polls, tree.parent + base, tree.token + base, est_value + base);
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");            // the rows are read back below
         if (tid == 0) {
             *lds_at<int>(lds + BuildLds::n_built) = n;
@@ -694,7 +695,7 @@ __global__ __launch_bounds__(kBuildThreads) void build_tree_waves_kernel(
     __builtin_amdgcn_s_setprio(0);
     __syncthreads();
     // ---- the tree is known: links, depths and masks, all rows at once
-    const int n = *lds_at<int>(lds + BuildLds::n_built);
+    const int ended = *lds_at<int>(lds + BuildLds::n_built), n = ended < 0 ? ~ended : ended;
     lds_t<int>* const first = lds_at<int>(nodes);             // the nodes' place is free now
     lds_t<int>* const next = first + widest;
     lds_t<uint32_t>* const from = lds_at<uint32_t>(nodes + 8 * widest);
@@ -734,7 +735,7 @@ __global__ __launch_bounds__(kBuildThreads) void build_tree_waves_kernel(
         for (; word >= 0; --word) { mrow[word] = bits; bits = 0ull; }
         tree.depth[base + i] = depth;
     }
-    if (tid == 0) n_built[seq] = n;
+    if (tid == 0) n_built[seq] = ended < 0 ? -1 : n;
 }
 
 // The root's row is kept in LDS where it fits beside the node state (32000 tokens: up to 556 rows,
@@ -754,7 +755,7 @@ size_t build_tree_workspace_bytes(int total_rows) { return (size_t)total_rows * 
 
 hipError_t launch_build_tree(const float* draft_logits, int V, const SeqArgs& sa, uint64_t seed,
                              const dyspec_tree& tree, float* est_value, uint64_t* anc_mask,
-                             int mask_words, int* n_built, void* workspace, size_t workspace_bytes, hipStream_t stream)
+                             int mask_words, int* n_built, void* workspace, size_t workspace_bytes, int max_polls, hipStream_t stream)
 {
     const int rows = sa.node_off[sa.n_seq];
     double* ws = static_cast<double*>(workspace);
@@ -769,11 +770,11 @@ hipError_t launch_build_tree(const float* draft_logits, int V, const SeqArgs& sa
         if (V % 4 == 0) {
             draft_row_sums_kernel<true><<<rows, kBlock, 0, stream>>>(draft_logits, V, sa, ws);
             build_tree_waves_kernel<true><<<sa.n_seq, kBuildThreads, lds_bytes, stream>>>(
-                draft_logits, V, sa, seed, tree, est_value, anc_mask, mask_words, n_built, ws, widest, root_ring);
+                draft_logits, V, sa, seed, tree, est_value, anc_mask, mask_words, n_built, ws, widest, root_ring, max_polls);
         } else {
             draft_row_sums_kernel<false><<<rows, kBlock, 0, stream>>>(draft_logits, V, sa, ws);
             build_tree_waves_kernel<false><<<sa.n_seq, kBuildThreads, lds_bytes, stream>>>(
-                draft_logits, V, sa, seed, tree, est_value, anc_mask, mask_words, n_built, ws, widest, root_ring);
+                draft_logits, V, sa, seed, tree, est_value, anc_mask, mask_words, n_built, ws, widest, root_ring, max_polls);
         }
     } else if (V % 4 == 0) {
         build_tree_kernel<true><<<sa.n_seq, kBlock, 0, stream>>>(draft_logits, V, sa, seed, tree, est_value,

@@ -48,10 +48,13 @@ struct AttnArgs {
     long long q_stride, kvp_stride, kvt_stride;
 };
 
+// Looks for draws that are still out, of a whole tree: about a second, no build comes near and none can outlast it.
+constexpr int kBuildPolls = 1 << 24;
+
 // Launchers (one per source file); each returns the launch status.
 hipError_t launch_build_tree(const float* draft_logits, int V, const SeqArgs& sa, uint64_t seed,
                              const dyspec_tree& tree, float* est_value, uint64_t* anc_mask,
-                             int mask_words, int* n_built, void* workspace, size_t workspace_bytes, hipStream_t stream);
+                             int mask_words, int* n_built, void* workspace, size_t workspace_bytes, int max_polls, hipStream_t stream);
 size_t build_tree_workspace_bytes(int total_rows);
 hipError_t launch_build_threshold(const float* draft_logits, int V, const SeqArgs& sa, const double* threshold,
                                   uint64_t seed, const dyspec_tree& tree, float* est_value, uint64_t* anc_mask,
