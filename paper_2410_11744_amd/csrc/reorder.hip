@@ -23,6 +23,9 @@ namespace dyspec {
 
 constexpr int kReorderThreads = 1024;
 constexpr int kSliceRows = 256;
+// Widest tree of a batch up to which one lane walks the links: the doubling's rounds take 5.3 us whatever they find (2 rows
+// 5.3 -> 3.3 us, 12 rows 6.5 -> 5.6), and from 16 rows on the walk is no shorter (6.6 against 6.5; 24 rows 7.6 against 6.8).
+constexpr int kShortTree = 12;
 constexpr int kJumps = 11;                                  // 2^11 = DYSPEC_MAX_NODES steps cover any walk
 constexpr int kMaskWordsMax = DYSPEC_MAX_NODES / 64;
 constexpr int kNodesPerThread = DYSPEC_MAX_NODES / kReorderThreads;
@@ -66,6 +69,8 @@ __device__ void walk_literally(ReorderShared& sh, int N)
         if (sh.rank[i] < 0) { sh.rank[i] = (short)n; sh.order[n++] = (short)i; }
 }
 
+// SHORT: no tree has more than kShortTree rows.
+template <bool SHORT>
 __global__ __launch_bounds__(kReorderThreads) void dfs_reorder_kernel(SeqArgs sa, dyspec_tree in, dyspec_tree out,
                                                                       int* __restrict__ order_out,
                                                                       uint64_t* __restrict__ mask_out, int mask_words)
@@ -90,92 +95,96 @@ __global__ __launch_bounds__(kReorderThreads) void dfs_reorder_kernel(SeqArgs sa
         sh.rank[i] = -1;
     }
     __syncthreads();
-    // every link agrees with the parents it implies: then a walk without a cycle meets every node
-    // at most once and climbs every edge at most once, and is the literal walk
-    bool bad = tid == 0 && sh.parent[0] >= 0;
-    for (int i = tid; i < N; i += kReorderThreads) {
-        const int c = sh.first_child[i], s = sh.next_sibling[i];
-        bad |= c >= 0 && sh.parent[c] != i;
-        bad |= s >= 0 && (sh.parent[i] < 0 || sh.parent[s] != sh.parent[i]);
-    }
-    // what follows a subtree: every round replaces "as for u" by u's own answer or by u's reference.
-    // (in place: whatever a reader finds in u's word is equivalent to what stood there before)
-    bool open = true;
-    for (int r = 0; r <= kJumps && open; ++r) {
-        open = false;
-        for (int i = tid; i < N; i += kReorderThreads) {
-            const int a = sh.after[i];
-            if (a <= -2) {
-                const int up = sh.after[-2 - a];
-                sh.after[i] = up;
-                open |= up <= -2;
-            }
-        }
-        open = __syncthreads_or(open);
-    }
-    bad |= open;                                            // a cycle of parents
-    // ---- successors, and successors of successors
-    int rounds = 0;
-    while ((1 << rounds) < N) ++rounds;                     // a walk of N nodes has N - 1 steps
-    for (int i = tid; i < N; i += kReorderThreads) {
-        const int c = sh.first_child[i];
-        sh.jump[0][i] = c >= 0 ? (short)c : (short)max(sh.after[i], -1);
-    }
-    __syncthreads();
-    for (int r = 1; r < rounds; ++r) {
-        for (int i = tid; i < N; i += kReorderThreads) {
-            const int h = sh.jump[r - 1][i];
-            sh.jump[r][i] = h >= 0 ? sh.jump[r - 1][h] : (short)-1;
-        }
-        __syncthreads();
-    }
-    // 2^rounds >= N steps from the root must lead past the end
-    if (tid == 0) {
-        if (rounds > 0) {
-            const int h = sh.jump[rounds - 1][0];
-            bad |= h >= 0 && sh.jump[rounds - 1][h] >= 0;
-        }
-        sh.rank[0] = 0;
-    }
-    __syncthreads();
-    // ---- positions: the node 2^r steps after one at position k is at k + 2^r
-    // (a node reached and read within one round only writes positions that are right as well)
-    for (int r = rounds - 1; r >= 0; --r) {
-        for (int i = tid; i < N; i += kReorderThreads) {
-            const int k = sh.rank[i];
-            if (k >= 0) {
-                const int h = sh.jump[r][i];
-                if (h >= 0) sh.rank[h] = (short)(k + (1 << r));
-            }
-        }
-        __syncthreads();
-    }
-    // ---- rows that were never attached follow in index order; one that names a parent is no such row
-    int visited = 0;
-    bool mine_loose[kNodesPerThread];
-    unsigned long long lanes[kNodesPerThread];
-#pragma unroll
-    for (int k = 0; k < kNodesPerThread; ++k) {
-        const int i = tid + k * kReorderThreads;
-        mine_loose[k] = i < N && sh.rank[i] < 0;
-        bad |= mine_loose[k] && sh.parent[i] >= 0;
-        lanes[k] = __ballot(mine_loose[k]);
-        if ((tid & 63) == 0) sh.loose[tid >> 6][k] = __popcll(lanes[k]);
-        visited += __syncthreads_count(i < N && sh.rank[i] >= 0);
-    }
-    if (__syncthreads_or(bad)) {
+    if constexpr (SHORT) {
         if (tid == 0) walk_literally(sh, N);
     } else {
+        // every link agrees with the parents it implies: then a walk without a cycle meets every node
+        // at most once and climbs every edge at most once, and is the literal walk
+        bool bad = tid == 0 && sh.parent[0] >= 0;
+        for (int i = tid; i < N; i += kReorderThreads) {
+            const int c = sh.first_child[i], s = sh.next_sibling[i];
+            bad |= c >= 0 && sh.parent[c] != i;
+            bad |= s >= 0 && (sh.parent[i] < 0 || sh.parent[s] != sh.parent[i]);
+        }
+        // what follows a subtree: every round replaces "as for u" by u's own answer or by u's reference.
+        // (in place: whatever a reader finds in u's word is equivalent to what stood there before)
+        bool open = true;
+        for (int r = 0; r <= kJumps && open; ++r) {
+            open = false;
+            for (int i = tid; i < N; i += kReorderThreads) {
+                const int a = sh.after[i];
+                if (a <= -2) {
+                    const int up = sh.after[-2 - a];
+                    sh.after[i] = up;
+                    open |= up <= -2;
+                }
+            }
+            open = __syncthreads_or(open);
+        }
+        bad |= open;                                            // a cycle of parents
+        // ---- successors, and successors of successors
+        int rounds = 0;
+        while ((1 << rounds) < N) ++rounds;                     // a walk of N nodes has N - 1 steps
+        for (int i = tid; i < N; i += kReorderThreads) {
+            const int c = sh.first_child[i];
+            sh.jump[0][i] = c >= 0 ? (short)c : (short)max(sh.after[i], -1);
+        }
+        __syncthreads();
+        for (int r = 1; r < rounds; ++r) {
+            for (int i = tid; i < N; i += kReorderThreads) {
+                const int h = sh.jump[r - 1][i];
+                sh.jump[r][i] = h >= 0 ? sh.jump[r - 1][h] : (short)-1;
+            }
+            __syncthreads();
+        }
+        // 2^rounds >= N steps from the root must lead past the end
+        if (tid == 0) {
+            if (rounds > 0) {
+                const int h = sh.jump[rounds - 1][0];
+                bad |= h >= 0 && sh.jump[rounds - 1][h] >= 0;
+            }
+            sh.rank[0] = 0;
+        }
+        __syncthreads();
+        // ---- positions: the node 2^r steps after one at position k is at k + 2^r
+        // (a node reached and read within one round only writes positions that are right as well)
+        for (int r = rounds - 1; r >= 0; --r) {
+            for (int i = tid; i < N; i += kReorderThreads) {
+                const int k = sh.rank[i];
+                if (k >= 0) {
+                    const int h = sh.jump[r][i];
+                    if (h >= 0) sh.rank[h] = (short)(k + (1 << r));
+                }
+            }
+            __syncthreads();
+        }
+        // ---- rows that were never attached follow in index order; one that names a parent is no such row
+        int visited = 0;
+        bool mine_loose[kNodesPerThread];
+        unsigned long long lanes[kNodesPerThread];
 #pragma unroll
         for (int k = 0; k < kNodesPerThread; ++k) {
             const int i = tid + k * kReorderThreads;
-            if (mine_loose[k]) {
-                int pos = visited + __popcll(lanes[k] & ((1ull << (tid & 63)) - 1ull));
-                for (int kk = 0; kk <= k; ++kk)
-                    for (int w = 0; w < (kk < k ? kReorderThreads / kWave : tid >> 6); ++w) pos += sh.loose[w][kk];
-                sh.rank[i] = (short)pos;
+            mine_loose[k] = i < N && sh.rank[i] < 0;
+            bad |= mine_loose[k] && sh.parent[i] >= 0;
+            lanes[k] = __ballot(mine_loose[k]);
+            if ((tid & 63) == 0) sh.loose[tid >> 6][k] = __popcll(lanes[k]);
+            visited += __syncthreads_count(i < N && sh.rank[i] >= 0);
+        }
+        if (__syncthreads_or(bad)) {
+            if (tid == 0) walk_literally(sh, N);
+        } else {
+#pragma unroll
+            for (int k = 0; k < kNodesPerThread; ++k) {
+                const int i = tid + k * kReorderThreads;
+                if (mine_loose[k]) {
+                    int pos = visited + __popcll(lanes[k] & ((1ull << (tid & 63)) - 1ull));
+                    for (int kk = 0; kk <= k; ++kk)
+                        for (int w = 0; w < (kk < k ? kReorderThreads / kWave : tid >> 6); ++w) pos += sh.loose[w][kk];
+                    sh.rank[i] = (short)pos;
+                }
+                if (i < N) sh.order[sh.rank[i]] = (short)i;
             }
-            if (i < N) sh.order[sh.rank[i]] = (short)i;
         }
     }
     __syncthreads();
@@ -215,8 +224,10 @@ __global__ __launch_bounds__(kReorderThreads) void dfs_reorder_kernel(SeqArgs sa
 // the positions of the largest tree take more LDS than a kernel gets by default
 hipError_t prepare_reorder()
 {
-    static std::atomic<unsigned long long> done{0};
-    return raise_dynamic_lds_once(reinterpret_cast<const void*>(&dfs_reorder_kernel), (int)sizeof(ReorderShared), done);
+    static std::atomic<unsigned long long> done_short{0}, done{0};
+    const hipError_t e = raise_dynamic_lds_once(reinterpret_cast<const void*>(&dfs_reorder_kernel<true>), (int)sizeof(ReorderShared), done_short);
+    if (e != hipSuccess) return e;
+    return raise_dynamic_lds_once(reinterpret_cast<const void*>(&dfs_reorder_kernel<false>), (int)sizeof(ReorderShared), done);
 }
 
 hipError_t launch_dfs_reorder(const SeqArgs& sa, const dyspec_tree& in, const dyspec_tree& out, int* order,
@@ -226,8 +237,11 @@ hipError_t launch_dfs_reorder(const SeqArgs& sa, const dyspec_tree& in, const dy
     for (int s = 0; s < sa.n_seq; ++s) widest = max(widest, sa.node_off[s + 1] - sa.node_off[s]);
     const hipError_t e = prepare_reorder();
     if (e != hipSuccess) return e;
-    dfs_reorder_kernel<<<dim3(sa.n_seq, (widest + kSliceRows - 1) / kSliceRows), kReorderThreads, sizeof(ReorderShared), stream>>>(
-        sa, in, out, order, mask_out, mask_words);
+    const dim3 grid(sa.n_seq, (widest + kSliceRows - 1) / kSliceRows);
+    if (widest <= kShortTree)
+        dfs_reorder_kernel<true><<<grid, kReorderThreads, sizeof(ReorderShared), stream>>>(sa, in, out, order, mask_out, mask_words);
+    else
+        dfs_reorder_kernel<false><<<grid, kReorderThreads, sizeof(ReorderShared), stream>>>(sa, in, out, order, mask_out, mask_words);
     return hipGetLastError();
 }
 

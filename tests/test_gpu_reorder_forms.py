@@ -66,6 +66,14 @@ def forms(name, rng):
     if name == "trees":
         sizes = [1, 2, 3, 63, 64, 65, 255, 256, 257, 1023, 1025]
         return [links(random_parents(n, rng), rng) for n in sizes]
+    if name.startswith("short"):                            # the widest tree on either side of the size from which positions are doubled
+        n = 12 if name.startswith("short 12") else 13
+        out = [links(random_parents(k, rng), rng) for k in (n, 1, 2, n, n - 1)] + [links(np.arange(-1, n - 1)), links(np.array([-1] + [0] * (n - 1)))]
+        if name.endswith("no tree"):
+            for par, fc, ns in out:
+                for a in (par, fc, ns):
+                    a[int(rng.integers(0, len(a)))] = int(rng.integers(-3, n + 3))
+        return out
     if name == "largest":
         return [links(random_parents(2048, rng), rng)]
     if name == "chain":
@@ -93,7 +101,8 @@ def forms(name, rng):
 
 
 @pytest.mark.parametrize("name,seed", [("trees", 0), ("largest", 1), ("chain", 2), ("star", 3), ("never attached", 4)]
-                         + [("no tree", s) for s in range(5, 17)])
+                         + [("no tree", s) for s in range(5, 17)] + [("short 12", 17), ("short 13", 18)]
+                         + [("short 12 no tree", s) for s in range(19, 25)] + [("short 13 no tree", s) for s in range(25, 29)])
 def test_every_form_of_links(name, seed):
     if not torch.cuda.is_available():
         pytest.skip("no GPU")
