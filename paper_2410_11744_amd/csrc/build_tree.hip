@@ -739,7 +739,9 @@ __global__ __launch_bounds__(kBuildThreads) void build_tree_waves_kernel(
 }
 
 // The root's row is kept in LDS where it fits beside the node state (32000 tokens: up to 556 rows,
-// 32768: up to 489); else the root's draws are made like every other node's.
+// 32768: up to 489) and is drawn from often enough to pay for its loading (2 rows of 32000 tokens 26.0 us with it, 17.9
+// without; 8 rows 30.3 and 30.0; 16 rows 35.8 and 45.5); else the root's draws are made like every other node's.
+constexpr int kRingRows = 10;
 static size_t build_lds_bytes(int V, int widest, bool root_ring) { return BuildLds::row(widest) + (root_ring ? row_lds_bytes(V) : 0); }
 
 // the builder takes up to a whole CU's LDS: the kernels' limit is raised once
@@ -763,7 +765,7 @@ hipError_t launch_build_tree(const float* draft_logits, int V, const SeqArgs& sa
     if (cached) {
         int widest = 0;
         for (int s = 0; s < sa.n_seq; ++s) widest = max(widest, sa.node_off[s + 1] - sa.node_off[s]);
-        const int root_ring = build_lds_bytes(V, widest, true) <= kLdsPerWorkgroup;
+        const int root_ring = widest >= kRingRows && build_lds_bytes(V, widest, true) <= kLdsPerWorkgroup;
         const size_t lds_bytes = build_lds_bytes(V, widest, root_ring);
         const hipError_t ea = prepare_build_tree();
         if (ea != hipSuccess) return ea;

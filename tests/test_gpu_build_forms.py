@@ -45,6 +45,8 @@ CASES = [("normal", n, v) for n, v in (((2,), 1), ((1,), 5), ((3,), 2), ((40,), 
                                        ((300,), 32767), ((895, 896, 897, 898), 700))]
 CASES += [(k, n, v) for k in ("chain", "child", "equal", "few", "peaked", "odd")
           for n, v in (((60,), 64), ((200, 31), 1000), ((140,), 2047), ((260,), 32000), ((900,), 32768))]
+CASES += [(k, n, v) for k in ("normal", "chain", "few", "odd")      # both sides of the size from which the root's row is kept in LDS
+          for n, v in (((8, 9), 1000), ((9,), 5), ((9,), 32001), ((10,), 5), ((9, 10), 129), ((10,), 32000), ((11, 2), 2050))]
 CASES += [("two", (9,), 40), ("two", (1024,), 600), ("equal", (1024,), 2), ("equal", (600,), 4)]
 
 
