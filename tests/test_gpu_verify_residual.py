@@ -53,9 +53,25 @@ def test_many_rejections(dy, kids, V, tt, bf16):
     d = (rng.standard_normal((n, V)) * 2.0).astype(np.float32)
     t = (rng.standard_normal((n, V)) * 2.0).astype(np.float32)          # unrelated to the draft: most children are rejected
     tokens = np.argsort(-(d[0] / f32(0.9) + rng.gumbel(size=V)))[:kids]  # a sample without replacement
+    compare(dy, tokens, d, t, 0.9, tt, 5 + kids, bf16)
+
+
+@pytest.mark.parametrize("bf16", [False, True])
+@pytest.mark.parametrize("kids,late,V,tt", [(65, 63, 2048, 0.6), (65, 64, 2049, 1.0), (130, 127, 4100, 0.6), (130, 129, 1000, 1.0), (200, 128, 32000, 1.0),
+                                            (200, 199, 32765, 0.6), (200, 65, 32768, 0.0)])
+def test_child_far_down_the_scan_is_accepted(dy, kids, late, V, tt, bf16):
+    """The children before number `late` are impossible for the target, which puts most of its weight on that one: all of
+    them are tested, rejected, and it is accepted, whatever the draws."""
+    rng = np.random.default_rng(kids * 1000 + late)
+    d = (rng.standard_normal((kids + 1, V)) * 2.0).astype(np.float32)
+    t = (rng.standard_normal((kids + 1, V)) * 2.0).astype(np.float32)
+    tokens = np.argsort(-(d[0] / f32(0.9) + rng.gumbel(size=V)))[:kids]
+    t[0, tokens[:late]] = -np.inf
+    t[0, tokens[late]] = 20.0
     out, _ = compare(dy, tokens, d, t, 0.9, tt, 5 + kids, bf16)
-    if kids >= 63 and tt > 0:
-        assert (out.accept_ratio.cpu().numpy()[1:] >= 0).sum() >= 1
+    assert out.n_accepted.item() == 1 and out.accepted_nodes[0].item() == late + 1
+    ratio = out.accept_ratio.cpu().numpy()
+    assert (ratio[1:late + 1] == 0.0).all() and ratio[late + 1] >= 1.0 and (ratio[late + 2:] == -2.0).all()
 
 
 @pytest.mark.parametrize("V,tt", [(6, 1.0), (6, 0.0), (2100, 1.0), (2100, 0.0), (32000, 0.7)])
