@@ -127,9 +127,9 @@ dyspec_status dyspec_init(void);
  *                 or the device, not of the tables; the rows it had built stand)
  *   workspace     DEVICE, dyspec_workspace_bytes(DYSPEC_WS_BUILD_TREE, ...) bytes, 8-byte
  *                 aligned, contents overwritten (about 4.2 KB per row): every row's
- *                 maximum and the totals of its 16 vocabulary segments, computed for all
- *                 rows at once before the serial expansion, and one bit per token drawn
- *                 from the row so far; a draw then touches a 16th of the parent's row.
+ *                 maximum and the totals of its runs of 128 tokens, computed for all
+ *                 rows at once before the serial expansion, and the tokens drawn from
+ *                 the row so far; a draw then touches one run of the parent's row.
  *                 NULL or fewer bytes: the expansion makes a pass over the parent's whole
  *                 row at every draw instead (same arithmetic, same tree, several times
  *                 slower).
@@ -165,9 +165,9 @@ dyspec_status dyspec_build_tree(const float* draft_logits, int32_t vocab,
  *   workspace     DEVICE, 8-byte aligned, dyspec_build_tree_threshold_workspace_bytes()
  *                 bytes, REQUIRED (DYSPEC_WORKSPACE_TOO_SMALL otherwise)
  *   all other arguments, and the limits on vocab and N, as for dyspec_build_tree.
- * The call copies one small record per level back to the host and waits for it (it sizes
- * the next level's launch), so it returns with the tree complete and cannot be captured
- * in a graph.
+ * The call waits for every level (the device reports the level's size, which sizes the next
+ * launch), so it returns with the tree complete and cannot be captured in a graph: a stream
+ * that is capturing is refused with DYSPEC_HIP_ERROR before anything is launched.
  */
 dyspec_status dyspec_build_tree_threshold(const float* draft_logits, int32_t vocab,
                                           const dyspec_batch* batch, const float* draft_temp,

@@ -247,9 +247,10 @@ __global__ __launch_bounds__(kBlock) void build_tree_kernel(
 // What bounds it: the number of instructions of control's pop and of wave 1's draw (a wave alone issues one in
 // eight cycles, whatever it is; an LDS read is back after 52), and where a node is popped again at once or a tree is
 // one chain, those of a draw from memory (the trip itself is over before the Philox blocks made meanwhile).
-// Measured against a workgroup that popped and drew in turn, two barriers a draw, with the pass over the rows: 512 rows of 32000 tokens 1378 -> 508 us (with eight drawing waves, not fourteen,
-// 543: a request waits for the draw its wave is at), 128 rows 346 -> 134, 32 rows of 1000 tokens 92 -> 55; a
-// single chain of 512 nodes 1413 -> 1130.
+// Measured against a workgroup that popped and drew in turn, two barriers a draw, with the pass over the rows: 512 rows of 32000 tokens 1378 -> 508 us (with eight drawing waves on two
+// SIMDs 562, on all four 543: a request waits for the draw its wave is at), 128 rows 346 -> 134, 32 rows of 1000 tokens
+// 92 -> 55; a single chain of 512 nodes 1413 -> 1130.  Of one size the time depends on the table, that is, on how often nodes
+// other than the root are popped again: 458 to 707 us over nine tables of 512 rows of independent normal logits.
 constexpr int kBuildThreads = 1024;
 constexpr int kDrawWaves = kBuildThreads / kWave - 2;
 constexpr int kRing = 16;
@@ -345,7 +346,7 @@ __device__ __attribute__((noinline)) void draw_for_root(uint32_t lds_, uint32_t 
     }
 }
 
-// A draw wave's copy of a node's totals (lane l: totals 4 l .. 4 l + 3) and row maximum.
+// A draw wave's copy of a node's totals (lane l: totals 4 l .. 4 l + 3) and row maximum; which copies it keeps: row_copies.h.
 struct HeldRow {
     int node;               // -1: none
     double tot[4], m;

@@ -1,5 +1,5 @@
 // Device-side helpers shared by the gfx950 kernels: Philox4x32-10 draws named by the
-// sibling-rank path, and workgroup reductions / scans for 1024-thread workgroups.
+// sibling-rank path, and workgroup reductions and scans.
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>

@@ -390,7 +390,12 @@ __device__ __forceinline__ int draw_from_row(const RowVec (&w)[4], double u, Dra
 // before: 4.4 us each, 2.0 now (32000 tokens).  Both rows' loads are in flight together and every load is issued
 // before the first is used: a node's rows 5.8 -> 5.3 us in fp32, 12.9 -> 5.4 in bf16.
 // Verification of the ragged batch of eight 143 -> 105 us.
-// (R's sum shrinks with every rejection; below kSmallMass the weights are brought back to a sum of 1.)
+// (R's sum shrinks with every rejection; below kSmallMass the weights are brought back to a sum of 1, as they are
+// where mass * scale_d would leave the range.)
+//
+// Rows that are no distribution (all -inf, NaN, +inf) end as they would with a normalised R: under such a target row no
+// child is accepted and no last token comes out; after such a draft row the scan ends with the first child and the
+// last token comes from the target row.  In both, the sweep finds no mass left, which is where they are told from R == D.
 constexpr float kSmallMass = 9.5367431640625e-7f;     // 2^-20: weights of 1e-32 of the sum are still normal numbers
 struct WalkShared {
     DrawScratch draw;

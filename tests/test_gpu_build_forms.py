@@ -1,7 +1,8 @@
 """dyspec_build_tree with a workspace (draws made ahead by waves of their own) against the form without one, over the
 shapes of trees and tables it accepts: whole numbers and fp32 values must be equal.  Both forms sum the same fp64
 weights in different orders, so a decision could differ only where its margin is near 1e-13, and a stored
-fp32 value only where the fp64 one lies that close to a rounding boundary."""
+fp32 value only where the fp64 one lies that close to a rounding boundary.  (Many small trees at a time, where the
+order in which nodes are served matters most: test_gpu_build_small.py.)"""
 import numpy as np
 import pytest
 
