@@ -77,6 +77,12 @@ constexpr size_t kAttnCounterBytes = DYSPEC_ATTN_COUNTER_BYTES;     // arrival c
 struct AttnCut { int splits, tree_split; };
 AttnCut tree_attn_cut(const SeqArgs& sa, int Hq, int Hkv, int layers);
 size_t tree_attn_workspace_bytes(const SeqArgs& sa, int Hq, int Hkv, int d, int layers);
+// The kernel for short walks: waves per workgroup (0: the call is not for it) and parts of the prefix, given how the other
+// kernel would split it and the workspace there is.
+struct ShortPlan { int waves, splits; };
+ShortPlan tree_attn_short_plan(const SeqArgs& sa, int Hq, int Hkv, int d, int layers, int long_splits, size_t workspace_bytes);
+hipError_t launch_tree_attn_short(const AttnArgs& a, const SeqArgs& sa, int waves, hipStream_t stream);
+hipError_t prepare_tree_attn_short();
 
 // Raises a kernel's dynamic-LDS limit to `bytes`, once per device (`done`: one bit per device,
 // owned by the call site).  Touching the kernel this way also makes the runtime load its code.

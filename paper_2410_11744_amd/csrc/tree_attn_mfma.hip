@@ -1,5 +1,5 @@
 // Tree attention on the matrix cores (Section 2, "Tree Attention"; Appendix C) for gfx950:
-// bf16 tensors, head_dim 64 or 128, fp32 accumulation.
+// bf16 tensors, head_dim 64 or 128, fp32 accumulation.  (Short walks: tree_attn_short.hip.)
 //
 // Row folding.  All G = Hq/Hkv query heads that share a KV head are folded into the row
 // dimension (row = node*G + head), so a workgroup tile of 128 rows streams the prefix K/V
@@ -36,40 +36,11 @@
 // following half step so that they drain while the matrix pipe works.  Rows sit unpadded in
 // LDS; 16-byte chunks of a row are XOR-swizzled so that the 16-byte K reads and the
 // transposing V reads of a wave spread over all 64 banks.
-#include <utility>
-
 #include <atomic>
 #include <cstdlib>
-#include "dyspec_device.h"
+#include "attn_mfma.h"
 
 namespace dyspec {
-
-// Compile-time loop: f(integral_constant<int, 0>), ..., f(integral_constant<int, N-1>).
-template <typename F, int... I>
-__device__ __forceinline__ void static_for_impl(F&& f, std::integer_sequence<int, I...>)
-{
-    (f(std::integral_constant<int, I>{}), ...);
-}
-template <int N, typename F>
-__device__ __forceinline__ void static_for(F&& f)
-{
-    static_for_impl(static_cast<F&&>(f), std::make_integer_sequence<int, N>{});
-}
-template <typename F>
-__device__ __forceinline__ void with_bool(bool b, F&& f)
-{
-    if (b) f(std::true_type{}); else f(std::false_type{});
-}
-
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-typedef float floatx16 __attribute__((ext_vector_type(16)));
-typedef float floatx2 __attribute__((ext_vector_type(2)));
-typedef __attribute__((address_space(1))) const void* global_ptr;
-typedef __attribute__((address_space(3))) void* lds_ptr;
-typedef short short4v __attribute__((ext_vector_type(4)));
-typedef __attribute__((address_space(3))) short4v* lds_short4;
-typedef __attribute__((address_space(3))) const bf16x8* lds_bf16x8;
 
 #ifdef DYSPEC_STAMPS
 // Timing build only: thread 0 of every workgroup records the 100 MHz wall clock at a few points.
@@ -92,33 +63,6 @@ constexpr int kLead = DYSPEC_ATTN_LEAD;   // fragment slots between an LDS read 
 #endif
 constexpr int kQB = DYSPEC_ATTN_QB;       // 32-row query blocks per wave (see the kernel)
 
-// v_exp_f32 without the denormal-range fix-up: inputs below -126 give 0, which is what the
-// softmax wants.
-__device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
-__device__ __forceinline__ float and_bits(float x, int m) { return __int_as_float(__float_as_int(x) & m); }
-// One wave-wide direct load: lane i moves 16 bytes from (base + voff_i) to LDS byte
-// lds_base + 16*i.  Issued as inline assembly so that the compiler does not pair every later
-// LDS read with a wait for these loads; the caller waits (wait_direct_loads) before the
-// barrier that publishes the stage.
-__device__ __forceinline__ void direct_load_16(const void* base, uint32_t voff, uint32_t lds_base)
-{
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
-                 :: "s"(lds_base), "v"(voff), "s"(base) : "m0", "memory");
-}
-__device__ __forceinline__ void wait_direct_loads() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
-__device__ __forceinline__ uint32_t lds_address(const void* p)
-{
-    return (uint32_t)(size_t)(lds_ptr)(p);
-}
-
-// max of three without the NaN-quieting moves fmaxf would add in front
-__device__ __forceinline__ float max3(float a, float b, float c)
-{
-    float r;
-    asm("v_max3_f32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
-    return r;
-}
-
 template <int D> struct Geo {
     static constexpr int kRowBytes = 2 * D;
     static constexpr int kChunks = D / 8;                        // 16-byte chunks per row
@@ -128,9 +72,6 @@ template <int D> struct Geo {
     static constexpr int kVBase = 2 * kSlotBytes;                // K slots 0 and 1, then V slots 0 and 1
     static constexpr int kLdsBytes = 4 * kSlotBytes;
     static constexpr int kLoadsPerMat = kKeysPerTile / kRowsPerLoad;
-    // chunk c of K row r sits at chunk position c ^ swz_k(r); of V row r at c ^ swz_v(r)
-    __device__ static __forceinline__ int swz_k(int r) { return D == 128 ? (r & 15) : ((r >> 1) & 7); }
-    __device__ static __forceinline__ int swz_v(int r) { return D == 128 ? ((r & 3) << 2) : 0; }
 };
 
 // QB = 32-row query blocks per wave.  Every K/V fragment read from LDS feeds QB MFMAs, so
@@ -236,7 +177,7 @@ __global__ __launch_bounds__(64 * 2 * (4 / QB)) void tree_attn_mfma_kernel(AttnA
 #pragma unroll
         for (int xm = 0; xm < 4; ++xm) {
             const int row = L::kRowsPerLoad * xm + ld_lrow;
-            const int c = ld_cpos ^ (is_v ? L::swz_v(row) : L::swz_k(row));
+            const int c = ld_cpos ^ (is_v ? swz_v<D>(row) : swz_k<D>(row));
             voff[xm] = ld_lrow * (int)kv_row_bytes + 16 * c;
         }
     };
@@ -284,7 +225,7 @@ __global__ __launch_bounds__(64 * 2 * (4 / QB)) void tree_attn_mfma_kernel(AttnA
     // ---- LDS read addresses of this lane (the LDS base and the even/odd tile choice of the wave folded in)
     int k_off[KK];                               // K fragment of k-step kk, key row n of a half tile
     {
-        const int h = g ^ L::swz_k(n);           // (2*kk + g) ^ swz == (2*kk) ^ (g ^ swz)
+        const int h = g ^ swz_k<D>(n);           // (2*kk + g) ^ swz == (2*kk) ^ (g ^ swz)
 #pragma unroll
         for (int kk = 0; kk < KK; ++kk) k_off[kk] = (int)lds0 + wk * L::kMatBytes + n * L::kRowBytes + (((2 * kk) ^ h) << 4);
     }
@@ -303,7 +244,7 @@ __global__ __launch_bounds__(64 * 2 * (4 / QB)) void tree_attn_mfma_kernel(AttnA
 #pragma unroll
         for (int db = 0; db < DB; ++db) {
             const int chunk = 4 * db + 2 * grp + ((sl & 3) >> 1);
-            v_off[db] = (int)lds0 + L::kVBase + wk * L::kMatBytes + row * L::kRowBytes + ((chunk ^ L::swz_v(row)) << 4) + 8 * (sl & 1);
+            v_off[db] = (int)lds0 + L::kVBase + wk * L::kMatBytes + row * L::kRowBytes + ((chunk ^ swz_v<D>(row)) << 4) + 8 * (sl & 1);
         }
     }
 
@@ -563,7 +504,7 @@ __global__ __launch_bounds__(64 * 2 * (4 / QB)) void tree_attn_mfma_kernel(AttnA
             const int R = X * L::kRowsPerLoad + ld_lrow;
             const int rc = min(r0 + R, rows - 1);
             const int j = rc / G, h = kvh * G + rc % G;
-            const uint32_t off = (uint32_t)(j * a.Hq + h) * (uint32_t)(D * 2) + 16u * (uint32_t)(ld_cpos ^ L::swz_k(R));
+            const uint32_t off = (uint32_t)(j * a.Hq + h) * (uint32_t)(D * 2) + 16u * (uint32_t)(ld_cpos ^ swz_k<D>(R));
             direct_load_16(q_seq, off, q_lds + X * 1024);
         }
     }
@@ -617,7 +558,7 @@ __global__ __launch_bounds__(64 * 2 * (4 / QB)) void tree_attn_mfma_kernel(AttnA
 #pragma unroll
     for (int kk = 0; kk < KK; ++kk) {
         const int R = 32 * wq + n;
-        qf[0][kk] = *(lds_bf16x8)(uint32_t)(q_lds + R * L::kRowBytes + (((2 * kk + g) ^ L::swz_k(R)) << 4));
+        qf[0][kk] = *(lds_bf16x8)(uint32_t)(q_lds + R * L::kRowBytes + (((2 * kk + g) ^ swz_k<D>(R)) << 4));
     }
     const uint32_t active = squeeze ? (uint32_t)__builtin_amdgcn_readfirstlane((int)*tile_flag) : first_set;
     const int nAct = __builtin_popcount(active);
@@ -963,20 +904,27 @@ __global__ __launch_bounds__(64 * 2 * (4 / QB)) void tree_attn_mfma_kernel(AttnA
     }
 }
 
-hipError_t prepare_tree_attn()
+// the kernel needs more dynamic LDS than the default limit
+template <int D>
+static hipError_t raise_lds()
 {
-    static std::atomic<unsigned long long> done128{0}, done64{0};
-    hipError_t e = raise_dynamic_lds_once(reinterpret_cast<const void*>(&tree_attn_mfma_kernel<128, kQB>), Geo<128>::kLdsBytes + 16, done128);
-    if (e != hipSuccess) return e;
-    return raise_dynamic_lds_once(reinterpret_cast<const void*>(&tree_attn_mfma_kernel<64, kQB>), Geo<64>::kLdsBytes + 16, done64);
+    static std::atomic<unsigned long long> done{0};
+    return raise_dynamic_lds_once(reinterpret_cast<const void*>(&tree_attn_mfma_kernel<D, kQB>), Geo<D>::kLdsBytes + 16, done);
 }
 
-template <int D, int QB>
+hipError_t prepare_tree_attn()
+{
+    hipError_t e = raise_lds<128>();
+    if (e == hipSuccess) e = raise_lds<64>();
+    return e == hipSuccess ? prepare_tree_attn_short() : e;
+}
+
+template <int D>
 static hipError_t launch_one(const AttnArgs& a, const SeqArgs& sa, int tiles, hipStream_t stream)
 {
-    const hipError_t e = prepare_tree_attn();              // the kernel needs more dynamic LDS than the default limit
+    const hipError_t e = raise_lds<D>();
     if (e != hipSuccess) return e;
-    tree_attn_mfma_kernel<D, QB><<<dim3(tiles * a.Hkv, a.splits, a.layers), 64 * 2 * (4 / QB), Geo<D>::kLdsBytes + 16, stream>>>(a, sa);
+    tree_attn_mfma_kernel<D, kQB><<<dim3(tiles * a.Hkv, a.splits, a.layers), 64 * 2 * (4 / kQB), Geo<D>::kLdsBytes + 16, stream>>>(a, sa);
     return hipGetLastError();
 }
 
@@ -1055,11 +1003,17 @@ hipError_t launch_tree_attn_mfma(AttnArgs a, const SeqArgs& sa, void* workspace,
     const size_t need = tree_attn_workspace_bytes(sa, a.Hq, a.Hkv, a.d, a.layers);
     if (a.splits > 1 && (workspace == nullptr || workspace_bytes < need || (reinterpret_cast<size_t>(workspace) & 15)))
         a.splits = 1, a.tree_split = 0;                        // no room for partial results: one workgroup walks it all
-    if (a.splits > 1) {
+    const ShortPlan plan = tree_attn_short_plan(sa, a.Hq, a.Hkv, a.d, a.layers, a.splits, a.splits > 1 ? need : 0);
+    const bool parts = plan.waves ? plan.splits > 1 : a.splits > 1;
+    if (parts) {
         a.counters = static_cast<unsigned*>(workspace);
         a.part = reinterpret_cast<uint32_t*>(static_cast<char*>(workspace) + kAttnCounterBytes);
     }
-    return a.d == 128 ? launch_one<128, kQB>(a, sa, tiles, stream) : launch_one<64, kQB>(a, sa, tiles, stream);
+    if (plan.waves) {
+        a.splits = plan.splits;
+        return launch_tree_attn_short(a, sa, plan.waves, stream);
+    }
+    return a.d == 128 ? launch_one<128>(a, sa, tiles, stream) : launch_one<64>(a, sa, tiles, stream);
 }
 
 #ifdef DYSPEC_STAMPS
