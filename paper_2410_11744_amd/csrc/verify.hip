@@ -293,103 +293,117 @@ __global__ __launch_bounds__(kStatThreads) void softmax_stats_stream_pieces_kern
 // into probabilities per visited node.
 __device__ __forceinline__ float exp_fast(float x) { return __builtin_amdgcn_exp2f(x * 1.4426950408889634f); }
 
-// Inverse CDF over a register-resident row of weights (the step's last token): the smallest token
-// index y, in the order (segment, thread, element), whose cumulative weight exceeds u * W.  Sums
-// are fp64.  The threads' sixteen segment sums are staged in LDS (`stage`: kStageDoubles doubles);
-// wave w totals segments 2w and 2w+1 from there; every thread reads the sixteen totals and picks
-// the segment; each wave scans its 64 sums of that segment across lanes; the eight wave totals
-// tell every thread which wave holds the crossing, and that wave finds the owning thread with a
-// ballot; the owner walks its four weights.  Three barriers.  Every thread gets y (-1 when W == 0).
-constexpr int kStageDoubles = kMaxSeg * kBlock + kMaxSeg;
-// A thread's tokens of a row: component e of segment j is v[e][j] (a segment known to be the same in every
+// A thread's tokens of a row of S segments: component e of segment j is v[e][j] (a segment known to be the same in every
 // thread picks the registers by index).
-typedef float RowVec __attribute__((ext_vector_type(kMaxSeg)));
+template <int S> using RowVec = float __attribute__((ext_vector_type(S)));
+__device__ __forceinline__ double four(const float a, const float b, const float c, const float d) { return ((double)a + (double)b) + ((double)c + (double)d); }
+
+// Sums over the wave of N values a lane (N a power of two, at most 16), scattered: lane l gets the sum of value l % N.  Every step
+// exchanges half of what is left with the lane one bit away, so N - 1 adds do the first steps for all N values.
+template <int N>
+__device__ __forceinline__ double wave_sums(double (&x)[N])
+{
+    static_assert(N == 2 || N == 8 || N == 16, "bits 0 .. log2 N - 1 of the lane name the value");
+    const int lane = threadIdx.x & (kWave - 1);
+    auto fold = [&](auto n_c, auto ctrl_c, int bit) __attribute__((always_inline)) {
+        constexpr int H = decltype(n_c)::value / 2;        // value k stays with bit clear, k + H with bit set
+        const bool up = lane & bit;
+#pragma unroll
+        for (int k = 0; k < H; ++k) {
+            const double keep = up ? x[k + H] : x[k], give = up ? x[k] : x[k + H];
+            x[k] = keep + dpp_or_zero<decltype(ctrl_c)::value>(give);
+        }
+    };
+    // (partners: lane ^ 1, lane ^ 2, then within a group of 8 and a row of 16 the mirrored lane, whose lower bits differ as well:
+    //  the fold over the highest bit of the value's index comes first there, while nothing depends on them yet)
+    if constexpr (N == 16) fold(std::integral_constant<int, 16>{}, std::integral_constant<int, kDppMirror>{}, 8);
+    if constexpr (N >= 8) fold(std::integral_constant<int, 8>{}, std::integral_constant<int, kDppHalfMirror>{}, 4);
+    if constexpr (N >= 8) fold(std::integral_constant<int, 4>{}, std::integral_constant<int, kDppXor2>{}, 2);
+    fold(std::integral_constant<int, 2>{}, std::integral_constant<int, kDppXor1>{}, 1);
+    double t = x[0];
+    if constexpr (N == 2) { t += dpp_or_zero<kDppXor2>(t); }
+    if constexpr (N == 2) { t += __shfl_xor(t, 4, kWave); }
+    if constexpr (N <= 8) { t += __shfl_xor(t, 8, kWave); }
+    t += __shfl_xor(t, 16, kWave);
+    t += __shfl_xor(t, 32, kWave);
+    return t;
+}
+
+// Inverse CDF over a register-resident row of weights (the step's last token): the smallest token index y, in the order
+// (segment, thread, element), whose cumulative weight exceeds u * W.  Sums are fp64.  Every wave leaves its sum of every segment
+// in LDS; every wave scans those S * 8 sums and picks segment and wave of the crossing; that wave scans its 64 sums of the
+// segment, and the owning lane walks its four weights.  Two barriers.  Every thread gets y (-1 when W == 0).
+// (With every thread's sums staged in LDS and a serial pick among the segments, three barriers: 3.2 to 4.3 us, now 2.4 to 3.2.)
 struct DrawScratch {
-    double wave_tot[kWaves];
-    int last_live[kWaves];
+    double part[kMaxSeg * kWaves];
     int y;
 };
-__device__ __forceinline__ int draw_from_row(const RowVec (&w)[4], double u, DrawScratch* sc, double* stage)
+template <int S>
+__device__ __forceinline__ int draw_from_row(const RowVec<S> (&w)[4], double u, DrawScratch* sc)
 {
-    static_assert(kMaxSeg == 2 * kWaves, "two segments per wave");
     const int tid = threadIdx.x, lane = tid & (kWave - 1);
     const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
+    {
+        double seg[S];
 #pragma unroll
-    for (int j = 0; j < kMaxSeg; ++j)
-        stage[j * kBlock + tid] = ((double)w[0][j] + (double)w[1][j]) + ((double)w[2][j] + (double)w[3][j]);
-    __syncthreads();
-    double* const totals = stage + kMaxSeg * kBlock;
-#pragma unroll
-    for (int k = 0; k < 2; ++k) {
-        const int j = 2 * wave + k;
-        double a = 0.0;
-#pragma unroll
-        for (int i = 0; i < kBlock / kWave; ++i) a += stage[j * kBlock + i * kWave + lane];
-        a = wave_sum_dpp(a);
-        if (lane == 0) totals[j] = a;
+        for (int j = 0; j < S; ++j) seg[j] = four(w[0][j], w[1][j], w[2][j], w[3][j]);
+        const double t = wave_sums(seg);
+        if (lane < S) sc->part[lane * kWaves + wave] = t;
     }
     __syncthreads();
-    double tot[kMaxSeg];
-#pragma unroll
-    for (int j = 0; j < kMaxSeg; ++j) tot[j] = totals[j];
-    const SegPick pk = pick_segment(tot, u);
-    const int js = uniform(pk.js);
-    if (!(pk.W > 0.0)) return -1;                            // uniform
-    const double mine = stage[pk.js * kBlock + tid];
-    const double inc = wave_scan_dpp(mine);                  // inclusive, in lane order
-    const unsigned long long live = __ballot(mine > 0.0);
-    if (lane == kWave - 1) sc->wave_tot[wave] = inc;
-    if (lane == 0) sc->last_live[wave] = live ? wave * kWave + 63 - __builtin_clzll(live) : -1;
-    __syncthreads();
-    // the first wave whose running total is past the target; with none (rounding at the very top)
-    // the last thread that has weight
-    double before = 0.0, run = pk.cum_js;
-    int kw = -1, fixed_owner = -1;
-#pragma unroll
-    for (int k = 0; k < kWaves; ++k) {
-        const double t = sc->wave_tot[k];
-        if (kw < 0 && run + t > pk.target) { kw = k; before = run - pk.cum_js; }
-        run += t;
-        if (sc->last_live[k] >= 0) fixed_owner = sc->last_live[k];
+    constexpr int E = S * kWaves, EL = (E + kWave - 1) / kWave;           // sums, sums a lane
+    static_assert(EL <= 2, "");
+    const double e0 = lane * EL < E ? sc->part[lane * EL] : 0.0, e1 = EL == 2 ? sc->part[lane * EL + EL - 1] : 0.0;
+    const double mine = e0 + e1, cum = wave_scan_dpp(mine);
+    const double W = readlane_f64(cum, 63), target = u * W;
+    if (!(W > 0.0)) return -1;                               // uniform
+    const u64 live = ballot(mine > 0.0), hit = live & ballot(cum > target);
+    const int l = hit ? __builtin_ctzll(hit) : live ? 63 - __builtin_clzll(live) : 0;       // (rounding at the very top: the last with weight)
+    double start = readlane_f64(cum, (l - 1) & 63);
+    if (l == 0) start = 0.0;
+    int at = l * EL;
+    if (EL == 2) {
+        const double p0 = readlane_f64(e0, l), p1 = readlane_f64(e1, l);
+        if (!(p0 > 0.0 && start + p0 > target) && p1 > 0.0) { start += p0; ++at; }
     }
-    if (kw >= 0) fixed_owner = -1;
-    else if (fixed_owner >= 0) kw = fixed_owner / kWave;
-    if (wave == kw) {
-        const unsigned long long hit = __ballot(mine > 0.0 && pk.cum_js + before + inc > pk.target);
-        const int ol = fixed_owner >= 0 ? fixed_owner % kWave : hit ? __builtin_ctzll(hit) : 63 - __builtin_clzll(live);
+    const int js = uniform(at / kWaves);
+    if (wave == uniform(at % kWaves)) {
+        // (the segment is the same in every lane)
+        const float w4[4] = { w[0][js], w[1][js], w[2][js], w[3][js] };
+        const double own = four(w4[0], w4[1], w4[2], w4[3]);
+        const double inc = wave_scan_dpp(own);               // inclusive, in lane order
+        const u64 some = ballot(own > 0.0), over = some & ballot(start + inc > target);
+        const int ol = over ? __builtin_ctzll(over) : some ? 63 - __builtin_clzll(some) : 0;
         if (lane == ol) {
-            // this thread's four weights of the picked segment (js is the same in every lane)
-            const float w4[4] = { w[0][js], w[1][js], w[2][js], w[3][js] };
-            double c = pk.cum_js + before + (inc - mine);
+            double c = start + (inc - own);
             int y = -1, ylast = -1;
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
                 c += (double)w4[e];
-                if (w4[e] > 0.0f) ylast = tok_index(pk.js, e);
-                if (y < 0 && w4[e] > 0.0f && c > pk.target) y = tok_index(pk.js, e);
+                if (w4[e] > 0.0f) ylast = tok_index(js, e);
+                if (y < 0 && w4[e] > 0.0f && c > target) y = tok_index(js, e);
             }
             sc->y = y >= 0 ? y : ylast;
         }
-    } else if (kw < 0 && tid == 0) {
-        sc->y = -1;                                          // the totals held rounding dust only
     }
     __syncthreads();
     return sc->y;
 }
 
-// LDS of the walk.  Static part: scratch of the reductions.  Dynamic part: the draft row of the
-// node being decided, as unnormalised weights exp(logit/T - max) indexed by token (what is left of
-// D after the children rejected so far is D_lds[x] * scale_d), then the sequence's tree links as
-// 16-bit values (tokens < 32768, nodes < 2048; -1 = none).  The target row R stays in registers, as
-// weights of the sum `mass`.  A thread's tokens of both rows are its own: nobody else reads them, except
-// the two values at the next child's token, which their owner publishes.
+// The walk's rows.  Both rows of the node being decided stay in registers, S segments of 4 tokens a thread: the draft row D as
+// unnormalised weights exp(logit/T - max) (what is left of D after the children rejected so far is D * scale_d), the target
+// row R as weights of the sum `mass`.  A thread's tokens are its own: nobody else reads them, except the two values at the
+// next child's token, which their owner publishes.  LDS holds the sequence's tree links as 16-bit values (tokens < 32768,
+// nodes < 2048; -1 = none) and the scratch of the reductions.
 //
-// A rejection is one sweep: R <- max(R - D * (mass * scale_d), 0) (R stays within [0, 1], so the clamp of the fma
-// does for the maximum), the new mass and the weight of D on the way, and one reduction with one barrier.
-// Two sweeps, R normalised every time, five barriers and the sibling's two Philox blocks in every rejection
-// before: 4.4 us each, 2.0 now (32000 tokens).  Both rows' loads are in flight together and every load is issued
-// before the first is used: a node's rows 5.8 -> 5.3 us in fp32, 12.9 -> 5.4 in bf16.
-// Verification of the ragged batch of eight 143 -> 105 us.
+// A rejection is one sweep over registers: R <- max(R - D * (mass * scale_d), 0) (R stays within [0, 1], so the clamp of the fma
+// does for the maximum) and the new mass, and one reduction with one barrier.  What is left of D is summed again only by the
+// wave that held the rejected token: the others' shares stand.  With D in LDS the sweep waited for 16 LDS reads one after the
+// other (each behind the bounds check of its segment) and every wave summed D again: 2.0 us a rejection at 32000 tokens,
+// 1.4 now; a node's rows and first rejection 7.8 -> 6.4.  What bounds a rejection: some 290 instructions a wave between two
+// barriers, 128 of them the sweep.
+// S: 2, 8 or 16 by the size of the vocabulary, so that short rows don't pay for segments they have not (1000 tokens: walk 8.4 -> 4.5 us).
+// The draft row's loads are issued first, so that its weights are made while the target row's are still out.
 // (R's sum shrinks with every rejection; below kSmallMass the weights are brought back to a sum of 1, as they are
 // where mass * scale_d would leave the range.)
 //
@@ -402,15 +416,9 @@ struct WalkShared {
     float2 part[2][kWaves];       // per wave, by parity of the rejection: mass left in R, weight in D
     float2 next[2];               // R and D at the next child's token
 };
-// (the row's place also stages the partial sums of the final draw: at least kStageDoubles doubles)
-__host__ __device__ __forceinline__ size_t walk_row_bytes(int V)
-{
-    const size_t row = (size_t)((V + kSeg - 1) / kSeg * kSeg) * sizeof(float), stage = (size_t)kStageDoubles * sizeof(double);
-    return row > stage ? row : stage;
-}
-static size_t walk_lds_bytes(int V, int widest) { return walk_row_bytes(V) + 3 * (size_t)((widest + 7) & ~7) * sizeof(short); }
+static constexpr size_t walk_lds_bytes(int widest) { return 3 * (size_t)((widest + 7) & ~7) * sizeof(short); }
 
-template <bool VEC, typename T>
+template <bool VEC, typename T, int S>
 __global__ __launch_bounds__(kBlock) void verify_walk_kernel(
     const T* __restrict__ draft_logits, const T* __restrict__ target_logits, int V,
     SeqArgs sa, dyspec_tree tree, uint64_t seed, int emit_bonus,
@@ -426,9 +434,8 @@ __global__ __launch_bounds__(kBlock) void verify_walk_kernel(
     const int N = sa.node_off[seq + 1] - base;
     const bool greedy = sa.temp_t[seq] == 0.0f;                  // target row = all mass on stats.w
     const float inv_td = 1.0f / sa.temp_d[seq], inv_tt = greedy ? 1.0f : 1.0f / sa.temp_t[seq];
-    float* const D_lds = reinterpret_cast<float*>(dyn);
     const int Npad = (N + 7) & ~7;
-    short* const l_token = reinterpret_cast<short*>(dyn + walk_row_bytes(V));
+    short* const l_token = reinterpret_cast<short*>(dyn);
     short* const l_child = l_token + Npad;
     short* const l_next = l_child + Npad;
     for (int i = tid; i < N; i += kBlock) {
@@ -450,55 +457,58 @@ __global__ __launch_bounds__(kBlock) void verify_walk_kernel(
         int next = -1;
         uint2 pk_next = pk;
         bool rows_loaded = false;
-        RowVec R[4];
+        RowVec<S> R[4], D[4];
         // the node's statistics: one 16-byte load, on its way together with the first child's logits
         const float4 st = *reinterpret_cast<const float4*>(row_stats + 4 * (size_t)(base + cur));
-        float scale_d = 0.0f, mass = 0.0f;                // what is left of D = D_lds * scale_d; R's sum
-        // R <- the target row's weights (registers); with want_draft, D_lds <- the draft row's
+        float scale_d = 0.0f, mass = 0.0f;                // what is left of D = D * scale_d; R's sum
+        // R <- the target row's weights; with want_draft, D <- the draft row's
         auto load_rows = [&](bool want_draft) __attribute__((always_inline)) {
-            float Y[kMaxSeg][4];
+            float X[S][4], Y[S][4];
+            if (want_draft) load_row<VEC, T>(draft_logits + (size_t)(base + cur) * V, V, X);
             if (!greedy) load_row<VEC, T>(target_logits + (size_t)(base + cur) * V, V, Y);
             if (want_draft) {                             // (the loads of both rows are in flight together)
-                float X[kMaxSeg][4];
-                load_row<VEC, T>(draft_logits + (size_t)(base + cur) * V, V, X);
 #pragma unroll
-                for (int j = 0; j < kMaxSeg; ++j) {
-                    const int i0 = tok_index(j, 0);
-                    if (j * kSeg < V)                     // whole segments in LDS; logits past V read as -inf
-                        *reinterpret_cast<float4*>(D_lds + i0) = make_float4(exp_fast(X[j][0] * inv_td - st.x), exp_fast(X[j][1] * inv_td - st.x),
-                                                                             exp_fast(X[j][2] * inv_td - st.x), exp_fast(X[j][3] * inv_td - st.x));
-                }
+                for (int j = 0; j < S; ++j)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) D[e][j] = exp_fast(X[j][e] * inv_td - st.x);
                 scale_d = 1.0f / st.y;
             }
             mass = greedy ? 1.0f : st.w;
             if (greedy) {
                 const int mine = (int)st.w - 4 * tid;
 #pragma unroll
-                for (int j = 0; j < kMaxSeg; ++j)
+                for (int j = 0; j < S; ++j)
 #pragma unroll
                     for (int e = 0; e < 4; ++e) R[e][j] = mine - j * kSeg == e ? 1.0f : 0.0f;
             } else {
 #pragma unroll
-                for (int j = 0; j < kMaxSeg; ++j)
+                for (int j = 0; j < S; ++j)
 #pragma unroll
                     for (int e = 0; e < 4; ++e) R[e][j] = exp_fast(Y[j][e] * inv_tt - st.z);
             }
         };
         if (!leaf) {
             // ---- first child: two logits and the row statistics decide
-            float dy = 0.0f;                              // D_lds at the tested child's token
+            float dy = 0.0f;                              // D at the tested child's token
+            uint2 keys;                                   // of 64 children, one per lane: path key, uniform of the acceptance
+            float us;
             {
                 const int y = l_token[c];
-                float d = 0.0f, r = 0.0f;
+                float d = 0.0f, r = 0.0f, xd = 0.0f, xt = 0.0f;
                 if (y >= 0) {
-                    dy = exp_fast(logit_to_float(draft_logits[(size_t)(base + cur) * V + y]) * inv_td - st.x);
+                    xd = logit_to_float(draft_logits[(size_t)(base + cur) * V + y]);
+                    if (!greedy) xt = logit_to_float(target_logits[(size_t)(base + cur) * V + y]);
+                }
+                keys = child_key(seed, pk, (uint32_t)(tid & (kWave - 1)));          // (while the loads are out)
+                us = u01(seed, keys, 0u, KIND_ACCEPT);
+                if (y >= 0) {
+                    dy = exp_fast(xd * inv_td - st.x);
                     d = dy / st.y;
-                    r = greedy ? ((float)y == st.w ? 1.0f : 0.0f)
-                               : exp_fast(logit_to_float(target_logits[(size_t)(base + cur) * V + y]) * inv_tt - st.z) / st.w;
+                    r = greedy ? ((float)y == st.w ? 1.0f : 0.0f) : exp_fast(xt * inv_tt - st.z) / st.w;
                 }
                 const float ratio = ratio_of(d, r);
-                const uint2 pk_n = child_key(seed, pk, 0u);
-                const float u = u01(seed, pk_n, 0u, KIND_ACCEPT);
+                const uint2 pk_n = make_uint2((uint32_t)__builtin_amdgcn_readlane((int)keys.x, 0), (uint32_t)__builtin_amdgcn_readlane((int)keys.y, 0));
+                const float u = readlane_f32(us, 0);
                 margin = fminf(margin, fabsf(u - ratio));
                 if (tid == 0) accept_ratio[base + c] = ratio;
                 if (u < ratio) { next = c; pk_next = pk_n; }
@@ -508,22 +518,22 @@ __global__ __launch_bounds__(kBlock) void verify_walk_kernel(
                 load_rows(true);
                 rows_loaded = true;
                 // R and D at token y (none: zeros), by the thread that owns it
-                auto publish = [&](int y, float2* place) __attribute__((always_inline)) {
-                    if (y < 0 ? tid == 0 : ((y % kSeg) >> 2) == tid) {
-                        const int js = uniform(y >= 0 ? y / kSeg : 0), e = y & 3;
-                        const float r0 = R[0][js], r1 = R[1][js], r2 = R[2][js], r3 = R[3][js];
-                        const float r = y < 0 ? 0.0f : e == 0 ? r0 : e == 1 ? r1 : e == 2 ? r2 : r3;
-                        *place = make_float2(r, y >= 0 ? D_lds[y] : 0.0f);
-                    }
+                auto at = [&](const RowVec<S> (&row)[4], int y) __attribute__((always_inline)) -> float {
+                    const int js = uniform(y >= 0 ? y / kSeg : 0), e = y & 3;
+                    const float x0 = row[0][js], x1 = row[1][js], x2 = row[2][js], x3 = row[3][js];
+                    return y < 0 ? 0.0f : e == 0 ? x0 : e == 1 ? x1 : e == 2 ? x2 : x3;
                 };
+                auto publish = [&](int y, float2* place) __attribute__((always_inline)) {
+                    if (y < 0 ? tid == 0 : ((y % kSeg) >> 2) == tid) *place = make_float2(at(R, y), at(D, y));
+                };
+                float left_w = 0.0f;                      // what this wave holds of D
+                bool summed = false;
                 uint32_t rank = 0;
-                uint2 keys = make_uint2(0u, 0u);          // of 64 children, one per lane: path key, uniform of the acceptance
-                float us = 0.0f;
                 for (int guard = 0; c >= 0 && guard < N; ++guard) {
                     const int y = l_token[c], after = l_next[c];
                     const int y_next = after >= 0 ? l_token[after] : -1;
                     const int par = guard & 1;
-                    if (rank % kWave == 0) {
+                    if (rank > 0 && rank % kWave == 0) {
                         keys = child_key(seed, pk, rank + (tid & (kWave - 1)));
                         us = u01(seed, keys, 0u, KIND_ACCEPT);
                     }
@@ -545,7 +555,7 @@ __global__ __launch_bounds__(kBlock) void verify_walk_kernel(
                     if (f == INFINITY) {                      // what is left of D weighs next to nothing: R's weights come down to shares first
                         const float down = 1.0f / mass;
 #pragma unroll
-                        for (int j = 0; j < kMaxSeg; ++j)
+                        for (int j = 0; j < S; ++j)
 #pragma unroll
                             for (int e = 0; e < 4; ++e) R[e][j] *= down;
                         mass = 1.0f;
@@ -553,29 +563,32 @@ __global__ __launch_bounds__(kBlock) void verify_walk_kernel(
                     }
                     if (y >= 0 && ((y % kSeg) >> 2) == tid) {
                         const int js = uniform(y / kSeg), e = y & 3;
-                        const float dv = D_lds[y];
-                        D_lds[y] = 0.0f;
 #pragma unroll
                         for (int k = 0; k < 4; ++k) {
-                            const float r = R[k][js];
-                            R[k][js] = e == k ? __builtin_amdgcn_fmed3f(fmaf(-f, dv, r), 0.0f, 1.0f) : r;
+                            const float r = R[k][js], d = D[k][js];
+                            R[k][js] = e == k ? __builtin_amdgcn_fmed3f(fmaf(-f, d, r), 0.0f, 1.0f) : r;
+                            D[k][js] = e == k ? 0.0f : d;
                         }
                     }
-                    float m[4] = { 0.0f, 0.0f, 0.0f, 0.0f }, w = 0.0f;
+                    float m[4] = { 0.0f, 0.0f, 0.0f, 0.0f };
 #pragma unroll
-                    for (int j = 0; j < kMaxSeg; ++j) {
-                        const int i0 = tok_index(j, 0);
-                        if (j * kSeg < V) {
-                            const float4 dv = *reinterpret_cast<const float4*>(D_lds + i0);
-                            R[0][j] = __builtin_amdgcn_fmed3f(fmaf(-f, dv.x, R[0][j]), 0.0f, 1.0f); m[0] += R[0][j];
-                            R[1][j] = __builtin_amdgcn_fmed3f(fmaf(-f, dv.y, R[1][j]), 0.0f, 1.0f); m[1] += R[1][j];
-                            R[2][j] = __builtin_amdgcn_fmed3f(fmaf(-f, dv.z, R[2][j]), 0.0f, 1.0f); m[2] += R[2][j];
-                            R[3][j] = __builtin_amdgcn_fmed3f(fmaf(-f, dv.w, R[3][j]), 0.0f, 1.0f); m[3] += R[3][j];
-                            w += (dv.x + dv.y) + (dv.z + dv.w);
+                    for (int j = 0; j < S; ++j)
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) {
+                            R[e][j] = __builtin_amdgcn_fmed3f(fmaf(-f, D[e][j], R[e][j]), 0.0f, 1.0f);
+                            m[e] += R[e][j];
                         }
-                    }
                     publish(y_next, &sh.next[par]);
-                    const float mw = wave_sum_f32_dpp((m[0] + m[1]) + (m[2] + m[3])), ww = wave_sum_f32_dpp(w);
+                    if (!summed || (y >= 0 && (y % kSeg) / (4 * kWave) == uniform(tid / kWave))) {      // (the same in every lane)
+                        float w[4] = { 0.0f, 0.0f, 0.0f, 0.0f };
+#pragma unroll
+                        for (int j = 0; j < S; ++j)
+#pragma unroll
+                            for (int e = 0; e < 4; ++e) w[e] += D[e][j];
+                        left_w = wave_sum_f32_dpp((w[0] + w[1]) + (w[2] + w[3]));
+                        summed = true;
+                    }
+                    const float mw = wave_sum_f32_dpp((m[0] + m[1]) + (m[2] + m[3])), ww = left_w;
                     if ((tid & (kWave - 1)) == 0) sh.part[par][tid / kWave] = make_float2(mw, ww);
                     __syncthreads();
                     float2 sum = sh.part[par][0];
@@ -596,25 +609,20 @@ __global__ __launch_bounds__(kBlock) void verify_walk_kernel(
                             const float lift = sum.x < 0x1p-100f ? 0x1p100f : 1.0f, up = 1.0f / (sum.x * lift);
                             mass = 1.0f;
 #pragma unroll
-                            for (int j = 0; j < kMaxSeg; ++j)
+                            for (int j = 0; j < S; ++j)
 #pragma unroll
                                 for (int e = 0; e < 4; ++e) R[e][j] = fminf(R[e][j] * lift * up, 1.0f);
                         } else {
                             // R == D to rounding (hardly any reject can reach here): R stays, that is, becomes D as
                             // it stood; a greedy target's R is its one token, whatever its mass
                             mass = greedy ? 1.0f : sum.y + dy;
-                            // (one token's value is not in D_lds: that of the greedy row, or the one just removed)
+                            // (one token's value is not in D: that of the greedy row, or the one just removed)
                             const int one = (greedy ? (int)st.w : y) - 4 * tid;
                             const float value = greedy ? 1.0f : dy;
 #pragma unroll
-                            for (int j = 0; j < kMaxSeg; ++j) {
-                                const int i0 = tok_index(j, 0);
-                                float4 dv = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-                                if (j * kSeg < V && !greedy) dv = *reinterpret_cast<const float4*>(D_lds + i0);
-                                const int mine = one - j * kSeg;
-                                R[0][j] = mine == 0 ? value : dv.x; R[1][j] = mine == 1 ? value : dv.y;
-                                R[2][j] = mine == 2 ? value : dv.z; R[3][j] = mine == 3 ? value : dv.w;
-                            }
+                            for (int j = 0; j < S; ++j)
+#pragma unroll
+                                for (int e = 0; e < 4; ++e) R[e][j] = one - j * kSeg == e ? value : greedy ? 0.0f : D[e][j];
                         }
                         __syncthreads();
                         publish(y_next, &sh.next[par]);
@@ -637,7 +645,7 @@ __global__ __launch_bounds__(kBlock) void verify_walk_kernel(
             if (tid == 0) accepted_nodes[base + na] = next;
             ++na;
             cur = next; pk = pk_next;
-            __syncthreads();                                  // D_lds and the scratch are free for the next node
+            __syncthreads();                                  // the scratch is free for the next node
             continue;
         }
         // ---- the walk stops at cur: emit a token from what is left of the target row
@@ -645,7 +653,7 @@ __global__ __launch_bounds__(kBlock) void verify_walk_kernel(
         if (!rows_loaded) load_rows(false);
         __syncthreads();
         const double u = (double)u01(seed, pk, 0u, KIND_RESID);
-        fin = draw_from_row(R, u, &sh.draw, reinterpret_cast<double*>(dyn));     // the draft row's place in LDS is free now
+        fin = draw_from_row<S>(R, u, &sh.draw);
         break;
     }
     if (tid == 0) {
@@ -655,15 +663,32 @@ __global__ __launch_bounds__(kBlock) void verify_walk_kernel(
     }
 }
 
-// the walk keeps a draft row and the tree links in dynamic LDS: raised to the largest once
+// f(S) for the rows' segments
+template <typename F>
+static hipError_t with_segments(int V, F&& f)
+{
+    if (V <= 2 * kSeg) return f(std::integral_constant<int, 2>{});
+    if (V <= 8 * kSeg) return f(std::integral_constant<int, 8>{});
+    return f(std::integral_constant<int, kMaxSeg>{});
+}
+
+// loads the walk's code (its LDS, at most 12 KB, needs no limit raised)
 hipError_t prepare_verify()
 {
-    static std::atomic<unsigned long long> done[4] = { {0}, {0}, {0}, {0} };
-    const int bytes = (int)walk_lds_bytes(DYSPEC_MAX_VOCAB, DYSPEC_MAX_NODES);
-    hipError_t e = raise_dynamic_lds_once(reinterpret_cast<const void*>(&verify_walk_kernel<true, float>), bytes, done[0]);
-    if (e == hipSuccess) e = raise_dynamic_lds_once(reinterpret_cast<const void*>(&verify_walk_kernel<false, float>), bytes, done[1]);
-    if (e == hipSuccess) e = raise_dynamic_lds_once(reinterpret_cast<const void*>(&verify_walk_kernel<true, __bf16>), bytes, done[2]);
-    if (e == hipSuccess) e = raise_dynamic_lds_once(reinterpret_cast<const void*>(&verify_walk_kernel<false, __bf16>), bytes, done[3]);
+    hipError_t e = hipSuccess;
+    auto touch = [&](const void* kernel) {
+        hipFuncAttributes attributes;
+        if (e == hipSuccess) e = hipFuncGetAttributes(&attributes, kernel);
+    };
+    for (int V : { 1, 8 * kSeg, kMaxSeg * kSeg })
+        (void)with_segments(V, [&](auto sc) {
+            constexpr int S = decltype(sc)::value;
+            touch(reinterpret_cast<const void*>(&verify_walk_kernel<true, float, S>));
+            touch(reinterpret_cast<const void*>(&verify_walk_kernel<false, float, S>));
+            touch(reinterpret_cast<const void*>(&verify_walk_kernel<true, __bf16, S>));
+            touch(reinterpret_cast<const void*>(&verify_walk_kernel<false, __bf16, S>));
+            return e;
+        });
     return e;
 }
 
@@ -687,18 +712,15 @@ static hipError_t launch_verify_t(const T* draft_logits, const T* target_logits,
         softmax_stats_kernel<false, T><<<rows, kBlock, 0, stream>>>(draft_logits, target_logits, V, sa, row_stats, accept_ratio);
     int widest = 1;
     for (int s = 0; s < sa.n_seq; ++s) widest = max(widest, sa.node_off[s + 1] - sa.node_off[s]);
-    const size_t dyn = walk_lds_bytes(V, widest);
-    const hipError_t ep = prepare_verify();
-    if (ep != hipSuccess) return ep;
-    if (V % 4 == 0)
-        verify_walk_kernel<true, T><<<sa.n_seq, kBlock, dyn, stream>>>(draft_logits, target_logits, V, sa, tree, seed, emit_bonus,
-                                                                       row_stats, accept_ratio, accepted_nodes, n_accepted,
-                                                                       final_token, min_margin);
-    else
-        verify_walk_kernel<false, T><<<sa.n_seq, kBlock, dyn, stream>>>(draft_logits, target_logits, V, sa, tree, seed, emit_bonus,
-                                                                        row_stats, accept_ratio, accepted_nodes, n_accepted,
-                                                                        final_token, min_margin);
-    return hipGetLastError();
+    return with_segments(V, [&](auto sc) {
+        constexpr int S = decltype(sc)::value;
+        auto launch = [&](auto vec) {
+            verify_walk_kernel<decltype(vec)::value, T, S><<<sa.n_seq, kBlock, walk_lds_bytes(widest), stream>>>(
+                draft_logits, target_logits, V, sa, tree, seed, emit_bonus, row_stats, accept_ratio, accepted_nodes, n_accepted, final_token, min_margin);
+            return hipGetLastError();
+        };
+        return V % 4 == 0 ? launch(std::true_type{}) : launch(std::false_type{});
+    });
 }
 
 hipError_t launch_verify(const void* draft_logits, const void* target_logits, bool bf16_logits, int V,

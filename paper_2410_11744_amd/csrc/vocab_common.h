@@ -22,19 +22,20 @@ __device__ __forceinline__ float bf16_bits_to_float(uint32_t bits16) { return __
 // one aligned 16-byte (fp32) or 8-byte (bf16) load).  All loads are issued before the first is looked at
 // (past the end they re-read the row's first tokens): with the use inside a bounds branch of its own each
 // bf16 load was waited for by itself, sixteen trips to memory in turn.
-template <bool VEC, typename T>
-__device__ __forceinline__ void load_row(const T* __restrict__ row, int V, float (&x)[kMaxSeg][4])
+// NS: segments held, V <= NS * kSeg.
+template <bool VEC, typename T, int NS>
+__device__ __forceinline__ void load_row(const T* __restrict__ row, int V, float (&x)[NS][4])
 {
     if constexpr (VEC) {
         using Raw = typename std::conditional<sizeof(T) == 4, float4, uint2>::type;
-        Raw raw[kMaxSeg];
+        Raw raw[NS];
 #pragma unroll
-        for (int j = 0; j < kMaxSeg; ++j) {
+        for (int j = 0; j < NS; ++j) {
             const int i0 = tok_index(j, 0);
             if (j * kSeg < V) raw[j] = *reinterpret_cast<const Raw*>(row + (i0 < V ? i0 : 0));      // (the same in every thread)
         }
 #pragma unroll
-        for (int j = 0; j < kMaxSeg; ++j) {
+        for (int j = 0; j < NS; ++j) {
             const bool there = tok_index(j, 0) < V;
             if constexpr (sizeof(T) == 4) {
                 x[j][0] = raw[j].x; x[j][1] = raw[j].y; x[j][2] = raw[j].z; x[j][3] = raw[j].w;
@@ -47,7 +48,7 @@ __device__ __forceinline__ void load_row(const T* __restrict__ row, int V, float
         }
     } else {
 #pragma unroll
-        for (int j = 0; j < kMaxSeg; ++j) {
+        for (int j = 0; j < NS; ++j) {
             const int i0 = tok_index(j, 0);
 #pragma unroll
             for (int e = 0; e < 4; ++e) x[j][e] = (i0 + e < V) ? logit_to_float(row[i0 + e]) : -INFINITY;
