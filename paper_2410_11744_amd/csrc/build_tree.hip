@@ -247,10 +247,11 @@ __global__ __launch_bounds__(kBlock) void build_tree_kernel(
 // What bounds it: the number of instructions of control's pop and of wave 1's draw (a wave alone issues one in
 // eight cycles, whatever it is; an LDS read is back after 52), and where a node is popped again at once or a tree is
 // one chain, those of a draw from memory (the trip itself is over before the Philox blocks made meanwhile).
-// Measured against a workgroup that popped and drew in turn, two barriers a draw, with the pass over the rows: 512 rows of 32000 tokens 1378 -> 508 us (with eight drawing waves on two
-// SIMDs 562, on all four 543: a request waits for the draw its wave is at), 128 rows 346 -> 134, 32 rows of 1000 tokens
-// 92 -> 55; a single chain of 512 nodes 1413 -> 1130.  Of one size the time depends on the table, that is, on how often nodes
-// other than the root are popped again: 458 to 707 us over nine tables of 512 rows of independent normal logits.
+// Measured against a workgroup that popped and drew in turn, two barriers a draw, with the pass over the rows: 512 rows of
+// 32000 tokens 1378 -> 508 us (with eight drawing waves on two SIMDs 562, on all four 543: a request waits for the draw its
+// wave is at), 128 rows 346 -> 134, 32 rows of 1000 tokens 92 -> 55; a single chain of 512 nodes 1413 -> 1130.  (All before
+// the sorted list of slots, see pop_nodes.)  Of one size the time depends on the table, that is, on how often nodes
+// other than the root are popped again: 440 to 600 us over tables of 512 rows of independent normal logits.
 constexpr int kBuildThreads = 1024;
 constexpr int kDrawWaves = kBuildThreads / kWave - 2;
 constexpr int kRing = 16;
@@ -360,16 +361,37 @@ __device__ __forceinline__ void fetch_row(double* ws, int base, int i, HeldRow& 
     h.m = *ws_rowmax(ws, base + i);
 }
 
+// Of 64 ranks of a node's draws (first + lane): the draw's uniform, the path key of the node the draw makes, that node's first uniform.
+// A node drawn from again gets them for the next 64 draws at once; the first draw, the only one of most nodes, makes its own.
+struct DrawNames {
+    int node, first;
+    float u, child_u;
+    u64 child;
+};
+__device__ __forceinline__ void make_names(DrawNames& d, uint64_t seed, u64 key_word, int node, int rank)
+{
+    const uint2 key = split_key(key_word);
+    d.node = node;
+    d.first = rank & ~(kWave - 1);
+    const uint32_t r = (uint32_t)(d.first + (int)(threadIdx.x & 63));
+    const uint2 child = child_key(seed, key, r);
+    d.u = u01(seed, key, r, KIND_BUILD);
+    d.child_u = u01(seed, child, 0u, KIND_BUILD);
+    d.child = join_key(child);
+}
+
 // One draw for node i of a sequence by a wave, the node's row in global memory: what is left of its
 // totals lies in the workspace (totals 4 l .. 4 l + 3 are read and written by lane l), as do the tokens drawn
 // before (entry r by lane r % 64); this wave alone draws for the node.
 template <bool VEC>
 __device__ __forceinline__ void draw_for_node(uint32_t place, uint32_t gone, const float* __restrict__ row, int V,
-                                              double inv_temp, uint64_t seed, double* ws, int ws_row, HeldRow& h, int rank)
+                                              double inv_temp, uint64_t seed, double* ws, int ws_row, HeldRow& h, DrawNames& names, int node, int rank)
 {
     const int lane = threadIdx.x & 63;
-    const double u = (double)*lds_at<float>(place + kUAt);
     const u64 key_word = *lds_at<u64>(place + kKeyAt);
+    if (rank > 0 && (rank & (kWave - 1)) == 0) make_names(names, seed, key_word, node, rank);     // (the draw before has not left this one's uniform)
+    const bool named = names.node == node && names.first == (rank & ~(kWave - 1));                 // uniform
+    const double u = (double)(named ? readlane_f32(names.u, rank & (kWave - 1)) : *lds_at<float>(place + kUAt));
     // ---- the run: the lane of the crossing, then one of its four totals (every lane walks its own)
     const double t01 = h.tot[0] + h.tot[1], four = t01 + (h.tot[2] + h.tot[3]);
     const double cum = wave_scan_dpp(four);
@@ -419,13 +441,23 @@ __device__ __forceinline__ void draw_for_node(uint32_t place, uint32_t gone, con
         }
         out = lds_now(lds_at<uint32_t>(gone + 4 * (lane / 16))) >> (2 * (lane & 15));
     }
-    // ---- while the logits are on their way: lane 0 the key of the node this draw makes, lane 1 the
-    //      uniform of this node's next draw; then the first uniform of the new node
-    const uint2 key = split_key(key_word);
-    const uint4 blk = philox4x32_10(make_uint4(key.x, key.y, (uint32_t)rank + (lane & 1), (lane & 1) ? KIND_BUILD : KIND_PATH), seed_key(seed));
-    const uint2 child = make_uint2((uint32_t)__builtin_amdgcn_readlane((int)blk.x, 0), (uint32_t)__builtin_amdgcn_readlane((int)blk.y, 0));
-    const float next_u = (float)(blk.x >> 8) * (1.0f / 16777216.0f);                // lane 1's counts
-    const float child_u = u01(seed, child, 0u, KIND_BUILD);
+    // ---- while the logits are on their way: the key of the node this draw makes, its first uniform, the uniform of this node's next draw
+    uint2 child;
+    float next_u, child_u;
+    if (rank == 0) {
+        // lane 0 the key, lane 1 the next draw's uniform
+        const uint2 key = split_key(key_word);
+        const uint4 blk = philox4x32_10(make_uint4(key.x, key.y, (uint32_t)(lane & 1), (lane & 1) ? KIND_BUILD : KIND_PATH), seed_key(seed));
+        child = make_uint2((uint32_t)__builtin_amdgcn_readlane((int)blk.x, 0), (uint32_t)__builtin_amdgcn_readlane((int)blk.y, 0));
+        next_u = (float)(blk.x >> 8) * (1.0f / 16777216.0f);                        // lane 1's counts
+        child_u = u01(seed, child, 0u, KIND_BUILD);
+    } else {
+        if (!named) make_names(names, seed, key_word, node, rank);
+        const int at = rank & (kWave - 1);
+        child = make_uint2((uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)names.child, at), (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(names.child >> 32), at));
+        next_u = names.u;                                                           // lane at + 1's counts
+        child_u = readlane_f32(names.child_u, at);
+    }
     // ---- the token: as above among the run's 128
     double z[2], w[2];
 #pragma unroll
@@ -446,7 +478,7 @@ __device__ __forceinline__ void draw_for_node(uint32_t place, uint32_t gone, con
     const int e = __builtin_amdgcn_readlane(second, ol);
     const int y = run0 + 2 * ol + e;
     const double wy = readlane_f64(e ? w[1] : w[0], ol);
-    if (lane == 1) *lds_at<float>(place + kUAt) = next_u;
+    if (lane == ((rank + 1) & (kWave - 1))) *lds_at<float>(place + kUAt) = next_u;
     if (lane == 0) publish(place, wy / W, join_key(child), child_u, kAnswer | ((uint32_t)rank << 15) | (uint32_t)y);
     // what is left of the run
     const double left = wave_sum_dpp(lane == ol ? (e ? w[0] : w[1]) : mine);
@@ -473,6 +505,7 @@ __device__ __attribute__((noinline)) void draw_for_nodes(uint32_t lds_, int mine
     const uint32_t nodes = lds + BuildLds::nodes, gone = lds + BuildLds::gone + mine * (kRun / 8);
     RowCopies<HeldRow> rows;
     rows.open(mine);
+    DrawNames names = { -1, 0, 0.f, 0.f, 0ull };
     const auto fetch = [&](int i, HeldRow& h) __attribute__((always_inline)) { fetch_row(ws, base, i, h); };
     uint32_t seen = 1u << 31;                       // the news last looked at (none yet)
     bool look = mine == 0;                          // requests may be open (node 0's, at the start)
@@ -515,29 +548,82 @@ __device__ __attribute__((noinline)) void draw_for_nodes(uint32_t lds_, int mine
             rank = (int)(w >> 15);
         }
         rows.hold(i, kDrawWaves, fetch);
-        draw_for_node<VEC>(nodes + kNode * i, gone, draft_logits + (size_t)(base + i) * V, V, inv_temp, seed, ws, base + i, rows.held, rank);
+        const float* const row = draft_logits + (size_t)(base + i) * V;
+        draw_for_node<VEC>(nodes + kNode * i, gone, row, V, inv_temp, seed, ws, base + i, rows.held, names, i, rank);
         if (uniform(lds_now(lds_at<uint32_t>(lds + BuildLds::news))) == kStop) return;
     }
 }
 
-// Among the lanes of `cand` (of equal slot values) those of the slot opened first.
-__device__ __forceinline__ u64 opened_first(u64 cand, uint32_t opened_at)
-{
-    int first = 0;
-    if ((cand >> (threadIdx.x & 63)) & 1u) first = 0xffff - (int)lds_now(lds_at<unsigned short>(opened_at));
-    return cand & ballot(first == wave_max_dpp_int(first));
-}
-// Largest of the upper words over rows of 16 lanes (every lane of a row gets its row's).
-__device__ __forceinline__ int row_max(int x)
-{
-    x = max(x, dpp_or_zero<kDppXor1>(x));
-    x = max(x, dpp_or_zero<kDppXor2>(x));
-    x = max(x, dpp_or_zero<kDppHalfMirror>(x));
-    return max(x, dpp_or_zero<kDppMirror>(x));
-}
-
 // Wave 0: pops and appends.  Returns the number of rows built, its complement if a draw stayed out.  Row i's parent | rank << 10 | previous
 // sibling << 20 goes to `parent` for the time being.
+//
+// The frontier is a sorted list in the lanes: lane k holds the k-th best open slot, of equal values the one opened first (an
+// empty place: value -1).  A pop takes lane 0; the popped node's next slot goes where its value belongs, and the lanes before
+// that place move up by one; the new node's slot makes the lanes behind its place move down.  A slot that finds no place among
+// the 64 is left out: `unlisted` is the largest value left out so far, and while lane 0 is above it the list is as good as the
+// whole frontier.  Else the list is made again from the slots in LDS (`relist`), the first kRelisted of them: a few times
+// in trees of many equally good slots, never in 512 rows of 1000 or 32000 tokens of independent normal logits.
+// Against the best of each lane's nodes kept in the lane and the maximum over the lanes found at each pop, and the other
+// nodes of the popped one's lane looked over again: a pop whose draw is there 0.61 -> 0.51 us; with the draws' names
+// for 64 ranks at once (DrawNames) 512 rows of 32000 tokens 441 -> 417, 495 -> 471 and 570 -> 547 us on three tables.
+constexpr int kRelisted = 16;
+constexpr int kDppWaveShl1 = 0x130;     // lane i: lane i + 1's
+constexpr int kDppWaveShr1 = 0x138;     // lane i: lane i - 1's
+template <int CTRL> __device__ __forceinline__ int dpp_or_own(int x) { return __builtin_amdgcn_update_dpp(x, x, CTRL, 0xf, 0xf, false); }
+template <int CTRL> __device__ __forceinline__ double dpp_or_own(double x)
+{
+    return __hiloint2double(dpp_or_own<CTRL>(__double2hiint(x)), dpp_or_own<CTRL>(__double2loint(x)));
+}
+struct Slots {
+    double value;           // lane k: of the k-th best open slot,
+    int node;               // and its node (| kSure: no slot left out comes before it, even if one is as large)
+    double unlisted;        // no open slot outside the list is larger (the same in every lane)
+};
+constexpr int kSure = 1 << 16;
+
+// The list made again from the slots of nodes 0 .. n - 1.
+__device__ __attribute__((noinline)) Slots relist(uint32_t nodes_, int n_)
+{
+    const uint32_t nodes = uniform(nodes_);
+    const int n = uniform(n_), lane = threadIdx.x & 63;
+    constexpr int Q = DYSPEC_MAX_BUILD_NODES / kWave;
+    double val[Q];
+    int opened[Q];
+#pragma unroll
+    for (int k = 0; k < Q; ++k) {
+        const int q = lane + kWave * k;
+        val[k] = -1.0;
+        opened[k] = 0;
+        if (q < n) {
+            const double v = *lds_at<double>(nodes + kNode * q + kValueAt);
+            val[k] = v > 0.0 ? v : -1.0;
+            opened[k] = (int)*lds_at<uint32_t>(nodes + kNode * q + kOpenedAt);
+        }
+    }
+    Slots s = { -1.0, 0, -1.0 };
+    for (int t = 0; t <= kRelisted; ++t) {
+        double best = -1.0;
+        int at = 0, when = 0;
+#pragma unroll
+        for (int k = 0; k < Q; ++k)
+            if (val[k] > best || (val[k] == best && opened[k] < when)) { best = val[k]; at = k; when = opened[k]; }
+        const double top = wave_max_dpp(best);
+        if (!(uniform(top) > 0.0)) break;
+        if (t == kRelisted) { s.unlisted = top; break; }
+        u64 cand = ballot(best == top);
+        if (cand & (cand - 1)) {
+            const int first = best == top ? 0xffff - when : 0;
+            cand &= ballot(first == wave_max_dpp_int(first));
+        }
+        const int winner = __builtin_ctzll(cand);
+        const int node = winner + kWave * __builtin_amdgcn_readlane(at, winner);
+        if (lane == t) { s.value = top; s.node = node | kSure; }
+#pragma unroll
+        for (int k = 0; k < Q; ++k) if (lane == winner && k == at) val[k] = -1.0;
+    }
+    return s;
+}
+
 __device__ __attribute__((noinline)) int pop_nodes(uint32_t lds_, int root_ring_, int N_, int max_polls_, int* parent_, int* token_, float* est_value_)
 {
     const uint32_t lds = uniform(lds_), nodes = lds + BuildLds::nodes;
@@ -546,45 +632,33 @@ __device__ __attribute__((noinline)) int pop_nodes(uint32_t lds_, int root_ring_
     int *const parent = uniform(parent_), *const token = uniform(token_);
     float* const est_value = uniform(est_value_);
     const int lane = threadIdx.x & 63;
-    double best_v = lane == 0 ? 1.0 : -1.0;         // the best open slot of the nodes lane, lane + 64, ...; <= 0: none
-    int best_i = lane;
+    Slots s = { lane == 0 ? 1.0 : -1.0, 0, -1.0 };
     int n = 1, root_rank = 0, polls = uniform(max_polls_);
     bool lost = false;
     uint32_t place_n = nodes + kNode;               // LDS of node n
     int tokens = -1, froms = 0;                     // of the last 64 rows, row i in lane i % 64; written out together
     float values = 1.0f;
     while (n < N) {
-        // ---- the largest value: by its upper word first (positive doubles order like integers)
-        const int hi = __double2hiint(best_v);
-        const int rows_hi = row_max(hi);
-        const int top = max(max(__builtin_amdgcn_readlane(rows_hi, 0), __builtin_amdgcn_readlane(rows_hi, 16)),
-                            max(__builtin_amdgcn_readlane(rows_hi, 32), __builtin_amdgcn_readlane(rows_hi, 48)));
-        u64 cand = ballot(hi == top);
-        if (cand & (cand - 1)) {                    // the lower word; equal values: the slot opened first
-            cand = ballot(best_v == wave_max_dpp(hi == top ? best_v : -1.0));
-            if ((cand & (cand - 1)) && uniform(top) >= 0) cand = opened_first(cand, nodes + kNode * best_i + kOpenedAt);
+        // ---- the largest value
+        if (!(ballot(s.value > s.unlisted) & 1ull) && !(__builtin_amdgcn_readfirstlane(s.node) & kSure)) {
+            if (!(ballot(s.unlisted > 0.0) & 1ull)) break;              // no slot is open
+            s = relist(nodes, n);
         }
-        const int lp = __builtin_ctzll(cand);
-        const int p = __builtin_amdgcn_readlane(best_i, lp);
-        const double v = readlane_f64(best_v, lp);
-        const int v_hi = __double2hiint(v);
-        if (v_hi <= 0 && !(v > 0.0)) break;         // no slot is open
-        // ---- the other slots of p's lane (lanes 0..15: nodes lp, lp + 64, ...)
-        const int q = lp + kWave * (lane & 15);
-        double other = -1.0;
-        if (q < N && q != p) other = *lds_at<double>(nodes + kNode * q + kValueAt);
-        // ---- the node's next draw
+        if (!(ballot(s.value > 0.0) & 1ull)) break;
+        const int p = __builtin_amdgcn_readfirstlane(s.node) & (kSure - 1);
+        const double v = uniform(s.value);
+        // ---- its node's next draw
         const bool from_ring = root_ring && p == 0;
         const uint32_t place_p = nodes + kNode * (uint32_t)p;
         const uint32_t place = from_ring ? lds + BuildLds::ring + kNode * (uint32_t)(root_rank % kRing) : place_p;
         // the bits of the word that tell: the answer's, in the ring the draw's rank as well
         const uint32_t mask = from_ring ? kAnswer | (1023u << 15) : kAnswer, want = from_ring ? kAnswer | (uint32_t)root_rank << 15 : kAnswer;
+        const uint32_t o = *lds_at<uint32_t>(place_p + kOpenedAt);
         uint32_t w = uniform(lds_now(lds_at<uint32_t>(place + kWordAt)));
         while ((w & mask) != want && --polls > 0) w = uniform(lds_now(lds_at<uint32_t>(place + kWordAt)));
         double R = *lds_at<double>(place);
         const u64 child = *lds_at<u64>(place + kChildKeyAt);
         const uint32_t child_u = *lds_at<uint32_t>(place + kChildUAt);
-        const uint32_t o = *lds_at<uint32_t>(place_p + kOpenedAt);
         const int R_hi = uniform(__double2hiint(R));
         if (R_hi < 0 || polls <= 0) {
             lost = polls <= 0;
@@ -609,21 +683,29 @@ __device__ __attribute__((noinline)) int pop_nodes(uint32_t lds_, int root_ring_
             lds_set(lds_at<uint32_t>(lds + BuildLds::news), (uint32_t)n | ((uint32_t)p << 10) | (from_ring ? 0u : kRequest));
         }
         if (from_ring) root_rank = (int)rank + 1;
-        // ---- the best of p's lane again, then the new node's
-        const int other_hi = __double2hiint(other);
-        const int other_top = uniform(row_max(other_hi));
-        u64 same = ballot(other_hi == other_top) & 0xffffull;
-        if ((same & (same - 1)) && other_top >= 0) {
-            const double ov = wave_max_dpp(other);
-            same = ballot(other == ov) & 0xffffull;
-            if ((same & (same - 1)) && readlane_f64(ov, 0) > 0.0) same = opened_first(same, nodes + kNode * q + kOpenedAt);
+        // ---- p's next slot goes behind the slots at least as good, which move up (a closed one to the end, as an empty place)
+        const double x1 = v1 > 0.0 ? v1 : -1.0;
+        const int c = __builtin_popcountll(ballot(s.value >= x1) >> 1);
+        if (c == 0) {
+            if (lane == 0) { s.value = x1; s.node = p; }           // (its next slot is a new one: not kSure)
+        } else {
+            const double up_v = dpp_or_own<kDppWaveShl1>(s.value);
+            const int up_n = dpp_or_own<kDppWaveShl1>(s.node);
+            s.value = lane < c ? up_v : lane == c ? x1 : s.value;
+            s.node = lane < c ? up_n : lane == c ? p : s.node;
         }
-        const int ok = __builtin_ctzll(same);
-        const double ov = readlane_f64(other, ok);
-        const bool p_best = v1 > ov;                // equal: the other one was opened before
-        if (lane == lp) { best_v = p_best ? v1 : ov; best_i = p_best ? p : lp + kWave * ok; }
+        // ---- the new node's likewise, the ones behind it move down; what finds no place is left out
+        if (ballot(v0 > s.unlisted && v0 > 0.0)) {
+            const int at = __builtin_popcountll(ballot(s.value >= v0));
+            const double last = readlane_f64(s.value, 63);
+            const double out = at < kWave ? last : v0;
+            const double down_v = dpp_or_own<kDppWaveShr1>(s.value);
+            const int down_n = dpp_or_own<kDppWaveShr1>(s.node);
+            s.value = lane > at ? down_v : lane == at ? v0 : s.value;
+            s.node = lane > at ? down_n : lane == at ? n : s.node;
+            s.unlisted = fmax(s.unlisted, out);
+        }
         if (lane == (n & 63)) {
-            if (v0 > best_v) { best_v = v0; best_i = n; }
             tokens = (int)(w & 0x7fffu);
             values = (float)v;
             froms = (int)((uint32_t)p | (rank << 10) | ((o >> 1) << 20));

@@ -1,0 +1,32 @@
+"""The builder with a workspace keeps the 64 best open slots of a tree in order and makes that list again when it runs short.
+Here it runs short: many slots of equal value (the one opened first is popped first), more than 64 of them open at a time, against
+the form without a workspace, which compares all slots at every pop."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+
+# equal tokens: a value is a quotient of small integers, exact or rounded alike in both forms, so whole numbers must be equal
+@pytest.mark.parametrize("V,live", [(2, 2), (3, 3), (8, 8), (64, 16), (129, 64), (1000, 4), (1000, 256)])
+@pytest.mark.parametrize("nodes", [(64, 65, 66), (127, 128, 129, 130), (700,), (1024, 300)])
+def test_more_equal_slots_than_the_list_holds(nodes, V, live):
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2410_11744_amd as dy
+    print(f"nodes={nodes} V={V} live={live}", flush=True)
+    rng = np.random.default_rng(V + live + nodes[0])
+    x = np.full((sum(nodes), V), -np.inf, np.float32)
+    for row in x:
+        row[rng.choice(V, live, replace=False)] = 0.25
+    batch = dy.Batch.from_sizes(nodes)
+    dd = torch.from_numpy(x).cuda()
+    a = dy.build_tree(dd, batch, 1.0, 5)
+    b = dy.build_tree(dd, batch, 1.0, 5, use_workspace=False)
+    torch.cuda.synchronize()
+    assert torch.equal(a.n_built, b.n_built)
+    for name in ("parent", "token", "sib_rank", "first_child", "next_sibling", "depth"):
+        assert torch.equal(getattr(a.tree, name), getattr(b.tree, name)), name
+    assert torch.equal(a.anc_mask, b.anc_mask) and torch.equal(a.est_value, b.est_value)
