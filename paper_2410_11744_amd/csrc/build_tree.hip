@@ -38,8 +38,14 @@ __host__ __device__ inline double* ws_rowmax(double* ws, int row) { return ws_to
 __host__ __device__ inline unsigned short* ws_drawn(double* ws, int row) { return reinterpret_cast<unsigned short*>(ws_totals(ws, row) + kDrawnOffset); }
 
 // Data-parallel part (the draft softmax of every node, Algorithm 1's model call output):
-// one workgroup per row writes the row's totals and maximum.
-template <bool VEC>
+// one workgroup per row writes the row's totals and maximum.  S: segments held, V <= S * kSeg.
+// Bound in turn by the trip to memory (every load is issued before the maximum is known) and by the vector ALU: some 28
+// instructions a token, 22 of them the fp64 exponential.  Segments past the end of the row cost nothing, and the sums of a run's lanes
+// are folded into one another (row_sums) instead of summed one by one, five steps each: 32 rows of 1000 tokens
+// 9.8 -> 3.8 us, 128 rows of 32000 14.6 -> 12.8, 512 rows 27.3 -> 25.9 (66 MB; nothing is left to overlap loads with: all
+// rows are in flight at once).  S: 2 holds 4096 tokens, 8 16384; where the unused segments were skipped in the code for 16 their
+// registers and code stayed.
+template <bool VEC, int S>
 __global__ __launch_bounds__(kBlock) void draft_row_sums_kernel(const float* __restrict__ draft_logits, int V, SeqArgs sa,
                                                                 double* __restrict__ ws)
 {
@@ -47,24 +53,32 @@ __global__ __launch_bounds__(kBlock) void draft_row_sums_kernel(const float* __r
     const int row = blockIdx.x;
     const int seq = find_seq(sa, row);
     const double inv_temp = 1.0 / (double)sa.temp_d[seq];
-    double m, seg[kMaxSeg];
-    row_segment_sums<VEC>(draft_logits + (size_t)row * V, V, inv_temp, 0ull, fred, &m, seg);
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    // half a wave holds a run of a segment: its sum ends up in all lanes of the half's second row of 16,
-    // of which lane j keeps segment j's
-    static_assert(4 * kWave == 2 * kRun && kMaxSeg == 16, "two runs per wave and segment, a lane per segment");
-    double mine = 0.0;
+    float x[S][4];
+    load_row<VEC, float>(draft_logits + (size_t)row * V, V, x);
+    float mx[1] = { -INFINITY };
 #pragma unroll
-    for (int j = 0; j < kMaxSeg; ++j) {
-        double t = seg[j];
-        t += dpp_or_zero<kDppXor1>(t);
-        t += dpp_or_zero<kDppXor2>(t);
-        t += dpp_or_zero<kDppHalfMirror>(t);
-        t += dpp_or_zero<kDppMirror>(t);
-        t += dpp_or_zero<kDppBcast15, 0xa>(t);
-        if ((lane & 15) == j) mine = t;
+    for (int j = 0; j < S; ++j)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) mx[0] = fmaxf(mx[0], x[j][e]);
+    block_max<1>(mx, fred);
+    const double m = (double)mx[0] * inv_temp;
+    double seg[S];
+#pragma unroll
+    for (int j = 0; j < S; ++j) {
+        seg[j] = 0.0;
+        if (j * kSeg >= V) continue;                    // uniform
+        double z[4], w4[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) z[e] = fma((double)x[j][e], inv_temp, -m);
+        exp_nonpos_xn<4>(z, w4);                        // (tokens past the end: exp(-inf) = 0)
+        seg[j] = (w4[0] + w4[1]) + (w4[2] + w4[3]);
     }
-    if (lane & 16) ws_totals(ws, row)[(lane & 15) * (kSeg / kRun) + 2 * wave + (lane >> 5)] = mine;
+    // half a wave holds a run of a segment: lane j % 16 of the half gets segment j's sum
+    static_assert(4 * kWave == 2 * kRun && kMaxSeg == 16, "two runs per wave and segment, a lane per segment");
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, j = lane & 15;
+    double t = row_sums(seg);
+    t += __shfl_xor(t, 16, kWave);
+    if (lane & 16) ws_totals(ws, row)[j * (kSeg / kRun) + 2 * wave + (lane >> 5)] = j < S ? t : 0.0;
     if (threadIdx.x == 0) *ws_rowmax(ws, row) = m;
 }
 
@@ -222,9 +236,8 @@ __global__ __launch_bounds__(kBlock) void build_tree_kernel(
 
 // The form with a workspace: waves with roles.
 //
-// Wave 0 (control) pops.  Every node has one open slot, its next draw; lane l of control keeps the best
-// slot of the nodes l, l + 64, ... in registers (the slots themselves lie in LDS), so the pop is a maximum over
-// the wave.  It takes the popped node's next draw (token, R[y], the new node's path key and first uniform) from
+// Wave 0 (control) pops.  Every node has one open slot, its next draw; the lanes of control hold the best 64 in
+// order (the slots themselves lie in LDS), so the pop is lane 0's.  It takes the popped node's next draw (token, R[y], the new node's path key and first uniform) from
 // LDS, opens the new node's slot and the parent's next one.
 // Wave 1 draws from the root's row, which it keeps in LDS (wave_draw.h), up to kRing draws
 // ahead: the root is popped most often in wide trees.
@@ -838,6 +851,21 @@ hipError_t prepare_build_tree()
 
 size_t build_tree_workspace_bytes(int total_rows) { return (size_t)total_rows * kRowSumDoubles * sizeof(double); }
 
+template <int S>
+static void launch_draft_row_sums_s(const float* draft_logits, int V, const SeqArgs& sa, double* ws, hipStream_t stream)
+{
+    const int rows = sa.node_off[sa.n_seq];
+    if (V % 4 == 0) draft_row_sums_kernel<true, S><<<rows, kBlock, 0, stream>>>(draft_logits, V, sa, ws);
+    else draft_row_sums_kernel<false, S><<<rows, kBlock, 0, stream>>>(draft_logits, V, sa, ws);
+}
+static hipError_t launch_draft_row_sums(const float* draft_logits, int V, const SeqArgs& sa, double* ws, hipStream_t stream)
+{
+    if (V <= 2 * kSeg) launch_draft_row_sums_s<2>(draft_logits, V, sa, ws, stream);
+    else if (V <= 8 * kSeg) launch_draft_row_sums_s<8>(draft_logits, V, sa, ws, stream);
+    else launch_draft_row_sums_s<kMaxSeg>(draft_logits, V, sa, ws, stream);
+    return hipGetLastError();
+}
+
 hipError_t launch_build_tree(const float* draft_logits, int V, const SeqArgs& sa, uint64_t seed,
                              const dyspec_tree& tree, float* est_value, uint64_t* anc_mask,
                              int mask_words, int* n_built, void* workspace, size_t workspace_bytes, int max_polls, hipStream_t stream)
@@ -852,12 +880,12 @@ hipError_t launch_build_tree(const float* draft_logits, int V, const SeqArgs& sa
         const size_t lds_bytes = build_lds_bytes(V, widest, root_ring);
         const hipError_t ea = prepare_build_tree();
         if (ea != hipSuccess) return ea;
+        const hipError_t es = launch_draft_row_sums(draft_logits, V, sa, ws, stream);
+        if (es != hipSuccess) return es;
         if (V % 4 == 0) {
-            draft_row_sums_kernel<true><<<rows, kBlock, 0, stream>>>(draft_logits, V, sa, ws);
             build_tree_waves_kernel<true><<<sa.n_seq, kBuildThreads, lds_bytes, stream>>>(
                 draft_logits, V, sa, seed, tree, est_value, anc_mask, mask_words, n_built, ws, widest, root_ring, max_polls);
         } else {
-            draft_row_sums_kernel<false><<<rows, kBlock, 0, stream>>>(draft_logits, V, sa, ws);
             build_tree_waves_kernel<false><<<sa.n_seq, kBuildThreads, lds_bytes, stream>>>(
                 draft_logits, V, sa, seed, tree, est_value, anc_mask, mask_words, n_built, ws, widest, root_ring, max_polls);
         }

@@ -90,6 +90,38 @@ __device__ __forceinline__ double wave_sum_dpp(double x)
         r[k] = __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(x), 16 * k), __builtin_amdgcn_readlane(__double2loint(x), 16 * k));
     return (r[0] + r[1]) + (r[2] + r[3]);
 }
+// Sums over each row of 16 lanes of N values a lane (N = 2, 8 or 16), scattered: lane l gets the sum of value l % N.  Values are
+// added to the mirrored lane's until the lane's lower bits can name what is left; from there on every step exchanges half of the
+// values with a lane that differs in the bit which names the half.  (Mirrored lanes differ in the lower bits as well: the steps
+// of the higher bits come first, while nothing depends on the lower ones.)  N = 16: 15 adds against 64.
+template <int N>
+__device__ __forceinline__ double row_sums(double (&x)[N])
+{
+    static_assert(N == 2 || N == 8 || N == 16, "bits 0 .. log2 N - 1 of the lane name the value");
+    const int lane = threadIdx.x & (kWave - 1);
+    auto all = [&](auto ctrl_c) __attribute__((always_inline)) {
+#pragma unroll
+        for (int k = 0; k < N; ++k) x[k] += dpp_or_zero<decltype(ctrl_c)::value>(x[k]);
+    };
+    auto fold = [&](auto n_c, auto ctrl_c, int bit) __attribute__((always_inline)) {
+        constexpr int H = decltype(n_c)::value / 2;        // value k stays with bit clear, k + H with bit set
+        const bool up = lane & bit;
+#pragma unroll
+        for (int k = 0; k < H; ++k) {
+            const double keep = up ? x[k + H] : x[k], give = up ? x[k] : x[k + H];
+            x[k] = keep + dpp_or_zero<decltype(ctrl_c)::value>(give);
+        }
+    };
+    const std::integral_constant<int, kDppMirror> mirror;
+    const std::integral_constant<int, kDppHalfMirror> half_mirror;
+    const std::integral_constant<int, kDppXor2> xor2;
+    const std::integral_constant<int, kDppXor1> xor1;
+    if constexpr (N == 16) fold(std::integral_constant<int, 16>{}, mirror, 8); else all(mirror);
+    if constexpr (N >= 8) fold(std::integral_constant<int, 8>{}, half_mirror, 4); else all(half_mirror);
+    if constexpr (N >= 8) fold(std::integral_constant<int, 4>{}, xor2, 2); else all(xor2);
+    fold(std::integral_constant<int, 2>{}, xor1, 1);
+    return x[0];
+}
 __device__ __forceinline__ float readlane_f32(float x, int l);
 // The same in fp32.
 __device__ __forceinline__ float wave_sum_f32_dpp(float x)

@@ -298,32 +298,11 @@ __device__ __forceinline__ float exp_fast(float x) { return __builtin_amdgcn_exp
 template <int S> using RowVec = float __attribute__((ext_vector_type(S)));
 __device__ __forceinline__ double four(const float a, const float b, const float c, const float d) { return ((double)a + (double)b) + ((double)c + (double)d); }
 
-// Sums over the wave of N values a lane (N a power of two, at most 16), scattered: lane l gets the sum of value l % N.  Every step
-// exchanges half of what is left with the lane one bit away, so N - 1 adds do the first steps for all N values.
+// Sums over the wave of N values a lane (N = 2, 8 or 16), scattered: lane l gets the sum of value l % N.
 template <int N>
 __device__ __forceinline__ double wave_sums(double (&x)[N])
 {
-    static_assert(N == 2 || N == 8 || N == 16, "bits 0 .. log2 N - 1 of the lane name the value");
-    const int lane = threadIdx.x & (kWave - 1);
-    auto fold = [&](auto n_c, auto ctrl_c, int bit) __attribute__((always_inline)) {
-        constexpr int H = decltype(n_c)::value / 2;        // value k stays with bit clear, k + H with bit set
-        const bool up = lane & bit;
-#pragma unroll
-        for (int k = 0; k < H; ++k) {
-            const double keep = up ? x[k + H] : x[k], give = up ? x[k] : x[k + H];
-            x[k] = keep + dpp_or_zero<decltype(ctrl_c)::value>(give);
-        }
-    };
-    // (partners: lane ^ 1, lane ^ 2, then within a group of 8 and a row of 16 the mirrored lane, whose lower bits differ as well:
-    //  the fold over the highest bit of the value's index comes first there, while nothing depends on them yet)
-    if constexpr (N == 16) fold(std::integral_constant<int, 16>{}, std::integral_constant<int, kDppMirror>{}, 8);
-    if constexpr (N >= 8) fold(std::integral_constant<int, 8>{}, std::integral_constant<int, kDppHalfMirror>{}, 4);
-    if constexpr (N >= 8) fold(std::integral_constant<int, 4>{}, std::integral_constant<int, kDppXor2>{}, 2);
-    fold(std::integral_constant<int, 2>{}, std::integral_constant<int, kDppXor1>{}, 1);
-    double t = x[0];
-    if constexpr (N == 2) { t += dpp_or_zero<kDppXor2>(t); }
-    if constexpr (N == 2) { t += __shfl_xor(t, 4, kWave); }
-    if constexpr (N <= 8) { t += __shfl_xor(t, 8, kWave); }
+    double t = row_sums(x);
     t += __shfl_xor(t, 16, kWave);
     t += __shfl_xor(t, 32, kWave);
     return t;
