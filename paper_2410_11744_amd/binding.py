@@ -184,13 +184,23 @@ class Tree:
     depth: "torch.Tensor"
 
     def _c(self) -> _Tree:
-        return _Tree(*[_ptr(getattr(self, n), "int32") for n in
-                       ("parent", "token", "sib_rank", "first_child", "next_sibling", "depth")])
+        return _Tree(_ptr(self.parent, "int32"), _ptr(self.token, "int32"), _ptr(self.sib_rank, "int32"),
+                     _ptr(self.first_child, "int32"), _ptr(self.next_sibling, "int32"), _ptr(self.depth, "int32"))
 
     @staticmethod
     def empty(total_nodes: int, device) -> "Tree":
+        # one allocation, every array aligned as an allocation of its own would be (512 bytes)
         import torch
-        return Tree(*[torch.empty(total_nodes, dtype=torch.int32, device=device) for _ in range(6)])
+        rows = torch.empty((6, -(-total_nodes // 128) * 128), dtype=torch.int32, device=device)
+        return Tree(*rows[:, :total_nodes].unbind(0))
+
+
+_dtypes: dict = {}
+
+
+def _dtype(name: str):
+    import torch
+    return _dtypes.setdefault(name, getattr(torch, name))
 
 
 def _ptr(t, want: Optional[str] = None) -> int:
@@ -200,7 +210,7 @@ def _ptr(t, want: Optional[str] = None) -> int:
         raise ValueError("device tensor required")
     if not t.is_contiguous():
         raise ValueError("contiguous tensor required")
-    if want is not None and str(t.dtype) != "torch." + want:
+    if want is not None and t.dtype is not (_dtypes.get(want) or _dtype(want)):
         raise ValueError(f"expected {want}, got {t.dtype}")
     return t.data_ptr()
 
@@ -213,6 +223,13 @@ def _stream(stream=None) -> int:
 
 
 def _temps(x, n_seq: int):
+    """fp32 per sequence, as a C array: a number for all, or one each."""
+    if type(x) is float:
+        a = (ctypes.c_float * n_seq)(*([x] * n_seq))
+        return a, a
+    if (type(x) is list or type(x) is tuple) and len(x) == n_seq and all(type(v) is float for v in x):
+        a = (ctypes.c_float * n_seq)(*x)
+        return a, a
     a = np.ascontiguousarray(np.broadcast_to(np.asarray(x, dtype=np.float32), (n_seq,)))
     return a, a.ctypes.data_as(ctypes.POINTER(ctypes.c_float))
 
@@ -247,12 +264,15 @@ def build_tree(draft_logits, batch: Batch, draft_temp, seed: int, stream=None, u
     tarr, tptr = _temps(draft_temp, batch.n_seq)
     ws, ws_bytes = None, 0
     if use_workspace:
-        ws_bytes = int(lib.dyspec_workspace_bytes(WS_BUILD_TREE, ctypes.byref(cb), V, 0, 0, 0))
+        memo, wkey = batch._memo(), ("ws_build", V)
+        if wkey not in memo:
+            memo[wkey] = int(lib.dyspec_workspace_bytes(WS_BUILD_TREE, ctypes.byref(cb), V, 0, 0, 0))
+        ws_bytes = memo[wkey]
         if ws_bytes:
             ws = torch.empty(ws_bytes // 8, dtype=torch.float64, device=dev)
     st = lib.dyspec_build_tree(_ptr(draft_logits, "float32"), V, ctypes.byref(cb), tptr, ctypes.c_uint64(seed),
-                               ctypes.byref(ct), _ptr(est), _ptr(mask), _ptr(nb),
-                               _ptr(ws) if ws is not None else None, ctypes.c_size_t(ws_bytes), _stream(stream))
+                               ctypes.byref(ct), est.data_ptr(), mask.data_ptr(), nb.data_ptr(),
+                               ws.data_ptr() if ws is not None else None, ctypes.c_size_t(ws_bytes), _stream(stream))
     _check(st, "dyspec_build_tree")
     return BuiltTrees(tree, est, mask, nb)
 
