@@ -360,10 +360,12 @@ __device__ __attribute__((noinline)) void draw_for_root(uint32_t lds_, uint32_t 
     }
 }
 
-// A draw wave's copy of a node's totals (lane l: totals 4 l .. 4 l + 3) and row maximum; which copies it keeps: row_copies.h.
+// A draw wave's copy of a node's totals (lane l: totals 4 l .. 4 l + 3), row maximum and first 64 tokens drawn (lane r: draw r's,
+// once it is made); which copies it keeps: row_copies.h.
 struct HeldRow {
     int node;               // -1: none
     double tot[4], m;
+    int drawn;
 };
 __device__ __forceinline__ void fetch_row(double* ws, int base, int i, HeldRow& h)
 {
@@ -372,6 +374,7 @@ __device__ __forceinline__ void fetch_row(double* ws, int base, int i, HeldRow& 
 #pragma unroll
     for (int k = 0; k < 4; ++k) h.tot[k] = t[k];
     h.m = *ws_rowmax(ws, base + i);
+    h.drawn = ws_drawn(ws, base + i)[threadIdx.x & 63];
 }
 
 // Of 64 ranks of a node's draws (first + lane): the draw's uniform, the path key of the node the draw makes, that node's first uniform.
@@ -393,28 +396,41 @@ __device__ __forceinline__ void make_names(DrawNames& d, uint64_t seed, u64 key_
     d.child = join_key(child);
 }
 
-// One draw for node i of a sequence by a wave, the node's row in global memory: what is left of its
+// One draw for a node of a sequence by a wave, the node's row in global memory: what is left of its
 // totals lies in the workspace (totals 4 l .. 4 l + 3 are read and written by lane l), as do the tokens drawn
-// before (entry r by lane r % 64); this wave alone draws for the node.
+// before (entry r by lane r % 64); this wave alone draws for the node.  In two parts: what can be done before the draw is asked
+// for (the run, its logits on their way, the names), and the token.  A node that has been drawn from twice is likely to be popped
+// again at once, and its wave is then all that control waits for (some 560 instructions a draw): the first part of its next draw
+// is done while control is at the pop.  512 rows of 32000 tokens, three tables: 496 -> 471, 465 -> 443, 544 -> 524 us, of which
+// 9, 8 and 7 by totals held in registers (below).  (Done after looking at all of the wave's requests instead of before: 4 % slower
+// than without.)
+struct NextDraw {
+    int node, rank;         // -1: none
+    int gl, k, run0;        // the run: total k of lane gl (gl < 0: nothing left to sample under the node), its first token
+    double W, target, run_start;
+    u64 key_word;           // the node's path key
+    float x[2];             // the run's logits, two a lane
+    uint32_t out;           // bit e: token e of the lane was drawn here before
+};
 template <bool VEC>
-__device__ __forceinline__ void draw_for_node(uint32_t place, uint32_t gone, const float* __restrict__ row, int V,
-                                              double inv_temp, uint64_t seed, double* ws, int ws_row, HeldRow& h, DrawNames& names, int node, int rank)
+__device__ __forceinline__ void prepare_draw(NextDraw& d, uint32_t place, uint32_t gone, const float* __restrict__ row, int V,
+                                             uint64_t seed, double* ws, int ws_row, const HeldRow& h, DrawNames& names, int node, int rank)
 {
     const int lane = threadIdx.x & 63;
-    const u64 key_word = *lds_at<u64>(place + kKeyAt);
-    if (rank > 0 && (rank & (kWave - 1)) == 0) make_names(names, seed, key_word, node, rank);     // (the draw before has not left this one's uniform)
+    d.node = node;
+    d.rank = rank;
+    d.key_word = *lds_at<u64>(place + kKeyAt);
+    if (rank > 0 && (rank & (kWave - 1)) == 0) make_names(names, seed, d.key_word, node, rank);     // (the draw before has not left this one's uniform)
     const bool named = names.node == node && names.first == (rank & ~(kWave - 1));                 // uniform
     const double u = (double)(named ? readlane_f32(names.u, rank & (kWave - 1)) : *lds_at<float>(place + kUAt));
     // ---- the run: the lane of the crossing, then one of its four totals (every lane walks its own)
     const double t01 = h.tot[0] + h.tot[1], four = t01 + (h.tot[2] + h.tot[3]);
     const double cum = wave_scan_dpp(four);
-    const double W = readlane_f64(cum, 63);
-    if (!(W > 0.0)) {                               // nothing left to sample under the node
-        if (lane == 0) publish(place, -1.0, 0ull, 0.f, kAnswer);
-        return;
-    }
-    const double target = u * W;
-    const int gl = pick_lane(ballot(four > 0.0) & ballot(cum > target), ballot(four > 0.0));
+    d.W = readlane_f64(cum, 63);
+    d.gl = -1;
+    if (!(d.W > 0.0)) return;
+    const double target = d.target = u * d.W;
+    const int gl = d.gl = pick_lane(ballot(four > 0.0) & ballot(cum > target), ballot(four > 0.0));
     const double start = scan_at(cum, gl - 1);
     double run_start = start;
     int k = -1;
@@ -431,41 +447,52 @@ __device__ __forceinline__ void draw_for_node(uint32_t place, uint32_t gone, con
         }
         if (k < 0) { k = last; run_start = last_start; }            // rounding at the top
     }
-    k = __builtin_amdgcn_readlane(k, gl);
-    run_start = readlane_f64(run_start, gl);
-    const int run0 = (4 * gl + k) * kRun;
+    d.k = __builtin_amdgcn_readlane(k, gl);
+    d.run_start = readlane_f64(run_start, gl);
+    const int run0 = d.run0 = (4 * gl + d.k) * kRun;
     const int tok0 = run0 + 2 * lane;               // this lane's two tokens of the run
-    float x[2];
     if constexpr (VEC) {
         const float2 v = tok0 < V ? *reinterpret_cast<const float2*>(row + tok0) : make_float2(-INFINITY, -INFINITY);
-        x[0] = v.x; x[1] = v.y;
+        d.x[0] = v.x; d.x[1] = v.y;
     } else {
-        x[0] = tok0 < V ? row[tok0] : -INFINITY;
-        x[1] = tok0 + 1 < V ? row[tok0 + 1] : -INFINITY;
+        d.x[0] = tok0 < V ? row[tok0] : -INFINITY;
+        d.x[1] = tok0 + 1 < V ? row[tok0 + 1] : -INFINITY;
     }
-    unsigned short* const drawn = ws_drawn(ws, ws_row);
-    uint32_t out = 0u;                              // bit e: token tok0 + e was drawn here before
+    d.out = 0u;
     if (rank > 0) {
         if (lane < kRun / 32) lds_set(lds_at<uint32_t>(gone + 4 * lane), 0u);
-        for (int c = lane; c < rank; c += kWave) {
-            const int t = drawn[c];
+        auto leave_out = [&](int t) __attribute__((always_inline)) {
             if (t / kRun * kRun == run0)
                 __hip_atomic_fetch_or(lds_at<uint32_t>(gone + 4 * (t % kRun / 32)), 1u << (t % 32), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-        }
-        out = lds_now(lds_at<uint32_t>(gone + 4 * (lane / 16))) >> (2 * (lane & 15));
+        };
+        if (lane < rank) leave_out(h.drawn);
+        const unsigned short* const drawn = ws_drawn(ws, ws_row);
+        for (int c = lane + kWave; c < rank; c += kWave) leave_out(drawn[c]);
+        d.out = lds_now(lds_at<uint32_t>(gone + 4 * (lane / 16))) >> (2 * (lane & 15));
+        if (!named) make_names(names, seed, d.key_word, node, rank);             // (while the logits are on their way)
     }
-    // ---- while the logits are on their way: the key of the node this draw makes, its first uniform, the uniform of this node's next draw
+}
+
+template <bool VEC>
+__device__ __forceinline__ void finish_draw(const NextDraw& d, uint32_t place, double inv_temp, uint64_t seed, double* ws, int ws_row,
+                                            HeldRow& h, const DrawNames& names)
+{
+    const int lane = threadIdx.x & 63, rank = d.rank;
+    if (d.gl < 0) {                                 // nothing left to sample under the node
+        if (lane == 0) publish(place, -1.0, 0ull, 0.f, kAnswer);
+        return;
+    }
+    // ---- the key of the node this draw makes, its first uniform, the uniform of this node's next draw
     uint2 child;
     float next_u, child_u;
     if (rank == 0) {
-        // lane 0 the key, lane 1 the next draw's uniform
-        const uint2 key = split_key(key_word);
+        // (while the logits are on their way) lane 0 the key, lane 1 the next draw's uniform
+        const uint2 key = split_key(d.key_word);
         const uint4 blk = philox4x32_10(make_uint4(key.x, key.y, (uint32_t)(lane & 1), (lane & 1) ? KIND_BUILD : KIND_PATH), seed_key(seed));
         child = make_uint2((uint32_t)__builtin_amdgcn_readlane((int)blk.x, 0), (uint32_t)__builtin_amdgcn_readlane((int)blk.y, 0));
         next_u = (float)(blk.x >> 8) * (1.0f / 16777216.0f);                        // lane 1's counts
         child_u = u01(seed, child, 0u, KIND_BUILD);
     } else {
-        if (!named) make_names(names, seed, key_word, node, rank);
         const int at = rank & (kWave - 1);
         child = make_uint2((uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)names.child, at), (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(names.child >> 32), at));
         next_u = names.u;                                                           // lane at + 1's counts
@@ -474,10 +501,10 @@ __device__ __forceinline__ void draw_for_node(uint32_t place, uint32_t gone, con
     // ---- the token: as above among the run's 128
     double z[2], w[2];
 #pragma unroll
-    for (int e = 0; e < 2; ++e) z[e] = fma((double)x[e], inv_temp, -h.m);
+    for (int e = 0; e < 2; ++e) z[e] = fma((double)d.x[e], inv_temp, -h.m);
     exp_nonpos_xn<2>(z, w);
-    if (out & 1u) w[0] = 0.0;
-    if (out & 2u) w[1] = 0.0;
+    if (d.out & 1u) w[0] = 0.0;
+    if (d.out & 2u) w[1] = 0.0;
     const double mine = w[0] + w[1];
     const double inc = wave_scan_dpp(mine);
     const u64 live = ballot(mine > 0.0);
@@ -485,22 +512,24 @@ __device__ __forceinline__ void draw_for_node(uint32_t place, uint32_t gone, con
         if (lane == 0) publish(place, -1.0, 0ull, 0.f, kAnswer);
         return;
     }
-    const int ol = pick_lane(live & ballot(run_start + inc > target), live);
-    const double mid = run_start + scan_at(inc, ol - 1) + w[0];     // (of interest in lane ol)
-    const int second = (w[0] > 0.0 && (mid > target || !(w[1] > 0.0))) ? 0 : 1;
+    const int ol = pick_lane(live & ballot(d.run_start + inc > d.target), live);
+    const double mid = d.run_start + scan_at(inc, ol - 1) + w[0];   // (of interest in lane ol)
+    const int second = (w[0] > 0.0 && (mid > d.target || !(w[1] > 0.0))) ? 0 : 1;
     const int e = __builtin_amdgcn_readlane(second, ol);
-    const int y = run0 + 2 * ol + e;
+    const int y = d.run0 + 2 * ol + e;
     const double wy = readlane_f64(e ? w[1] : w[0], ol);
     if (lane == ((rank + 1) & (kWave - 1))) *lds_at<float>(place + kUAt) = next_u;
-    if (lane == 0) publish(place, wy / W, join_key(child), child_u, kAnswer | ((uint32_t)rank << 15) | (uint32_t)y);
+    if (lane == 0) publish(place, wy / d.W, join_key(child), child_u, kAnswer | ((uint32_t)rank << 15) | (uint32_t)y);
     // what is left of the run
     const double left = wave_sum_dpp(lane == ol ? (e ? w[0] : w[1]) : mine);
-    if (lane == gl) {
+    const bool here = lane == d.gl;
 #pragma unroll
-        for (int q = 0; q < 4; ++q) if (q == k) h.tot[q] = left;
-        ws_totals(ws, ws_row)[4 * lane + k] = left;
+    for (int q = 0; q < 4; ++q) h.tot[q] = here && q == d.k ? left : h.tot[q];     // (selects: a store to tot[k] puts the array in scratch memory)
+    if (here) ws_totals(ws, ws_row)[4 * lane + d.k] = left;
+    if (lane == (rank & 63)) {
+        ws_drawn(ws, ws_row)[rank] = (unsigned short)y;
+        if (rank < kWave) h.drawn = y;
     }
-    if (lane == (rank & 63)) drawn[rank] = (unsigned short)y;
 }
 
 // Draw wave `mine`: serves the requests of its nodes, the largest slot value first, until told to stop.
@@ -519,13 +548,21 @@ __device__ __attribute__((noinline)) void draw_for_nodes(uint32_t lds_, int mine
     RowCopies<HeldRow> rows;
     rows.open(mine);
     DrawNames names = { -1, 0, 0.f, 0.f, 0ull };
+    NextDraw next;
+    next.node = next.rank = -1;
     const auto fetch = [&](int i, HeldRow& h) __attribute__((always_inline)) { fetch_row(ws, base, i, h); };
     uint32_t seen = 1u << 31;                       // the news last looked at (none yet)
     bool look = mine == 0;                          // requests may be open (node 0's, at the start)
     for (;;) {
         rows.look_ahead(N, fetch);
         int i = -1, rank = 0;
-        if (look) {
+        const auto prepared = [&]() __attribute__((always_inline)) {    // the draw made ready has been asked for
+            return next.node >= 0 && !(uniform(lds_now(lds_at<uint32_t>(nodes + kNode * next.node + kWordAt))) & kAnswer);
+        };
+        if (prepared()) {
+            i = next.node;
+            rank = next.rank;
+        } else if (look) {
             // the best request of each lane's nodes, then of the wave
             int best = 0, node = 0;
 #pragma unroll
@@ -551,18 +588,32 @@ __device__ __attribute__((noinline)) void draw_for_nodes(uint32_t lds_, int mine
             // the requests of one pop, if it is the one after the last seen; else look at all
             const int a = (int)(m & 1023u), p = (int)(m >> 10) & 1023;
             const bool a_mine = a % kDrawWaves == mine, p_mine = (m & kRequest) && p % kDrawWaves == mine;
-            look = a != (int)(seen & 1023u) + 1 || (a_mine && p_mine);
+            const bool one = a == (int)(seen & 1023u) + 1;
             seen = m;
-            if (look || !(a_mine || p_mine)) continue;
-            look = true;                            // ... after it has been served
-            i = a_mine ? a : p;
-            const uint32_t w = uniform(lds_now(lds_at<uint32_t>(nodes + kNode * i + kWordAt)));
-            if (w & kAnswer) continue;              // served already
-            rank = (int)(w >> 15);
+            if (p_mine && p == next.node && prepared()) {
+                look = !one || a_mine;              // after it has been served
+                i = next.node;
+                rank = next.rank;
+            } else {
+                look = !one || (a_mine && p_mine);
+                if (look || !(a_mine || p_mine)) continue;
+                look = true;                        // ... after it has been served
+                i = a_mine ? a : p;
+                const uint32_t w = uniform(lds_now(lds_at<uint32_t>(nodes + kNode * i + kWordAt)));
+                if (w & kAnswer) continue;          // served already
+                rank = (int)(w >> 15);
+            }
         }
-        rows.hold(i, kDrawWaves, fetch);
-        const float* const row = draft_logits + (size_t)(base + i) * V;
-        draw_for_node<VEC>(nodes + kNode * i, gone, row, V, inv_temp, seed, ws, base + i, rows.held, names, i, rank);
+        for (bool asked = true, ready = next.node == i && next.rank == rank; ; asked = ready = false, ++rank) {
+            if (!ready) {
+                rows.hold(i, kDrawWaves, fetch);
+                prepare_draw<VEC>(next, nodes + kNode * i, gone, draft_logits + (size_t)(base + i) * V, V, seed, ws, base + i, rows.held, names, i, rank);
+            }
+            if (!asked) break;                      // (the next draw of a node that is drawn from again is made ready before it is asked for)
+            finish_draw<VEC>(next, nodes + kNode * i, inv_temp, seed, ws, base + i, rows.held, names);
+            next.node = -1;
+            if (rank == 0) break;
+        }
         if (uniform(lds_now(lds_at<uint32_t>(lds + BuildLds::news))) == kStop) return;
     }
 }
@@ -575,7 +626,9 @@ __device__ __attribute__((noinline)) void draw_for_nodes(uint32_t lds_, int mine
 // that place move up by one; the new node's slot makes the lanes behind its place move down.  A slot that finds no place among
 // the 64 is left out: `unlisted` is the largest value left out so far, and while lane 0 is above it the list is as good as the
 // whole frontier.  Else the list is made again from the slots in LDS (`relist`), the first kRelisted of them: a few times
-// in trees of many equally good slots, never in 512 rows of 1000 or 32000 tokens of independent normal logits.
+// in trees of many equally good slots, never in 512 rows of 1000 or 32000 tokens of independent normal logits. (512 rows with two equal
+// tokens each, where every sixteenth pop does: 482 us, 505 with the maximum found at each pop, 720 with a list
+// made by sixteen comparisons a lane for each of its entries.)
 // Against the best of each lane's nodes kept in the lane and the maximum over the lanes found at each pop, and the other
 // nodes of the popped one's lane looked over again: a pop whose draw is there 0.61 -> 0.51 us; with the draws' names
 // for 64 ranks at once (DrawNames) 512 rows of 32000 tokens 441 -> 417, 495 -> 471 and 570 -> 547 us on three tables.
@@ -594,32 +647,26 @@ struct Slots {
 };
 constexpr int kSure = 1 << 16;
 
-// The list made again from the slots of nodes 0 .. n - 1.
+// The list made again from the slots of nodes 0 .. n - 1: every lane's best of the nodes lane, lane + 64, ..; the best of
+// those is listed and its lane's next one looked up by sixteen lanes at once.
 __device__ __attribute__((noinline)) Slots relist(uint32_t nodes_, int n_)
 {
     const uint32_t nodes = uniform(nodes_);
     const int n = uniform(n_), lane = threadIdx.x & 63;
     constexpr int Q = DYSPEC_MAX_BUILD_NODES / kWave;
-    double val[Q];
-    int opened[Q];
-#pragma unroll
-    for (int k = 0; k < Q; ++k) {
+    static_assert(Q == 16, "a row of lanes looks at a lane's nodes");
+    double best = -1.0;
+    int at = 0, when = 0;
+    for (int k = 0; kWave * k < n; ++k) {
         const int q = lane + kWave * k;
-        val[k] = -1.0;
-        opened[k] = 0;
-        if (q < n) {
-            const double v = *lds_at<double>(nodes + kNode * q + kValueAt);
-            val[k] = v > 0.0 ? v : -1.0;
-            opened[k] = (int)*lds_at<uint32_t>(nodes + kNode * q + kOpenedAt);
-        }
+        if (q >= n) break;
+        const double v = *lds_at<double>(nodes + kNode * q + kValueAt);
+        const int o = (int)*lds_at<uint32_t>(nodes + kNode * q + kOpenedAt);
+        if (v > 0.0 && (v > best || (v == best && o < when))) { best = v; at = k; when = o; }
     }
+    uint32_t listed = 0;                            // bit k: node lane + 64 k is in the list
     Slots s = { -1.0, 0, -1.0 };
     for (int t = 0; t <= kRelisted; ++t) {
-        double best = -1.0;
-        int at = 0, when = 0;
-#pragma unroll
-        for (int k = 0; k < Q; ++k)
-            if (val[k] > best || (val[k] == best && opened[k] < when)) { best = val[k]; at = k; when = opened[k]; }
         const double top = wave_max_dpp(best);
         if (!(uniform(top) > 0.0)) break;
         if (t == kRelisted) { s.unlisted = top; break; }
@@ -628,11 +675,29 @@ __device__ __attribute__((noinline)) Slots relist(uint32_t nodes_, int n_)
             const int first = best == top ? 0xffff - when : 0;
             cand &= ballot(first == wave_max_dpp_int(first));
         }
-        const int winner = __builtin_ctzll(cand);
-        const int node = winner + kWave * __builtin_amdgcn_readlane(at, winner);
-        if (lane == t) { s.value = top; s.node = node | kSure; }
-#pragma unroll
-        for (int k = 0; k < Q; ++k) if (lane == winner && k == at) val[k] = -1.0;
+        const int winner = __builtin_ctzll(cand), k = __builtin_amdgcn_readlane(at, winner);
+        if (lane == t) { s.value = top; s.node = (winner + kWave * k) | kSure; }
+        if (lane == winner) listed |= 1u << k;
+        const int q = winner + kWave * (lane & 15);
+        double v = -1.0;
+        int o = 0;
+        if (q < n && !(((uint32_t)__builtin_amdgcn_readlane((int)listed, winner) >> (lane & 15)) & 1u)) {
+            v = *lds_at<double>(nodes + kNode * q + kValueAt);
+            o = (int)*lds_at<uint32_t>(nodes + kNode * q + kOpenedAt);
+            if (!(v > 0.0)) v = -1.0;
+        }
+        double m = v;                               // (every row of 16 lanes holds the same)
+        m = fmax(m, dpp_or_zero<kDppXor1>(m));
+        m = fmax(m, dpp_or_zero<kDppXor2>(m));
+        m = fmax(m, dpp_or_zero<kDppHalfMirror>(m));
+        m = fmax(m, dpp_or_zero<kDppMirror>(m));
+        u64 same = ballot(v == m);
+        if (same & 0xffffull & ((same & 0xffffull) - 1)) {
+            const int first = v == m ? 0xffff - o : 0;
+            same &= ballot(first == wave_max_dpp_int(first));
+        }
+        const int next = __builtin_ctzll(same), o_next = __builtin_amdgcn_readlane(o, next);
+        if (lane == winner) { best = m; at = next; when = o_next; }
     }
     return s;
 }
