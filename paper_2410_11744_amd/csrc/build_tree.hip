@@ -27,12 +27,13 @@ constexpr int kMaxSlots = 2 * DYSPEC_MAX_BUILD_NODES + 2;
 
 // Workspace, per row (kRowSumDoubles doubles): the totals of kSums runs of kRun tokens, the row maximum
 // (already divided by the temperature), and from kDrawnOffset on the tokens drawn at this position, two
-// bytes each in the order of the draws (their weights are no longer in the totals).
+// bytes each in the order of the draws (their weights are no longer in the totals), at kMadeOffset a draw made but not asked for.
 constexpr int kRun = 128;
 constexpr int kSums = DYSPEC_MAX_VOCAB / kRun;
 constexpr int kRowSumDoubles = kMaxSeg + 8 + DYSPEC_MAX_VOCAB / 64;
 constexpr int kDrawnOffset = kSums + 2;
-static_assert((kRowSumDoubles - kDrawnOffset) * 4 >= DYSPEC_MAX_BUILD_NODES, "room for every draw a row can see");
+constexpr int kMadeOffset = kDrawnOffset + DYSPEC_MAX_BUILD_NODES / 4;
+static_assert(kRowSumDoubles >= kMadeOffset + 3, "room for every draw a row can see, and one that is made");
 __host__ __device__ inline double* ws_totals(double* ws, int row) { return ws + (size_t)row * kRowSumDoubles; }
 __host__ __device__ inline double* ws_rowmax(double* ws, int row) { return ws_totals(ws, row) + kSums; }
 __host__ __device__ inline unsigned short* ws_drawn(double* ws, int row) { return reinterpret_cast<unsigned short*>(ws_totals(ws, row) + kDrawnOffset); }
@@ -241,8 +242,8 @@ __global__ __launch_bounds__(kBlock) void build_tree_kernel(
 // LDS, opens the new node's slot and the parent's next one.
 // Wave 1 draws from the root's row, which it keeps in LDS (wave_draw.h), up to kRing draws
 // ahead: the root is popped most often in wide trees.
-// kDrawWaves waves draw for the other nodes (node i: wave i % kDrawWaves of them), one draw ahead per node,
-// the node of the largest slot value first: totals from the workspace (a new node's were fetched before it
+// kDrawWaves waves draw for the other nodes (node i: wave i % kDrawWaves of them), one draw ahead per node and a
+// second one put aside where the node has been drawn from twice, the node of the largest slot value first: totals from the workspace (a new node's were fetched before it
 // was made: its row is known), a wave scan, the picked run's 128 logits, two per lane, a wave scan.
 //
 // LDS words, one writer at a time.  A node's word is, with the top bit clear, a request of control for
@@ -396,41 +397,73 @@ __device__ __forceinline__ void make_names(DrawNames& d, uint64_t seed, u64 key_
     d.child = join_key(child);
 }
 
+// A draw made, as it is handed to control.
+struct MadeDraw {
+    int node, rank;         // -1: none
+    double R;
+    u64 child;
+    float child_u;
+    uint32_t word;
+};
+// One that has not been asked for waits in the workspace (lane 0 writes and reads it).
+__device__ __forceinline__ void put_made(double* ws, int ws_row, const MadeDraw& d)
+{
+    double* const at = ws_totals(ws, ws_row) + kMadeOffset;
+    at[0] = d.R;
+    at[1] = __longlong_as_double((long long)d.child);
+    at[2] = __hiloint2double((int)d.word, __float_as_int(d.child_u));
+}
+__device__ __forceinline__ void get_made(double* ws, int ws_row, MadeDraw& d)
+{
+    const double* const at = ws_totals(ws, ws_row) + kMadeOffset;
+    const double last = at[2];
+    d.R = at[0];
+    d.child = (u64)__double_as_longlong(at[1]);
+    d.child_u = __int_as_float(__double2loint(last));
+    d.word = (uint32_t)__double2hiint(last);
+}
+
 // One draw for a node of a sequence by a wave, the node's row in global memory: what is left of its
 // totals lies in the workspace (totals 4 l .. 4 l + 3 are read and written by lane l), as do the tokens drawn
-// before (entry r by lane r % 64); this wave alone draws for the node.  In two parts: what can be done before the draw is asked
-// for (the run, its logits on their way, the names), and the token.  A node that has been drawn from twice is likely to be popped
-// again at once, and its wave is then all that control waits for (some 560 instructions a draw): the first part of its next draw
-// is done while control is at the pop.  512 rows of 32000 tokens, three tables: 496 -> 471, 465 -> 443, 544 -> 524 us, of which
-// 9, 8 and 7 by totals held in registers (below).  (Done after looking at all of the wave's requests instead of before: 4 % slower
-// than without.)
-struct NextDraw {
-    int node, rank;         // -1: none
-    int gl, k, run0;        // the run: total k of lane gl (gl < 0: nothing left to sample under the node), its first token
-    double W, target, run_start;
-    u64 key_word;           // the node's path key
-    float x[2];             // the run's logits, two a lane
-    uint32_t out;           // bit e: token e of the lane was drawn here before
-};
+// before (entry r by lane r % 64); this wave alone draws for the node.  `asked`: control waits for it, else it is put aside.
+//
+// A node that has been drawn from twice is likely to be popped several times in a row, and control then waits for its wave alone,
+// some 560 instructions a draw.  So from its third draw on a node's draw is made when the one before is handed over, and handed over at
+// once when it is asked for.  512 rows of 32000 tokens, three tables: 470 -> 409, 441 -> 404, 520 -> 490 us, 1024 rows of 32768 1542 -> 1311,
+// of which half by the logits' load, which is no longer waited for where it is made (the Philox blocks follow).
+// (Only the run, its logits and names made ready ahead, the draw made when asked for: 471, 441, 524; the same after a look
+// at the wave's other requests: 524, 484, 562.)
 template <bool VEC>
-__device__ __forceinline__ void prepare_draw(NextDraw& d, uint32_t place, uint32_t gone, const float* __restrict__ row, int V,
-                                             uint64_t seed, double* ws, int ws_row, const HeldRow& h, DrawNames& names, int node, int rank)
+__device__ __forceinline__ void draw_for_node(MadeDraw& d, uint32_t place, uint32_t gone, const float* __restrict__ row, int V, double inv_temp,
+                                              uint64_t seed, double* ws, int ws_row, HeldRow& h, DrawNames& names, int node, int rank, bool asked)
 {
     const int lane = threadIdx.x & 63;
-    d.node = node;
+    d.node = asked ? -1 : node;
     d.rank = rank;
-    d.key_word = *lds_at<u64>(place + kKeyAt);
-    if (rank > 0 && (rank & (kWave - 1)) == 0) make_names(names, seed, d.key_word, node, rank);     // (the draw before has not left this one's uniform)
+    d.R = -1.0;
+    d.child = 0ull;
+    d.child_u = 0.f;
+    d.word = kAnswer;
+    const auto hand_over = [&]() __attribute__((always_inline)) {
+        if (lane == 0) {
+            if (asked) publish(place, d.R, d.child, d.child_u, d.word);
+            else put_made(ws, ws_row, d);
+        }
+    };
+    const u64 key_word = *lds_at<u64>(place + kKeyAt);
+    if (rank > 0 && (rank & (kWave - 1)) == 0) make_names(names, seed, key_word, node, rank);     // (the draw before has not left this one's uniform)
     const bool named = names.node == node && names.first == (rank & ~(kWave - 1));                 // uniform
     const double u = (double)(named ? readlane_f32(names.u, rank & (kWave - 1)) : *lds_at<float>(place + kUAt));
     // ---- the run: the lane of the crossing, then one of its four totals (every lane walks its own)
     const double t01 = h.tot[0] + h.tot[1], four = t01 + (h.tot[2] + h.tot[3]);
     const double cum = wave_scan_dpp(four);
-    d.W = readlane_f64(cum, 63);
-    d.gl = -1;
-    if (!(d.W > 0.0)) return;
-    const double target = d.target = u * d.W;
-    const int gl = d.gl = pick_lane(ballot(four > 0.0) & ballot(cum > target), ballot(four > 0.0));
+    const double W = readlane_f64(cum, 63);
+    if (!(W > 0.0)) {                               // nothing left to sample under the node
+        hand_over();
+        return;
+    }
+    const double target = u * W;
+    const int gl = pick_lane(ballot(four > 0.0) & ballot(cum > target), ballot(four > 0.0));
     const double start = scan_at(cum, gl - 1);
     double run_start = start;
     int k = -1;
@@ -447,52 +480,41 @@ __device__ __forceinline__ void prepare_draw(NextDraw& d, uint32_t place, uint32
         }
         if (k < 0) { k = last; run_start = last_start; }            // rounding at the top
     }
-    d.k = __builtin_amdgcn_readlane(k, gl);
-    d.run_start = readlane_f64(run_start, gl);
-    const int run0 = d.run0 = (4 * gl + d.k) * kRun;
+    k = __builtin_amdgcn_readlane(k, gl);
+    run_start = readlane_f64(run_start, gl);
+    const int run0 = (4 * gl + k) * kRun;
     const int tok0 = run0 + 2 * lane;               // this lane's two tokens of the run
+    // (past the end of the row a token that is there is read: with the loads in a branch of their own they are waited for in it)
+    float2 x;
     if constexpr (VEC) {
-        const float2 v = tok0 < V ? *reinterpret_cast<const float2*>(row + tok0) : make_float2(-INFINITY, -INFINITY);
-        d.x[0] = v.x; d.x[1] = v.y;
+        x = *reinterpret_cast<const float2*>(row + (tok0 < V ? tok0 : 0));
     } else {
-        d.x[0] = tok0 < V ? row[tok0] : -INFINITY;
-        d.x[1] = tok0 + 1 < V ? row[tok0 + 1] : -INFINITY;
+        x.x = row[min(tok0, V - 1)];
+        x.y = row[min(tok0 + 1, V - 1)];
     }
-    d.out = 0u;
-    if (rank > 0) {
+    unsigned short* const drawn = ws_drawn(ws, ws_row);
+    uint32_t out = 0u;                              // bit e: token tok0 + e was drawn here before
+    uint2 child;
+    float next_u, child_u;
+    // ---- while the logits are on their way: the tokens drawn before, the key of the node this draw makes, its first uniform, the
+    //      uniform of this node's next draw
+    if (rank == 0) {
+        // lane 0 the key, lane 1 the next draw's uniform
+        const uint2 key = split_key(key_word);
+        const uint4 blk = philox4x32_10(make_uint4(key.x, key.y, (uint32_t)(lane & 1), (lane & 1) ? KIND_BUILD : KIND_PATH), seed_key(seed));
+        child = make_uint2((uint32_t)__builtin_amdgcn_readlane((int)blk.x, 0), (uint32_t)__builtin_amdgcn_readlane((int)blk.y, 0));
+        next_u = (float)(blk.x >> 8) * (1.0f / 16777216.0f);                        // lane 1's counts
+        child_u = u01(seed, child, 0u, KIND_BUILD);
+    } else {
         if (lane < kRun / 32) lds_set(lds_at<uint32_t>(gone + 4 * lane), 0u);
         auto leave_out = [&](int t) __attribute__((always_inline)) {
             if (t / kRun * kRun == run0)
                 __hip_atomic_fetch_or(lds_at<uint32_t>(gone + 4 * (t % kRun / 32)), 1u << (t % 32), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
         };
         if (lane < rank) leave_out(h.drawn);
-        const unsigned short* const drawn = ws_drawn(ws, ws_row);
         for (int c = lane + kWave; c < rank; c += kWave) leave_out(drawn[c]);
-        d.out = lds_now(lds_at<uint32_t>(gone + 4 * (lane / 16))) >> (2 * (lane & 15));
-        if (!named) make_names(names, seed, d.key_word, node, rank);             // (while the logits are on their way)
-    }
-}
-
-template <bool VEC>
-__device__ __forceinline__ void finish_draw(const NextDraw& d, uint32_t place, double inv_temp, uint64_t seed, double* ws, int ws_row,
-                                            HeldRow& h, const DrawNames& names)
-{
-    const int lane = threadIdx.x & 63, rank = d.rank;
-    if (d.gl < 0) {                                 // nothing left to sample under the node
-        if (lane == 0) publish(place, -1.0, 0ull, 0.f, kAnswer);
-        return;
-    }
-    // ---- the key of the node this draw makes, its first uniform, the uniform of this node's next draw
-    uint2 child;
-    float next_u, child_u;
-    if (rank == 0) {
-        // (while the logits are on their way) lane 0 the key, lane 1 the next draw's uniform
-        const uint2 key = split_key(d.key_word);
-        const uint4 blk = philox4x32_10(make_uint4(key.x, key.y, (uint32_t)(lane & 1), (lane & 1) ? KIND_BUILD : KIND_PATH), seed_key(seed));
-        child = make_uint2((uint32_t)__builtin_amdgcn_readlane((int)blk.x, 0), (uint32_t)__builtin_amdgcn_readlane((int)blk.y, 0));
-        next_u = (float)(blk.x >> 8) * (1.0f / 16777216.0f);                        // lane 1's counts
-        child_u = u01(seed, child, 0u, KIND_BUILD);
-    } else {
+        out = lds_now(lds_at<uint32_t>(gone + 4 * (lane / 16))) >> (2 * (lane & 15));
+        if (!named) make_names(names, seed, key_word, node, rank);
         const int at = rank & (kWave - 1);
         child = make_uint2((uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)names.child, at), (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(names.child >> 32), at));
         next_u = names.u;                                                           // lane at + 1's counts
@@ -500,34 +522,38 @@ __device__ __forceinline__ void finish_draw(const NextDraw& d, uint32_t place, d
     }
     // ---- the token: as above among the run's 128
     double z[2], w[2];
-#pragma unroll
-    for (int e = 0; e < 2; ++e) z[e] = fma((double)d.x[e], inv_temp, -h.m);
+    z[0] = fma((double)(tok0 < V ? x.x : -INFINITY), inv_temp, -h.m);
+    z[1] = fma((double)(tok0 + 1 < V ? x.y : -INFINITY), inv_temp, -h.m);
     exp_nonpos_xn<2>(z, w);
-    if (d.out & 1u) w[0] = 0.0;
-    if (d.out & 2u) w[1] = 0.0;
+    if (out & 1u) w[0] = 0.0;
+    if (out & 2u) w[1] = 0.0;
     const double mine = w[0] + w[1];
     const double inc = wave_scan_dpp(mine);
     const u64 live = ballot(mine > 0.0);
     if (!live) {                                    // (the run's total says otherwise: not while totals and logits belong together)
-        if (lane == 0) publish(place, -1.0, 0ull, 0.f, kAnswer);
+        hand_over();
         return;
     }
-    const int ol = pick_lane(live & ballot(d.run_start + inc > d.target), live);
-    const double mid = d.run_start + scan_at(inc, ol - 1) + w[0];   // (of interest in lane ol)
-    const int second = (w[0] > 0.0 && (mid > d.target || !(w[1] > 0.0))) ? 0 : 1;
+    const int ol = pick_lane(live & ballot(run_start + inc > target), live);
+    const double mid = run_start + scan_at(inc, ol - 1) + w[0];     // (of interest in lane ol)
+    const int second = (w[0] > 0.0 && (mid > target || !(w[1] > 0.0))) ? 0 : 1;
     const int e = __builtin_amdgcn_readlane(second, ol);
-    const int y = d.run0 + 2 * ol + e;
+    const int y = run0 + 2 * ol + e;
     const double wy = readlane_f64(e ? w[1] : w[0], ol);
     if (lane == ((rank + 1) & (kWave - 1))) *lds_at<float>(place + kUAt) = next_u;
-    if (lane == 0) publish(place, wy / d.W, join_key(child), child_u, kAnswer | ((uint32_t)rank << 15) | (uint32_t)y);
+    d.R = wy / W;
+    d.child = join_key(child);
+    d.child_u = child_u;
+    d.word = kAnswer | ((uint32_t)rank << 15) | (uint32_t)y;
+    hand_over();
     // what is left of the run
     const double left = wave_sum_dpp(lane == ol ? (e ? w[0] : w[1]) : mine);
-    const bool here = lane == d.gl;
+    const bool here = lane == gl;
 #pragma unroll
-    for (int q = 0; q < 4; ++q) h.tot[q] = here && q == d.k ? left : h.tot[q];     // (selects: a store to tot[k] puts the array in scratch memory)
-    if (here) ws_totals(ws, ws_row)[4 * lane + d.k] = left;
+    for (int q = 0; q < 4; ++q) h.tot[q] = here && q == k ? left : h.tot[q];       // (selects: a store to tot[k] puts the array in scratch memory)
+    if (here) ws_totals(ws, ws_row)[4 * lane + k] = left;
     if (lane == (rank & 63)) {
-        ws_drawn(ws, ws_row)[rank] = (unsigned short)y;
+        drawn[rank] = (unsigned short)y;
         if (rank < kWave) h.drawn = y;
     }
 }
@@ -548,20 +574,20 @@ __device__ __attribute__((noinline)) void draw_for_nodes(uint32_t lds_, int mine
     RowCopies<HeldRow> rows;
     rows.open(mine);
     DrawNames names = { -1, 0, 0.f, 0.f, 0ull };
-    NextDraw next;
-    next.node = next.rank = -1;
+    MadeDraw made;                                  // the last draw put aside
+    made.node = made.rank = -1;
     const auto fetch = [&](int i, HeldRow& h) __attribute__((always_inline)) { fetch_row(ws, base, i, h); };
     uint32_t seen = 1u << 31;                       // the news last looked at (none yet)
     bool look = mine == 0;                          // requests may be open (node 0's, at the start)
     for (;;) {
         rows.look_ahead(N, fetch);
         int i = -1, rank = 0;
-        const auto prepared = [&]() __attribute__((always_inline)) {    // the draw made ready has been asked for
-            return next.node >= 0 && !(uniform(lds_now(lds_at<uint32_t>(nodes + kNode * next.node + kWordAt))) & kAnswer);
+        const auto wanted = [&]() __attribute__((always_inline)) {      // that draw has been asked for
+            return made.node >= 0 && !(uniform(lds_now(lds_at<uint32_t>(nodes + kNode * made.node + kWordAt))) & kAnswer);
         };
-        if (prepared()) {
-            i = next.node;
-            rank = next.rank;
+        if (wanted()) {
+            i = made.node;
+            rank = made.rank;
         } else if (look) {
             // the best request of each lane's nodes, then of the wave
             int best = 0, node = 0;
@@ -590,10 +616,10 @@ __device__ __attribute__((noinline)) void draw_for_nodes(uint32_t lds_, int mine
             const bool a_mine = a % kDrawWaves == mine, p_mine = (m & kRequest) && p % kDrawWaves == mine;
             const bool one = a == (int)(seen & 1023u) + 1;
             seen = m;
-            if (p_mine && p == next.node && prepared()) {
+            if (p_mine && p == made.node && wanted()) {
                 look = !one || a_mine;              // after it has been served
-                i = next.node;
-                rank = next.rank;
+                i = made.node;
+                rank = made.rank;
             } else {
                 look = !one || (a_mine && p_mine);
                 if (look || !(a_mine || p_mine)) continue;
@@ -604,15 +630,19 @@ __device__ __attribute__((noinline)) void draw_for_nodes(uint32_t lds_, int mine
                 rank = (int)(w >> 15);
             }
         }
-        for (bool asked = true, ready = next.node == i && next.rank == rank; ; asked = ready = false, ++rank) {
-            if (!ready) {
-                rows.hold(i, kDrawWaves, fetch);
-                prepare_draw<VEC>(next, nodes + kNode * i, gone, draft_logits + (size_t)(base + i) * V, V, seed, ws, base + i, rows.held, names, i, rank);
-            }
-            if (!asked) break;                      // (the next draw of a node that is drawn from again is made ready before it is asked for)
-            finish_draw<VEC>(next, nodes + kNode * i, inv_temp, seed, ws, base + i, rows.held, names);
-            next.node = -1;
-            if (rank == 0) break;
+        bool asked = true;
+        if (rank > 1) {                             // made when the one before was asked for
+            if (made.node != i) get_made(ws, base + i, made);
+            if (lane == 0) publish(nodes + kNode * i, made.R, made.child, made.child_u, made.word);
+            asked = false;
+            ++rank;
+        }
+        for (;;) {
+            rows.hold(i, kDrawWaves, fetch);
+            draw_for_node<VEC>(made, nodes + kNode * i, gone, draft_logits + (size_t)(base + i) * V, V, inv_temp, seed, ws, base + i, rows.held, names, i, rank, asked);
+            if (!asked || rank == 0) break;
+            asked = false;
+            ++rank;
         }
         if (uniform(lds_now(lds_at<uint32_t>(lds + BuildLds::news))) == kStop) return;
     }
