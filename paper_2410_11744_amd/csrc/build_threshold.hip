@@ -100,9 +100,9 @@ __global__ __launch_bounds__(256) void threshold_init_kernel(SeqArgs sa, dyspec_
 
 // One workgroup per node of the current level: blockIdx.x = position in the level.  All waves bring
 // the node's row into LDS (logits, leaf sums); then the first one draws and the others leave.
-// Bound by the instructions of a draw (a lone wave issues one in eight cycles, about 170 of them): 0.6 us each,
+// Bound by the instructions of a draw (a lone wave issues one in eight cycles, about 160 of them): 0.57 us each,
 // against 1.5 us when the whole workgroup made every draw, with two barriers and eight waves doing every
-// scan: the 384-row tree of the Zipf table (383 draws under the root) 587 -> 235 us.  A second wave that takes
+// scan: the 384-row tree of the Zipf table (383 draws under the root) 587 -> 235 us, now 227.  A second wave that takes
 // over the division and the writing through a ring of draws in LDS makes it 256: keeping the ring costs the
 // drawing wave more instructions than it saves.
 constexpr int kExpandThreads = 1024;

@@ -5,8 +5,8 @@
 // CDF through the three levels: the wave compares its inclusive scan of the group totals with u * W, scans
 // the picked group's leaves, turns the picked leaf's logits into weights and scans those.  Nothing
 // but the wave's own instructions lies between two draws: no barrier, no trip to global memory.
-// Bound by the number of instructions, about 170 a draw: a wave alone issues one in eight cycles, dependent or not
-// (0.6 us a draw in the threshold builder; a workgroup of eight waves with two barriers a draw took 1.5).
+// Bound by the number of instructions, about 160 a draw: a wave alone issues one in eight cycles, dependent or not
+// (0.57 us a draw in the threshold builder; a workgroup of eight waves with two barriers a draw took 1.5).
 //
 // The sums are never updated by subtraction: the drawn token's leaf, its group and the scan of the
 // groups are each made of what is left (sum before + sum after the gap), so they are zero exactly
@@ -128,23 +128,33 @@ __device__ __forceinline__ int pick_lane(u64 hit, u64 live)
     return hit ? __builtin_ctzll(hit) : 63 - __builtin_clzll(live);
 }
 
-// One draw with uniform u; the token leaves the row.  False (nothing changed) when the row is empty.
-// Every lane gets the same result.
-__device__ __forceinline__ bool draw_wave_row(WaveRow& r, double u, Drawn* d)
+// One draw with uniform u of a row with weight left; the token leaves the row.  Every lane gets the same result.
+// A crossing is looked for where sums are compared with the target alone: of non-negative values in one order, the first sum above it
+// belongs to a positive one.  Sums of one scan are made in different orders, though, and may miss the target or cross it at a zero
+// by a rounding: if there is no crossing at the last level, or at a zero, nothing has been changed, the result is false,
+// and the draw is made again with EXACT, which asks for positive values at each level and takes the last one if there is no crossing
+// (what was picked otherwise is what EXACT picks).  A 383-draw row: 276 -> 268 us a call; with a branch at each level instead of
+// one at the end 286.
+template <bool EXACT>
+__device__ __forceinline__ bool draw_wave_row(WaveRow& r, double u, double W, Drawn* d)
 {
     const int lane = threadIdx.x & 63;
-    const double W = readlane_f64(r.cum, 63);
-    if (!(W > 0.0)) return false;
     const double target = u * W;
-    const u64 live_g = ballot(r.tot > 0.0);
-    const int g = pick_lane(live_g & ballot(r.cum > target), live_g);
+    const auto pick = [](u64 hit, int last, auto&& positive) __attribute__((always_inline)) {
+        if constexpr (EXACT) {
+            const u64 live = positive();
+            return pick_lane(live & hit, live);
+        } else {
+            return (int)__builtin_ctzll(hit | (1ull << last));
+        }
+    };
+    const int g = pick(ballot(r.cum > target), 63, [&]() { return ballot(r.tot > 0.0); });
     // lanes 0..15 (and 32..47) hold the group's leaves, lanes 16..31 (48..63) the same in reverse order
     const double b = r.leaf[g * kGroupLeaves + ((lane & 15) ^ ((lane & 16) ? 15 : 0))];
     const double below_g = scan_at(r.cum, g - 1);
     const double cb = scan16_dpp(b);
     const double eb = dpp_or_zero<0x111>(cb);               // what lies before each leaf (row_shr:1; 0 at the start of a row)
-    const u64 live_l = ballot(b > 0.0) & 0xffffull;
-    const int l = pick_lane(live_l & ballot(below_g + cb > target), live_l);
+    const int l = pick(ballot(below_g + cb > target) & 0xffffull, 15, [&]() { return ballot(b > 0.0) & 0xffffull; });
     // lanes 0..31: the leaf's tokens, lanes 32..63: the same in reverse order
     const int leaf0 = (g * kGroupLeaves + l) * kLeafTokens;
     const float x = r.logits[leaf0 + ((lane & 31) ^ ((lane & 32) ? 31 : 0))];
@@ -154,17 +164,26 @@ __device__ __forceinline__ bool draw_wave_row(WaveRow& r, double u, Drawn* d)
     double z[1] = { fma((double)x, r.inv_temp, -r.m) }, w[1];
     exp_nonpos_xn<1>(z, w);
     const double cw = scan32_dpp(w[0]);
-    const u64 live_e = ballot(w[0] > 0.0) & 0xffffffffull;
-    const int e = pick_lane(live_e & ballot(below_l + cw > target), live_e);
+    const u64 over = ballot(below_l + cw > target) & 0xffffffffull;
+    const int e = pick(over, 31, [&]() { return ballot(w[0] > 0.0) & 0xffffffffull; });
     d->y = leaf0 + e;
     d->wy = readlane_f64(w[0], e);
     d->W = W;
+    if (!EXACT && (over == 0ull || !(d->wy > 0.0))) return false;
     const double left = scan_at(cw, e - 1) + (e < 31 ? readlane_f64(cw, 62 - e) : 0.0);
     const double t = (leaves_before + left) + leaves_after;
     r.cum = rest + (lane >= g ? t : 0.0);
     if (lane == g) r.tot = t;
     if (lane == e) r.logits[leaf0 + e] = -INFINITY;
     if (lane == 0) r.leaf[g * kGroupLeaves + l] = left;
+    return true;
+}
+// The same; false (nothing changed) when the row is empty.
+__device__ __forceinline__ bool draw_wave_row(WaveRow& r, double u, Drawn* d)
+{
+    const double W = readlane_f64(r.cum, 63);
+    if (!(W > 0.0)) return false;
+    if (__builtin_expect(!draw_wave_row<false>(r, u, W, d), 0)) draw_wave_row<true>(r, u, W, d);
     return true;
 }
 
