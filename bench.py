@@ -396,6 +396,8 @@ def main() -> int:
             roofline["frac_of_measured_ceiling"] = round(achieved_tflops / ceilings["mfma_bf16_tflops"], 4)
     else:
         gbs = bytes_attn_launch / (launch_ms * 1e-3) / 1e9
+        if cfg.dtype == "bf16":        # short walks take the other kernel (the rule: csrc/tree_attn_short.hip)
+            kernel += " / tree_attn_short_kernel<%d, ..>" % cfg.head_dim
         roofline = {"kernel": kernel, "bound": "hbm", "achieved": round(gbs, 1), "peak": PEAK_HBM_GBS,
                     "unit": "GB/s", "frac": round(gbs / PEAK_HBM_GBS, 4)}
         if ceilings:

@@ -7,9 +7,9 @@
 // row form otherwise).  verify_walk_kernel is Algorithm 3 itself,
 // one workgroup per sequence walking from the root: the first child of a node is tested
 // from two logits and the row statistics alone; only after a rejection are the node's two
-// rows brought into registers and LDS (as weights of a known sum, no reduction) for the residual
-// updates R <- norm(max(R-D,0)), D[y] <- 0, D <- norm(D), one sweep and one workgroup reduction per
-// rejected child, stopping at the first accepted one.  Tree links and statistics of the
+// rows brought into registers (as weights of a known sum, no reduction) for the residual
+// updates R <- norm(max(R-D,0)), D[y] <- 0, D <- norm(D), one pass over the registers and one workgroup reduction per
+// rejected child, stopping at the first accepted one.  Tree links of the
 // sequence are staged in LDS so the walk chases pointers there, not in HBM.
 //
 // A target temperature of 0 (the temperature-0 rows of Section 5's tables) makes the target
