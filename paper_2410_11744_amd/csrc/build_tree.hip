@@ -238,7 +238,8 @@ __global__ __launch_bounds__(kBlock) void build_tree_kernel(
 // The form with a workspace: waves with roles.
 //
 // Wave 0 (control) pops.  Every node has one open slot, its next draw; the lanes of control hold the best 64 in
-// order (the slots themselves lie in LDS), so the pop is lane 0's.  It takes the popped node's next draw (token, R[y], the new node's path key and first uniform) from
+// order (the slots themselves lie in LDS), so the pop is lane 0's.  It takes the popped node's next draw (token, R[y], the
+// new node's path key and first uniform) from
 // LDS, opens the new node's slot and the parent's next one.
 // Wave 1 draws from the root's row, which it keeps in LDS (wave_draw.h), up to kRing draws
 // ahead: the root is popped most often in wide trees.
@@ -265,7 +266,7 @@ __global__ __launch_bounds__(kBlock) void build_tree_kernel(
 // 32000 tokens 1378 -> 508 us (with eight drawing waves on two SIMDs 562, on all four 543: a request waits for the draw its
 // wave is at), 128 rows 346 -> 134, 32 rows of 1000 tokens 92 -> 55; a single chain of 512 nodes 1413 -> 1130.  (All before
 // the sorted list of slots, see pop_nodes.)  Of one size the time depends on the table, that is, on how often nodes
-// other than the root are popped again: 440 to 600 us over tables of 512 rows of independent normal logits.
+// other than the root are popped again: 385 to 515 us over tables of 512 rows of independent normal logits.
 constexpr int kBuildThreads = 1024;
 constexpr int kDrawWaves = kBuildThreads / kWave - 2;
 constexpr int kRing = 16;
@@ -656,8 +657,8 @@ __device__ __attribute__((noinline)) void draw_for_nodes(uint32_t lds_, int mine
 // that place move up by one; the new node's slot makes the lanes behind its place move down.  A slot that finds no place among
 // the 64 is left out: `unlisted` is the largest value left out so far, and while lane 0 is above it the list is as good as the
 // whole frontier.  Else the list is made again from the slots in LDS (`relist`), the first kRelisted of them: a few times
-// in trees of many equally good slots, never in 512 rows of 1000 or 32000 tokens of independent normal logits. (512 rows with two equal
-// tokens each, where every sixteenth pop does: 482 us, 505 with the maximum found at each pop, 720 with a list
+// in trees of many equally good slots, never in 512 rows of 1000 or 32000 tokens of independent normal logits.
+// (512 rows with two equal tokens each, where every sixteenth pop does: 482 us, 505 with the maximum found at each pop, 720 with a list
 // made by sixteen comparisons a lane for each of its entries.)
 // Against the best of each lane's nodes kept in the lane and the maximum over the lanes found at each pop, and the other
 // nodes of the popped one's lane looked over again: a pop whose draw is there 0.61 -> 0.51 us; with the draws' names
