@@ -107,11 +107,13 @@ struct WaveRow {
     lds_t<float>* logits;
     double m, inv_temp;
     double tot, cum;            // lane l: total of group l, inclusive scan over the groups
+    int last_leaf;              // of the row's logits
 };
 
 __device__ __forceinline__ void open_wave_row(WaveRow& r, int V)
 {
     const int lane = threadIdx.x & 63;
+    r.last_leaf = row_logits(V) / kLeafTokens - 1;
     r.tot = 0.0;
     if (lane < row_leaves(V) / kGroupLeaves) {
 #pragma unroll
@@ -133,8 +135,9 @@ __device__ __forceinline__ int pick_lane(u64 hit, u64 live)
 // belongs to a positive one.  Sums of one scan are made in different orders, though, and may miss the target or cross it at a zero
 // by a rounding: if there is no crossing at the last level, or at a zero, nothing has been changed, the result is false,
 // and the draw is made again with EXACT, which asks for positive values at each level and takes the last one if there is no crossing
-// (what was picked otherwise is what EXACT picks).  A 383-draw row: 276 -> 268 us a call; with a branch at each level instead of
-// one at the end 286.
+// (what was picked otherwise is what EXACT picks).  Without a crossing at an earlier level (an infinite weight: none at any)
+// the row's last group, the group's last leaf that has logits, goes on: nothing past the row is read.
+// A 383-draw row: 276 -> 270 us a call (268 without the bounds of group and leaf); with a branch at each level instead of one at the end 286.
 template <bool EXACT>
 __device__ __forceinline__ bool draw_wave_row(WaveRow& r, double u, double W, Drawn* d)
 {
@@ -145,16 +148,16 @@ __device__ __forceinline__ bool draw_wave_row(WaveRow& r, double u, double W, Dr
             const u64 live = positive();
             return pick_lane(live & hit, live);
         } else {
-            return (int)__builtin_ctzll(hit | (1ull << last));
+            return (int)min(hit ? (uint32_t)__builtin_ctzll(hit) : ~0u, (uint32_t)last);
         }
     };
-    const int g = pick(ballot(r.cum > target), 63, [&]() { return ballot(r.tot > 0.0); });
+    const int g = pick(ballot(r.cum > target), r.last_leaf / kGroupLeaves, [&]() { return ballot(r.tot > 0.0); });
     // lanes 0..15 (and 32..47) hold the group's leaves, lanes 16..31 (48..63) the same in reverse order
     const double b = r.leaf[g * kGroupLeaves + ((lane & 15) ^ ((lane & 16) ? 15 : 0))];
     const double below_g = scan_at(r.cum, g - 1);
     const double cb = scan16_dpp(b);
     const double eb = dpp_or_zero<0x111>(cb);               // what lies before each leaf (row_shr:1; 0 at the start of a row)
-    const int l = pick(ballot(below_g + cb > target) & 0xffffull, 15, [&]() { return ballot(b > 0.0) & 0xffffull; });
+    const int l = pick(ballot(below_g + cb > target), min(r.last_leaf - g * kGroupLeaves, kGroupLeaves - 1), [&]() { return ballot(b > 0.0) & 0xffffull; });
     // lanes 0..31: the leaf's tokens, lanes 32..63: the same in reverse order
     const int leaf0 = (g * kGroupLeaves + l) * kLeafTokens;
     const float x = r.logits[leaf0 + ((lane & 31) ^ ((lane & 32) ? 31 : 0))];
