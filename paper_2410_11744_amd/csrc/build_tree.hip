@@ -19,24 +19,12 @@
 #include "draft_row.h"
 #include "lane_ops.h"
 #include "row_copies.h"
+#include "row_workspace.h"
 #include "wave_draw.h"
 
 namespace dyspec {
 
 constexpr int kMaxSlots = 2 * DYSPEC_MAX_BUILD_NODES + 2;
-
-// Workspace, per row (kRowSumDoubles doubles): the totals of kSums runs of kRun tokens, the row maximum
-// (already divided by the temperature), and from kDrawnOffset on the tokens drawn at this position, two
-// bytes each in the order of the draws (their weights are no longer in the totals), at kMadeOffset a draw made but not asked for.
-constexpr int kRun = 128;
-constexpr int kSums = DYSPEC_MAX_VOCAB / kRun;
-constexpr int kRowSumDoubles = kMaxSeg + 8 + DYSPEC_MAX_VOCAB / 64;
-constexpr int kDrawnOffset = kSums + 2;
-constexpr int kMadeOffset = kDrawnOffset + DYSPEC_MAX_BUILD_NODES / 4;
-static_assert(kRowSumDoubles >= kMadeOffset + 3, "room for every draw a row can see, and one that is made");
-__host__ __device__ inline double* ws_totals(double* ws, int row) { return ws + (size_t)row * kRowSumDoubles; }
-__host__ __device__ inline double* ws_rowmax(double* ws, int row) { return ws_totals(ws, row) + kSums; }
-__host__ __device__ inline unsigned short* ws_drawn(double* ws, int row) { return reinterpret_cast<unsigned short*>(ws_totals(ws, row) + kDrawnOffset); }
 
 // Data-parallel part (the draft softmax of every node, Algorithm 1's model call output):
 // one workgroup per row writes the row's totals and maximum.  S: segments held, V <= S * kSeg.
@@ -409,14 +397,14 @@ struct MadeDraw {
 // One that has not been asked for waits in the workspace (lane 0 writes and reads it).
 __device__ __forceinline__ void put_made(double* ws, int ws_row, const MadeDraw& d)
 {
-    double* const at = ws_totals(ws, ws_row) + kMadeOffset;
+    double* const at = ws_made(ws, ws_row);
     at[0] = d.R;
     at[1] = __longlong_as_double((long long)d.child);
     at[2] = __hiloint2double((int)d.word, __float_as_int(d.child_u));
 }
 __device__ __forceinline__ void get_made(double* ws, int ws_row, MadeDraw& d)
 {
-    const double* const at = ws_totals(ws, ws_row) + kMadeOffset;
+    const double* const at = ws_made(ws, ws_row);
     const double last = at[2];
     d.R = at[0];
     d.child = (u64)__double_as_longlong(at[1]);

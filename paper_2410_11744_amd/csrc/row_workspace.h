@@ -1,0 +1,28 @@
+// The greedy builder's workspace, per row (kRowSumDoubles doubles): the totals of kSums runs of kRun tokens, the row maximum
+// (already divided by the temperature), from kDrawnOffset on the tokens drawn at this position, two bytes each in the
+// order of the draws (their weights are no longer in the totals), at kMadeOffset a draw made but not asked for.
+// Host code as well as device code.
+#pragma once
+#include <stddef.h>
+
+#include "../../include/dyspec.h"
+
+namespace dyspec {
+
+constexpr int kRun = 128;
+constexpr int kSums = DYSPEC_MAX_VOCAB / kRun;
+constexpr int kRowSumDoubles = 24 + DYSPEC_MAX_VOCAB / 64;
+constexpr int kDrawnOffset = kSums + 2;
+// A node's draws have ranks up to DYSPEC_MAX_BUILD_NODES: each of the tree's other rows may be a child, the last pop asks for the
+// draw after the last child's, and the one after that is made ahead.
+constexpr int kDrawnEntries = DYSPEC_MAX_BUILD_NODES + 1;
+constexpr int kMadeOffset = kDrawnOffset + (kDrawnEntries + 3) / 4;
+constexpr int kMadeDoubles = 3;
+static_assert(kRowSumDoubles >= kMadeOffset + kMadeDoubles, "room for every draw of a row, and for one that is put aside");
+
+__host__ __device__ inline double* ws_totals(double* ws, int row) { return ws + (size_t)row * kRowSumDoubles; }
+__host__ __device__ inline double* ws_rowmax(double* ws, int row) { return ws_totals(ws, row) + kSums; }
+__host__ __device__ inline unsigned short* ws_drawn(double* ws, int row) { return reinterpret_cast<unsigned short*>(ws_totals(ws, row) + kDrawnOffset); }
+__host__ __device__ inline double* ws_made(double* ws, int row) { return ws_totals(ws, row) + kMadeOffset; }
+
+}  // namespace dyspec
