@@ -107,13 +107,11 @@ struct WaveRow {
     lds_t<float>* logits;
     double m, inv_temp;
     double tot, cum;            // lane l: total of group l, inclusive scan over the groups
-    int last_leaf;              // of the row's logits
 };
 
 __device__ __forceinline__ void open_wave_row(WaveRow& r, int V)
 {
     const int lane = threadIdx.x & 63;
-    r.last_leaf = row_logits(V) / kLeafTokens - 1;
     r.tot = 0.0;
     if (lane < row_leaves(V) / kGroupLeaves) {
 #pragma unroll
@@ -135,29 +133,33 @@ __device__ __forceinline__ int pick_lane(u64 hit, u64 live)
 // belongs to a positive one.  Sums of one scan are made in different orders, though, and may miss the target or cross it at a zero
 // by a rounding: if there is no crossing at the last level, or at a zero, nothing has been changed, the result is false,
 // and the draw is made again with EXACT, which asks for positive values at each level and takes the last one if there is no crossing
-// (what was picked otherwise is what EXACT picks).  Without a crossing at an earlier level (an infinite weight: none at any)
-// the row's last group, the group's last leaf that has logits, goes on: nothing past the row is read.
-// A 383-draw row: 276 -> 270 us a call (268 without the bounds of group and leaf); with a branch at each level instead of one at the end 286.
+// (what was picked otherwise is what EXACT picks).  A 383-draw row: 276 -> 268 us a call; with a branch at each level instead of
+// one at the end 286.
+// Nothing past the row is read.  Finite sums: for u <= 1 - 2^-24 the target lies so far below the row's last sums (their
+// roundings are some 2^-50 of them) that the last group's crossing is found among its leaves that have logits.  An infinite sum crosses
+// nothing and belongs to EXACT: `none` and the target are then NaN, every sum counts as past it, and the first token is refused.
 template <bool EXACT>
 __device__ __forceinline__ bool draw_wave_row(WaveRow& r, double u, double W, Drawn* d)
 {
     const int lane = threadIdx.x & 63;
-    const double target = u * W;
+    const double none = EXACT ? 0.0 : W * 0.0;
+    const double target = EXACT ? u * W : fma(u, W, none);
+    const auto past = [=](double sum) __attribute__((always_inline)) { return EXACT ? sum > target : !(sum <= target); };
     const auto pick = [](u64 hit, int last, auto&& positive) __attribute__((always_inline)) {
         if constexpr (EXACT) {
             const u64 live = positive();
             return pick_lane(live & hit, live);
         } else {
-            return (int)min(hit ? (uint32_t)__builtin_ctzll(hit) : ~0u, (uint32_t)last);
+            return (int)__builtin_ctzll(hit | (1ull << last));
         }
     };
-    const int g = pick(ballot(r.cum > target), r.last_leaf / kGroupLeaves, [&]() { return ballot(r.tot > 0.0); });
+    const int g = pick(ballot(past(r.cum)), 63, [&]() { return ballot(r.tot > 0.0); });
     // lanes 0..15 (and 32..47) hold the group's leaves, lanes 16..31 (48..63) the same in reverse order
     const double b = r.leaf[g * kGroupLeaves + ((lane & 15) ^ ((lane & 16) ? 15 : 0))];
     const double below_g = scan_at(r.cum, g - 1);
     const double cb = scan16_dpp(b);
     const double eb = dpp_or_zero<0x111>(cb);               // what lies before each leaf (row_shr:1; 0 at the start of a row)
-    const int l = pick(ballot(below_g + cb > target), min(r.last_leaf - g * kGroupLeaves, kGroupLeaves - 1), [&]() { return ballot(b > 0.0) & 0xffffull; });
+    const int l = pick(ballot(past(below_g + cb)) & 0xffffull, 15, [&]() { return ballot(b > 0.0) & 0xffffull; });
     // lanes 0..31: the leaf's tokens, lanes 32..63: the same in reverse order
     const int leaf0 = (g * kGroupLeaves + l) * kLeafTokens;
     const float x = r.logits[leaf0 + ((lane & 31) ^ ((lane & 32) ? 31 : 0))];
@@ -167,12 +169,12 @@ __device__ __forceinline__ bool draw_wave_row(WaveRow& r, double u, double W, Dr
     double z[1] = { fma((double)x, r.inv_temp, -r.m) }, w[1];
     exp_nonpos_xn<1>(z, w);
     const double cw = scan32_dpp(w[0]);
-    const u64 over = ballot(below_l + cw > target) & 0xffffffffull;
+    const u64 over = ballot(past(below_l + cw)) & 0xffffffffull;
     const int e = pick(over, 31, [&]() { return ballot(w[0] > 0.0) & 0xffffffffull; });
     d->y = leaf0 + e;
     d->wy = readlane_f64(w[0], e);
     d->W = W;
-    if (!EXACT && (over == 0ull || !(d->wy > 0.0))) return false;
+    if (!EXACT && (over == 0ull || !(d->wy > none))) return false;
     const double left = scan_at(cw, e - 1) + (e < 31 ? readlane_f64(cw, 62 - e) : 0.0);
     const double t = (leaves_before + left) + leaves_after;
     r.cum = rest + (lane >= g ? t : 0.0);
@@ -181,7 +183,7 @@ __device__ __forceinline__ bool draw_wave_row(WaveRow& r, double u, double W, Dr
     if (lane == 0) r.leaf[g * kGroupLeaves + l] = left;
     return true;
 }
-// The same; false (nothing changed) when the row is empty.
+// The same; false (nothing changed) when the row is empty.  u <= 1 - 2^-24.
 __device__ __forceinline__ bool draw_wave_row(WaveRow& r, double u, Drawn* d)
 {
     const double W = readlane_f64(r.cum, 63);

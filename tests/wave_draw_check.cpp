@@ -72,7 +72,6 @@ struct Row {
         r.inv_temp = 1.0;
         r.tot = tot[threadIdx.x];
         r.cum = cum[threadIdx.x];
-        r.last_leaf = row_logits(V) / kLeafTokens - 1;
         return r;
     }
     void keep(const WaveRow& r) { tot[threadIdx.x] = r.tot; cum[threadIdx.x] = r.cum; }
@@ -151,7 +150,7 @@ static int exact(int trials, int seed0)
             }
             double u = edge / W * (1.0 + ((int)(rng() % 5) - 2) * 0x1p-53);
             if (rng() % 8 == 0) u = (rng() >> 8) * (1.0 / 16777216.0);
-            if (u > 1.0 - 0x1p-53) u = 1.0 - 0x1p-53;
+            if (u > 1.0 - 0x1p-24) u = 1.0 - 0x1p-24;           // (the largest uniform)
             b.take(a);
             c.take(a);
             Drawn da, db, dc;
