@@ -422,6 +422,8 @@ __device__ __forceinline__ void get_made(double* ws, int ws_row, MadeDraw& d)
 // of which half by the logits' load, which is no longer waited for where it is made (the Philox blocks follow).
 // (Only the run, its logits and names made ready ahead, the draw made when asked for: 471, 441, 524; the same after a look
 // at the wave's other requests: 524, 484, 562.)
+// Rank r + 1 is of use in trees of at least r + 3 rows; smaller ones only ended after the draw (2 rows of 32000 tokens 18.1 us,
+// with it 19.2; 3 rows of 32001 25.5, 26.8).
 template <bool VEC>
 __device__ __forceinline__ void draw_for_node(MadeDraw& d, uint32_t place, uint32_t gone, const float* __restrict__ row, int V, double inv_temp,
                                               uint64_t seed, double* ws, int ws_row, HeldRow& h, DrawNames& names, int node, int rank, bool asked)
@@ -629,7 +631,7 @@ __device__ __attribute__((noinline)) void draw_for_nodes(uint32_t lds_, int mine
         for (;;) {
             rows.hold(i, kDrawWaves, fetch);
             draw_for_node<VEC>(made, nodes + kNode * i, gone, draft_logits + (size_t)(base + i) * V, V, inv_temp, seed, ws, base + i, rows.held, names, i, rank, asked);
-            if (!asked || rank == 0) break;
+            if (!asked || rank == 0 || rank + 3 > N) break;     // (a tree complete by then: its last pop's request is nobody's to wait for)
             asked = false;
             ++rank;
         }
