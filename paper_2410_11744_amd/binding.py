@@ -348,6 +348,18 @@ def _scratch(device, nbytes: int):
     return buf
 
 
+def tree_attn_form(batch: "Batch", n_q_heads: int, n_kv_heads: int, head_dim: int, layers: int = 1, use_workspace: bool = True):
+    """What a bf16 tree_attn call (with `layers`, a tree_attn_layers call) is launched as: (waves of a workgroup of the kernel
+    for short walks or 0 for the kernel for long ones, parts of the prefix, 1 if the tree has a part of its own).
+    For tests and benchmarks that name the kernel they are about; not an entry point of the C interface."""
+    lib = load_library()
+    cb, form = batch._c(), (ctypes.c_int32 * 3)()
+    nbytes = lib.dyspec_tree_attn_layers_workspace_bytes(ctypes.byref(cb), layers, n_q_heads, n_kv_heads, head_dim) if use_workspace else 0
+    _check(lib.dyspec_tree_attn_form(ctypes.byref(cb), layers, n_q_heads, n_kv_heads, head_dim, ctypes.c_size_t(nbytes), form),
+           "dyspec_tree_attn_form")
+    return tuple(form)
+
+
 class PreparedCall:
     """One library call with its arguments checked and marshalled once.  Calling the object issues
     the call again on the stream it was prepared for (the current one at that time unless given),

@@ -235,7 +235,8 @@ static dyspec_status tree_attn_common(const void* q, const void* k_prefix, const
                                       const dyspec_batch* batch, int32_t n_layers, long long q_stride,
                                       long long kvp_stride, long long kvt_stride, int32_t n_q_heads,
                                       int32_t n_kv_heads, int32_t head_dim, int32_t dtype, float softmax_scale,
-                                      void* out, void* workspace, size_t workspace_bytes, void* hip_stream)
+                                      void* out, void* workspace, size_t workspace_bytes, void* hip_stream,
+                                      const AttnForm* form = nullptr)
 {
     SeqArgs sa;
     const dyspec_status st = check_batch(batch, true, &sa);
@@ -264,6 +265,9 @@ static dyspec_status tree_attn_common(const void* q, const void* k_prefix, const
     } else {
         return DYSPEC_UNSUPPORTED;
     }
+    if (form && (dtype != DYSPEC_BF16 || force_simple ||
+                 !tree_attn_has_form(sa, n_q_heads, n_kv_heads, head_dim, n_layers, workspace ? workspace_bytes : 0, *form)))
+        return DYSPEC_UNSUPPORTED;
     AttnArgs a;
     a.q = q; a.kp = k_prefix; a.vp = v_prefix; a.kt = k_tree; a.vt = v_tree;
     a.mask = anc_mask; a.out = out;
@@ -274,7 +278,7 @@ static dyspec_status tree_attn_common(const void* q, const void* k_prefix, const
     const hipStream_t stream = static_cast<hipStream_t>(hip_stream);
     const bool one_launch = dtype == DYSPEC_BF16 && !force_simple;      // the matrix-core kernel takes a layer plane
     if (one_launch || n_layers == 1)
-        return launch_tree_attn(a, sa, dtype, force_simple, workspace, workspace_bytes, stream) == hipSuccess
+        return launch_tree_attn(a, sa, dtype, force_simple, form, workspace, workspace_bytes, stream) == hipSuccess
                    ? DYSPEC_OK : DYSPEC_HIP_ERROR;
     auto at = [](const void* p, long long off) { return p ? static_cast<const char*>(p) + off : nullptr; };
     for (int l = 0; l < n_layers; ++l) {                                 // the per-row kernels: one launch per layer
@@ -283,7 +287,7 @@ static dyspec_status tree_attn_common(const void* q, const void* k_prefix, const
         b.q = at(q, l * q_stride); b.out = static_cast<char*>(out) + l * q_stride;
         b.kp = at(k_prefix, l * kvp_stride); b.vp = at(v_prefix, l * kvp_stride);
         b.kt = at(k_tree, l * kvt_stride); b.vt = at(v_tree, l * kvt_stride);
-        if (launch_tree_attn(b, sa, dtype, force_simple, nullptr, 0, stream) != hipSuccess) return DYSPEC_HIP_ERROR;
+        if (launch_tree_attn(b, sa, dtype, force_simple, nullptr, nullptr, 0, stream) != hipSuccess) return DYSPEC_HIP_ERROR;
     }
     return DYSPEC_OK;
 }
@@ -296,6 +300,35 @@ dyspec_status dyspec_tree_attn(const void* q, const void* k_prefix, const void* 
 {
     return tree_attn_common(q, k_prefix, v_prefix, k_tree, v_tree, anc_mask, batch, 1, 0, 0, 0, n_q_heads,
                             n_kv_heads, head_dim, dtype, softmax_scale, out, workspace, workspace_bytes, hip_stream);
+}
+
+// What a bf16 call with head_dim 64 or 128 and a workspace of that size is launched as: form[0] waves per workgroup of the kernel for
+// short walks (0: the kernel for long ones), form[1] parts of the prefix, form[2] 1 if the tree has a part of its own.
+// dyspec_tree_attn_in_form launches dyspec_tree_attn as another form, DYSPEC_UNSUPPORTED where there is no such form.
+// Exported, but no part of the interface: tests ask which kernel a case is for, and run it through the others.
+dyspec_status dyspec_tree_attn_form(const dyspec_batch* batch, int32_t n_layers, int32_t n_q_heads, int32_t n_kv_heads,
+                                    int32_t head_dim, size_t workspace_bytes, int32_t* form)
+{
+    SeqArgs sa;
+    const dyspec_status st = check_batch(batch, true, &sa);
+    if (st != DYSPEC_OK) return st;
+    if (!form) return DYSPEC_BAD_ARG;
+    if (n_layers < 1 || n_q_heads < 1 || n_kv_heads < 1 || n_q_heads % n_kv_heads != 0) return DYSPEC_BAD_SHAPE;
+    if (head_dim != 64 && head_dim != 128) return DYSPEC_UNSUPPORTED;
+    const AttnForm f = tree_attn_form(sa, n_q_heads, n_kv_heads, head_dim, n_layers, workspace_bytes);
+    form[0] = f.waves; form[1] = f.splits; form[2] = f.tree_split;
+    return DYSPEC_OK;
+}
+dyspec_status dyspec_tree_attn_in_form(const int32_t* form, const void* q, const void* k_prefix, const void* v_prefix,
+                                       const void* k_tree, const void* v_tree, const uint64_t* anc_mask,
+                                       const dyspec_batch* batch, int32_t n_q_heads, int32_t n_kv_heads,
+                                       int32_t head_dim, int32_t dtype, float softmax_scale, void* out,
+                                       void* workspace, size_t workspace_bytes, void* hip_stream)
+{
+    if (!form) return DYSPEC_BAD_ARG;
+    const AttnForm f = { form[0], form[1], form[2] };
+    return tree_attn_common(q, k_prefix, v_prefix, k_tree, v_tree, anc_mask, batch, 1, 0, 0, 0, n_q_heads,
+                            n_kv_heads, head_dim, dtype, softmax_scale, out, workspace, workspace_bytes, hip_stream, &f);
 }
 
 dyspec_status dyspec_tree_attn_static_scratch(const void* q, const void* k_prefix, const void* v_prefix,

@@ -66,9 +66,15 @@ hipError_t launch_verify(const void* draft_logits, const void* target_logits, bo
                          const SeqArgs& sa, const dyspec_tree& tree, uint64_t seed, int emit_bonus,
                          float* row_stats, float* accept_ratio, int* accepted_nodes, int* n_accepted,
                          int* final_token, float* min_margin, hipStream_t stream);
-hipError_t launch_tree_attn(AttnArgs a, const SeqArgs& sa, int dtype, bool per_wave, void* workspace, size_t workspace_bytes,
-                            hipStream_t stream);
-hipError_t launch_tree_attn_mfma(AttnArgs a, const SeqArgs& sa, void* workspace, size_t workspace_bytes, hipStream_t stream);
+// How the matrix cores take a call: waves per workgroup of the kernel for short walks (0: the kernel for long ones), parts
+// of the prefix, and whether the tree has a part of its own.
+struct AttnForm { int waves, splits, tree_split; };
+AttnForm tree_attn_form(const SeqArgs& sa, int Hq, int Hkv, int d, int layers, size_t workspace_bytes);
+bool tree_attn_has_form(const SeqArgs& sa, int Hq, int Hkv, int d, int layers, size_t workspace_bytes, const AttnForm& form);
+// (`form`: nullptr for the one that tree_attn_form names)
+hipError_t launch_tree_attn(AttnArgs a, const SeqArgs& sa, int dtype, bool per_wave, const AttnForm* form, void* workspace,
+                            size_t workspace_bytes, hipStream_t stream);
+hipError_t launch_tree_attn_mfma(AttnArgs a, const SeqArgs& sa, const AttnForm* form, void* workspace, size_t workspace_bytes, hipStream_t stream);
 // 32-bit words one workgroup of the matrix-core kernel leaves per split: 4 row blocks x 64 lanes x
 // (d/4 packed bf16 pairs + max + sum)
 constexpr int attn_part_words(int d) { return 4 * 64 * (d / 4 + 2); }
@@ -80,6 +86,7 @@ size_t tree_attn_workspace_bytes(const SeqArgs& sa, int Hq, int Hkv, int d, int 
 // The kernel for short walks: waves per workgroup (0: the call is not for it) and parts of the prefix, given how the other
 // kernel would split it and the workspace there is.
 struct ShortPlan { int waves, splits; };
+bool tree_attn_short_has(const SeqArgs& sa, int Hq, int Hkv, int d, int layers, size_t workspace_bytes, int waves, int splits);
 ShortPlan tree_attn_short_plan(const SeqArgs& sa, int Hq, int Hkv, int d, int layers, int long_splits, size_t workspace_bytes);
 hipError_t launch_tree_attn_short(const AttnArgs& a, const SeqArgs& sa, int waves, hipStream_t stream);
 hipError_t prepare_tree_attn_short();

@@ -202,12 +202,12 @@ static void launch_simple(const AttnArgs& a, const SeqArgs& sa, int blocks, hipS
     else tree_attn_simple_kernel<T, 4><<<blocks, kSimpleWaves * kWave, 0, stream>>>(a, sa);
 }
 
-hipError_t launch_tree_attn(AttnArgs a, const SeqArgs& sa, int dtype, bool per_wave, void* workspace, size_t workspace_bytes,
-                            hipStream_t stream)
+hipError_t launch_tree_attn(AttnArgs a, const SeqArgs& sa, int dtype, bool per_wave, const AttnForm* form, void* workspace,
+                            size_t workspace_bytes, hipStream_t stream)
 {
     const int total_rows = sa.node_off[sa.n_seq];
     if (dtype == DYSPEC_BF16 && !per_wave && (a.d == 128 || a.d == 64))
-        return launch_tree_attn_mfma(a, sa, workspace, workspace_bytes, stream);
+        return launch_tree_attn_mfma(a, sa, form, workspace, workspace_bytes, stream);
     if (total_rows == 0) return hipSuccess;
     const long long groups = (long long)total_rows * a.Hq;    // one workgroup per (row, head)
     if (groups > 0x7fffffffLL) return hipErrorInvalidValue;

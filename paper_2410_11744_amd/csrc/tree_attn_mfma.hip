@@ -994,25 +994,34 @@ size_t tree_attn_workspace_bytes(const SeqArgs& sa, int Hq, int Hkv, int d, int 
     return kAttnCounterBytes + groups * splits * attn_part_words(d) * sizeof(uint32_t);
 }
 
-hipError_t launch_tree_attn_mfma(AttnArgs a, const SeqArgs& sa, void* workspace, size_t workspace_bytes, hipStream_t stream)
+AttnForm tree_attn_form(const SeqArgs& sa, int Hq, int Hkv, int d, int layers, size_t workspace_bytes)
+{
+    AttnCut cut = tree_attn_cut(sa, Hq, Hkv, layers);
+    const size_t need = tree_attn_workspace_bytes(sa, Hq, Hkv, d, layers);
+    if (workspace_bytes < need) cut = { 1, 0 };                // no room for partial results: one workgroup walks it all
+    const ShortPlan plan = tree_attn_short_plan(sa, Hq, Hkv, d, layers, cut.splits, cut.splits > 1 ? need : 0);
+    return plan.waves ? AttnForm{ plan.waves, plan.splits, 0 } : AttnForm{ 0, cut.splits, cut.tree_split };
+}
+
+bool tree_attn_has_form(const SeqArgs& sa, int Hq, int Hkv, int d, int layers, size_t workspace_bytes, const AttnForm& form)
+{
+    if (form.waves) return form.tree_split == 0 && tree_attn_short_has(sa, Hq, Hkv, d, layers, workspace_bytes, form.waves, form.splits);
+    const AttnCut cut = tree_attn_cut(sa, Hq, Hkv, layers);
+    return (form.splits == 1 && form.tree_split == 0) ||
+           (form.splits == cut.splits && form.tree_split == cut.tree_split && workspace_bytes >= tree_attn_workspace_bytes(sa, Hq, Hkv, d, layers));
+}
+
+hipError_t launch_tree_attn_mfma(AttnArgs a, const SeqArgs& sa, const AttnForm* given, void* workspace, size_t workspace_bytes, hipStream_t stream)
 {
     const int tiles = row_tiles(sa, a.Hq / a.Hkv, a.tile_off);
     if (tiles == 0) return hipSuccess;
-    const AttnCut cut = tree_attn_cut(sa, a.Hq, a.Hkv, a.layers);
-    a.splits = cut.splits; a.tree_split = cut.tree_split;
-    const size_t need = tree_attn_workspace_bytes(sa, a.Hq, a.Hkv, a.d, a.layers);
-    if (a.splits > 1 && (workspace == nullptr || workspace_bytes < need || (reinterpret_cast<size_t>(workspace) & 15)))
-        a.splits = 1, a.tree_split = 0;                        // no room for partial results: one workgroup walks it all
-    const ShortPlan plan = tree_attn_short_plan(sa, a.Hq, a.Hkv, a.d, a.layers, a.splits, a.splits > 1 ? need : 0);
-    const bool parts = plan.waves ? plan.splits > 1 : a.splits > 1;
-    if (parts) {
+    const AttnForm form = given ? *given : tree_attn_form(sa, a.Hq, a.Hkv, a.d, a.layers, workspace ? workspace_bytes : 0);
+    a.splits = form.splits; a.tree_split = form.tree_split;
+    if (a.splits > 1) {
         a.counters = static_cast<unsigned*>(workspace);
         a.part = reinterpret_cast<uint32_t*>(static_cast<char*>(workspace) + kAttnCounterBytes);
     }
-    if (plan.waves) {
-        a.splits = plan.splits;
-        return launch_tree_attn_short(a, sa, plan.waves, stream);
-    }
+    if (form.waves) return launch_tree_attn_short(a, sa, form.waves, stream);
     return a.d == 128 ? launch_one<128>(a, sa, tiles, stream) : launch_one<64>(a, sa, tiles, stream);
 }
 

@@ -18,7 +18,6 @@
 // two sequences of 37 and 5 rows, 100 and 33 keys 9.3 -> 5.7.
 // Without effect: V's fragments read ahead of the softmax, the first product as two chains, K's loads behind the first product.
 #include <atomic>
-#include <cstdlib>
 
 #include "attn_mfma.h"
 
@@ -556,14 +555,31 @@ static CallTime call_time(const CallCost& c, const SeqArgs& sa, int G, int Hkv, 
     return t;
 }
 
+static long long row_blocks(const SeqArgs& sa, int G)
+{
+    long long blocks = 0;
+    for (int s = 0; s < sa.n_seq; ++s) blocks += ((long long)G * (sa.node_off[s + 1] - sa.node_off[s]) + kShortRows - 1) / kShortRows;
+    return blocks;
+}
+
+// The forms there are; parts only as many as are resident at once and as the workspace has room for.
+bool tree_attn_short_has(const SeqArgs& sa, int Hq, int Hkv, int d, int layers, size_t workspace_bytes, int waves, int splits)
+{
+    const int G = Hq / Hkv;
+    const long long blocks = row_blocks(sa, G), groups = blocks * Hkv * layers;
+    // (grid limits; rows divided by G through a product with 32-bit factors)
+    if (blocks == 0 || blocks > 65535 || (long long)layers * kShortSplits > 65535 || G > 1024) return false;
+    if (waves != 8 && waves != 4 && !(waves == 2 && d == 128)) return false;
+    if (splits == 1) return true;
+    const size_t part = (size_t)(kShortRows * (d / 4 + 1)) * sizeof(unsigned long long);
+    return waves == 8 && splits > 1 && splits <= kShortSplits && groups * splits <= 256 && kAttnCounterBytes + (size_t)groups * splits * part <= workspace_bytes;
+}
+
 ShortPlan tree_attn_short_plan(const SeqArgs& sa, int Hq, int Hkv, int d, int layers, int long_splits, size_t workspace_bytes)
 {
     const int G = Hq / Hkv;
-    long long blocks = 0;
-    for (int s = 0; s < sa.n_seq; ++s) blocks += ((long long)G * (sa.node_off[s + 1] - sa.node_off[s]) + kShortRows - 1) / kShortRows;
     ShortPlan best = { 0, 1 };
-    // (grid limits; rows divided by G through a product with 32-bit factors)
-    if (blocks == 0 || blocks > 65535 || (long long)layers * kShortSplits > 65535 || G > 1024) return best;
+    if (!tree_attn_short_has(sa, Hq, Hkv, d, layers, 0, 8, 1)) return best;
     // Where the long kernel has no parts to merge either, the choice is the same whatever the number of layers (one layer's
     // result does not depend on the others): this kernel has to be better for a call by itself and with the chip full.
     const bool any_layers = long_splits == 1;
@@ -581,10 +597,8 @@ ShortPlan tree_attn_short_plan(const SeqArgs& sa, int Hq, int Hkv, int d, int la
     if (d == 128) consider(costs.short2, 2, 1);
     consider(costs.short4, 4, 1);
     consider(costs.short8, 8, 1);
-    const long long groups = blocks * Hkv * layers;
-    const size_t part = (size_t)(kShortRows * (d / 4 + 1)) * sizeof(unsigned long long);
-    for (int splits = 2; !any_layers && splits <= kShortSplits && groups * splits <= 256; ++splits)
-        if (kAttnCounterBytes + (size_t)groups * splits * part <= workspace_bytes) consider(costs.short8, 8, splits);
+    for (int splits = 2; !any_layers && tree_attn_short_has(sa, Hq, Hkv, d, layers, workspace_bytes, 8, splits); ++splits)
+        consider(costs.short8, 8, splits);
     return best;
 }
 

@@ -150,3 +150,28 @@ def oracle_attention_rows(q, kp, vp, kt, vt, mask_u64, batch, seq, scale, rows_j
     words = (b - a + 63) // 64
     return oracle.tree_attn_rows(q[a:b], kp[k0:k0 + P], vp[k0:k0 + P], kt[a:b], vt[a:b],
                                  np.ascontiguousarray(mask_u64[a:b, :words]), scale, rows_j, rows_h)
+
+
+def attn_in_form(dy, form, q, kp, vp, kt, vt, mask, batch, scale):
+    """dyspec_tree_attn launched as `form` (see binding.tree_attn_form) whatever the sizes would choose, with a workspace of its own
+    whose counters are zero before and must be zero after."""
+    import ctypes
+
+    import torch
+
+    from paper_2410_11744_amd import binding
+    lib = dy.load_library()
+    total, Hq, d = q.shape
+    Hkv = int(kt.shape[1])
+    cb, f = batch._c(), (ctypes.c_int32 * 3)(*form)
+    need = int(lib.dyspec_workspace_bytes(binding.WS_TREE_ATTN, ctypes.byref(cb), 0, Hq, Hkv, d))
+    ws = torch.zeros((max(need, 8 << 20) + 3) // 4, dtype=torch.float32, device=q.device)
+    out = torch.full_like(q, float("nan"))
+    p = lambda t: ctypes.c_void_p(t.data_ptr())
+    st = lib.dyspec_tree_attn_in_form(f, p(q), p(kp), p(vp), p(kt), p(vt), p(mask), ctypes.byref(cb), Hq, Hkv, d, binding.BF16,
+                                      ctypes.c_float(scale), p(out), p(ws), ctypes.c_size_t(ws.numel() * 4),
+                                      ctypes.c_void_p(torch.cuda.current_stream().cuda_stream))
+    binding._check(st, "dyspec_tree_attn_in_form")
+    torch.cuda.synchronize()
+    assert int(ws[:1024].view(torch.int32).abs().max().item()) == 0
+    return out

@@ -5,7 +5,7 @@ import numpy as np
 import pytest
 
 import oracle
-from helpers import ATTN_TOL, oracle_attention_rows
+from helpers import ATTN_TOL, attn_in_form, oracle_attention_rows
 
 pytestmark = pytest.mark.gpu
 
@@ -106,12 +106,12 @@ def test_bf16_matrix_core_kernel(dy, nodes, prefix, Hq, Hkv, d, seed):
 
 
 def test_bf16_long_prefix_wide_tree(dy):
-    # nine whole prefix tiles and a ragged one, a tree of sixteen key tiles
+    # eighteen whole prefix blocks and a ragged one, a tree of thirty-two blocks
     run_and_compare(dy, (1024,), (64 * 9 + 5,), 8, 1, 128, "bf16", 12)
 
 
 def test_bf16_shallow_tree_leaves_tiles_out(dy):
-    # ancestors all sit in the first key tile: most tree tiles hold no visible key for a row tile
+    # ancestors all sit in the first key block: most tree blocks hold no visible key for a row block
     run_and_compare(dy, (1024, 300), (512, 700), 8, 2, 128, "bf16", 13, shallow=True)
 
 
@@ -121,12 +121,14 @@ def test_bf16_rising_scores_raise_the_reference(dy):
     run_and_compare(dy, (200,), (640,), 4, 4, 64, "bf16", 15, qscale=4.0, ramp=2.0)
 
 
+# These sizes take the kernel for short walks, in parts; the workspace is sized for the other kernel's `parts` of its
+# `groups` row tiles (that kernel's own split walks: test_gpu_attn_long.py).
 @pytest.mark.parametrize("nodes,prefix,Hq,Hkv,groups,parts", [
-    ((32,), (4096,), 64, 8, 16, 8),               # 70B shape, narrow tree: 16 workgroups become 128
-    ((128,), (1024 + 37,), 8, 8, 8, 4),           # ragged last prefix tile; the last split holds the tree alone already
-    ((40, 9), (64 * 22, 64 * 17 + 1), 4, 2, 4, 4),   # shares of uneven size, ragged batch
-    ((128,), (1024,), 32, 32, 32, 5),             # 7B shape: four prefix splits and one for the two tree tiles
-    ((128, 64), (1024, 640), 8, 8, 16, 3),        # ragged batch with a split for the trees: two, one tree tiles
+    ((32,), (4096,), 64, 8, 16, 8),               # 70B shape, narrow tree: 4 parts
+    ((128,), (1024 + 37,), 8, 8, 8, 4),           # ragged last prefix block; 4 parts
+    ((40, 9), (64 * 22, 64 * 17 + 1), 4, 2, 4, 4),   # shares of uneven size, ragged batch; 8 parts
+    ((128,), (1024,), 32, 32, 32, 5),             # 7B shape: 2 parts
+    ((128, 64), (1024, 640), 8, 8, 16, 3),        # ragged batch; 4 parts
 ])
 def test_bf16_prefix_split_matches_unsplit_and_oracle(dy, nodes, prefix, Hq, Hkv, groups, parts):
     batch = dy.Batch.from_sizes(nodes, prefix)
@@ -136,18 +138,22 @@ def test_bf16_prefix_split_matches_unsplit_and_oracle(dy, nodes, prefix, Hq, Hkv
     args = [t.cuda() for t in (q, kp, vp, kt, vt)]
     need = dy.load_library().dyspec_workspace_bytes(1, __import__("ctypes").byref(batch._c()), 0, Hq, Hkv, 128)
     # arrival counters, then per (row tile, KV head) and part 4 x 64 lanes x (32 + 2) words
-    assert need == 4096 + groups * parts * 4 * 64 * 34 * 4, "the cut this case is meant to exercise"
+    assert need == 4096 + groups * parts * 4 * 64 * 34 * 4
+    from paper_2410_11744_amd import binding
+    form = binding.tree_attn_form(batch, Hq, Hkv, 128)
+    assert form[0] == 8 and form[1] > 1
     split = dy.tree_attn(*args, mask_dev, batch, scale)
-    whole = dy.tree_attn(*args, mask_dev, batch, scale, use_workspace=False)
+    whole = attn_in_form(dy, (8, 1, 0), *args, mask_dev, batch, scale)
+    other = dy.tree_attn(*args, mask_dev, batch, scale, use_workspace=False)
     torch.cuda.synchronize()
     # same products; every split's share of a row is rounded to bf16 before the merge
     assert float((split.float() - whole.float()).abs().max()) <= 2.0 ** -6
+    assert float((split.float() - other.float()).abs().max()) <= 2.0 ** -6
     # the merge sums the parts in split order whoever performs it: the same bits on every launch
     for _ in range(3):
         again = dy.tree_attn(*args, mask_dev, batch, scale)
         assert torch.equal(again.view(torch.int16), split.view(torch.int16))
     # and the arrival counters at the head of the workspace are zero again for the next call
-    from paper_2410_11744_amd import binding
     torch.cuda.synchronize()
     ws = binding._scratch_cache[str(args[0].device)]
     assert int(ws[:1024].view(torch.int32).abs().max().item()) == 0
@@ -155,31 +161,33 @@ def test_bf16_prefix_split_matches_unsplit_and_oracle(dy, nodes, prefix, Hq, Hkv
 
 
 def test_bf16_prefix_split_head_dim_64(dy):
-    """The split walk and its merged, staged rows at head_dim 64 (half rows of 64 bytes), with a ragged
-    last row tile and a tree that gets a split of its own."""
-    import ctypes
+    """The split walk and its merged rows at head_dim 64, with a ragged last row block."""
+    from paper_2410_11744_amd import binding
     for nodes, prefix, Hq, Hkv, seed in (((70,), (2048 + 5,), 8, 8, 31), ((128, 33), (1024, 700), 4, 4, 32)):
         batch = dy.Batch.from_sizes(nodes, prefix)
-        assert dy.load_library().dyspec_workspace_bytes(1, ctypes.byref(batch._c()), 0, Hq, Hkv, 64) > 0, "meant to be split"
+        form = binding.tree_attn_form(batch, Hq, Hkv, 64)
+        assert form[0] == 8 and form[1] > 1
         run_and_compare(dy, nodes, prefix, Hq, Hkv, 64, "bf16", seed)
         q, kp, vp, kt, vt, mask = make_case(nodes, prefix, Hq, Hkv, 64, "bf16", seed)
         args = [t.cuda() for t in (q, kp, vp, kt, vt)]
         mask_dev = torch.from_numpy(mask.view(np.int64)).cuda()
         split = dy.tree_attn(*args, mask_dev, batch, 0.125)
-        whole = dy.tree_attn(*args, mask_dev, batch, 0.125, use_workspace=False)
+        whole = attn_in_form(dy, (8, 1, 0), *args, mask_dev, batch, 0.125)
+        other = dy.tree_attn(*args, mask_dev, batch, 0.125, use_workspace=False)
         torch.cuda.synchronize()
         assert float((split.float() - whole.float()).abs().max()) <= 2.0 ** -6
+        assert float((split.float() - other.float()).abs().max()) <= 2.0 ** -6
 
 
 def test_split_needs_zeroed_counters_only_once(dy):
-    """A caller's own workspace: cleared once after allocation, then used for calls of different shapes
-    and split counts in a row, never cleared again; results equal to the unsplit call's within the
+    """A caller's own workspace: cleared once after allocation, then used for calls of different shapes,
+    split counts and both kernels in a row, never cleared again; results equal to the unsplit call's within the
     bf16 rounding of the parts."""
     import ctypes
     lib = dy.load_library()
     ws = torch.zeros(3 << 20, dtype=torch.float32, device="cuda")            # 12 MB, zero-filled once
     for k, (nodes, prefix, Hq, Hkv) in enumerate([((32,), (4096,), 64, 8), ((128,), (1024,), 8, 8), ((40, 9), (64 * 22, 64 * 17 + 1), 4, 2),
-                                                  ((32,), (4096,), 64, 8)]):
+                                                  ((256,), (2048,), 40, 40), ((32,), (4096,), 64, 8), ((99,), (1038,), 40, 40)]):
         batch = dy.Batch.from_sizes(nodes, prefix)
         q, kp, vp, kt, vt, mask = make_case(nodes, prefix, Hq, Hkv, 128, "bf16", 40 + k)
         args = [t.cuda() for t in (q, kp, vp, kt, vt)]
@@ -199,7 +207,7 @@ def test_split_needs_zeroed_counters_only_once(dy):
 
 
 def test_bf16_tree_only_large_trees(dy):
-    # no prefix and a short one ahead of sixteen tree tiles: the tile set is agreed on before the first loads
+    # no prefix and a short one ahead of large trees
     run_and_compare(dy, (1024,), (0,), 8, 1, 128, "bf16", 16)
     run_and_compare(dy, (1024, 640), (0, 100), 4, 4, 128, "bf16", 17, shallow=True)
     run_and_compare(dy, (900,), (130,), 8, 8, 64, "bf16", 18, shallow=True)

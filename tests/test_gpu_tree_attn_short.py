@@ -21,30 +21,32 @@ def dy():
     return m
 
 
-# the comments name the form these sizes are meant to take: waves, and parts of the prefix where it is split
-@pytest.mark.parametrize("nodes,prefix,Hq,Hkv,d,shallow", [
-    ((1,), (65,), 8, 8, 128, False),                    # 8: one row, a block of one key, waves without any
-    ((1, 1, 3), (0, 1, 64), 4, 4, 128, False),          # 8: a sequence without prefix, one whose blocks are of a key each
-    ((33,), (31,), 32, 32, 128, False),                 # 4: a second block of one row and one key, prefix short of a block
-    ((95,), (33,), 32, 32, 128, False),                 # 4
-    ((768,), (129,), 8, 1, 128, False),                 # 4: four nodes to a row block
-    ((700,), (100,), 32, 32, 128, True),                # 2: tree blocks left out, prefix blocks before them
-    ((1100,), (0,), 32, 32, 128, False),                # 2: tree only
-    ((2048,), (0,), 8, 8, 128, False),                  # 2: all 64 tree blocks
-    ((70,), (1500,), 32, 32, 128, False),               # 8 in 2 parts
-    ((33,), (4095,), 64, 8, 128, False),                # 8 in 3 parts: shares of unequal size
-    ((9,), (700,), 6, 2, 128, False),                   # 8 in 7 parts, three heads to a row block's nodes
-    ((7, 1, 90), (2100, 800, 1500), 10, 2, 128, False),  # split, sequences of unequal length, five heads to a KV head
-    ((3, 50, 17), (300, 31, 0), 10, 2, 128, False),
-    ((5,), (40,), 8, 8, 64, False),
-    ((31, 5), (129, 1), 40, 40, 64, False),             # 4
-    ((65,), (300,), 8, 8, 64, False),
-    ((600,), (0,), 9, 3, 64, True),
-    ((2048,), (0,), 64, 64, 64, False),
-    ((64,), (2000,), 32, 32, 64, False),                # 8 in 4 parts
-    ((7,), (2100,), 10, 2, 64, False),
+# (waves, parts): the form that these sizes are there for, and take
+@pytest.mark.parametrize("waves,parts,nodes,prefix,Hq,Hkv,d,shallow", [
+    (8, 1, (1,), (65,), 8, 8, 128, False),              # one row, a block of one key, waves without any
+    (8, 1, (1, 1, 3), (0, 1, 64), 4, 4, 128, False),    # a sequence without prefix, one whose blocks are of a key each
+    (4, 1, (33,), (31,), 32, 32, 128, False),           # a second block of one row and one key, prefix short of a block
+    (4, 1, (95,), (33,), 32, 32, 128, False),
+    (4, 1, (768,), (129,), 8, 1, 128, False),           # four nodes to a row block
+    (2, 1, (700,), (100,), 32, 32, 128, True),          # tree blocks left out, prefix blocks before them
+    (2, 1, (1100,), (0,), 32, 32, 128, False),          # tree only
+    (2, 1, (2048,), (0,), 8, 8, 128, False),            # all 64 tree blocks
+    (8, 2, (70,), (1500,), 32, 32, 128, False),
+    (8, 3, (33,), (4095,), 64, 8, 128, False),          # shares of unequal size
+    (8, 7, (9,), (700,), 6, 2, 128, False),             # three heads to a row block's nodes
+    (8, 4, (7, 1, 90), (2100, 800, 1500), 10, 2, 128, False),    # sequences of unequal length, five heads to a KV head
+    (4, 1, (3, 50, 17), (300, 31, 0), 10, 2, 128, False),
+    (8, 1, (5,), (40,), 8, 8, 64, False),
+    (4, 1, (31, 5), (129, 1), 40, 40, 64, False),
+    (8, 1, (65,), (300,), 8, 8, 64, False),
+    (4, 1, (600,), (0,), 9, 3, 64, True),
+    (4, 1, (2048,), (0,), 64, 64, 64, False),
+    (8, 4, (64,), (2000,), 32, 32, 64, False),
+    (8, 8, (7,), (2100,), 10, 2, 64, False),
 ])
-def test_short_walks_match_the_oracle(dy, nodes, prefix, Hq, Hkv, d, shallow):
+def test_short_walks_match_the_oracle(dy, waves, parts, nodes, prefix, Hq, Hkv, d, shallow):
+    from paper_2410_11744_amd import binding
+    assert binding.tree_attn_form(dy.Batch.from_sizes(nodes, prefix), Hq, Hkv, d) == (waves, parts, 0)
     run_and_compare(dy, nodes, prefix, Hq, Hkv, d, "bf16", 70, shallow=shallow, max_rows=2500)
 
 

@@ -77,8 +77,9 @@ def one_case(dy, nodes, prefix, Hq, Hkv, d, seed):
 
 def test_static_scratch_matches_workspace_call_twice_in_a_row(dy):
     print("static scratch: 70B-shaped narrow tree, then a smaller ragged batch", flush=True)
-    one_case(dy, (32,), (4096,), 64, 8, 128, 1)            # 8-way split
-    one_case(dy, (20, 7), (2100, 1500), 64, 8, 128, 2)     # smaller, ragged, fewer splits
+    one_case(dy, (32,), (4096,), 64, 8, 128, 1)            # four parts, by the kernel for short walks
+    one_case(dy, (20, 7), (2100, 1500), 64, 8, 128, 2)     # smaller, ragged
+    one_case(dy, (16, 117), (3810, 639), 40, 40, 64, 4)    # three parts, by the kernel for long walks
     one_case(dy, (32,), (4096,), 64, 8, 128, 3)            # and the larger one again
 
 
