@@ -532,10 +532,10 @@ constexpr CallCosts kCosts64 = { { 3.95f, 2.7f, 0.657f, 0.12f, 4.54f, 0.928f, 1.
                                  {} };                                 // (two waves: never the best at head_dim 64)
 constexpr float kClearlyLess = 0.9f;       // this kernel is taken where it is this much better: the model's error
 
-struct CallTime { float once, work; };     // of one call on an idle chip; its share of a full chip
+struct CallTime { float once, work, whole; };     // of one call on an idle chip; its share of a full chip; once, no workgroup shared by two CUs
 static CallTime call_time(const CallCost& c, const SeqArgs& sa, int G, int Hkv, int d, int layers, int splits, int rows_per_group, int keys_per_unit)
 {
-    float longest = 0.0f, work = 0.0f, keys = 0.0f;
+    float longest = 0.0f, work = 0.0f, keys = 0.0f, workgroups = 0.0f;
     for (int s = 0; s < sa.n_seq; ++s) {
         const int N = sa.node_off[s + 1] - sa.node_off[s];
         if (N == 0) continue;
@@ -546,12 +546,16 @@ static CallTime call_time(const CallCost& c, const SeqArgs& sa, int G, int Hkv, 
         longest = fmaxf(longest, units * (1.0f + c.alone / (float)groups));
         work += (float)groups * (float)splits * (c.work0 + c.work * units);
         keys += (float)sa.prefix_len[s];
+        workgroups += (float)groups;
     }
     work *= (float)Hkv * (float)layers / 256.0f;
+    workgroups *= (float)splits * (float)Hkv * (float)layers / 256.0f;        // a CU
     const float bytes = keys * (float)Hkv * (float)d * 4e-6f * (float)layers / c.bytes;
     CallTime t;
     t.work = fmaxf(work, bytes);
-    t.once = c.launch + fmaxf(c.walk0 + c.walk * longest, t.work) + (splits > 1 ? c.merge + c.merge_part * (float)splits : 0.0f);
+    const float walk = c.walk0 + c.walk * longest, rest = c.launch + (splits > 1 ? c.merge + c.merge_part * (float)splits : 0.0f);
+    t.once = rest + fmaxf(walk, t.work);
+    t.whole = rest + fmaxf(walk, fmaxf(work * ceilf(workgroups) / workgroups, bytes));
     return t;
 }
 
@@ -587,9 +591,13 @@ ShortPlan tree_attn_short_plan(const SeqArgs& sa, int Hq, int Hkv, int d, int la
     const CallCosts& costs = d == 128 ? kCosts128 : kCosts64;
     const CallTime other = call_time(costs.tall, sa, G, Hkv, d, L, long_splits, 128, 64);
     float least = kClearlyLess * other.once;
+    // Several layers of which the long kernel splits the prefix are about one workgroup a CU there; a few more of this kernel's
+    // than one a CU take as long as two.  2 KV heads of 6, 23 rows, 5271 keys, head_dim 64, 32 layers: 320 workgroups, 66 us for
+    // the other's 40.  (One layer is bound by its longest walk: there the whole workgroups say nothing.)
+    const bool whole_counts = !any_layers && layers > 1;
     auto consider = [&](const CallCost& c, int waves, int splits) {
         const CallTime t = call_time(c, sa, G, Hkv, d, L, splits, kShortRows, 32);
-        if (t.once < least && (!any_layers || t.work < kClearlyLess * other.work)) {
+        if (t.once < least && (!any_layers || t.work < kClearlyLess * other.work) && (!whole_counts || kClearlyLess * t.whole < other.whole)) {
             least = t.once;
             best = { waves, splits };
         }

@@ -58,6 +58,14 @@ def test_unsplit_calls_choose_alike_for_any_number_of_layers():
             assert binding.tree_attn_form(batch, Hq, Hkv, d, layers, use_workspace=False) == one
 
 
+# Measured: the kernel for long walks 40, 21 and 28 us, the one for short walks (8, 4 and 8 waves) 66, 34 and 41: a quarter
+# more workgroups than CUs, where the other kernel has at most one to a CU.
+@pytest.mark.parametrize("layers,nodes,prefix,Hq,Hkv,d", [(32, 23, 5271, 12, 2, 64), (8, 234, 2360, 5, 5, 64), (8, 45, 3349, 24, 8, 64)])
+def test_stacked_calls_count_whole_workgroups(layers, nodes, prefix, Hq, Hkv, d):
+    waves, parts, _ = binding.tree_attn_form(binding.Batch.from_sizes([nodes], [prefix]), Hq, Hkv, d, layers)
+    assert waves == 0 and parts > 1
+
+
 def test_more_heads_to_a_kv_head_than_the_short_kernel_divides_by():
     batch = binding.Batch.from_sizes([3], [40])
     assert binding.tree_attn_form(batch, 1024, 1, 64)[0] != 0
