@@ -604,7 +604,15 @@ ShortPlan tree_attn_short_plan(const SeqArgs& sa, int Hq, int Hkv, int d, int la
     };
     if (d == 128) consider(costs.short2, 2, 1);
     consider(costs.short4, 4, 1);
-    consider(costs.short8, 8, 1);
+    // At head_dim 64 a walk of at most four blocks of keys has no use for eight waves: half of them bring no keys and still join in the
+    // merge (25 rows alone, 64/8 heads: 80 layers 36 us, 18 with four waves, 27 with the other kernel; one layer 5.0 and 4.6).  At head_dim
+    // 128 eight are better by 1 - 2 % in one layer, as each finishes fewer rows.
+    int most_blocks = 0;
+    for (int s = 0; s < sa.n_seq; ++s) {
+        const int N = sa.node_off[s + 1] - sa.node_off[s];
+        if (N > 0) most_blocks = max(most_blocks, (sa.prefix_len[s] + 31) / 32 + (N + 31) / 32);
+    }
+    if (d == 128 || most_blocks > 4) consider(costs.short8, 8, 1);
     for (int splits = 2; !any_layers && tree_attn_short_has(sa, Hq, Hkv, d, layers, workspace_bytes, 8, splits); ++splits)
         consider(costs.short8, 8, splits);
     return best;

@@ -66,6 +66,13 @@ def test_stacked_calls_count_whole_workgroups(layers, nodes, prefix, Hq, Hkv, d)
     assert waves == 0 and parts > 1
 
 
+@pytest.mark.parametrize("layers", [1, 80])
+@pytest.mark.parametrize("nodes,prefix,Hq,Hkv", [((25,), (0,), 64, 8), ((14,), (24,), 64, 8), ((19,), (54,), 16, 1), ((40, 64), (33, 64), 8, 8)])
+def test_walks_of_four_blocks_of_keys_take_no_eight_waves(nodes, prefix, Hq, Hkv, layers):
+    form = binding.tree_attn_form(binding.Batch.from_sizes(nodes, prefix), Hq, Hkv, 64, layers)
+    assert form == (4, 1, 0)
+
+
 def test_more_heads_to_a_kv_head_than_the_short_kernel_divides_by():
     batch = binding.Batch.from_sizes([3], [40])
     assert binding.tree_attn_form(batch, 1024, 1, 64)[0] != 0
