@@ -37,7 +37,7 @@ def dy():
     (8, 4, (7, 1, 90), (2100, 800, 1500), 10, 2, 128, False),    # sequences of unequal length, five heads to a KV head
     (4, 1, (3, 50, 17), (300, 31, 0), 10, 2, 128, False),
     (4, 1, (5,), (40,), 8, 8, 64, False),
-    (8, 1, (5,), (97,), 8, 8, 64, False),               # five blocks: three waves without keys
+    (8, 1, (5,), (257,), 8, 8, 64, False),              # ten blocks, the last of the prefix a key
     (4, 1, (31, 5), (129, 1), 40, 40, 64, False),
     (8, 1, (65,), (300,), 8, 8, 64, False),
     (4, 1, (600,), (0,), 9, 3, 64, True),
