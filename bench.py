@@ -388,7 +388,12 @@ def main() -> int:
     hbm_gbs = bytes_step / (ms_per_step * 1e-3) / 1e9
     # which roof bounds the kernel at this shape: flops per algorithmic byte against the ridge
     ridge = PEAK_BF16_TFLOPS * 1e12 / (PEAK_HBM_GBS * 1e9)
-    kernel = "tree_attn_mfma_kernel<%d, 1>" % cfg.head_dim if cfg.dtype == "bf16" else "tree_attn_simple_kernel<float, %d>" % ((cfg.head_dim // 4 + 15) // 16)
+    if cfg.dtype == "bf16":        # the kernel these calls are launched as (the rule: csrc/tree_attn_short.hip)
+        from paper_2410_11744_amd import binding
+        waves = binding.tree_attn_form(batch, cfg.n_q_heads, cfg.n_kv_heads, cfg.head_dim, layers=cfg.layers if args.batched_layers else 1)[0]
+        kernel = "tree_attn_short_kernel<%d, %d>" % (cfg.head_dim, waves) if waves else "tree_attn_mfma_kernel<%d, 1>" % cfg.head_dim
+    else:
+        kernel = "tree_attn_simple_kernel<float, %d>" % ((cfg.head_dim // 4 + 15) // 16)
     if cfg.dtype == "bf16" and flops_per_launch / bytes_attn_launch >= ridge:
         roofline = {"kernel": kernel, "bound": "mfma", "achieved": round(achieved_tflops, 2), "peak": PEAK_BF16_TFLOPS,
                     "unit": "TFLOP/s", "frac": round(achieved_tflops / PEAK_BF16_TFLOPS, 4)}
@@ -396,8 +401,6 @@ def main() -> int:
             roofline["frac_of_measured_ceiling"] = round(achieved_tflops / ceilings["mfma_bf16_tflops"], 4)
     else:
         gbs = bytes_attn_launch / (launch_ms * 1e-3) / 1e9
-        if cfg.dtype == "bf16":        # short walks take the other kernel (the rule: csrc/tree_attn_short.hip)
-            kernel += " / tree_attn_short_kernel<%d, ..>" % cfg.head_dim
         roofline = {"kernel": kernel, "bound": "hbm", "achieved": round(gbs, 1), "peak": PEAK_HBM_GBS,
                     "unit": "GB/s", "frac": round(gbs / PEAK_HBM_GBS, 4)}
         if ceilings:
