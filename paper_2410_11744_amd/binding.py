@@ -189,7 +189,8 @@ class Tree:
 
     @staticmethod
     def empty(total_nodes: int, device) -> "Tree":
-        # one allocation, every array aligned as an allocation of its own would be (512 bytes)
+        """Room for total_nodes rows.  The six arrays lie in one allocation, each aligned as one of its own would be (512 bytes):
+        whoever holds one of them holds the memory of all."""
         import torch
         rows = torch.empty((6, -(-total_nodes // 128) * 128), dtype=torch.int32, device=device)
         return Tree(*rows[:, :total_nodes].unbind(0))

@@ -31,7 +31,7 @@ constexpr int kMaxSlots = 2 * DYSPEC_MAX_BUILD_NODES + 2;
 // Bound in turn by the trip to memory (every load is issued before the maximum is known) and by the vector ALU: some 28
 // instructions a token, 22 of them the fp64 exponential.  Segments past the end of the row cost nothing, and the sums of a run's lanes
 // are folded into one another (row_sums) instead of summed one by one, five steps each: 32 rows of 1000 tokens
-// 9.8 -> 3.8 us, 128 rows of 32000 14.6 -> 12.8, 512 rows 27.3 -> 25.9 (66 MB; nothing is left to overlap loads with: all
+// 9.8 -> 3.6 us, 128 rows of 32000 14.6 -> 12.4, 512 rows 27.3 -> 26.2 (66 MB; nothing is left to overlap loads with: all
 // rows are in flight at once).  S: 2 holds 4096 tokens, 8 16384; where the unused segments were skipped in the code for 16 their
 // registers and code stayed.
 template <bool VEC, int S>

@@ -943,8 +943,8 @@ static int row_tiles(const SeqArgs& sa, int G, int* tile_off)
 // when that leaves most of the 256 CUs idle (narrow trees, few KV heads) the prefix is split
 // until the workgroups fill the chip once, as long as every split keeps at least four 64-key
 // tiles of every sequence's prefix, and into at most eight parts (what the finishing workgroup
-// fetches in one trip to memory).  Measured per layer: 1024 keys over 32 workgroups run best in 4
-// parts, 2048 keys over 80 in 3, 4096 keys over 16 in 8.
+// fetches in one trip to memory).  Measured per layer: 2048 keys over 80 workgroups run best in 3 parts
+// (1024 keys over 32 in 4 and 4096 over 16 in 8, when such walks were this kernel's: tree_attn_short.hip).
 //
 // The split that also walks the tree ends last (a tree tile goes through the masked loop and
 // costs about two prefix tiles).  If one more workgroup per group still fits on the chip and

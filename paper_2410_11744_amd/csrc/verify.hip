@@ -381,7 +381,7 @@ __device__ __forceinline__ int draw_from_row(const RowVec<S> (&w)[4], double u, 
 // other (each behind the bounds check of its segment) and every wave summed D again: 2.0 us a rejection at 32000 tokens,
 // 1.4 now; a node's rows and first rejection 7.8 -> 6.4.  What bounds a rejection: some 290 instructions a wave between two
 // barriers, 128 of them the sweep.
-// S: 2, 8 or 16 by the size of the vocabulary, so that short rows don't pay for segments they have not (1000 tokens: walk 8.4 -> 4.5 us).
+// S: 2, 8 or 16 by the size of the vocabulary, so that short rows don't pay for segments they have not (1000 tokens: walk 8.6 -> 4.6 us).
 // The draft row's loads are issued first, so that its weights are made while the target row's are still out.
 // (R's sum shrinks with every rejection; below kSmallMass the weights are brought back to a sum of 1, as they are
 // where mass * scale_d would leave the range.)
