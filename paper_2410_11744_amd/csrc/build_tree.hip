@@ -309,7 +309,8 @@ __device__ __forceinline__ void publish(uint32_t place, double r, u64 key, float
 // in vector registers and are declared uniform again.
 
 // Wave 1: the root's draws, in order, up to kRing ahead of control.
-__device__ __attribute__((noinline)) void draw_for_root(uint32_t lds_, uint32_t row_at, double inv_temp, double m, int V_, int N_, uint64_t seed_, uint32_t seq)
+// (aligned: with the functions wherever the one before ends, all trees' times move by 1 - 2 % with any change to it)
+__device__ __attribute__((noinline, aligned(64))) void draw_for_root(uint32_t lds_, uint32_t row_at, double inv_temp, double m, int V_, int N_, uint64_t seed_, uint32_t seq)
 {
     const uint32_t lds = uniform(lds_);
     const int V = uniform(V_), N = uniform(N_);
@@ -551,7 +552,7 @@ __device__ __forceinline__ void draw_for_node(MadeDraw& d, uint32_t place, uint3
 
 // Draw wave `mine`: serves the requests of its nodes, the largest slot value first, until told to stop.
 template <bool VEC>
-__device__ __attribute__((noinline)) void draw_for_nodes(uint32_t lds_, int mine_, const float* draft_logits_, int V_,
+__device__ __attribute__((noinline, aligned(64))) void draw_for_nodes(uint32_t lds_, int mine_, const float* draft_logits_, int V_,
                                                          double inv_temp_, uint64_t seed_, double* ws_, int base_, int N_)
 {
     const uint32_t lds = uniform(lds_);
@@ -646,14 +647,14 @@ __device__ __attribute__((noinline)) void draw_for_nodes(uint32_t lds_, int mine
 // empty place: value -1).  A pop takes lane 0; the popped node's next slot goes where its value belongs, and the lanes before
 // that place move up by one; the new node's slot makes the lanes behind its place move down.  A slot that finds no place among
 // the 64 is left out: `unlisted` is the largest value left out so far, and while lane 0 is above it the list is as good as the
-// whole frontier.  Else the list is made again from the slots in LDS (`relist`), the first kRelisted of them: a few times
-// in trees of many equally good slots, never in 512 rows of 1000 or 32000 tokens of independent normal logits.
+// whole frontier.  Else the list is made again from the slots in LDS (`relist`): a few times in trees of many equally good
+// slots and in large ones of peaked tables, seldom in 512 rows of 1000 or 32000 tokens of independent normal logits of deviation 5.
 // (512 rows with two equal tokens each, where every sixteenth pop does: 482 us, 505 with the maximum found at each pop, 720 with a list
 // made by sixteen comparisons a lane for each of its entries.)
 // Against the best of each lane's nodes kept in the lane and the maximum over the lanes found at each pop, and the other
 // nodes of the popped one's lane looked over again: a pop whose draw is there 0.61 -> 0.51 us; with the draws' names
 // for 64 ranks at once (DrawNames) 512 rows of 32000 tokens 441 -> 417, 495 -> 471 and 570 -> 547 us on three tables.
-constexpr int kRelisted = 16;
+constexpr int kRelisted = 16;           // found one after the other
 constexpr int kDppWaveShl1 = 0x130;     // lane i: lane i + 1's
 constexpr int kDppWaveShr1 = 0x138;     // lane i: lane i - 1's
 template <int CTRL> __device__ __forceinline__ int dpp_or_own(int x) { return __builtin_amdgcn_update_dpp(x, x, CTRL, 0xf, 0xf, false); }
@@ -668,14 +669,79 @@ struct Slots {
 };
 constexpr int kSure = 1 << 16;
 
-// The list made again from the slots of nodes 0 .. n - 1: every lane's best of the nodes lane, lane + 64, ..; the best of
-// those is listed and its lane's next one looked up by sixteen lanes at once.
+// The list made again from the slots of nodes 0 .. n - 1, node q in lane q % 64: the slots whose value's high word is above a line that
+// is searched for, 32 to 64 of them where that can be had in few steps, each put where it belongs as a pop does.  Where the values
+// near that line are too many of a kind (their high words equal), the kRelisted best, found one after the other: every lane's best;
+// the best of those is listed and its lane's next one looked up by sixteen lanes at once.
+// A peaked table's tree needs it most: of its first 1000 rows hundreds of slots lie within a factor of two, and a list of sixteen
+// lasted sixteen pops at some 8 us a list.  960 rows of 32000 tokens, normal logits of deviation 10 at temperature 1: 812 us before there
+// was a list, 1029 with sixteen slots at a time, 838 now; deviation 7.5: 935, 945, 814.  (Where most values are equal the search
+// is for nothing: 1024 rows of two equal tokens 1095 -> 1118, 512 rows 482 -> 487.)
 __device__ __attribute__((noinline)) Slots relist(uint32_t nodes_, int n_)
 {
     const uint32_t nodes = uniform(nodes_);
     const int n = uniform(n_), lane = threadIdx.x & 63;
     constexpr int Q = DYSPEC_MAX_BUILD_NODES / kWave;
     static_assert(Q == 16, "a row of lanes looks at a lane's nodes");
+    {
+        int high[Q], most = 0;                      // of positive values; as integers they are in the values' order
+#pragma unroll
+        for (int k = 0; k < Q; ++k) {
+            const int q = lane + kWave * k;
+            high[k] = q < n ? *lds_at<int>(nodes + kNode * q + kValueAt + 4) : 0;
+            most = max(most, high[k]);
+        }
+        most = wave_max_dpp_int(most);
+        const auto above = [&](int line) __attribute__((always_inline)) {      // (line >= 0: no closed slot)
+            int c = 0;
+#pragma unroll
+            for (int k = 0; k < Q; ++k) c += __builtin_popcountll(ballot(high[k] > line));
+            return c;
+        };
+        // `line` has at most 64 slots above it, `low` more, or is 0
+        int line = most, listed = 0, step = 1 << 18, low = most, c = 0;
+        do {
+            low = max(low - step, 0);
+            step <<= 2;
+            c = above(low);
+            if (c <= kWave) { line = low; listed = c; }
+        } while (c < kWave / 2 && low > 0);
+        for (int t = 0; t < 4 && listed < kWave / 2 && line - low > 1; ++t) {
+            const int mid = low + (line - low) / 2;
+            c = above(mid);
+            if (c <= kWave) { line = mid; listed = c; } else low = mid;
+        }
+        if (listed >= kRelisted || (listed > 0 && line == 0)) {
+            Slots s = { -1.0, 0, -1.0 };
+            int opened = 0;
+            double left = -1.0;
+            for (int k = 0; kWave * k < n; ++k) {
+                const int q = lane + kWave * k;
+                double v = -1.0;
+                int o = 0;
+                if (q < n) {
+                    v = *lds_at<double>(nodes + kNode * q + kValueAt);
+                    o = (int)*lds_at<uint32_t>(nodes + kNode * q + kOpenedAt);
+                }
+                const bool take = __double2hiint(v) > line;
+                left = fmax(left, take ? -1.0 : v);
+                for (u64 m = ballot(take); m; m &= m - 1) {
+                    const int l = __builtin_ctzll(m);
+                    const double x = readlane_f64(v, l);
+                    const int xo = __builtin_amdgcn_readlane(o, l);
+                    const int at = __builtin_popcountll(ballot(s.value > x) | (ballot(s.value == x) & ballot(opened < xo)));
+                    const double down_v = dpp_or_own<kDppWaveShr1>(s.value);
+                    const int down_n = dpp_or_own<kDppWaveShr1>(s.node), down_o = dpp_or_own<kDppWaveShr1>(opened);
+                    s.value = lane > at ? down_v : lane == at ? x : s.value;
+                    s.node = lane > at ? down_n : lane == at ? (l + kWave * k) | kSure : s.node;
+                    opened = lane > at ? down_o : lane == at ? xo : opened;
+                }
+            }
+            left = wave_max_dpp(left);
+            s.unlisted = left > 0.0 ? left : -1.0;
+            return s;
+        }
+    }
     double best = -1.0;
     int at = 0, when = 0;
     for (int k = 0; kWave * k < n; ++k) {
@@ -723,7 +789,7 @@ __device__ __attribute__((noinline)) Slots relist(uint32_t nodes_, int n_)
     return s;
 }
 
-__device__ __attribute__((noinline)) int pop_nodes(uint32_t lds_, int root_ring_, int N_, int max_polls_, int* parent_, int* token_, float* est_value_)
+__device__ __attribute__((noinline, aligned(64))) int pop_nodes(uint32_t lds_, int root_ring_, int N_, int max_polls_, int* parent_, int* token_, float* est_value_)
 {
     const uint32_t lds = uniform(lds_), nodes = lds + BuildLds::nodes;
     const bool root_ring = uniform(root_ring_) != 0;

@@ -21,6 +21,10 @@ def test_more_equal_slots_than_the_list_holds(nodes, V, live):
     x = np.full((sum(nodes), V), -np.inf, np.float32)
     for row in x:
         row[rng.choice(V, live, replace=False)] = 0.25
+    check_against_no_workspace(dy, x, nodes)
+
+
+def check_against_no_workspace(dy, x, nodes):
     batch = dy.Batch.from_sizes(nodes)
     dd = torch.from_numpy(x).cuda()
     a = dy.build_tree(dd, batch, 1.0, 5)
@@ -30,3 +34,22 @@ def test_more_equal_slots_than_the_list_holds(nodes, V, live):
     for name in ("parent", "token", "sib_rank", "first_child", "next_sibling", "depth"):
         assert torch.equal(getattr(a.tree, name), getattr(b.tree, name)), name
     assert torch.equal(a.anc_mask, b.anc_mask) and torch.equal(a.est_value, b.est_value)
+
+
+# Many different slots of like size: the list is made again from those above a line.  With equal tokens, some rows of few and
+# some of many, the line meets groups of equal values, of fewer than it can list and of more.
+@pytest.mark.parametrize("V,live", [(1000, None), (4099, None), (1000, (2, 3, 5, 16, 40)), (300, (1, 2, 7)), (64, (2, 2, 2, 3, 64))])
+@pytest.mark.parametrize("nodes", [(330, 400, 65), (960,), (1024, 1023)])
+def test_more_slots_of_like_size_than_the_list_holds(nodes, V, live):
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2410_11744_amd as dy
+    print(f"nodes={nodes} V={V} live={live}", flush=True)
+    rng = np.random.default_rng(V + nodes[0])
+    if live is None:
+        x = (10.0 * rng.standard_normal((sum(nodes), V))).astype(np.float32)
+    else:
+        x = np.full((sum(nodes), V), -np.inf, np.float32)
+        for row in x:
+            row[rng.choice(V, rng.choice(live), replace=False)] = 0.25
+    check_against_no_workspace(dy, x, nodes)
