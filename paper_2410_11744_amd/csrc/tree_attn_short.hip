@@ -615,6 +615,13 @@ ShortPlan tree_attn_short_plan(const SeqArgs& sa, int Hq, int Hkv, int d, int la
     if (d == 128 || most_blocks > 4) consider(costs.short8, 8, 1);
     for (int splits = 2; !any_layers && tree_attn_short_has(sa, Hq, Hkv, d, layers, workspace_bytes, 8, splits); ++splits)
         consider(costs.short8, 8, splits);
+    // Two waves are for many row blocks of short walks.  Where one long walk is twice the chip's share, that walk is what is waited for
+    // and four waves take 0.61 of the time (one layer; 0.76 two or four layers, 1.03 more): trees of 10, 1005, 32 .. 5 rows, the third
+    // behind 6883 keys, one KV head of 8: 73 us by the other kernel, 91 with two waves, 47 with four.
+    if (best.waves == 2) {
+        const CallTime t = call_time(costs.short2, sa, G, Hkv, d, L, 1, kShortRows, 32);
+        if (t.once > 2.0f * (costs.short2.launch + t.work)) best.waves = 4;
+    }
     return best;
 }
 

@@ -73,6 +73,13 @@ def test_walks_of_four_blocks_of_keys_take_no_eight_waves(nodes, prefix, Hq, Hkv
     assert form == (4, 1, 0)
 
 
+# Measured: the kernel for long walks 73 and 70 us, two waves 91 and 88, four 47 and 45.
+@pytest.mark.parametrize("layers,nodes,prefix,Hq,Hkv", [(1, (10, 1005, 32, 55, 29, 184, 153, 5), (437, 22, 6883, 178, 68, 63, 48, 34), 8, 1),
+                                                        (2, (7, 314), (6731, 32), 16, 1)])
+def test_one_long_walk_among_many_short_ones_takes_four_waves(layers, nodes, prefix, Hq, Hkv):
+    assert binding.tree_attn_form(binding.Batch.from_sizes(nodes, prefix), Hq, Hkv, 128, layers) == (4, 1, 0)
+
+
 def test_more_heads_to_a_kv_head_than_the_short_kernel_divides_by():
     batch = binding.Batch.from_sizes([3], [40])
     assert binding.tree_attn_form(batch, 1024, 1, 64)[0] != 0
