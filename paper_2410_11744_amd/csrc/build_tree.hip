@@ -307,11 +307,14 @@ __device__ __forceinline__ void publish(uint32_t place, double r, u64 key, float
 
 // The roles are functions of their own, so that each has the scalar registers to itself; their arguments arrive
 // in vector registers and are declared uniform again.
+// Where in a 64-byte line of instructions their loops lie moves all times by 1 - 2 %, so each begins at a line and so many
+// instructions behind: against none, 512 rows of 32000 tokens 608 -> 603, 462 -> 455 and (flat rows) 389 -> 382 us, a chain 1121 -> 1110.
+template <int N> __device__ __forceinline__ void begin_behind() { asm volatile(".rept %0\n\ts_nop 0\n\t.endr" :: "n"(N)); }
 
 // Wave 1: the root's draws, in order, up to kRing ahead of control.
-// (aligned: with the functions wherever the one before ends, all trees' times move by 1 - 2 % with any change to it)
 __device__ __attribute__((noinline, aligned(64))) void draw_for_root(uint32_t lds_, uint32_t row_at, double inv_temp, double m, int V_, int N_, uint64_t seed_, uint32_t seq)
 {
+    begin_behind<15>();
     const uint32_t lds = uniform(lds_);
     const int V = uniform(V_), N = uniform(N_);
     const u64 seed = uniform((u64)seed_);
@@ -555,6 +558,7 @@ template <bool VEC>
 __device__ __attribute__((noinline, aligned(64))) void draw_for_nodes(uint32_t lds_, int mine_, const float* draft_logits_, int V_,
                                                          double inv_temp_, uint64_t seed_, double* ws_, int base_, int N_)
 {
+    begin_behind<15>();
     const uint32_t lds = uniform(lds_);
     const int mine = uniform(mine_), V = uniform(V_), base = uniform(base_), N = uniform(N_);
     const float* __restrict__ const draft_logits = uniform(draft_logits_);
@@ -675,8 +679,8 @@ constexpr int kSure = 1 << 16;
 // the best of those is listed and its lane's next one looked up by sixteen lanes at once.
 // A peaked table's tree needs it most: of its first 1000 rows hundreds of slots lie within a factor of two, and a list of sixteen
 // lasted sixteen pops at some 8 us a list.  960 rows of 32000 tokens, normal logits of deviation 10 at temperature 1: 812 us before there
-// was a list, 1029 with sixteen slots at a time, 838 now; deviation 7.5: 935, 945, 814.  (Where most values are equal the search
-// is for nothing: 1024 rows of two equal tokens 1095 -> 1118, 512 rows 482 -> 487.)
+// was a list, 1029 with sixteen slots at a time, 827 now; deviation 7.5: 935, 947, 806.  (Where most values are equal the search
+// is for nothing: 1024 rows of two equal tokens 1098 -> 1105.)
 __device__ __attribute__((noinline)) Slots relist(uint32_t nodes_, int n_)
 {
     const uint32_t nodes = uniform(nodes_);
@@ -791,6 +795,7 @@ __device__ __attribute__((noinline)) Slots relist(uint32_t nodes_, int n_)
 
 __device__ __attribute__((noinline, aligned(64))) int pop_nodes(uint32_t lds_, int root_ring_, int N_, int max_polls_, int* parent_, int* token_, float* est_value_)
 {
+    begin_behind<5>();
     const uint32_t lds = uniform(lds_), nodes = lds + BuildLds::nodes;
     const bool root_ring = uniform(root_ring_) != 0;
     const int N = uniform(N_);
