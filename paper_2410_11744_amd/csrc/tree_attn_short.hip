@@ -510,10 +510,12 @@ static hipError_t launch_short(const ShortArgs& s, int Hkv, int blocks, int laye
 }
 
 // Time of a call by either kernel, in us, from what its sizes are: the launch and a workgroup's fixed part, then whichever
-// is longest: the longest walk, all workgroups' work over the chip, the prefix's bytes.  Fitted to 600 shapes (1 to 8
+// is longest: the longest walk, all workgroups' work over the chip, the prefix's bytes.  Fitted to 600 one-layer shapes (1 to 8
 // sequences, trees of 8 to 2048 rows, prefixes of 0 to 8192 keys, 32 / 40 / 64 heads, head_dim 64 and 128; K and V of
-// successive launches not in cache) and right to 11 - 15 % rms.  Over these shapes the choice is within 4 % (head_dim 64: 7 %)
-// of always taking the faster form.
+// successive launches not in cache), there right to 11 - 15 % rms and the choice within 4 % (head_dim 64: 7 %) of always the faster form.
+// Over 33000 shapes with 1 to 64 KV heads and 1 to 80 layers it is right to 20 - 35 % and the calls take 0.72 of the other kernel's
+// time (the fastest form of each: 0.64); one layer is slower by more than 5 % in 0.2 - 0.4 % of the calls that this kernel takes, 8 to 80
+// layers in 2 - 4 %.  The exceptions in tree_attn_short_plan are for kinds of calls that came out slower.
 struct CallCost {
     float launch, walk0, walk;      // launch; the longest walk: fixed part, per unit of keys
     float alone;                    // a unit of keys takes this share more if no other row block walks it (k row blocks: 1/k of that)
