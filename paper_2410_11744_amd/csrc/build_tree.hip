@@ -14,6 +14,7 @@
 // rows at once) has stored every row's maximum and group totals before.  Without a workspace the builder (build_tree_kernel)
 // recomputes the sums of the parent's row for every draw; both ways take the same decisions
 // and build the same tree.
+#include <algorithm>
 #include <cstddef>
 
 #include "draft_row.h"
@@ -24,6 +25,7 @@
 
 namespace dyspec {
 
+constexpr int kRing = 8, kRings = 8;        // places of a helper's ring, helpers of a tree
 constexpr int kMaxSlots = 2 * DYSPEC_MAX_BUILD_NODES + 2;
 
 // Data-parallel part (the draft softmax of every node, Algorithm 1's model call output):
@@ -36,7 +38,7 @@ constexpr int kMaxSlots = 2 * DYSPEC_MAX_BUILD_NODES + 2;
 // registers and code stayed.
 template <bool VEC, int S>
 __global__ __launch_bounds__(kBlock) void draft_row_sums_kernel(const float* __restrict__ draft_logits, int V, SeqArgs sa,
-                                                                double* __restrict__ ws)
+                                                                double* __restrict__ ws, int mails)
 {
     __shared__ float fred[kWaves];
     const int row = blockIdx.x;
@@ -69,6 +71,7 @@ __global__ __launch_bounds__(kBlock) void draft_row_sums_kernel(const float* __r
     t += __shfl_xor(t, 16, kWave);
     if (lane & 16) ws_totals(ws, row)[j * (kSeg / kRun) + 2 * wave + (lane >> 5)] = j < S ? t : 0.0;
     if (threadIdx.x == 0) *ws_rowmax(ws, row) = m;
+    if (mails && threadIdx.x < kMailDoubles && row - sa.node_off[seq] < kRings) ws_mail(ws, row)[threadIdx.x] = 0.0;
 }
 
 // LDS state of the form without a workspace.
@@ -229,16 +232,16 @@ __global__ __launch_bounds__(kBlock) void build_tree_kernel(
 // order (the slots themselves lie in LDS), so the pop is lane 0's.  It takes the popped node's next draw (token, R[y], the
 // new node's path key and first uniform) from
 // LDS, opens the new node's slot and the parent's next one.
-// Wave 1 draws from the root's row, which it keeps in LDS (wave_draw.h), up to kRing draws
-// ahead: the root is popped most often in wide trees.
+// Wave 1 draws from the root's row, which it keeps in LDS (wave_draw.h), up to kRootRing draws
+// ahead, or, in trees that have helpers (below), brings the draws that these make.
 // kDrawWaves waves draw for the other nodes (node i: wave i % kDrawWaves of them), one draw ahead per node and a
 // second one put aside where the node has been drawn from twice, the node of the largest slot value first: totals from the workspace (a new node's were fetched before it
 // was made: its row is known), a wave scan, the picked run's 128 logits, two per lane, a wave scan.
 //
 // LDS words, one writer at a time.  A node's word is, with the top bit clear, a request of control for
 // draw `rank` (low bits: the upper bits of the slot value, the order in which requests are
-// served), and with the top bit set the answer (the token; the rest of the draw lies beside it) or nothing at
-// all.  Control writes it only while the bit is set, the node's wave only while it is clear.  The root's
+// served), and with the top bit set the answer (the token; the rest of the draw lies beside it) or nothing (which may
+// say that the node's draws come from a ring).  Control writes it only while the bit is set, the node's wave only while it is clear.  The root's
 // draws go through a ring; `news` tells the draw waves which requests the last pop made.  LDS operations
 // of a wave take effect in their order, so data written before a word are there for whoever has read the word.
 //
@@ -257,30 +260,37 @@ __global__ __launch_bounds__(kBlock) void build_tree_kernel(
 // other than the root are popped again: 385 to 515 us over tables of 512 rows of independent normal logits.
 constexpr int kBuildThreads = 1024;
 constexpr int kDrawWaves = kBuildThreads / kWave - 2;
-constexpr int kRing = 16;
+constexpr int kRootRing = 16;
+static_assert(kRing * kRings == kWave, "a lane for every place");
 constexpr uint32_t kAnswer = 0x80000000u;
+constexpr uint32_t kFromRing = kAnswer | 1023u << 15;   // | k: the node's draws come from ring k (no tree goes on after a draw of rank 1023)
 constexpr uint32_t kStop = 0u;              // news of a pop is never 0: the new node's index is not
 static_assert(DYSPEC_MAX_BUILD_NODES <= 1024 && DYSPEC_MAX_VOCAB <= (1 << 15), "parent, rank and previous sibling share a word, rank and token too");
 
-// What LDS holds of a node.
+// What LDS holds of a node; its last 24 bytes are what a place in a ring holds.
 struct Node {
-    double r;               // its next draw, made ahead: R[y] (< 0: the row is empty),
-    unsigned long long child_key;   // path key of the node the draw makes
     double value;           // open slot (<= 0: none)
     unsigned long long key; // path key
+    uint32_t opened;        // order in which the open slot was opened (2 i + 1: first child, 2 i: next sampling of the parent of node i)
     float u;                // uniform of the next draw
     uint32_t word;          // request or answer: kAnswer | rank << 15 | token
     float child_u;          // uniform of the first draw of the node the draw makes
-    uint32_t opened;        // order in which the open slot was opened (2 i + 1: first child, 2 i: next sampling of the parent of node i)
+    double r;               // its next draw, made ahead: R[y] (< 0: the row is empty),
+    unsigned long long child_key;   // path key of the node the draw makes
 };
-constexpr uint32_t kNode = sizeof(Node), kChildKeyAt = 8, kValueAt = 16, kKeyAt = 24, kUAt = 32, kWordAt = 36, kChildUAt = 40, kOpenedAt = 44;
-static_assert(kNode == 48 && offsetof(Node, child_key) == kChildKeyAt && offsetof(Node, value) == kValueAt && offsetof(Node, key) == kKeyAt &&
-              offsetof(Node, u) == kUAt && offsetof(Node, word) == kWordAt && offsetof(Node, child_u) == kChildUAt && offsetof(Node, opened) == kOpenedAt, "");
+constexpr uint32_t kNode = sizeof(Node), kValueAt = 0, kKeyAt = 8, kOpenedAt = 16, kUAt = 20, kWordAt = 24, kChildUAt = 28, kRAt = 32, kChildKeyAt = 40;
+static_assert(kNode == 48 && offsetof(Node, value) == kValueAt && offsetof(Node, key) == kKeyAt && offsetof(Node, opened) == kOpenedAt && offsetof(Node, u) == kUAt &&
+              offsetof(Node, word) == kWordAt && offsetof(Node, child_u) == kChildUAt && offsetof(Node, r) == kRAt && offsetof(Node, child_key) == kChildKeyAt, "");
+constexpr uint32_t kPlace = kNode - kWordAt;                     // a place in a ring, addressed as if it were a node's
 // Dynamic LDS of the builder: byte offsets.
 struct BuildLds {
-    static constexpr uint32_t ring = 0;                                            // the root's draws: draw r at r % kRing (r, child's, word)
-    static constexpr uint32_t root_taken = ring + kRing * kNode;
-    static constexpr uint32_t news = root_taken + 4;                               // new node | popped node << 10 | kRequest if it was asked for another draw
+    static constexpr uint32_t ring = 0;                                            // the root's draws, draw r at r % kRootRing
+    static constexpr uint32_t here = ring + kRootRing * kPlace;                    // bit 8 k: helper k runs
+    static constexpr uint32_t taken = here + 8;                                    // per ring: draws below this rank are taken
+    static constexpr uint32_t hot = taken + 4 * kRings;                            // per ring: its node
+    static constexpr uint32_t claims = hot + 4 * kRings;                           // bit k: ring k has a node
+    static constexpr uint32_t bound = claims + 4;                                  // bit k: and its helper has been told
+    static constexpr uint32_t news = bound + 4;                                   // new node | popped node << 10 | kRequest if it was asked for another draw
     static constexpr uint32_t n_built = news + 4;
     static constexpr uint32_t fred = n_built + 4;
     static constexpr uint32_t gone = fred + 4 * (kBuildThreads / kWave);          // drawn tokens of the run a wave is drawing from
@@ -290,8 +300,6 @@ struct BuildLds {
 constexpr uint32_t kRequest = 1u << 20;
 constexpr size_t kLdsPerWorkgroup = 160 * 1024;
 static_assert(BuildLds::row(DYSPEC_MAX_BUILD_NODES) <= kLdsPerWorkgroup, "the node state of the largest tree fits in LDS");
-typedef uint32_t uint2v __attribute__((ext_vector_type(2)));
-typedef unsigned long long u64x2 __attribute__((ext_vector_type(2)));
 
 __device__ __forceinline__ u64 join_key(uint2 k) { return (u64)k.x | ((u64)k.y << 32); }
 __device__ __forceinline__ uint2 split_key(u64 k) { return make_uint2((uint32_t)k, (uint32_t)(k >> 32)); }
@@ -299,7 +307,7 @@ __device__ __forceinline__ void keep_order() { asm volatile("" ::: "memory"); }
 // What the lane publishes: the draw, then its word.
 __device__ __forceinline__ void publish(uint32_t place, double r, u64 key, float u, uint32_t word)
 {
-    *lds_at<double>(place) = r;
+    *lds_at<double>(place + kRAt) = r;
     *lds_at<u64>(place + kChildKeyAt) = key;
     *lds_at<float>(place + kChildUAt) = u;
     lds_set(lds_at<uint32_t>(place + kWordAt), word);
@@ -336,20 +344,20 @@ __device__ __attribute__((noinline, aligned(64))) void draw_for_root(uint32_t ld
             child = join_key(ck);
         }
         uint32_t news = lds_now(lds_at<uint32_t>(lds + BuildLds::news));
-        uint32_t taken = lds_now(lds_at<uint32_t>(lds + BuildLds::root_taken));
+        uint32_t taken = lds_now(lds_at<uint32_t>(lds + BuildLds::taken));
         Drawn d;
         const bool drawn = draw_wave_row(row, (double)readlane_f32(us, rank & 63), &d);
         const double R = drawn ? d.wy / d.W : -1.0;
         for (;;) {
             if (uniform(news) == kStop) return;
-            if (rank - (int)uniform(taken) < kRing) break;
+            if (rank - (int)uniform(taken) < kRootRing) break;
             __builtin_amdgcn_s_sleep(1);
             news = lds_now(lds_at<uint32_t>(lds + BuildLds::news));
-            taken = lds_now(lds_at<uint32_t>(lds + BuildLds::root_taken));
+            taken = lds_now(lds_at<uint32_t>(lds + BuildLds::taken));
         }
         // (lane rank % 64 has the child's key at hand)
         if (lane == (rank & 63))
-            publish(lds + BuildLds::ring + (uint32_t)(rank % kRing) * kNode, R, child, child_u, kAnswer | ((uint32_t)rank << 15) | (uint32_t)(drawn ? d.y : 0));
+            publish(lds + BuildLds::ring - kWordAt + (uint32_t)(rank % kRootRing) * kPlace, R, child, child_u, kAnswer | ((uint32_t)rank << 15) | (uint32_t)(drawn ? d.y : 0));
         if (!drawn) return;
     }
 }
@@ -644,6 +652,242 @@ __device__ __attribute__((noinline, aligned(64))) void draw_for_nodes(uint32_t l
     }
 }
 
+// ---- Helpers: workgroups on CUs of their own, each for one node that is drawn from again and again.
+//
+// A draw from global memory takes a wave 2.1 us, one from a row in LDS 0.6, and the tree's workgroup has room for the root's
+// row at most.  So a node that is popped kClaimRank times gets a helper, as long as there is one, the root at its first pop: a workgroup
+// that brings the node's row into its LDS, makes the node's draws from rank 0 on (they depend on the row and the path key alone)
+// and leaves them in a ring in memory.  Wave 1 of the tree's workgroup brings them to a ring in LDS, and from a rank
+// that the helper has reached by then on (kOwnDraws) control takes the node's draws from there, as it takes the root's where there are no helpers.
+//
+// Words in memory, all accesses relaxed and device-scope: the mailbox's state (the helper comes: kHere; wave 1 claims it; one that has
+// waited too long leaves), its other word (wave 1: draws taken, or that the tree is complete), the count of draws that can be read (helper;
+// written when they are there).  A helper waits for a claim, for room in the ring, and for the end, each a bounded number of looks.
+// Only a helper that is there is claimed: nobody waits for a workgroup that has no CU, and a tree without its helpers is built by its own waves.
+// (A draw is the same whoever makes it, to the rounding of the sums behind it.)
+//
+// Measured, with the pass over the rows, 512 rows of 32000 tokens, four tables: 966, 474, 584, 555 -> 334, 323, 336, 323 us; all draws from
+// the root 381 -> 361, from another node 1096 -> 372; 1024 rows of 32768 tokens 1874 -> 598 (the root's row never fitted there), 64 rows
+// 124 -> 80, 128 rows 222, 135, 178 -> 128, 111, 125; a chain 559 -> 553.  What is left is control's pop, 0.53 us, or where one
+// node has all the draws its helper's draw, 0.63.
+// kHelpedRows: below, a node has hardly the draws to pay for a row's loading (some 8 us before the first draw is there).
+constexpr int kClaimRank = 3, kOwnDraws = 8, kRootOwnDraws = 2;        // draws the node's own wave makes after the claim
+constexpr int kHelpedRows = 64;             // of the widest tree of a batch that has helpers,
+constexpr int kLeastHelped = 16;            // of any tree of it that has some (a mailbox each in its rows)
+constexpr int kHelpedLeft = 24;             // rows still to be built when a node is worth a helper
+constexpr int kHelpedBlocks = 256;          // one workgroup a CU
+constexpr int kHelperPolls = 1 << 22;       // some seconds
+static_assert(kLeastHelped >= kRings, "");
+constexpr uint32_t kHere = 1u, kClaimed = 2u;                   // mailbox state; claimed: | node << 2
+constexpr uint32_t kStopped = 0x80000000u;                      // beside the number of draws taken
+typedef double doublex2 __attribute__((ext_vector_type(2)));
+constexpr uint32_t kHelpPlace = 32;                             // wy, W, y of a draw
+struct HelpLds {
+    static constexpr uint32_t node = 0;
+    static constexpr uint32_t made = 4;                                            // draws made,
+    static constexpr uint32_t room = 8;                                            // draws that may be made (kStopped: no more)
+    static constexpr uint32_t fred = 16;
+    static constexpr uint32_t ring = fred + 4 * (kBuildThreads / kWave);
+    static constexpr uint32_t row = ring + kMailRing * kHelpPlace;
+};
+static_assert(HelpLds::row % 16 == 0, "");
+template <typename T> __device__ __forceinline__ T agent_load(const T* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+template <typename T> __device__ __forceinline__ void agent_store(T* p, T v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+__device__ __forceinline__ void memory_done() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+__device__ __forceinline__ u64* mail_words(double* mail) { return reinterpret_cast<u64*>(mail); }               // state | taken << 32
+__device__ __forceinline__ uint32_t* mail_state(double* mail) { return reinterpret_cast<uint32_t*>(mail); }
+__device__ __forceinline__ uint32_t* mail_taken(double* mail) { return reinterpret_cast<uint32_t*>(mail) + 1; }
+__device__ __forceinline__ u64* mail_key(double* mail) { return reinterpret_cast<u64*>(mail + 1); }
+__device__ __forceinline__ uint32_t* mail_count(double* mail) { return reinterpret_cast<uint32_t*>(mail + 2); }
+
+// A helper's first wave: draws rank 0 .. N - 2 of the row in LDS, as far as there is room, and leaves them in the ring in LDS.
+__device__ __attribute__((noinline, aligned(64))) void make_draws(uint32_t lds_, double inv_temp, double m, int V_, int N_, uint64_t seed_, u64 key_)
+{
+    const uint32_t lds = uniform(lds_), ring = lds + HelpLds::ring;
+    const int V = uniform(V_), N = uniform(N_);
+    const u64 seed = uniform((u64)seed_);
+    const uint2 key = split_key(uniform(key_));
+    WaveRow row;
+    row.leaf = lds_at<double>(lds + HelpLds::row);
+    row.logits = lds_at<float>(lds + HelpLds::row + 8 * row_leaves(V));
+    row.inv_temp = uniform(inv_temp);
+    row.m = uniform(m);
+    const int lane = threadIdx.x & 63;
+    open_wave_row(row, V);
+    float us = 0.f;                                 // the uniforms of 64 ranks
+    for (int rank = 0; rank < N - 1; ++rank) {
+        if ((rank & 3) == 0) {
+            if ((rank & 63) == 0) us = u01(seed, key, (uint32_t)(rank + lane), KIND_BUILD);
+            for (;;) {                              // (ends when the second wave ends, at the latest)
+                const uint32_t room = uniform(lds_now(lds_at<uint32_t>(lds + HelpLds::room)));
+                if (room == kStopped) return;
+                if (rank + 4 <= (int)room) break;
+                __builtin_amdgcn_s_sleep(2);
+            }
+        }
+        Drawn d;
+        const bool drawn = draw_wave_row(row, (double)readlane_f32(us, rank & 63), &d);
+        if (lane == 0) {
+            const uint32_t place = ring + kHelpPlace * (uint32_t)(rank & (kMailRing - 1));
+            *lds_at<doublex2>(place) = drawn ? doublex2{ d.wy, d.W } : doublex2{ -1.0, 1.0 };
+            *lds_at<uint32_t>(place + 16) = (uint32_t)(drawn ? d.y : 0);
+            lds_set(lds_at<uint32_t>(lds + HelpLds::made), (uint32_t)rank + 1u);
+        }
+        if (!drawn) return;
+    }
+}
+// Its second wave: brings them to memory, where wave 1 of the tree's workgroup reads them.
+__device__ __attribute__((noinline)) void ship_draws(uint32_t lds_, double* ws_, double* mail_, int row_)
+{
+    const uint32_t lds = uniform(lds_);
+    double *const mail = uniform(mail_), *const ring = ws_mail_ring(uniform(ws_), uniform(row_));
+    const int lane = threadIdx.x & 63;
+    int shipped = 0;
+    for (int polls = 0; polls < kHelperPolls; ++polls) {
+        const int made = (int)uniform(lds_now(lds_at<uint32_t>(lds + HelpLds::made)));
+        const u64 words = agent_load(mail_words(mail));
+        if (made > shipped) {
+            if (shipped + ((lane - shipped) & (kMailRing - 1)) < made) {
+                const uint32_t place = lds + HelpLds::ring + kHelpPlace * (uint32_t)lane;
+                const double wy = *lds_at<double>(place), W = *lds_at<double>(place + 8);
+                agent_store(ring + 2 * lane, wy / W);
+                agent_store(reinterpret_cast<uint32_t*>(ring + 2 * lane + 1), *lds_at<uint32_t>(place + 16));
+            }
+            memory_done();                          // they are where they can be read
+            if (lane == 0) agent_store(mail_count(mail), (uint32_t)made);
+            shipped = made;
+        }
+        const uint32_t taken = uniform((uint32_t)(words >> 32));
+        if (taken & kStopped) break;
+        if (lane == 0) lds_set(lds_at<uint32_t>(lds + HelpLds::room), taken + kMailRing);
+        if (polls == kHelperPolls - 1) {            // (the root's helper, whose tree's workgroup may have no CU yet)
+            uint32_t was = kHere;
+            if (lane == 0) __hip_atomic_compare_exchange_strong(mail_state(mail), &was, 0u, __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (uniform(was) != kHere) polls = 0;   // claimed: goes on
+        }
+    }
+    if (lane == 0) lds_set(lds_at<uint32_t>(lds + HelpLds::room), kStopped);
+}
+
+// Helper `mine` of a sequence.  The first one is the root's.
+template <bool VEC>
+__device__ __attribute__((noinline)) void help_build(uint32_t lds_, const float* draft_logits_, int V_, double inv_temp_, uint64_t seed_, double* ws_, int base_, int N_, int mine_, uint32_t seq_)
+{
+    const uint32_t lds = uniform(lds_);
+    const int V = uniform(V_), base = uniform(base_), N = uniform(N_), mine = uniform(mine_);
+    const float* const draft_logits = uniform(draft_logits_);
+    const double inv_temp = uniform(inv_temp_);
+    double* const ws = uniform(ws_);
+    double* const mail = ws_mail(ws, base + mine);
+    const int lane = threadIdx.x & 63, wave = uniform((int)(threadIdx.x >> 6));
+    int node = 0;
+    if (wave == 0 && lane == 0) {
+        agent_store(mail_state(mail), kHere);
+        *lds_at<uint32_t>(lds + HelpLds::made) = 0u;
+        *lds_at<uint32_t>(lds + HelpLds::room) = (uint32_t)kMailRing;
+    }
+    if (mine > 0) {
+        if (wave == 0) {
+            node = -1;
+            for (int polls = 0; polls < kHelperPolls; ++polls) {
+                const u64 w = uniform(agent_load(mail_words(mail)));
+                if ((uint32_t)(w >> 32) & kStopped) break;
+                if (((uint32_t)w & 3u) == kClaimed) {
+                    node = (int)((uint32_t)w >> 2);
+                    break;
+                }
+                if (polls == kHelperPolls - 1) {    // the tree's workgroup may have no CU yet: leaves, unless it has been claimed just now
+                    uint32_t was = kHere;
+                    if (lane == 0) __hip_atomic_compare_exchange_strong(mail_state(mail), &was, 0u, __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    was = uniform(was);
+                    if ((was & 3u) == kClaimed) node = (int)(was >> 2);
+                }
+                __builtin_amdgcn_s_sleep(4);
+            }
+            if (lane == 0) *lds_at<int>(lds + HelpLds::node) = node;
+        }
+        __syncthreads();
+        node = uniform(*lds_at<int>(lds + HelpLds::node));
+        if (node < 0 || node >= N) return;
+    }
+    const double m = load_row_lds<kBuildThreads, VEC>(draft_logits + (size_t)(base + node) * V, V, inv_temp, lds_at<double>(lds + HelpLds::row),
+                                                      lds_at<float>(lds + HelpLds::row + 8 * row_leaves(V)), (float*)lds_at<float>(lds + HelpLds::fred));
+    if (wave == 0) make_draws(lds, inv_temp, m, V, N, seed_, mine > 0 ? agent_load(mail_key(mail)) : join_key(root_key(uniform(seq_))));
+    else if (wave == 1) ship_draws(lds, ws, mail, base + node);
+}
+
+// Wave 1 of a tree with helpers: fills the rings in LDS from the helpers'.  Lane 8 k + j has place j of ring k.
+__device__ __attribute__((noinline, aligned(64))) void bring_draws(uint32_t lds_, uint32_t rings_, double* ws_, int base_, uint64_t seed_)
+{
+    const uint32_t lds = uniform(lds_), rings = uniform(rings_);
+    const int base = uniform(base_);
+    const u64 seed = uniform((u64)seed_);
+    double* const ws = uniform(ws_);
+    const int lane = threadIdx.x & 63, k = lane / kRing, j = lane % kRing;
+    double* const mail = ws_mail(ws, base + k);
+    const bool first = j == 0;
+    uint32_t asked = 0, claimed = 0;                // rings that have a node, and whose helper has been told
+    u64 here = 0, key = 0;
+    const double* ring = nullptr;
+    int put = -1, told = 0, count = 0;              // the draw last put into the place, what the helper knows to be taken, what it has told of
+    while (uniform(lds_now(lds_at<uint32_t>(lds + BuildLds::news))) != kStop) {
+        const uint32_t claims = uniform(lds_now(lds_at<uint32_t>(lds + BuildLds::claims)));
+        const bool used = claimed >> k & 1u, all_here = here == 0x0101010101010101ull;
+        const int taken = used ? (int)lds_now(lds_at<uint32_t>(lds + BuildLds::taken + 4 * k)) : 0;
+        const int rank = taken + ((j - taken) & (kRing - 1));        // the draw this place is for
+        const bool wanted = used && rank > put, get = wanted && rank < count;
+        // (all of a look's loads are on their way together)
+        const uint32_t state = all_here ? kHere : agent_load(mail_state(mail));
+        uint32_t now = 0, y = 0;
+        double R = 0.0;
+        if (wanted) now = agent_load(mail_count(mail));
+        if (get) {
+            const double* const at = ring + 2 * (rank & (kMailRing - 1));
+            R = agent_load(at);
+            y = agent_load(reinterpret_cast<const uint32_t*>(at + 1));
+        }
+        if (ballot(get)) {
+            const uint2 child = child_key(seed, split_key(key), (uint32_t)rank);
+            const float child_u = u01(seed, child, 0u, KIND_BUILD);
+            if (get) {
+                publish(rings - kWordAt + kPlace * (uint32_t)lane, R, join_key(child), child_u, kAnswer | ((uint32_t)rank << 15) | y);
+                put = rank;
+            }
+        }
+        count = max(count, (int)now);
+        if (!all_here) {
+            here |= ballot(first && state == kHere);
+            if (lane == 0) lds_set(lds_at<u64>(lds + BuildLds::here), here);
+        }
+        if (claims != asked) {
+            const bool mine = (claims & ~asked) >> k & 1u;
+            int node = 0;
+            if (mine) {
+                node = *lds_at<int>(lds + BuildLds::hot + 4 * k);
+                key = *lds_at<u64>(lds + BuildLds::nodes + kNode * (uint32_t)node + kKeyAt);
+                ring = ws_mail_ring(ws, base + node);
+                if (first) agent_store(mail_key(mail), key);
+            }
+            memory_done();
+            uint32_t was = 0;
+            if (mine && first) {
+                was = kHere;
+                __hip_atomic_compare_exchange_strong(mail_state(mail), &was, kClaimed | (uint32_t)node << 2, __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            }
+            const u64 got = ballot(was == kHere);    // bit 8 k; (a helper that has left meanwhile has not been got)
+            for (uint32_t q = 0; q < kRings; ++q) claimed |= (uint32_t)(got >> (kRing * q) & 1u) << q;
+            if (lane == 0) lds_set(lds_at<uint32_t>(lds + BuildLds::bound), claimed);
+            asked = claims;
+        }
+        if (used && first && taken > told) {
+            agent_store(mail_taken(mail), (uint32_t)taken);
+            told = taken;
+        }
+        if (!ballot(wanted)) __builtin_amdgcn_s_sleep(2);
+    }
+    if (first) agent_store(mail_taken(mail), kStopped);
+}
+
 // Wave 0: pops and appends.  Returns the number of rows built, its complement if a draw stayed out.  Row i's parent | rank << 10 | previous
 // sibling << 20 goes to `parent` for the time being.
 //
@@ -671,7 +915,7 @@ struct Slots {
     int node;               // and its node (| kSure: no slot left out comes before it, even if one is as large)
     double unlisted;        // no open slot outside the list is larger (the same in every lane)
 };
-constexpr int kSure = 1 << 16;
+constexpr int kSure = 1 << 16, kRingOne = 1 << 20;       // | kRingOne * k: the node's draws come from ring k
 
 // The list made again from the slots of nodes 0 .. n - 1, node q in lane q % 64: the slots whose value's high word is above a line that
 // is searched for, 32 to 64 of them where that can be had in few steps, each put where it belongs as a pop does.  Where the values
@@ -716,7 +960,7 @@ __device__ __attribute__((noinline)) Slots relist(uint32_t nodes_, int n_)
             if (c <= kWave) { line = mid; listed = c; } else low = mid;
         }
         if (listed >= kRelisted || (listed > 0 && line == 0)) {
-            Slots s = { -1.0, 0, -1.0 };
+            Slots s = { -1.0, 0, 0.0 };
             int opened = 0;
             double left = -1.0;
             for (int k = 0; kWave * k < n; ++k) {
@@ -742,7 +986,7 @@ __device__ __attribute__((noinline)) Slots relist(uint32_t nodes_, int n_)
                 }
             }
             left = wave_max_dpp(left);
-            s.unlisted = left > 0.0 ? left : -1.0;
+            s.unlisted = left > 0.0 ? left : 0.0;
             return s;
         }
     }
@@ -756,7 +1000,7 @@ __device__ __attribute__((noinline)) Slots relist(uint32_t nodes_, int n_)
         if (v > 0.0 && (v > best || (v == best && o < when))) { best = v; at = k; when = o; }
     }
     uint32_t listed = 0;                            // bit k: node lane + 64 k is in the list
-    Slots s = { -1.0, 0, -1.0 };
+    Slots s = { -1.0, 0, 0.0 };
     for (int t = 0; t <= kRelisted; ++t) {
         const double top = wave_max_dpp(best);
         if (!(uniform(top) > 0.0)) break;
@@ -793,46 +1037,66 @@ __device__ __attribute__((noinline)) Slots relist(uint32_t nodes_, int n_)
     return s;
 }
 
-__device__ __attribute__((noinline, aligned(64))) int pop_nodes(uint32_t lds_, int root_ring_, int N_, int max_polls_, int* parent_, int* token_, float* est_value_)
+__device__ __attribute__((noinline, aligned(64))) int pop_nodes(uint32_t lds_, uint32_t rings_, int root_ring_, int helped_, int N_, int max_polls_, int* parent_, int* token_, float* est_value_)
 {
-    begin_behind<5>();
-    const uint32_t lds = uniform(lds_), nodes = lds + BuildLds::nodes;
-    const bool root_ring = uniform(root_ring_) != 0;
-    const int N = uniform(N_);
+    const uint32_t lds = uniform(lds_), nodes = lds + BuildLds::nodes, rings = uniform(rings_) - kWordAt;
+    const bool root_ring = uniform(root_ring_) != 0, helped = uniform(helped_) != 0;
+    const uint32_t N = (uint32_t)uniform(N_);
+    const uint32_t ring_mask = root_ring ? kRootRing - 1 : kRing - 1;
     int *const parent = uniform(parent_), *const token = uniform(token_);
     float* const est_value = uniform(est_value_);
-    const int lane = threadIdx.x & 63;
-    Slots s = { lane == 0 ? 1.0 : -1.0, 0, -1.0 };
-    int n = 1, root_rank = 0, polls = uniform(max_polls_);
+    const uint32_t lane = threadIdx.x & 63;
+    Slots s = { lane == 0 ? 1.0 : -1.0, root_ring ? kRingOne : 0, 0.0 };
+    // ring k in lane k (1 ..): place of its next draw and how the word there begins; in lane 0 what an answer begins with
+    const uint32_t ring_first = rings + kPlace * kRing * (lane - 1u);
+    uint32_t ring_place = ring_first, ring_want = kAnswer;
+    int ring_node = -1;                             // its node, from the claim on; the first rank that the ring holds
+    uint32_t ring_from = 0, next_helper = 1, claims = 0;
+    uint32_t n = 1;
+    int polls = uniform(max_polls_);
     bool lost = false;
     uint32_t place_n = nodes + kNode;               // LDS of node n
-    int tokens = -1, froms = 0;                     // of the last 64 rows, row i in lane i % 64; written out together
+    uint32_t words = 0, froms = 0;                  // of the last 64 rows, row i in lane i % 64; written out together
     float values = 1.0f;
+    const auto write_out = [&](uint32_t first) __attribute__((always_inline)) {
+        token[first + lane] = first + lane == 0 ? -1 : (int)(words & 0x7fffu);
+        est_value[first + lane] = values;
+        parent[first + lane] = (int)((froms & 0xfff003ffu) | ((words >> 15) & 1023u) << 10);
+    };
     while (n < N) {
         // ---- the largest value
-        if (!(ballot(s.value > s.unlisted) & 1ull) && !(__builtin_amdgcn_readfirstlane(s.node) & kSure)) {
+        uint32_t slot = uniform((uint32_t)s.node);
+        if (__builtin_expect(!(ballot(s.value > s.unlisted) & 1ull) && !(slot & kSure), 0)) {
             if (!(ballot(s.unlisted > 0.0) & 1ull)) break;              // no slot is open
-            s = relist(nodes, n);
+            s = relist(nodes, (int)n);
+            const uint32_t told = *lds_at<uint32_t>(nodes + kNode * ((uint32_t)s.node & (kSure - 1)) + kWordAt);
+            if ((told & ~15u) == kFromRing) s.node += kRingOne * (int)(told & 15u);
+            if (!(ballot(s.value > 0.0) & 1ull)) break;
+            slot = uniform((uint32_t)s.node);
         }
-        if (!(ballot(s.value > 0.0) & 1ull)) break;
-        const int p = __builtin_amdgcn_readfirstlane(s.node) & (kSure - 1);
+        const uint32_t p = slot & (kSure - 1), ring = slot / kRingOne;
         const double v = uniform(s.value);
-        // ---- its node's next draw
-        const bool from_ring = root_ring && p == 0;
-        const uint32_t place_p = nodes + kNode * (uint32_t)p;
-        const uint32_t place = from_ring ? lds + BuildLds::ring + kNode * (uint32_t)(root_rank % kRing) : place_p;
-        // the bits of the word that tell: the answer's, in the ring the draw's rank as well
-        const uint32_t mask = from_ring ? kAnswer | (1023u << 15) : kAnswer, want = from_ring ? kAnswer | (uint32_t)root_rank << 15 : kAnswer;
+        // ---- its node's next draw; the bits of the word that tell: the answer's, in a ring the draw's rank as well
+        const uint32_t place_p = nodes + kNode * p;
+        const uint32_t ring_at = (uint32_t)__builtin_amdgcn_readlane((int)ring_place, (int)ring), want = (uint32_t)__builtin_amdgcn_readlane((int)ring_want, (int)ring);
+        const uint32_t place = ring ? ring_at : place_p, mask = ring ? kAnswer | (1023u << 15) : kAnswer;
+        uint32_t w = lds_now(lds_at<uint32_t>(place + kWordAt));
+        double R = __longlong_as_double((long long)lds_now(lds_at<u64>(place + kRAt)));   // (as good as the word that was read before it)
+        u64 child = lds_now(lds_at<u64>(place + kChildKeyAt));
+        uint32_t child_u = lds_now(lds_at<uint32_t>(place + kChildUAt));
         const uint32_t o = *lds_at<uint32_t>(place_p + kOpenedAt);
-        uint32_t w = uniform(lds_now(lds_at<uint32_t>(place + kWordAt)));
-        while ((w & mask) != want && --polls > 0) w = uniform(lds_now(lds_at<uint32_t>(place + kWordAt)));
-        double R = *lds_at<double>(place);
-        const u64 child = *lds_at<u64>(place + kChildKeyAt);
-        const uint32_t child_u = *lds_at<uint32_t>(place + kChildUAt);
+        w = uniform(w);
+        while ((w & mask) != want && --polls > 0) {
+            w = lds_now(lds_at<uint32_t>(place + kWordAt));
+            R = __longlong_as_double((long long)lds_now(lds_at<u64>(place + kRAt)));
+            child = lds_now(lds_at<u64>(place + kChildKeyAt));
+            child_u = lds_now(lds_at<uint32_t>(place + kChildUAt));
+            w = uniform(w);
+        }
+        if (polls <= 0) { lost = true; break; }
         const int R_hi = uniform(__double2hiint(R));
-        if (R_hi < 0 || polls <= 0) {
-            lost = polls <= 0;
-            if (lost || R_hi == (int)0xbff00000u) break;            // (-1) nothing left to sample under p
+        if (__builtin_expect(R_hi < 0, 0)) {
+            if (R_hi == (int)0xbff00000u) break;                        // (-1) nothing left to sample under p
             // the quotient of two infinite weights, a NaN with its sign bit set: the token holds all that is left, at a
             // temperature so small that the row's maximum over it is rounded by more than the range of exp
             R = 1.0;
@@ -840,60 +1104,89 @@ __device__ __attribute__((noinline, aligned(64))) int pop_nodes(uint32_t lds_, i
         // ---- node n = child number `rank` of p, its slot and p's next one (p's is opened first)
         const double v0 = v * R, v1 = v * (1.0 - R);
         const uint32_t rank = (w >> 15) & 1023u;
-        if (lane == 0) {
-            *lds_at<double>(place_n + kValueAt) = v0;
-            *lds_at<u64>(place_n + kKeyAt) = child;
-            keep_order();
-            *lds_at<uint2v>(place_n + kUAt) = uint2v{ child_u, (uint32_t)__double2hiint(v0) >> 16 };       // uniform, and word: request of draw 0
-            *lds_at<double>(place_p + kValueAt) = v1;
-            *lds_at<uint32_t>(place_p + kOpenedAt) = 2u * (uint32_t)n;
-            keep_order();
-            if (from_ring) lds_set(lds_at<uint32_t>(lds + BuildLds::root_taken), rank + 1u);
-            else lds_set(lds_at<uint32_t>(place_p + kWordAt), ((rank + 1u) << 15) | ((uint32_t)__double2hiint(v1) >> 16));
-            lds_set(lds_at<uint32_t>(lds + BuildLds::news), (uint32_t)n | ((uint32_t)p << 10) | (from_ring ? 0u : kRequest));
+        uint32_t next_slot = slot & ~(uint32_t)kSure, news = n | (p << 10);
+        uint32_t tell_at = place_p + kWordAt, tell = ((rank + 1u) << 15) | ((uint32_t)__double2hiint(v1) >> 16);
+        if (ring) {
+            tell_at = lds + BuildLds::taken - 4u + 4u * ring;
+            tell = rank + 1u;
+            const uint32_t to = kPlace * ((rank + 1u) & ring_mask);
+            ring_place = lane == ring ? ring_first + to : ring_place;
+            ring_want = lane == ring ? kAnswer | ((rank + 1u) << 15) : ring_want;
+        } else {
+            news |= kRequest;
+            if (__builtin_expect(helped && (rank >= (uint32_t)kClaimRank || p == 0), 0)) {
+                const u64 has = ballot(ring_node == (int)p);
+                if (has) {
+                    const uint32_t k = (uint32_t)__builtin_ctzll(has);
+                    if (rank + 1u >= (uint32_t)__builtin_amdgcn_readlane((int)ring_from, (int)k) &&
+                        (uniform(lds_now(lds_at<uint32_t>(lds + BuildLds::bound))) >> (k - 1u) & 1u)) {
+                        // p's draws come from the ring from the next one on
+                        next_slot += kRingOne * k;
+                        news ^= kRequest;
+                        tell = kFromRing | k;
+                        if (lane == 0) lds_set(lds_at<uint32_t>(lds + BuildLds::taken + 4 * (k - 1u)), rank + 1u);
+                        const uint32_t to = kPlace * ((rank + 1u) & ring_mask);
+                        if (lane == k) { ring_place = ring_first + to; ring_want = kAnswer | ((rank + 1u) << 15); }
+                    }
+                } else {
+                    const uint32_t k = p == 0 ? 0u : next_helper;
+                    if (k < kRings && rank < (uint32_t)kMailRanks / 2 && n + kHelpedLeft < N && ((uniform(lds_now(lds_at<u64>(lds + BuildLds::here))) >> (8 * k)) & 1ull)) {
+                        const uint32_t from = rank + 1u + (p == 0 ? kRootOwnDraws : kOwnDraws);
+                        claims |= 1u << k;
+                        if (lane == 0) {
+                            *lds_at<uint32_t>(lds + BuildLds::taken + 4 * k) = from;
+                            *lds_at<uint32_t>(lds + BuildLds::hot + 4 * k) = p;
+                            lds_set(lds_at<uint32_t>(lds + BuildLds::claims), claims);
+                        }
+                        if (p != 0) ++next_helper;
+                        if (lane == k + 1) { ring_node = (int)p; ring_from = from; }
+                    }
+                }
+            }
         }
-        if (from_ring) root_rank = (int)rank + 1;
-        // ---- p's next slot goes behind the slots at least as good, which move up (a closed one to the end, as an empty place)
-        const double x1 = v1 > 0.0 ? v1 : -1.0;
-        const int c = __builtin_popcountll(ballot(s.value >= x1) >> 1);
+        if (lane == 0) {                            // what other waves wait for first; the slots' values are control's own
+            *lds_at<u64>(place_n + kKeyAt) = child;
+            *lds_at<uint32_t>(place_n + kUAt) = child_u;
+            keep_order();
+            lds_set(lds_at<uint32_t>(place_n + kWordAt), (uint32_t)__double2hiint(v0) >> 16);       // request of draw 0
+            lds_set(lds_at<uint32_t>(tell_at), tell);
+            lds_set(lds_at<uint32_t>(lds + BuildLds::news), news);
+            *lds_at<double>(place_n + kValueAt) = v0;
+            *lds_at<double>(place_p + kValueAt) = v1;
+            *lds_at<uint32_t>(place_p + kOpenedAt) = 2u * n;
+        }
+        // ---- p's next slot goes behind the slots at least as good, which move up (a closed one, value 0, to the end)
+        const uint32_t c = (uint32_t)__builtin_popcountll(ballot(s.value >= v1) >> 1);
         if (c == 0) {
-            if (lane == 0) { s.value = x1; s.node = p; }           // (its next slot is a new one: not kSure)
+            if (lane == 0) { s.value = v1; s.node = (int)next_slot; }   // (its next slot is a new one: not kSure)
         } else {
             const double up_v = dpp_or_own<kDppWaveShl1>(s.value);
             const int up_n = dpp_or_own<kDppWaveShl1>(s.node);
-            s.value = lane < c ? up_v : lane == c ? x1 : s.value;
-            s.node = lane < c ? up_n : lane == c ? p : s.node;
+            s.value = lane < c ? up_v : lane == c ? v1 : s.value;
+            s.node = lane < c ? up_n : lane == c ? (int)next_slot : s.node;
         }
         // ---- the new node's likewise, the ones behind it move down; what finds no place is left out
-        if (ballot(v0 > s.unlisted && v0 > 0.0)) {
-            const int at = __builtin_popcountll(ballot(s.value >= v0));
+        if (ballot(v0 > s.unlisted)) {
+            const uint32_t at = (uint32_t)__builtin_popcountll(ballot(s.value >= v0));
             const double last = readlane_f64(s.value, 63);
             const double out = at < kWave ? last : v0;
             const double down_v = dpp_or_own<kDppWaveShr1>(s.value);
             const int down_n = dpp_or_own<kDppWaveShr1>(s.node);
             s.value = lane > at ? down_v : lane == at ? v0 : s.value;
-            s.node = lane > at ? down_n : lane == at ? n : s.node;
+            s.node = lane > at ? down_n : lane == at ? (int)n : s.node;
             s.unlisted = fmax(s.unlisted, out);
         }
         if (lane == (n & 63)) {
-            tokens = (int)(w & 0x7fffu);
+            words = w;
             values = (float)v;
-            froms = (int)((uint32_t)p | (rank << 10) | ((o >> 1) << 20));
+            froms = p | o << 19;                    // (a later child's o is twice the previous sibling)
         }
         ++n;
         place_n += kNode;
-        if ((n & 63) == 0) {                        // rows n - 64 .. n - 1 are complete
-            token[n - kWave + lane] = tokens;
-            est_value[n - kWave + lane] = values;
-            parent[n - kWave + lane] = froms;
-        }
+        if ((n & 63) == 0) write_out(n - kWave);    // rows n - 64 .. n - 1 are complete
     }
-    if ((n & 63) > lane) {
-        token[(n & ~63) + lane] = tokens;
-        est_value[(n & ~63) + lane] = values;
-        parent[(n & ~63) + lane] = froms;
-    }
-    return lost ? ~n : n;
+    if ((n & 63) > lane) write_out(n & ~63u);
+    return lost ? (int)~n : (int)n;
 }
 
 template <bool VEC>
@@ -907,22 +1200,33 @@ __global__ __launch_bounds__(kBuildThreads) void build_tree_waves_kernel(
     const uint32_t nodes = lds + BuildLds::nodes, row_at = lds + BuildLds::row(widest);
     const int tid = threadIdx.x;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int seq = blockIdx.x;
+    const int help = (int)blockIdx.x - sa.n_seq;                    // >= 0: this workgroup is a helper
+    const int seq = help >= 0 ? help / kRings : (int)blockIdx.x;
     const int base = sa.node_off[seq];
     const int N = sa.node_off[seq + 1] - base;
     const double inv_temp = 1.0 / (double)sa.temp_d[seq];
+    const bool helped = (int)gridDim.x > sa.n_seq && N >= kLeastHelped;
+    if (help >= 0) {
+        if (helped) help_build<VEC>(lds, draft_logits, V, inv_temp, seed, ws, base, N, help % kRings, (uint32_t)seq);
+        return;
+    }
     const uint2 key = root_key((uint32_t)seq);
     for (int i = tid; i < N; i += kBuildThreads) {
         const uint32_t place = nodes + kNode * i;
         *lds_at<double>(place + kValueAt) = i == 0 ? 1.0 : -1.0;
-        *lds_at<uint32_t>(place + kWordAt) = (i == 0 && !root_ring) ? 0x3ff0u : kAnswer;           // a request for draw 0, or nothing
+        *lds_at<uint32_t>(place + kWordAt) = i > 0 ? kAnswer : root_ring ? kFromRing | 1u : 0x3ff0u;           // nothing, or a request for draw 0
         *lds_at<uint32_t>(place + kOpenedAt) = 2u * (uint32_t)i + 1u;
     }
-    if (tid < kRing) *lds_at<uint32_t>(lds + BuildLds::ring + kNode * tid + kWordAt) = 0u;
+    // (with helpers the rings lie where the root's row would)
+    const uint32_t rings = helped ? row_at : lds + BuildLds::ring;
+    if (tid < (helped ? kRings * kRing : kRootRing)) *lds_at<uint32_t>(rings - kWordAt + kPlace * tid + kWordAt) = 0u;
     if (tid == 0) {
         *lds_at<u64>(nodes + kKeyAt) = join_key(key);
         *lds_at<float>(nodes + kUAt) = u01(seed, key, 0u, KIND_BUILD);
-        *lds_at<uint32_t>(lds + BuildLds::root_taken) = 0u;
+        *lds_at<uint32_t>(lds + BuildLds::taken) = 0u;
+        *lds_at<u64>(lds + BuildLds::here) = 0ull;
+        *lds_at<uint32_t>(lds + BuildLds::claims) = 0u;
+        *lds_at<uint32_t>(lds + BuildLds::bound) = 0u;
         *lds_at<uint32_t>(lds + BuildLds::news) = 1u << 31;
     }
     double m = 0.0;
@@ -933,15 +1237,16 @@ __global__ __launch_bounds__(kBuildThreads) void build_tree_waves_kernel(
     // (control and the root's wave share their SIMDs, but come first there)
     if (wave == 0) {
         __builtin_amdgcn_s_setprio(3);
-        const int n = pop_nodes(lds, root_ring, N, max_polls, tree.parent + base, tree.token + base, est_value + base);
+        const int n = pop_nodes(lds, rings, root_ring, helped, N, max_polls, tree.parent + base, tree.token + base, est_value + base);
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");            // the rows are read back below
         if (tid == 0) {
             *lds_at<int>(lds + BuildLds::n_built) = n;
             lds_set(lds_at<uint32_t>(lds + BuildLds::news), kStop);
         }
     } else if (wave == 1) {
-        __builtin_amdgcn_s_setprio(2);
-        if (root_ring && N > 1) draw_for_root(lds, row_at, inv_temp, m, V, N, seed, (uint32_t)seq);
+        if (!helped) __builtin_amdgcn_s_setprio(2);
+        if (helped) bring_draws(lds, rings, ws, base, seed);
+        else if (root_ring && N > 1) draw_for_root(lds, row_at, inv_temp, m, V, N, seed, (uint32_t)seq);
     } else {
         draw_for_nodes<VEC>(lds, wave - 2, draft_logits, V, inv_temp, seed, ws, base, N);
     }
@@ -1009,17 +1314,17 @@ hipError_t prepare_build_tree()
 size_t build_tree_workspace_bytes(int total_rows) { return (size_t)total_rows * kRowSumDoubles * sizeof(double); }
 
 template <int S>
-static void launch_draft_row_sums_s(const float* draft_logits, int V, const SeqArgs& sa, double* ws, hipStream_t stream)
+static void launch_draft_row_sums_s(const float* draft_logits, int V, const SeqArgs& sa, double* ws, int mails, hipStream_t stream)
 {
     const int rows = sa.node_off[sa.n_seq];
-    if (V % 4 == 0) draft_row_sums_kernel<true, S><<<rows, kBlock, 0, stream>>>(draft_logits, V, sa, ws);
-    else draft_row_sums_kernel<false, S><<<rows, kBlock, 0, stream>>>(draft_logits, V, sa, ws);
+    if (V % 4 == 0) draft_row_sums_kernel<true, S><<<rows, kBlock, 0, stream>>>(draft_logits, V, sa, ws, mails);
+    else draft_row_sums_kernel<false, S><<<rows, kBlock, 0, stream>>>(draft_logits, V, sa, ws, mails);
 }
-static hipError_t launch_draft_row_sums(const float* draft_logits, int V, const SeqArgs& sa, double* ws, hipStream_t stream)
+static hipError_t launch_draft_row_sums(const float* draft_logits, int V, const SeqArgs& sa, double* ws, int mails, hipStream_t stream)
 {
-    if (V <= 2 * kSeg) launch_draft_row_sums_s<2>(draft_logits, V, sa, ws, stream);
-    else if (V <= 8 * kSeg) launch_draft_row_sums_s<8>(draft_logits, V, sa, ws, stream);
-    else launch_draft_row_sums_s<kMaxSeg>(draft_logits, V, sa, ws, stream);
+    if (V <= 2 * kSeg) launch_draft_row_sums_s<2>(draft_logits, V, sa, ws, mails, stream);
+    else if (V <= 8 * kSeg) launch_draft_row_sums_s<8>(draft_logits, V, sa, ws, mails, stream);
+    else launch_draft_row_sums_s<kMaxSeg>(draft_logits, V, sa, ws, mails, stream);
     return hipGetLastError();
 }
 
@@ -1033,17 +1338,20 @@ hipError_t launch_build_tree(const float* draft_logits, int V, const SeqArgs& sa
     if (cached) {
         int widest = 0;
         for (int s = 0; s < sa.n_seq; ++s) widest = max(widest, sa.node_off[s + 1] - sa.node_off[s]);
-        const int root_ring = widest >= kRingRows && build_lds_bytes(V, widest, true) <= kLdsPerWorkgroup;
-        const size_t lds_bytes = build_lds_bytes(V, widest, root_ring);
+        const bool helped = widest >= kHelpedRows && sa.n_seq * (1 + kRings) <= kHelpedBlocks;
+        const int root_ring = !helped && widest >= kRingRows && build_lds_bytes(V, widest, true) <= kLdsPerWorkgroup;
+        const size_t lds_bytes = helped ? std::max((size_t)BuildLds::row(widest) + kRings * kRing * kPlace, HelpLds::row + row_lds_bytes(V))
+                                        : build_lds_bytes(V, widest, root_ring);
+        const int grid = sa.n_seq * (helped ? 1 + kRings : 1);
         const hipError_t ea = prepare_build_tree();
         if (ea != hipSuccess) return ea;
-        const hipError_t es = launch_draft_row_sums(draft_logits, V, sa, ws, stream);
+        const hipError_t es = launch_draft_row_sums(draft_logits, V, sa, ws, helped, stream);
         if (es != hipSuccess) return es;
         if (V % 4 == 0) {
-            build_tree_waves_kernel<true><<<sa.n_seq, kBuildThreads, lds_bytes, stream>>>(
+            build_tree_waves_kernel<true><<<grid, kBuildThreads, lds_bytes, stream>>>(
                 draft_logits, V, sa, seed, tree, est_value, anc_mask, mask_words, n_built, ws, widest, root_ring, max_polls);
         } else {
-            build_tree_waves_kernel<false><<<sa.n_seq, kBuildThreads, lds_bytes, stream>>>(
+            build_tree_waves_kernel<false><<<grid, kBuildThreads, lds_bytes, stream>>>(
                 draft_logits, V, sa, seed, tree, est_value, anc_mask, mask_words, n_built, ws, widest, root_ring, max_polls);
         }
     } else if (V % 4 == 0) {

@@ -1,6 +1,6 @@
 // The greedy builder's workspace, per row (kRowSumDoubles doubles): the totals of kSums runs of kRun tokens, the row maximum
 // (already divided by the temperature), from kDrawnOffset on the tokens drawn at this position, two bytes each in the
-// order of the draws (their weights are no longer in the totals), at kMadeOffset a draw made but not asked for.
+// order of the draws (their weights are no longer in the totals), at kMadeOffset a draw made but not asked for, at kMailOffset a mailbox.
 // Host code as well as device code.
 #pragma once
 #include <stddef.h>
@@ -18,11 +18,21 @@ constexpr int kDrawnOffset = kSums + 2;
 constexpr int kDrawnEntries = DYSPEC_MAX_BUILD_NODES + 1;
 constexpr int kMadeOffset = kDrawnOffset + (kDrawnEntries + 3) / 4;
 constexpr int kMadeDoubles = 3;
-static_assert(kRowSumDoubles >= kMadeOffset + kMadeDoubles, "room for every draw of a row, and for one that is put aside");
+// Draws of a node made by another workgroup: a ring in the row of the node, 16 bytes a draw, in the place of the tokens of ranks
+// kMailRanks and on (the node's own wave makes the first few draws of such a node only), and a mailbox in the row of the helper's number.
+constexpr int kMailOffset = kMadeOffset + kMadeDoubles;
+constexpr int kMailDoubles = 3;
+constexpr int kMailRing = 64;
+constexpr int kMailRanks = 512;
+constexpr int kMailRingOffset = kDrawnOffset + kMailRanks / 4;
+static_assert(kRowSumDoubles >= kMailOffset + kMailDoubles, "room for every draw of a row, one that is put aside, and a mailbox");
+static_assert(kMailRingOffset + 2 * kMailRing <= kMadeOffset && kMailRingOffset % 2 == 0 && kRowSumDoubles % 2 == 0, "16-byte entries among the drawn tokens");
 
 __host__ __device__ inline double* ws_totals(double* ws, int row) { return ws + (size_t)row * kRowSumDoubles; }
 __host__ __device__ inline double* ws_rowmax(double* ws, int row) { return ws_totals(ws, row) + kSums; }
 __host__ __device__ inline unsigned short* ws_drawn(double* ws, int row) { return reinterpret_cast<unsigned short*>(ws_totals(ws, row) + kDrawnOffset); }
 __host__ __device__ inline double* ws_made(double* ws, int row) { return ws_totals(ws, row) + kMadeOffset; }
+__host__ __device__ inline double* ws_mail(double* ws, int row) { return ws_totals(ws, row) + kMailOffset; }
+__host__ __device__ inline double* ws_mail_ring(double* ws, int row) { return ws_totals(ws, row) + kMailRingOffset; }
 
 }  // namespace dyspec
