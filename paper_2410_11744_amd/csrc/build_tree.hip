@@ -25,7 +25,7 @@
 
 namespace dyspec {
 
-constexpr int kRing = 8, kRings = 8;        // places of a helper's ring, helpers of a tree
+constexpr int kRing = 8, kRings = 8;        // places of a ring, rings (helpers) of a tree
 constexpr int kMaxSlots = 2 * DYSPEC_MAX_BUILD_NODES + 2;
 
 // Data-parallel part (the draft softmax of every node, Algorithm 1's model call output):
@@ -232,7 +232,7 @@ __global__ __launch_bounds__(kBlock) void build_tree_kernel(
 // order (the slots themselves lie in LDS), so the pop is lane 0's.  It takes the popped node's next draw (token, R[y], the
 // new node's path key and first uniform) from
 // LDS, opens the new node's slot and the parent's next one.
-// Wave 1 draws from the root's row, which it keeps in LDS (wave_draw.h), up to kRootRing draws
+// Wave 1 draws from the root's row, which it keeps in LDS (wave_draw.h), up to kRing draws
 // ahead, or, in trees that have helpers (below), brings the draws that these make.
 // kDrawWaves waves draw for the other nodes (node i: wave i % kDrawWaves of them), one draw ahead per node and a
 // second one put aside where the node has been drawn from twice, the node of the largest slot value first: totals from the workspace (a new node's were fetched before it
@@ -250,20 +250,19 @@ __global__ __launch_bounds__(kBlock) void build_tree_kernel(
 // control has set `news` to kStop, which it does after at most N - 1 pops.  (Were an answer to stay out all the
 // same, control gives up after kBuildPolls looks: the tree ends there, and n_built says so.)
 //
-// What bounds it: the number of instructions of control's pop and of wave 1's draw (a wave alone issues one in
-// eight cycles, whatever it is; an LDS read is back after 52), and where a node is popped again at once or a tree is
-// one chain, those of a draw from memory (the trip itself is over before the Philox blocks made meanwhile).
+// What bounds it: the number of instructions of control's pop and of wave 1's draw (a wave alone issues a vector one in 4.5
+// cycles, one of eight bytes or in doubles in 5.5, a DPP move of what was just made in 12.5; an LDS read is back after 52), and
+// where a node is popped again at once or a tree is one chain, those of a draw from memory (the trip itself is over before the Philox
+// blocks made meanwhile).
 // Measured against a workgroup that popped and drew in turn, two barriers a draw, with the pass over the rows: 512 rows of
 // 32000 tokens 1378 -> 508 us (with eight drawing waves on two SIMDs 562, on all four 543: a request waits for the draw its
 // wave is at), 128 rows 346 -> 134, 32 rows of 1000 tokens 92 -> 55; a single chain of 512 nodes 1413 -> 1130.  (All before
 // the sorted list of slots, see pop_nodes.)  Of one size the time depends on the table, that is, on how often nodes
-// other than the root are popped again: 385 to 515 us over tables of 512 rows of independent normal logits.
+// are popped again: 200 to 333 us over tables of 512 rows of independent normal logits (before there were helpers, below, 470 to 960).
 constexpr int kBuildThreads = 1024;
 constexpr int kDrawWaves = kBuildThreads / kWave - 2;
-constexpr int kRootRing = 16;
 static_assert(kRing * kRings == kWave, "a lane for every place");
 constexpr uint32_t kAnswer = 0x80000000u;
-constexpr uint32_t kFromRing = kAnswer | 1023u << 15;   // | k: the node's draws come from ring k (no tree goes on after a draw of rank 1023)
 constexpr uint32_t kStop = 0u;              // news of a pop is never 0: the new node's index is not
 static_assert(DYSPEC_MAX_BUILD_NODES <= 1024 && DYSPEC_MAX_VOCAB <= (1 << 15), "parent, rank and previous sibling share a word, rank and token too");
 
@@ -281,19 +280,28 @@ struct Node {
 constexpr uint32_t kNode = sizeof(Node), kValueAt = 0, kKeyAt = 8, kOpenedAt = 16, kUAt = 20, kWordAt = 24, kChildUAt = 28, kRAt = 32, kChildKeyAt = 40;
 static_assert(kNode == 48 && offsetof(Node, value) == kValueAt && offsetof(Node, key) == kKeyAt && offsetof(Node, opened) == kOpenedAt && offsetof(Node, u) == kUAt &&
               offsetof(Node, word) == kWordAt && offsetof(Node, child_u) == kChildUAt && offsetof(Node, r) == kRAt && offsetof(Node, child_key) == kChildKeyAt, "");
+// What LDS holds of a ring: the open slot of its node, the node's last child, the rank of the draw that opens next (draws below are taken).
+struct RingState {
+    double value;
+    uint32_t last, taken;
+};
+constexpr uint32_t kTakenAt = 12;
+static_assert(sizeof(RingState) == 16 && offsetof(RingState, taken) == kTakenAt, "");
 constexpr uint32_t kPlace = kNode - kWordAt;                     // a place in a ring, addressed as if it were a node's
 // Dynamic LDS of the builder: byte offsets.
 struct BuildLds {
-    static constexpr uint32_t ring = 0;                                            // the root's draws, draw r at r % kRootRing
-    static constexpr uint32_t here = ring + kRootRing * kPlace;                    // bit 8 k: helper k runs
-    static constexpr uint32_t taken = here + 8;                                    // per ring: draws below this rank are taken
-    static constexpr uint32_t hot = taken + 4 * kRings;                            // per ring: its node
-    static constexpr uint32_t claims = hot + 4 * kRings;                           // bit k: ring k has a node
+    static constexpr uint32_t ring = 0;                                            // places of the root's ring, draw r at r % kRing; with helpers the rings lie behind the nodes
+    static constexpr uint32_t state = ring + kRing * kPlace;                       // of every ring (RingState)
+    static constexpr uint32_t here = state + 16 * kRings;                          // bit 8 k: helper k runs
+    static constexpr uint32_t hot = here + 8;                                      // per ring: its node
+    static constexpr uint32_t from = hot + 4 * kRings;                             // per ring: the rank from which on it may be used
+    static constexpr uint32_t claims = from + 4 * kRings;                           // bit k: ring k has a node
     static constexpr uint32_t bound = claims + 4;                                  // bit k: and its helper has been told
     static constexpr uint32_t news = bound + 4;                                   // new node | popped node << 10 | kRequest if it was asked for another draw
     static constexpr uint32_t n_built = news + 4;
     static constexpr uint32_t fred = n_built + 4;
     static constexpr uint32_t gone = fred + 4 * (kBuildThreads / kWave);          // drawn tokens of the run a wave is drawing from
+    static_assert(state % 16 == 0 && here % 8 == 0, "");
     static constexpr uint32_t nodes = (gone + kDrawWaves * (kRun / 8) + 15) / 16 * 16;
     __host__ __device__ static constexpr uint32_t row(int widest) { return nodes + kNode * widest; }
 };
@@ -344,20 +352,20 @@ __device__ __attribute__((noinline, aligned(64))) void draw_for_root(uint32_t ld
             child = join_key(ck);
         }
         uint32_t news = lds_now(lds_at<uint32_t>(lds + BuildLds::news));
-        uint32_t taken = lds_now(lds_at<uint32_t>(lds + BuildLds::taken));
+        uint32_t taken = lds_now(lds_at<uint32_t>(lds + BuildLds::state + kTakenAt));
         Drawn d;
         const bool drawn = draw_wave_row(row, (double)readlane_f32(us, rank & 63), &d);
         const double R = drawn ? d.wy / d.W : -1.0;
         for (;;) {
             if (uniform(news) == kStop) return;
-            if (rank - (int)uniform(taken) < kRootRing) break;
+            if (rank - (int)uniform(taken) < kRing) break;
             __builtin_amdgcn_s_sleep(1);
             news = lds_now(lds_at<uint32_t>(lds + BuildLds::news));
-            taken = lds_now(lds_at<uint32_t>(lds + BuildLds::taken));
+            taken = lds_now(lds_at<uint32_t>(lds + BuildLds::state + kTakenAt));
         }
         // (lane rank % 64 has the child's key at hand)
         if (lane == (rank & 63))
-            publish(lds + BuildLds::ring - kWordAt + (uint32_t)(rank % kRootRing) * kPlace, R, child, child_u, kAnswer | ((uint32_t)rank << 15) | (uint32_t)(drawn ? d.y : 0));
+            publish(lds + BuildLds::ring - kWordAt + (uint32_t)(rank % kRing) * kPlace, R, child, child_u, kAnswer | ((uint32_t)rank << 15) | (uint32_t)(drawn ? d.y : 0));
         if (!drawn) return;
     }
 }
@@ -666,10 +674,11 @@ __device__ __attribute__((noinline, aligned(64))) void draw_for_nodes(uint32_t l
 // Only a helper that is there is claimed: nobody waits for a workgroup that has no CU, and a tree without its helpers is built by its own waves.
 // (A draw is the same whoever makes it, to the rounding of the sums behind it.)
 //
-// Measured, with the pass over the rows, 512 rows of 32000 tokens, four tables: 966, 474, 584, 555 -> 334, 323, 336, 323 us; all draws from
-// the root 381 -> 361, from another node 1096 -> 372; 1024 rows of 32768 tokens 1874 -> 598 (the root's row never fitted there), 64 rows
-// 124 -> 80, 128 rows 222, 135, 178 -> 128, 111, 125; a chain 559 -> 553.  What is left is control's pop, 0.53 us, or where one
-// node has all the draws its helper's draw, 0.63.
+// Measured, with the pass over the rows, 512 rows of 32000 tokens, four tables, without helpers, with them and with their draws popped
+// many at a time (pop_nodes): 961, 470, 582, 553 -> 334, 320, 332, 319 -> 332, 201, 225, 211 us; all draws from
+// the root 381 -> 360, from another node 1091 -> 371; 1024 rows of 32768 tokens 1876 -> 597 -> 550 (the root's row never fitted there), 64 rows
+// 124 -> 80, 128 rows 222, 134, 177 -> 128, 110, 123 -> 118, 88, 107; a chain 559 -> 554 -> 550.  What is left is, where one
+// node has all the draws, its helper's draw, 0.63 us, and where slots of single draws come between, their pop, 0.5 us.
 // kHelpedRows: below, a node has hardly the draws to pay for a row's loading (some 8 us before the first draw is there).
 constexpr int kClaimRank = 3, kOwnDraws = 8, kRootOwnDraws = 2;        // draws the node's own wave makes after the claim
 constexpr int kHelpedRows = 64;             // of the widest tree of a batch that has helpers,
@@ -833,7 +842,7 @@ __device__ __attribute__((noinline, aligned(64))) void bring_draws(uint32_t lds_
     while (uniform(lds_now(lds_at<uint32_t>(lds + BuildLds::news))) != kStop) {
         const uint32_t claims = uniform(lds_now(lds_at<uint32_t>(lds + BuildLds::claims)));
         const bool used = claimed >> k & 1u, all_here = here == 0x0101010101010101ull;
-        const int taken = used ? (int)lds_now(lds_at<uint32_t>(lds + BuildLds::taken + 4 * k)) : 0;
+        const int taken = used ? (int)lds_now(lds_at<uint32_t>(lds + BuildLds::state + 16 * k + kTakenAt)) : 0;
         const int rank = taken + ((j - taken) & (kRing - 1));        // the draw this place is for
         const bool wanted = used && rank > put, get = wanted && rank < count;
         // (all of a look's loads are on their way together)
@@ -888,6 +897,23 @@ __device__ __attribute__((noinline, aligned(64))) void bring_draws(uint32_t lds_
     if (first) agent_store(mail_taken(mail), kStopped);
 }
 
+// The larger of two values, neither a NaN (fmax would first quiet what it cannot know to be none).
+__device__ __forceinline__ double larger(double a, double b)
+{
+    double r;
+    asm("v_max_f64 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+    return r;
+}
+// Largest of the rings' non-negative values (the same in the kRing lanes of each), in scalar registers.
+__device__ __forceinline__ double largest_of_rings(double x)
+{
+    static_assert(kRing == 8 && kRings == 8, "eight by eight lanes");
+    x = larger(x, dpp_or_zero<0x118>(x));
+    x = larger(x, dpp_or_zero<kDppBcast15, 0xa>(x));
+    x = larger(x, dpp_or_zero<kDppBcast31, 0xc>(x));
+    return readlane_f64(x, 63);
+}
+
 // Wave 0: pops and appends.  Returns the number of rows built, its complement if a draw stayed out.  Row i's parent | rank << 10 | previous
 // sibling << 20 goes to `parent` for the time being.
 //
@@ -902,6 +928,16 @@ __device__ __attribute__((noinline, aligned(64))) void bring_draws(uint32_t lds_
 // Against the best of each lane's nodes kept in the lane and the maximum over the lanes found at each pop, and the other
 // nodes of the popped one's lane looked over again: a pop whose draw is there 0.61 -> 0.51 us; with the draws' names
 // for 64 ranks at once (DrawNames) 512 rows of 32000 tokens 441 -> 417, 495 -> 471 and 570 -> 547 us on three tables.
+//
+// The slots of nodes whose draws come from a ring are not in the list.  The lanes look at all rings at once, lane j of a ring at its j-th
+// next draw: the draws that are there give the slots that the node will have, v (1 - R[y]) from one to the next, and those of the nodes to be
+// made, v R[y].  The pops of an order are then known as far as slots are above every other one that may be open meanwhile: these draws are
+// popped together, each lane making a node (its index: how many of them are larger).  A ring's slots only get smaller, so a ring's draws
+// stay in their order.  Equal slots are popped singly, the one opened first first.  (What it gives: the helpers' figures.)
+//
+// Pops from the list make a loop of their own in which no branch depends on the lane: 768 rows, deviation 10, all pops but 49 from the list:
+// 657 us before there were rings, 691 with the stores and moves under `lane == 0`, 644 now.  (As a function that is called, it saved and restored 35
+// scalar registers and 2 vector registers in memory: 0.3 to 0.5 us of every tree, 11.9 us at the least.)
 constexpr int kRelisted = 16;           // found one after the other
 constexpr int kDppWaveShl1 = 0x130;     // lane i: lane i + 1's
 constexpr int kDppWaveShr1 = 0x138;     // lane i: lane i - 1's
@@ -915,7 +951,7 @@ struct Slots {
     int node;               // and its node (| kSure: no slot left out comes before it, even if one is as large)
     double unlisted;        // no open slot outside the list is larger (the same in every lane)
 };
-constexpr int kSure = 1 << 16, kRingOne = 1 << 20;       // | kRingOne * k: the node's draws come from ring k
+constexpr int kSure = 1 << 16;
 
 // The list made again from the slots of nodes 0 .. n - 1, node q in lane q % 64: the slots whose value's high word is above a line that
 // is searched for, 32 to 64 of them where that can be had in few steps, each put where it belongs as a pop does.  Where the values
@@ -1037,155 +1073,299 @@ __device__ __attribute__((noinline)) Slots relist(uint32_t nodes_, int n_)
     return s;
 }
 
-__device__ __attribute__((noinline, aligned(64))) int pop_nodes(uint32_t lds_, uint32_t rings_, int root_ring_, int helped_, int N_, int max_polls_, int* parent_, int* token_, float* est_value_)
+// A node that has no ring yet, popped for the draw of that rank: the ring (+ 1) that has its draws from the next one on, else 0.  Claims one
+// for it if it is time.  (Control alone; what it remembers is in LDS.)
+__device__ __forceinline__ uint32_t ring_for(uint32_t lds_, uint32_t p_, uint32_t rank_, uint32_t n_, uint32_t N_)
 {
-    const uint32_t lds = uniform(lds_), nodes = lds + BuildLds::nodes, rings = uniform(rings_) - kWordAt;
+    const uint32_t lds = uniform(lds_), p = uniform(p_), rank = uniform(rank_), n = uniform(n_), N = uniform(N_);
+    const uint32_t lane = threadIdx.x & 63, claims = uniform(*lds_at<uint32_t>(lds + BuildLds::claims));
+    const u64 has = ballot(*lds_at<uint32_t>(lds + BuildLds::hot + 4 * (lane % kRings)) == p) & claims & ((1u << kRings) - 1u);
+    if (has) {
+        const uint32_t c = (uint32_t)__builtin_ctzll(has);
+        const uint32_t from = uniform(*lds_at<uint32_t>(lds + BuildLds::from + 4 * c)), bound = uniform(lds_now(lds_at<uint32_t>(lds + BuildLds::bound)));
+        return rank + 1u >= from && (bound >> c & 1u) ? c + 1u : 0u;
+    }
+    const uint32_t c = p == 0 ? 0u : (uint32_t)__builtin_ctz(~(claims | 1u));
+    if (c < kRings && rank < (uint32_t)kMailRanks / 2 && n + kHelpedLeft < N && ((uniform(lds_now(lds_at<u64>(lds + BuildLds::here))) >> (8 * c)) & 1ull)) {
+        const uint32_t from = rank + 1u + (p == 0 ? kRootOwnDraws : kOwnDraws);
+        *lds_at<uint32_t>(lds + BuildLds::state + 16 * c + kTakenAt) = from;
+        *lds_at<uint32_t>(lds + BuildLds::from + 4 * c) = from;
+        *lds_at<uint32_t>(lds + BuildLds::hot + 4 * c) = p;
+        lds_set(lds_at<uint32_t>(lds + BuildLds::claims), claims | 1u << c);
+    }
+    return 0u;
+}
+
+// base[index], the index in a vector register
+template <typename T> __device__ __forceinline__ void put_row(T* base, uint32_t index, T value) { *reinterpret_cast<T*>(reinterpret_cast<char*>(base) + (size_t)(4u * index)) = value; }
+
+__device__ __forceinline__ int pop_nodes(uint32_t lds_, uint32_t rings_, int root_ring_, int helped_, int N_, int max_polls_, int* parent_, int* token_, float* est_value_)
+{
+    const uint32_t lds = uniform(lds_), nodes = lds + BuildLds::nodes, states = lds + BuildLds::state;
     const bool root_ring = uniform(root_ring_) != 0, helped = uniform(helped_) != 0;
     const uint32_t N = (uint32_t)uniform(N_);
-    const uint32_t ring_mask = root_ring ? kRootRing - 1 : kRing - 1;
     int *const parent = uniform(parent_), *const token = uniform(token_);
     float* const est_value = uniform(est_value_);
-    const uint32_t lane = threadIdx.x & 63;
-    Slots s = { lane == 0 ? 1.0 : -1.0, root_ring ? kRingOne : 0, 0.0 };
-    // ring k in lane k (1 ..): place of its next draw and how the word there begins; in lane 0 what an answer begins with
-    const uint32_t ring_first = rings + kPlace * kRing * (lane - 1u);
-    uint32_t ring_place = ring_first, ring_want = kAnswer;
-    int ring_node = -1;                             // its node, from the claim on; the first rank that the ring holds
-    uint32_t ring_from = 0, next_helper = 1, claims = 0;
+    const uint32_t lane = threadIdx.x & 63, k = lane / kRing, j = lane % kRing;
+    Slots s = { lane == 0 && !root_ring ? 1.0 : -1.0, 0, 0.0 };
+    // the rings that are in use (all lanes of one); per lane of ring k: its first place, its node, the
+    // rank of its next draw
+    u64 live = root_ring ? 0xffull : 0ull;
+    const uint32_t places = uniform(rings_) - kWordAt + (helped ? kPlace * kRing * k : 0u);
+    uint32_t ring_node = 0, next = 0;
     uint32_t n = 1;
     int polls = uniform(max_polls_);
-    bool lost = false;
-    uint32_t place_n = nodes + kNode;               // LDS of node n
-    uint32_t words = 0, froms = 0;                  // of the last 64 rows, row i in lane i % 64; written out together
-    float values = 1.0f;
-    const auto write_out = [&](uint32_t first) __attribute__((always_inline)) {
-        token[first + lane] = first + lane == 0 ? -1 : (int)(words & 0x7fffu);
-        est_value[first + lane] = values;
-        parent[first + lane] = (int)((froms & 0xfff003ffu) | ((words >> 15) & 1023u) << 10);
+    if (lane == 0) {
+        token[0] = -1;
+        est_value[0] = 1.0f;
+    }
+    // a new slot into the list, behind the slots (its first ones) of that mask; what finds no place is left out
+    const auto insert = [&](double x, int node, u64 before) __attribute__((always_inline)) {
+        const double out = before != ~0ull ? readlane_f64(s.value, 63) : x;
+        const double down_v = dpp_or_own<kDppWaveShr1>(s.value);
+        const int down_n = dpp_or_own<kDppWaveShr1>(s.node);
+        const u64 upto = before << 1 | 1ull, at = upto & ~before;
+        s.value = __builtin_amdgcn_inverse_ballot_w64(upto) ? s.value : down_v;
+        s.node = __builtin_amdgcn_inverse_ballot_w64(upto) ? s.node : down_n;
+        s.value = __builtin_amdgcn_inverse_ballot_w64(at) ? x : s.value;
+        s.node = __builtin_amdgcn_inverse_ballot_w64(at) ? node : s.node;
+        s.unlisted = larger(s.unlisted, out);
     };
+    const auto list_sure = [&]() __attribute__((always_inline)) {       // the list's first slot is the best of all that no ring has
+        return (ballot(s.value > s.unlisted) & 1ull) || (uniform((uint32_t)s.node) & kSure);
+    };
+    bool watch = helped, lost = false;              // for nodes to give a ring to
+    uint32_t to_ring = 0;                           // the ring + 1 that has taken over the node popped last
     while (n < N) {
-        // ---- the largest value
-        uint32_t slot = uniform((uint32_t)s.node);
-        if (__builtin_expect(!(ballot(s.value > s.unlisted) & 1ull) && !(slot & kSure), 0)) {
-            if (!(ballot(s.unlisted > 0.0) & 1ull)) break;              // no slot is open
-            s = relist(nodes, (int)n);
-            const uint32_t told = *lds_at<uint32_t>(nodes + kNode * ((uint32_t)s.node & (kSure - 1)) + kWordAt);
-            if ((told & ~15u) == kFromRing) s.node += kRingOne * (int)(told & 15u);
-            if (!(ballot(s.value > 0.0) & 1ull)) break;
-            slot = uniform((uint32_t)s.node);
-        }
-        const uint32_t p = slot & (kSure - 1), ring = slot / kRingOne;
-        const double v = uniform(s.value);
-        // ---- its node's next draw; the bits of the word that tell: the answer's, in a ring the draw's rank as well
-        const uint32_t place_p = nodes + kNode * p;
-        const uint32_t ring_at = (uint32_t)__builtin_amdgcn_readlane((int)ring_place, (int)ring), want = (uint32_t)__builtin_amdgcn_readlane((int)ring_want, (int)ring);
-        const uint32_t place = ring ? ring_at : place_p, mask = ring ? kAnswer | (1023u << 15) : kAnswer;
-        uint32_t w = lds_now(lds_at<uint32_t>(place + kWordAt));
-        double R = __longlong_as_double((long long)lds_now(lds_at<u64>(place + kRAt)));   // (as good as the word that was read before it)
-        u64 child = lds_now(lds_at<u64>(place + kChildKeyAt));
-        uint32_t child_u = lds_now(lds_at<uint32_t>(place + kChildUAt));
-        const uint32_t o = *lds_at<uint32_t>(place_p + kOpenedAt);
-        w = uniform(w);
-        while ((w & mask) != want && --polls > 0) {
-            w = lds_now(lds_at<uint32_t>(place + kWordAt));
-            R = __longlong_as_double((long long)lds_now(lds_at<u64>(place + kRAt)));
-            child = lds_now(lds_at<u64>(place + kChildKeyAt));
-            child_u = lds_now(lds_at<uint32_t>(place + kChildUAt));
-            w = uniform(w);
-        }
         if (polls <= 0) { lost = true; break; }
-        const int R_hi = uniform(__double2hiint(R));
-        if (__builtin_expect(R_hi < 0, 0)) {
-            if (R_hi == (int)0xbff00000u) break;                        // (-1) nothing left to sample under p
-            // the quotient of two infinite weights, a NaN with its sign bit set: the token holds all that is left, at a
-            // temperature so small that the row's maximum over it is rounded by more than the range of exp
-            R = 1.0;
+        if (to_ring) {                              // (the ring's words are control's own and in place)
+            const uint32_t state = states + 16u * (to_ring - 1u);
+            if (k == to_ring - 1u) {
+                ring_node = *lds_at<uint32_t>(lds + BuildLds::hot + 4u * (to_ring - 1u));
+                next = *lds_at<uint32_t>(state + kTakenAt);
+            }
+            live |= 0xffull << (kRing * (to_ring - 1u));
+            watch = live != ~0ull;
+            to_ring = 0;
         }
-        // ---- node n = child number `rank` of p, its slot and p's next one (p's is opened first)
-        const double v0 = v * R, v1 = v * (1.0 - R);
-        const uint32_t rank = (w >> 15) & 1023u;
-        uint32_t next_slot = slot & ~(uint32_t)kSure, news = n | (p << 10);
-        uint32_t tell_at = place_p + kWordAt, tell = ((rank + 1u) << 15) | ((uint32_t)__double2hiint(v1) >> 16);
-        if (ring) {
-            tell_at = lds + BuildLds::taken - 4u + 4u * ring;
-            tell = rank + 1u;
-            const uint32_t to = kPlace * ((rank + 1u) & ring_mask);
-            ring_place = lane == ring ? ring_first + to : ring_place;
-            ring_want = lane == ring ? kAnswer | ((rank + 1u) << 15) : ring_want;
-        } else {
-            news |= kRequest;
-            if (__builtin_expect(helped && (rank >= (uint32_t)kClaimRank || p == 0), 0)) {
-                const u64 has = ballot(ring_node == (int)p);
-                if (has) {
-                    const uint32_t k = (uint32_t)__builtin_ctzll(has);
-                    if (rank + 1u >= (uint32_t)__builtin_amdgcn_readlane((int)ring_from, (int)k) &&
-                        (uniform(lds_now(lds_at<uint32_t>(lds + BuildLds::bound))) >> (k - 1u) & 1u)) {
-                        // p's draws come from the ring from the next one on
-                        next_slot += kRingOne * k;
-                        news ^= kRequest;
-                        tell = kFromRing | k;
-                        if (lane == 0) lds_set(lds_at<uint32_t>(lds + BuildLds::taken + 4 * (k - 1u)), rank + 1u);
-                        const uint32_t to = kPlace * ((rank + 1u) & ring_mask);
-                        if (lane == k) { ring_place = ring_first + to; ring_want = kAnswer | ((rank + 1u) << 15); }
+        // ---- the rings' draws: lane j of a ring has the j-th next one
+        typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+        const double list = larger(uniform(s.value), s.unlisted);
+        const u32x4 state = *lds_at<u32x4>(states + 16u * k);
+        const double V = __hiloint2double((int)state.y, (int)state.x);
+        if (ballot(V >= list) & live) {             // the best slot is a ring's
+            const uint32_t rank = next + j, place = places + kPlace * (rank & (kRing - 1));
+            const uint32_t w = lds_now(lds_at<uint32_t>(place + kWordAt));
+            const double R = __longlong_as_double((long long)lds_now(lds_at<u64>(place + kRAt)));      // (as good as the word that was read before it)
+            const u64 child = lds_now(lds_at<u64>(place + kChildKeyAt));
+            const uint32_t child_u = lds_now(lds_at<uint32_t>(place + kChildUAt));
+            constexpr u64 kFirsts = 0x0101010101010101ull, kButLasts = ~(kFirsts << 7);
+            const bool there = (w >> 15) == (0x10000u | rank);
+            // those that are there one after the other
+            const u64 some = ballot(there && __double2hiint(R) >= 0) & live;
+            u64 ok = some & (((some & kButLasts) + kFirsts) ^ kButLasts);
+            // the slot that each is popped from, as deep as slots are above the list's, and what it opens
+            const double q = 1.0 - R;
+            double v = V;
+            u64 deep = kFirsts;
+#pragma unroll
+            for (int t = 1; t < kRing; ++t) {
+                if (!(ok & (kFirsts << (t - 1)) & ballot(v > list))) break;
+                const double up = dpp_or_zero<0x111>(v * q);
+                v = __builtin_amdgcn_inverse_ballot_w64(kFirsts << t) ? up : v;
+                deep |= kFirsts << t;
+            }
+            ok &= deep;
+            double v0 = v * R, v1 = v * q;
+            // No slot that may be open meanwhile is above `bar`: the list's, those of the draws that come next or are not there, and the
+            // first slots of the nodes that these draws make.  So all draws above it are popped, the largest first.  (High words;
+            // draws that differ from it below those come one at a time.)
+            int bar = __builtin_amdgcn_inverse_ballot_w64(ok) ? __double2hiint(v0) : 0;
+            bar = max(bar, __builtin_amdgcn_inverse_ballot_w64(ok & ~((ok >> 1) & kButLasts)) ? __double2hiint(v1) : __builtin_amdgcn_inverse_ballot_w64(live & ~ok & kFirsts) ? __double2hiint(V) : 0);
+            bar = wave_max_dpp_int(max(bar, __double2hiint(list)));
+            u64 take = ballot(__double2hiint(v) > bar) & ok;
+            uint32_t pos = 0;                       // how many are larger
+            if (take & (take - 1)) {
+                uint32_t same = 0;
+                for (u64 m = take; m; m &= m - 1) {
+                    const double x = readlane_f64(v, __builtin_ctzll(m));
+                    pos += x > v;
+                    same += x == v;
+                }
+                if (ballot(same > 1) & take) take = 0;      // two as large: one at a time
+            }
+            bool ring_next = true;
+            if (take == 0) {
+                // ---- one slot by itself: the best of the rings, of equal ones the one opened first (the order of the nodes' last
+                //      children), or the list's first if that is as good and was opened before
+                const double best_ring = largest_of_rings(__builtin_amdgcn_inverse_ballot_w64(live) ? V : 0.0);
+                u64 heads = ballot(V == best_ring) & live & kFirsts;
+                ring_next = (ballot(best_ring > 0.0) & 1ull) != 0;
+                if ((ballot(s.value == best_ring) | ballot(s.unlisted == best_ring)) & 1ull) {
+                    if (!list_sure()) {
+                        s = relist(nodes, (int)n);
+                        continue;
                     }
-                } else {
-                    const uint32_t k = p == 0 ? 0u : next_helper;
-                    if (k < kRings && rank < (uint32_t)kMailRanks / 2 && n + kHelpedLeft < N && ((uniform(lds_now(lds_at<u64>(lds + BuildLds::here))) >> (8 * k)) & 1ull)) {
-                        const uint32_t from = rank + 1u + (p == 0 ? kRootOwnDraws : kOwnDraws);
-                        claims |= 1u << k;
-                        if (lane == 0) {
-                            *lds_at<uint32_t>(lds + BuildLds::taken + 4 * k) = from;
-                            *lds_at<uint32_t>(lds + BuildLds::hot + 4 * k) = p;
-                            lds_set(lds_at<uint32_t>(lds + BuildLds::claims), claims);
+                    const uint32_t o = uniform(*lds_at<uint32_t>(nodes + kNode * (uniform((uint32_t)s.node) & (kSure - 1)) + kOpenedAt));
+                    if (!(ballot(s.value < best_ring) & 1ull) && !(ballot(2u * state.z < o) & heads)) ring_next = false;
+                }
+                if (ring_next) {
+                    int l = __builtin_ctzll(heads);
+                    uint32_t first = (uint32_t)__builtin_amdgcn_readlane((int)state.z, l);
+                    for (u64 m = heads & (heads - 1); m; m &= m - 1) {
+                        const uint32_t z = (uint32_t)__builtin_amdgcn_readlane((int)state.z, __builtin_ctzll(m));
+                        if (z < first) { first = z; l = __builtin_ctzll(m); }
+                    }
+                    take = 1ull << l;
+                    pos = 0;
+                    if (!(ok & take)) {
+                        if (!(ballot(there) & take)) {              // its draw is still out
+                            const uint32_t at = (uint32_t)__builtin_amdgcn_readlane((int)place, l), want = 0x10000u | (uint32_t)__builtin_amdgcn_readlane((int)rank, l);
+                            while ((uniform(lds_now(lds_at<uint32_t>(at + kWordAt))) >> 15) != want && --polls > 0);
+                            continue;
                         }
-                        if (p != 0) ++next_helper;
-                        if (lane == k + 1) { ring_node = (int)p; ring_from = from; }
+                        if (__builtin_amdgcn_readlane(__double2hiint(R), l) == (int)0xbff00000u) break;        // (-1) nothing left to sample
+                        v0 = v;                     // the quotient of two infinite weights (see below)
+                        v1 = 0.0;
                     }
                 }
             }
+            if (ring_next) {
+                // ---- nodes n .. by their places, and the rings' next slots
+                if ((uint32_t)__builtin_popcountll(take) > N - n) take &= ballot(pos < N - n);
+                const uint32_t i = n + pos;
+                const uint32_t beside = (uint32_t)dpp_or_zero<0x111>((int)i), before = j == 0 ? state.z : beside;         // the sibling before (asked for by all lanes)
+                if (__builtin_amdgcn_inverse_ballot_w64(take)) {
+                    const uint32_t place_i = nodes + kNode * i;
+                    *lds_at<u64>(place_i + kKeyAt) = child;
+                    *lds_at<uint32_t>(place_i + kUAt) = child_u;
+                    *lds_at<double>(place_i + kValueAt) = v0;
+                    keep_order();
+                    lds_set(lds_at<uint32_t>(place_i + kWordAt), (uint32_t)__double2hiint(v0) >> 16);          // request of draw 0
+                    put_row(token, i, (int)(w & 0x7fffu));
+                    put_row(est_value, i, (float)v);
+                    put_row(parent, i, (int)(ring_node | rank << 10 | before << 20));
+                }
+                const u64 ends = take & ~((take >> 1) & kButLasts);
+                if (__builtin_amdgcn_inverse_ballot_w64(ends))
+                    *lds_at<u32x4>(states + 16u * k) = u32x4{ (uint32_t)__double2loint(v1), (uint32_t)__double2hiint(v1), i, rank + 1u };
+                n = uniform(n + (uint32_t)__builtin_popcountll(take));
+                if (lane == 0) lds_set(lds_at<uint32_t>(lds + BuildLds::news), n - 1u);
+                next += (uint32_t)__builtin_popcount((uint32_t)(take >> (kRing * k)) & 0xffu);
+                // ---- the new nodes' slots
+                const double lowest = readlane_f64(s.value, 63);
+                for (u64 m = ballot(v0 > s.unlisted && !(v0 > lowest)) & take; m; m &= m - 1) s.unlisted = larger(s.unlisted, readlane_f64(v0, __builtin_ctzll(m)));
+                for (u64 m = ballot(v0 > s.unlisted && v0 > lowest) & take; m; m &= m - 1) {
+                    const int l = __builtin_ctzll(m);
+                    const double x = readlane_f64(v0, l);
+                    const int xi = __builtin_amdgcn_readlane((int)i, l);
+                    // (of equal ones the one opened first: those listed before, or this time as an earlier node)
+                    insert(x, xi, ballot(s.value > x) | (ballot(s.value == x) & ballot((s.node & (kSure - 1)) < xi)));
+                }
+                continue;
+            }
         }
-        if (lane == 0) {                            // what other waves wait for first; the slots' values are control's own
+        // ---- the largest value of the list
+        if (__builtin_expect(!list_sure(), 0)) {
+            if (!(ballot(s.unlisted > 0.0) & 1ull)) break;              // no slot is open
+            s = relist(nodes, (int)n);
+            continue;
+        }
+        // One after the other while it is above the rings' and those left out.  No branch here depends on the lane (and so all lanes write
+        // what one would): the loop is left to scalar branches as it stands then, else every path through it is a chain of copies.
+        double line = live ? larger(s.unlisted, largest_of_rings(__builtin_amdgcn_inverse_ballot_w64(live) ? V : 0.0)) : s.unlisted;
+        enum { kGoOn, kEnded, kLost };
+        int status = kGoOn;
+        do {
+            const uint32_t p = uniform((uint32_t)s.node) & (kSure - 1);
+            const double v = uniform(s.value);
+            // ---- its node's next draw
+            const uint32_t place_p = nodes + kNode * p;
+            uint32_t w = lds_now(lds_at<uint32_t>(place_p + kWordAt));
+            double R = __longlong_as_double((long long)lds_now(lds_at<u64>(place_p + kRAt)));       // (as good as the word that was read before it)
+            u64 child = lds_now(lds_at<u64>(place_p + kChildKeyAt));
+            uint32_t child_u = lds_now(lds_at<uint32_t>(place_p + kChildUAt));
+            const uint32_t o = *lds_at<uint32_t>(place_p + kOpenedAt);
+            w = uniform(w);
+            while (__builtin_expect(!(w & kAnswer), 0)) {
+                if (--polls <= 0) break;
+                w = lds_now(lds_at<uint32_t>(place_p + kWordAt));
+                R = __longlong_as_double((long long)lds_now(lds_at<u64>(place_p + kRAt)));
+                child = lds_now(lds_at<u64>(place_p + kChildKeyAt));
+                child_u = lds_now(lds_at<uint32_t>(place_p + kChildUAt));
+                w = uniform(w);
+            }
+            if (polls <= 0) { status = kLost; break; }
+            const int R_hi = uniform(__double2hiint(R));
+            if (__builtin_expect(R_hi < 0, 0)) {
+                if (R_hi == (int)0xbff00000u) { status = kEnded; break; }       // (-1) nothing left to sample under p
+                // the quotient of two infinite weights, a NaN with its sign bit set: the token holds all that is left, at a
+                // temperature so small that the row's maximum over it is rounded by more than the range of exp
+                R = 1.0;
+            }
+            // ---- node n = child number `rank` of p, its slot and p's next one (p's is opened first)
+            const double v0 = v * R;
+            double v1 = v * (1.0 - R);
+            const uint32_t rank = (w >> 15) & 1023u;
+            uint32_t news = n | (p << 10) | kRequest, tell = ((rank + 1u) << 15) | ((uint32_t)__double2hiint(v1) >> 16);
+            if (__builtin_expect(watch && (rank == (uint32_t)kClaimRank || rank >= (uint32_t)(kClaimRank + kOwnDraws) || p == 0), 0)) {
+                to_ring = ring_for(lds, p, rank, n, N);
+                if (to_ring) {                      // ... and p's slot is the ring's
+                    const uint32_t state = states + 16u * (to_ring - 1u);
+                    *lds_at<double>(state) = v1;
+                    *lds_at<uint32_t>(state + 8u) = n;
+                    lds_set(lds_at<uint32_t>(state + kTakenAt), rank + 1u);
+                    v1 = 0.0;
+                    news ^= kRequest;
+                    tell = kAnswer;
+                }
+            }
+            // what other waves wait for first; the slots' values are control's own
+            const uint32_t place_n = nodes + kNode * n;
             *lds_at<u64>(place_n + kKeyAt) = child;
             *lds_at<uint32_t>(place_n + kUAt) = child_u;
             keep_order();
             lds_set(lds_at<uint32_t>(place_n + kWordAt), (uint32_t)__double2hiint(v0) >> 16);       // request of draw 0
-            lds_set(lds_at<uint32_t>(tell_at), tell);
+            lds_set(lds_at<uint32_t>(place_p + kWordAt), tell);
             lds_set(lds_at<uint32_t>(lds + BuildLds::news), news);
             *lds_at<double>(place_n + kValueAt) = v0;
             *lds_at<double>(place_p + kValueAt) = v1;
             *lds_at<uint32_t>(place_p + kOpenedAt) = 2u * n;
+            put_row(token, n, (int)(w & 0x7fffu));
+            put_row(est_value, n, (float)v);
+            put_row(parent, n, (int)(p | rank << 10 | (o >> 1) << 20));
+            // ---- The first slot goes, p's next and the new node's come behind those at least as good: up to where the better one of the two
+            // goes the slots move up, behind the other's place down.  (Masks of lanes; the first slot is at least as good as either.)
+            const bool in = ballot(v0 > s.unlisted) & 1ull;         // (else the new one is left out, as it is if there is no place)
+            const u64 g1 = ballot(s.value >= v1) >> 1, g0 = in ? ballot(s.value >= v0) >> 1 : ~0ull;
+            const u64 high = g1 & g0, low = (g1 | g0) << 1 | 1ull;
+            const u64 first = ballot(!(v0 > v1)) | (in ? 0ull : ~0ull);         // p's is the better one (of equal ones it was opened first)
+            const bool p_first = first & 1ull;
+            const double best = __builtin_amdgcn_inverse_ballot_w64(first) ? v1 : v0, other = __builtin_amdgcn_inverse_ballot_w64(first) ? v0 : v1;
+            const int best_n = (int)(p_first ? p : n), other_n = (int)(p_first ? n : p);
+            if (in) {
+                const double out = low != ~0ull ? readlane_f64(s.value, 63) : other;
+                s.unlisted = larger(s.unlisted, out);
+                line = larger(line, out);
+            }
+            const double up_v = dpp_or_own<kDppWaveShl1>(s.value), down_v = dpp_or_own<kDppWaveShr1>(s.value);
+            const int up_n = dpp_or_own<kDppWaveShl1>(s.node), down_n = dpp_or_own<kDppWaveShr1>(s.node);
+            const u64 at_high = (high << 1 | 1ull) & ~high, at_low = (low << 1 | 1ull) & ~low, above = ~(low << 1 | 1ull);
+            const auto pick = [&](auto own, auto up, auto b, auto l, auto down) __attribute__((always_inline)) {
+                own = __builtin_amdgcn_inverse_ballot_w64(high) ? up : own;
+                own = __builtin_amdgcn_inverse_ballot_w64(at_high) ? b : own;
+                own = __builtin_amdgcn_inverse_ballot_w64(at_low) ? l : own;
+                return __builtin_amdgcn_inverse_ballot_w64(above) ? down : own;
+            };
+            s.value = pick(s.value, up_v, best, other, down_v);
+            s.node = pick(s.node, up_n, best_n, other_n, down_n);
+            ++n;
+        } while (n < N && !to_ring && (ballot(s.value > line) & 1ull));
+        if (status != kGoOn) {
+            lost = status == kLost;
+            break;
         }
-        // ---- p's next slot goes behind the slots at least as good, which move up (a closed one, value 0, to the end)
-        const uint32_t c = (uint32_t)__builtin_popcountll(ballot(s.value >= v1) >> 1);
-        if (c == 0) {
-            if (lane == 0) { s.value = v1; s.node = (int)next_slot; }   // (its next slot is a new one: not kSure)
-        } else {
-            const double up_v = dpp_or_own<kDppWaveShl1>(s.value);
-            const int up_n = dpp_or_own<kDppWaveShl1>(s.node);
-            s.value = lane < c ? up_v : lane == c ? v1 : s.value;
-            s.node = lane < c ? up_n : lane == c ? (int)next_slot : s.node;
-        }
-        // ---- the new node's likewise, the ones behind it move down; what finds no place is left out
-        if (ballot(v0 > s.unlisted)) {
-            const uint32_t at = (uint32_t)__builtin_popcountll(ballot(s.value >= v0));
-            const double last = readlane_f64(s.value, 63);
-            const double out = at < kWave ? last : v0;
-            const double down_v = dpp_or_own<kDppWaveShr1>(s.value);
-            const int down_n = dpp_or_own<kDppWaveShr1>(s.node);
-            s.value = lane > at ? down_v : lane == at ? v0 : s.value;
-            s.node = lane > at ? down_n : lane == at ? (int)n : s.node;
-            s.unlisted = fmax(s.unlisted, out);
-        }
-        if (lane == (n & 63)) {
-            words = w;
-            values = (float)v;
-            froms = p | o << 19;                    // (a later child's o is twice the previous sibling)
-        }
-        ++n;
-        place_n += kNode;
-        if ((n & 63) == 0) write_out(n - kWave);    // rows n - 64 .. n - 1 are complete
     }
-    if ((n & 63) > lane) write_out(n & ~63u);
     return lost ? (int)~n : (int)n;
 }
 
@@ -1196,7 +1376,8 @@ __global__ __launch_bounds__(kBuildThreads) void build_tree_waves_kernel(
     int mask_words, int* __restrict__ n_built, double* ws, int widest, int root_ring, int max_polls)
 {
     extern __shared__ __attribute__((aligned(16))) unsigned char dyn[];
-    const uint32_t lds = lds_base(dyn);
+    uint32_t lds = lds_base(dyn);
+    asm("" : "+s"(lds));        // (a constant known to the link only, else: the roles' loops would load it from memory time and again)
     const uint32_t nodes = lds + BuildLds::nodes, row_at = lds + BuildLds::row(widest);
     const int tid = threadIdx.x;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -1213,17 +1394,19 @@ __global__ __launch_bounds__(kBuildThreads) void build_tree_waves_kernel(
     const uint2 key = root_key((uint32_t)seq);
     for (int i = tid; i < N; i += kBuildThreads) {
         const uint32_t place = nodes + kNode * i;
-        *lds_at<double>(place + kValueAt) = i == 0 ? 1.0 : -1.0;
-        *lds_at<uint32_t>(place + kWordAt) = i > 0 ? kAnswer : root_ring ? kFromRing | 1u : 0x3ff0u;           // nothing, or a request for draw 0
+        *lds_at<double>(place + kValueAt) = i == 0 && !root_ring ? 1.0 : -1.0;        // (the root's slot is its ring's)
+        *lds_at<uint32_t>(place + kWordAt) = i == 0 && !root_ring ? 0x3ff0u : kAnswer;           // a request for draw 0, or nothing
         *lds_at<uint32_t>(place + kOpenedAt) = 2u * (uint32_t)i + 1u;
     }
     // (with helpers the rings lie where the root's row would)
     const uint32_t rings = helped ? row_at : lds + BuildLds::ring;
-    if (tid < (helped ? kRings * kRing : kRootRing)) *lds_at<uint32_t>(rings - kWordAt + kPlace * tid + kWordAt) = 0u;
+    if (tid < (helped ? kRings * kRing : kRing)) *lds_at<uint32_t>(rings + kPlace * tid) = 0u;
     if (tid == 0) {
         *lds_at<u64>(nodes + kKeyAt) = join_key(key);
         *lds_at<float>(nodes + kUAt) = u01(seed, key, 0u, KIND_BUILD);
-        *lds_at<uint32_t>(lds + BuildLds::taken) = 0u;
+        *lds_at<double>(lds + BuildLds::state) = 1.0;
+        *lds_at<uint32_t>(lds + BuildLds::state + 8) = 0u;
+        *lds_at<uint32_t>(lds + BuildLds::state + kTakenAt) = 0u;
         *lds_at<u64>(lds + BuildLds::here) = 0ull;
         *lds_at<uint32_t>(lds + BuildLds::claims) = 0u;
         *lds_at<uint32_t>(lds + BuildLds::bound) = 0u;

@@ -53,3 +53,24 @@ def test_more_slots_of_like_size_than_the_list_holds(nodes, V, live):
         for row in x:
             row[rng.choice(V, rng.choice(live), replace=False)] = 0.25
     check_against_no_workspace(dy, x, nodes)
+
+
+# Nodes that are drawn from again and again, their slots equal or nearly so: the draws of several of them are popped together, up to the
+# tree's last row, with the root's among them or with slots of single draws between them.
+@pytest.mark.parametrize("hot", [1, 2, 5, 8, 13])
+@pytest.mark.parametrize("live", [(40, 40), (300, 300), (300, 299), (299, 40)])
+@pytest.mark.parametrize("nodes", [(64, 65), (71, 72, 73, 200), (333,), (1024,)])
+def test_equal_slots_of_nodes_drawn_from_again_and_again(nodes, live, hot):
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2410_11744_amd as dy
+    print(f"nodes={nodes} live={live} hot={hot}", flush=True)
+    V = 300
+    rng = np.random.default_rng(hot + live[0] + nodes[0])
+    x = np.full((sum(nodes), V), -np.inf, np.float32)
+    base = 0
+    for n in nodes:
+        for i in range(n):
+            x[base + i, rng.choice(V, hot if i == 0 else live[i % 2] if i <= 2 * hot else 2 + i % 3, replace=False)] = 0.25
+        base += n
+    check_against_no_workspace(dy, x, nodes)
