@@ -679,8 +679,14 @@ __device__ __attribute__((noinline, aligned(64))) void draw_for_nodes(uint32_t l
 // the root 381 -> 360, from another node 1091 -> 371; 1024 rows of 32768 tokens 1876 -> 597 -> 550 (the root's row never fitted there), 64 rows
 // 124 -> 80, 128 rows 222, 134, 177 -> 128, 110, 123 -> 118, 88, 107; a chain 559 -> 554 -> 550.  What is left is, where one
 // node has all the draws, its helper's draw, 0.63 us, and where slots of single draws come between, their pop, 0.5 us.
+// (These with a claim at rank 3 and eight more draws of the node's own wave.)
+// kClaimRank, kOwnDraws: at the node's second pop and four draws, as a helper has its first draw 8 us after it is told: those four tables 329, 179, 198,
+// 209 us, 128 rows 111, 83, 86.  Of 190 shapes of 64 to 512 rows (1000 to 32000 tokens, deviation 2 and 3, Zipf) the times are 0.985 of those
+// with rank 3 and eight draws, the best 0.83, the worst 1.03; peaked rows (deviation 10), whose nodes are hardly popped three times, 1.01, the worst
+// 1.07.  A claim at the first pop: 0.983 and 1.03, the worst of the former 1.08; at the third 0.989 and 1.00, 1.04.  Told apart by R[y] (below
+// 1/4, 1/8, 1/16 at rank 1): 0.995, the peaked ones no better.
 // kHelpedRows: below, a node has hardly the draws to pay for a row's loading (some 8 us before the first draw is there).
-constexpr int kClaimRank = 3, kOwnDraws = 8, kRootOwnDraws = 2;        // draws the node's own wave makes after the claim
+constexpr int kClaimRank = 1, kOwnDraws = 4, kRootOwnDraws = 2;        // draws the node's own wave makes after the claim
 constexpr int kHelpedRows = 64;             // of the widest tree of a batch that has helpers,
 constexpr int kLeastHelped = 16;            // of any tree of it that has some (a mailbox each in its rows)
 constexpr int kHelpedLeft = 24;             // rows still to be built when a node is worth a helper
