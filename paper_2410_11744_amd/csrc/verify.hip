@@ -379,8 +379,14 @@ __device__ __forceinline__ int draw_from_row(const RowVec<S> (&w)[4], double u, 
 // does for the maximum) and the new mass, and one reduction with one barrier.  What is left of D is summed again only by the
 // wave that held the rejected token: the others' shares stand.  With D in LDS the sweep waited for 16 LDS reads one after the
 // other (each behind the bounds check of its segment) and every wave summed D again: 2.0 us a rejection at 32000 tokens,
-// 1.4 now; a node's rows and first rejection 7.8 -> 6.4.  What bounds a rejection: some 290 instructions a wave between two
-// barriers, 128 of them the sweep.
+// 1.4 with both in registers; a node's rows and first rejection 7.8 -> 6.4.  What bounds a rejection: the instructions between two
+// barriers, 128 of them the sweep, and the reads behind the barrier.  So the partial sums are read all at once, the next child's
+// links and token are on their way during the sweep, of D's sums only the one over the removed token's place in a thread's four is made again,
+// and the two quotients that the next child needs are one division in two lanes.  What a node's decision reads from memory first goes by vector
+// loads (by scalar ones a walk of two nodes without a rejection took 1 us longer), and segments that are whole for every V of the form
+// are loaded without bounds.  Calls with 512 rows of 32000 tokens and 8, 1 and 3 rejections 50.4, 36.5, 38.3 -> 47.2, 34.5, 36.4 us (statistics pass 21.6),
+// eight sequences, up to 23 rejections in one, 96 -> 91; 64 rows 38.1 -> 34.1; same results, bit for bit.
+// (Tried beside it: workgroups that read the first nodes' rows into the walk's L2, 0.5 to 2 us of those calls and 4 us more where a walk is short.)
 // S: 2, 8 or 16 by the size of the vocabulary, so that short rows don't pay for segments they have not (1000 tokens: walk 8.6 -> 4.6 us).
 // The draft row's loads are issued first, so that its weights are made while the target row's are still out.
 // (R's sum shrinks with every rejection; below kSmallMass the weights are brought back to a sum of 1, as they are
@@ -390,9 +396,10 @@ __device__ __forceinline__ int draw_from_row(const RowVec<S> (&w)[4], double u, 
 // child is accepted and no last token comes out; after such a draft row the scan ends with the first child and the
 // last token comes from the target row.  In both, the sweep finds no mass left, which is where they are told from R == D.
 constexpr float kSmallMass = 9.5367431640625e-7f;     // 2^-20: weights of 1e-32 of the sum are still normal numbers
+typedef float floatx4 __attribute__((ext_vector_type(4)));
 struct WalkShared {
     DrawScratch draw;
-    float2 part[2][kWaves];       // per wave, by parity of the rejection: mass left in R, weight in D
+    alignas(16) float2 part[2][kWaves];       // per wave, by parity of the rejection: mass left in R, weight in D
     float2 next[2];               // R and D at the next child's token
 };
 static constexpr size_t walk_lds_bytes(int widest) { return 3 * (size_t)((widest + 7) & ~7) * sizeof(short); }
@@ -437,14 +444,20 @@ __global__ __launch_bounds__(kBlock) void verify_walk_kernel(
         uint2 pk_next = pk;
         bool rows_loaded = false;
         RowVec<S> R[4], D[4];
-        // the node's statistics: one 16-byte load, on its way together with the first child's logits
-        const float4 st = *reinterpret_cast<const float4*>(row_stats + 4 * (size_t)(base + cur));
+        // the node's statistics: one 16-byte load, on its way together with the first child's logits (all with an address in vector
+        // registers; and what is read from LDS at one is waited for where it is used)
+        int lane_zero = 0;
+        asm volatile("" : "+v"(lane_zero));
+        const float4 st = *reinterpret_cast<const float4*>(row_stats + 4 * (size_t)(base + cur) + lane_zero);
         float scale_d = 0.0f, mass = 0.0f;                // what is left of D = D * scale_d; R's sum
         // R <- the target row's weights; with want_draft, D <- the draft row's
         auto load_rows = [&](bool want_draft) __attribute__((always_inline)) {
             float X[S][4], Y[S][4];
-            if (want_draft) load_row<VEC, T>(draft_logits + (size_t)(base + cur) * V, V, X);
-            if (!greedy) load_row<VEC, T>(target_logits + (size_t)(base + cur) * V, V, Y);
+            int v_here = V, own = 4 * tid;
+            asm volatile("" : "+s"(v_here), "+v"(own));   // (what follows from them for each segment isn't kept in registers from node to node)
+            constexpr int FULL = S == kMaxSeg ? 8 : S == 8 ? 2 : 0;         // (see with_segments)
+            if (want_draft) load_row<VEC, T, FULL>(draft_logits + (size_t)(base + cur) * V, v_here, X, own);
+            if (!greedy) load_row<VEC, T, FULL>(target_logits + (size_t)(base + cur) * V, v_here, Y, own);
             if (want_draft) {                             // (the loads of both rows are in flight together)
 #pragma unroll
                 for (int j = 0; j < S; ++j)
@@ -475,8 +488,8 @@ __global__ __launch_bounds__(kBlock) void verify_walk_kernel(
                 const int y = l_token[c];
                 float d = 0.0f, r = 0.0f, xd = 0.0f, xt = 0.0f;
                 if (y >= 0) {
-                    xd = logit_to_float(draft_logits[(size_t)(base + cur) * V + y]);
-                    if (!greedy) xt = logit_to_float(target_logits[(size_t)(base + cur) * V + y]);
+                    xd = logit_to_float((draft_logits + (size_t)(base + cur) * V)[y + lane_zero]);
+                    if (!greedy) xt = logit_to_float((target_logits + (size_t)(base + cur) * V)[y + lane_zero]);
                 }
                 keys = child_key(seed, pk, (uint32_t)(tid & (kWave - 1)));          // (while the loads are out)
                 us = u01(seed, keys, 0u, KIND_ACCEPT);
@@ -485,7 +498,7 @@ __global__ __launch_bounds__(kBlock) void verify_walk_kernel(
                     d = dy / st.y;
                     r = greedy ? ((float)y == st.w ? 1.0f : 0.0f) : exp_fast(xt * inv_tt - st.z) / st.w;
                 }
-                const float ratio = ratio_of(d, r);
+                const float ratio = uniform(ratio_of(d, r));
                 const uint2 pk_n = make_uint2((uint32_t)__builtin_amdgcn_readlane((int)keys.x, 0), (uint32_t)__builtin_amdgcn_readlane((int)keys.y, 0));
                 const float u = readlane_f32(us, 0);
                 margin = fminf(margin, fabsf(u - ratio));
@@ -497,30 +510,37 @@ __global__ __launch_bounds__(kBlock) void verify_walk_kernel(
                 load_rows(true);
                 rows_loaded = true;
                 // R and D at token y (none: zeros), by the thread that owns it
-                auto at = [&](const RowVec<S> (&row)[4], int y) __attribute__((always_inline)) -> float {
-                    const int js = uniform(y >= 0 ? y / kSeg : 0), e = y & 3;
-                    const float x0 = row[0][js], x1 = row[1][js], x2 = row[2][js], x3 = row[3][js];
-                    return y < 0 ? 0.0f : e == 0 ? x0 : e == 1 ? x1 : e == 2 ? x2 : x3;
-                };
                 auto publish = [&](int y, float2* place) __attribute__((always_inline)) {
-                    if (y < 0 ? tid == 0 : ((y % kSeg) >> 2) == tid) *place = make_float2(at(R, y), at(D, y));
+                    const int js = uniform(max(y, 0) / kSeg), e = y & 3;
+                    if (((max(y, 0) % kSeg) >> 2) == tid) {
+                        const float r0 = R[0][js], r1 = R[1][js], r2 = R[2][js], r3 = R[3][js];
+                        const float d0 = D[0][js], d1 = D[1][js], d2 = D[2][js], d3 = D[3][js];
+                        *place = y < 0 ? make_float2(0.0f, 0.0f)
+                                       : make_float2(e == 0 ? r0 : e == 1 ? r1 : e == 2 ? r2 : r3, e == 0 ? d0 : e == 1 ? d1 : e == 2 ? d2 : d3);
+                    }
                 };
-                float left_w = 0.0f;                      // what this wave holds of D
-                bool summed = false;
-                uint32_t rank = 0;
-                for (int guard = 0; c >= 0 && guard < N; ++guard) {
-                    const int y = l_token[c], after = l_next[c];
-                    const int y_next = after >= 0 ? l_token[after] : -1;
-                    const int par = guard & 1;
+                // D's sums: w[e] of a thread's tokens of place e, left_w of the wave's
+                float w[4], left_w = 0.0f;
+                const auto sum_place = [&](int e) __attribute__((always_inline)) {
+                    float s = 0.0f;
+#pragma unroll
+                    for (int j = 0; j < S; ++j) s += D[e][j];
+                    w[e] = s;
+                };
+                int y = l_token[c], after = l_next[c], y_next = after >= 0 ? l_token[after] : -1;
+                float2 rd = make_float2(0.0f, 0.0f);      // R and D at the tested child's token,
+                float share = 0.0f;                       // and R's part of its sum
+                for (int rank = 0; c >= 0 && rank < N; ++rank) {
+                    const int par = rank & 1;
+                    const int after_2 = l_next[max(after, 0) + lane_zero];
                     if (rank > 0 && rank % kWave == 0) {
                         keys = child_key(seed, pk, rank + (tid & (kWave - 1)));
                         us = u01(seed, keys, 0u, KIND_ACCEPT);
                     }
                     if (rank > 0) {
                         // ratio seen by this child after its earlier siblings were rejected
-                        const float2 rd = sh.next[par ^ 1];
                         dy = rd.y;
-                        const float ratio = ratio_of(rd.y * scale_d, rd.x / mass);
+                        const float ratio = uniform(ratio_of(rd.y * scale_d, share));
                         const uint2 pk_n = make_uint2((uint32_t)__builtin_amdgcn_readlane((int)keys.x, rank & 63), (uint32_t)__builtin_amdgcn_readlane((int)keys.y, rank & 63));
                         const float u = readlane_f32(us, rank & 63);
                         margin = fminf(margin, fabsf(u - ratio));
@@ -558,21 +578,33 @@ __global__ __launch_bounds__(kBlock) void verify_walk_kernel(
                             m[e] += R[e][j];
                         }
                     publish(y_next, &sh.next[par]);
-                    if (!summed || (y >= 0 && (y % kSeg) / (4 * kWave) == uniform(tid / kWave))) {      // (the same in every lane)
-                        float w[4] = { 0.0f, 0.0f, 0.0f, 0.0f };
+                    const int after_3 = l_token[max(after_2, 0)];
+                    if (rank == 0 || (y >= 0 && (y % kSeg) / (4 * kWave) == uniform(tid / kWave))) {      // (the same in every lane)
+                        const int e = y & 3;
+                        if (rank == 0) {
 #pragma unroll
-                        for (int j = 0; j < S; ++j)
-#pragma unroll
-                            for (int e = 0; e < 4; ++e) w[e] += D[e][j];
+                            for (int k = 0; k < 4; ++k) sum_place(k);
+                        } else if (e == 0) sum_place(0);
+                        else if (e == 1) sum_place(1);
+                        else if (e == 2) sum_place(2);
+                        else sum_place(3);
                         left_w = wave_sum_f32_dpp((w[0] + w[1]) + (w[2] + w[3]));
-                        summed = true;
                     }
                     const float mw = wave_sum_f32_dpp((m[0] + m[1]) + (m[2] + m[3])), ww = left_w;
                     if ((tid & (kWave - 1)) == 0) sh.part[par][tid / kWave] = make_float2(mw, ww);
                     __syncthreads();
-                    float2 sum = sh.part[par][0];
+                    // (all reads on their way together)
+                    floatx4 parts[kWaves / 2];
 #pragma unroll
-                    for (int k = 1; k < kWaves; ++k) { const float2 p = sh.part[par][k]; sum.x += p.x; sum.y += p.y; }
+                    for (int k = 0; k < kWaves / 2; ++k) parts[k] = *reinterpret_cast<const floatx4*>(&sh.part[par][2 * k]);
+                    rd = sh.next[par];
+                    static_assert(kWaves == 8, "");
+                    asm volatile("" : "+v"(parts[0]), "+v"(parts[1]), "+v"(parts[2]), "+v"(parts[3]), "+v"(rd.x), "+v"(rd.y));
+                    float2 sum = make_float2(parts[0].x, parts[0].y);
+#pragma unroll
+                    for (int k = 1; k < kWaves; ++k) { sum.x += parts[k / 2][2 * (k % 2)]; sum.y += parts[k / 2][2 * (k % 2) + 1]; }
+                    sum.x = uniform(sum.x); sum.y = uniform(sum.y);
+                    rd.x = uniform(rd.x); rd.y = uniform(rd.y);
                     // a draft row that is no distribution (no weight at all, or NaN among it) empties at once
                     const bool no_draft = !(sum.y + dy > 0.0f);
                     if (sum.x >= kSmallMass) {
@@ -591,32 +623,36 @@ __global__ __launch_bounds__(kBlock) void verify_walk_kernel(
                             for (int j = 0; j < S; ++j)
 #pragma unroll
                                 for (int e = 0; e < 4; ++e) R[e][j] = fminf(R[e][j] * lift * up, 1.0f);
+                            rd.x = uniform(fminf(rd.x * lift * up, 1.0f));
                         } else {
                             // R == D to rounding (hardly any reject can reach here): R stays, that is, becomes D as
                             // it stood; a greedy target's R is its one token, whatever its mass
                             mass = greedy ? 1.0f : sum.y + dy;
                             // (one token's value is not in D: that of the greedy row, or the one just removed)
-                            const int one = (greedy ? (int)st.w : y) - 4 * tid;
+                            const int one = greedy ? (int)st.w : y, mine = one - 4 * tid;
                             const float value = greedy ? 1.0f : dy;
 #pragma unroll
                             for (int j = 0; j < S; ++j)
 #pragma unroll
-                                for (int e = 0; e < 4; ++e) R[e][j] = one - j * kSeg == e ? value : greedy ? 0.0f : D[e][j];
+                                for (int e = 0; e < 4; ++e) R[e][j] = mine - j * kSeg == e ? value : greedy ? 0.0f : D[e][j];
+                            rd.x = uniform(y_next < 0 ? 0.0f : y_next == one ? value : greedy ? 0.0f : rd.y);
                         }
-                        __syncthreads();
-                        publish(y_next, &sh.next[par]);
-                        __syncthreads();
                     }
                     const float left = sum.y;                 // weight left in D
                     c = after;
-                    ++rank;
+                    y = y_next;
+                    after = c >= 0 ? uniform(after_2) : -1;
+                    y_next = after >= 0 ? uniform(after_3) : -1;
                     if (!(left > 0.0f) || no_draft) {         // D is empty: later children are not tried
                         if (tid == 0)
                             for (int k = 0, cc = c; cc >= 0 && k < N; ++k, cc = l_next[cc])
                                 accept_ratio[base + cc] = -1.0f;
                         break;
                     }
-                    scale_d = 1.0f / left;                    // D <- norm(D), kept as a factor
+                    // D <- norm(D), kept as a factor; the next child's R as a share: two lanes' quotients
+                    const float q = ((tid & 1) ? 1.0f : rd.x) / ((tid & 1) ? left : mass);
+                    scale_d = readlane_f32(q, 1);
+                    share = readlane_f32(q, 0);
                 }
             }
         }

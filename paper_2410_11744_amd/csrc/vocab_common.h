@@ -22,21 +22,22 @@ __device__ __forceinline__ float bf16_bits_to_float(uint32_t bits16) { return __
 // one aligned 16-byte (fp32) or 8-byte (bf16) load).  All loads are issued before the first is looked at
 // (past the end they re-read the row's first tokens): with the use inside a bounds branch of its own each
 // bf16 load was waited for by itself, sixteen trips to memory in turn.
-// NS: segments held, V <= NS * kSeg.
-template <bool VEC, typename T, int NS>
-__device__ __forceinline__ void load_row(const T* __restrict__ row, int V, float (&x)[NS][4])
+// NS: segments held, V <= NS * kSeg; FULL: segments known to be whole, V >= FULL * kSeg.
+template <bool VEC, typename T, int FULL = 0, int NS>
+__device__ __forceinline__ void load_row(const T* __restrict__ row, int V, float (&x)[NS][4], int own = 4 * (int)threadIdx.x)
 {
     if constexpr (VEC) {
         using Raw = typename std::conditional<sizeof(T) == 4, float4, uint2>::type;
         Raw raw[NS];
 #pragma unroll
         for (int j = 0; j < NS; ++j) {
-            const int i0 = tok_index(j, 0);
-            if (j * kSeg < V) raw[j] = *reinterpret_cast<const Raw*>(row + (i0 < V ? i0 : 0));      // (the same in every thread)
+            const int i0 = j * kSeg + own;
+            const uint32_t at = (uint32_t)sizeof(T) * (uint32_t)(j < FULL || i0 < V ? i0 : 0);
+            if (j < FULL || j * kSeg < V) raw[j] = *reinterpret_cast<const Raw*>(reinterpret_cast<const char*>(row) + at);      // (the same in every thread)
         }
 #pragma unroll
         for (int j = 0; j < NS; ++j) {
-            const bool there = tok_index(j, 0) < V;
+            const bool there = j < FULL || j * kSeg + own < V;
             if constexpr (sizeof(T) == 4) {
                 x[j][0] = raw[j].x; x[j][1] = raw[j].y; x[j][2] = raw[j].z; x[j][3] = raw[j].w;
             } else {
@@ -49,9 +50,9 @@ __device__ __forceinline__ void load_row(const T* __restrict__ row, int V, float
     } else {
 #pragma unroll
         for (int j = 0; j < NS; ++j) {
-            const int i0 = tok_index(j, 0);
+            const int i0 = j * kSeg + own;
 #pragma unroll
-            for (int e = 0; e < 4; ++e) x[j][e] = (i0 + e < V) ? logit_to_float(row[i0 + e]) : -INFINITY;
+            for (int e = 0; e < 4; ++e) x[j][e] = (j < FULL || i0 + e < V) ? logit_to_float(row[i0 + e]) : -INFINITY;
         }
     }
 }
