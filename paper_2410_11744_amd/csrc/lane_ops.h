@@ -33,7 +33,7 @@ __device__ __forceinline__ u64 ballot(bool b) { return __builtin_amdgcn_ballot_w
 __device__ __forceinline__ uint32_t uniform(uint32_t x) { return (uint32_t)__builtin_amdgcn_readfirstlane((int)x); }
 __device__ __forceinline__ u64 uniform(u64 x) { return (u64)uniform((uint32_t)x) | ((u64)uniform((uint32_t)(x >> 32)) << 32); }
 __device__ __forceinline__ int uniform(int x) { return __builtin_amdgcn_readfirstlane(x); }
-__device__ __forceinline__ float uniform(float x) { return __uint_as_float(uniform(__float_as_uint(x))); }
+__device__ __forceinline__ float uniform(float x) { return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(x))); }
 __device__ __forceinline__ double uniform(double x) { return __longlong_as_double((long long)uniform((u64)__double_as_longlong(x))); }
 template <typename T> __device__ __forceinline__ T* uniform(T* p) { return (T*)(T __attribute__((address_space(1)))*)uniform((u64)p); }      // global memory
 
