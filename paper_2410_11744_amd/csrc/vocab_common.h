@@ -18,6 +18,19 @@ __device__ __forceinline__ float logit_to_float(float x) { return x; }
 __device__ __forceinline__ float logit_to_float(__bf16 x) { return (float)x; }
 __device__ __forceinline__ float bf16_bits_to_float(uint32_t bits16) { return __uint_as_float(bits16 << 16); }
 
+// Four values of a table whose rows begin anywhere, and sixteen bytes of it.  (The hardware takes wide global loads at any address;
+// an access is as wide as the type says.)
+template <typename T> struct Unaligned;
+template <> struct Unaligned<float> {
+    typedef float Four __attribute__((ext_vector_type(4), aligned(4)));
+    typedef uint32_t Piece __attribute__((ext_vector_type(4), aligned(4)));
+};
+template <> struct Unaligned<__bf16> {
+    typedef uint32_t Four __attribute__((ext_vector_type(2), aligned(2)));
+    typedef uint32_t Piece __attribute__((ext_vector_type(4), aligned(2)));
+};
+__device__ __forceinline__ uint32_t bits_of(__bf16 x) { return (uint32_t)__builtin_bit_cast(unsigned short, x); }
+
 // Load one logits row; positions >= V read as -inf.  VEC: V % 4 == 0 (a thread's four tokens are
 // one aligned 16-byte (fp32) or 8-byte (bf16) load).  All loads are issued before the first is looked at
 // (past the end they re-read the row's first tokens): with the use inside a bounds branch of its own each
@@ -48,11 +61,32 @@ __device__ __forceinline__ void load_row(const T* __restrict__ row, int V, float
             for (int e = 0; e < 4; ++e) x[j][e] = there ? x[j][e] : -INFINITY;
         }
     } else {
+        // whole segments by loads that are aligned to a value only, the last one's tokens one by one (a uniform choice)
+        using Raw = typename Unaligned<T>::Four;
+        Raw raw[NS];
 #pragma unroll
         for (int j = 0; j < NS; ++j) {
             const int i0 = j * kSeg + own;
+            if (j < FULL || (j + 1) * kSeg <= V) {
+                raw[j] = *reinterpret_cast<const Raw*>(reinterpret_cast<const char*>(row) + (uint32_t)sizeof(T) * (uint32_t)i0);
+            } else if (j * kSeg < V) {
+                T tail[4];
 #pragma unroll
-            for (int e = 0; e < 4; ++e) x[j][e] = (j < FULL || i0 + e < V) ? logit_to_float(row[i0 + e]) : -INFINITY;
+                for (int e = 0; e < 4; ++e) tail[e] = row[min(i0 + e, V - 1)];
+                if constexpr (sizeof(T) == 4) raw[j] = Raw{ tail[0], tail[1], tail[2], tail[3] };
+                else raw[j] = Raw{ bits_of(tail[0]) | bits_of(tail[1]) << 16, bits_of(tail[2]) | bits_of(tail[3]) << 16 };
+            }
+        }
+#pragma unroll
+        for (int j = 0; j < NS; ++j) {
+            if constexpr (sizeof(T) == 4) {
+                x[j][0] = raw[j].x; x[j][1] = raw[j].y; x[j][2] = raw[j].z; x[j][3] = raw[j].w;
+            } else {
+                x[j][0] = bf16_bits_to_float(raw[j].x & 0xffffu); x[j][1] = bf16_bits_to_float(raw[j].x >> 16);
+                x[j][2] = bf16_bits_to_float(raw[j].y & 0xffffu); x[j][3] = bf16_bits_to_float(raw[j].y >> 16);
+            }
+#pragma unroll
+            for (int e = 0; e < 4; ++e) x[j][e] = j < FULL || j * kSeg + own + e < V ? x[j][e] : -INFINITY;
         }
     }
 }

@@ -66,6 +66,10 @@ __device__ __forceinline__ double load_row_lds(const float* __restrict__ row, in
         if constexpr (VEC) {
             const float4 v = i0 < V ? *reinterpret_cast<const float4*>(row + i0) : make_float4(-INFINITY, -INFINITY, -INFINITY, -INFINITY);
             x[s][0] = v.x; x[s][1] = v.y; x[s][2] = v.z; x[s][3] = v.w;
+        } else if (4 * NT * (s + 1) <= V) {                     // (uniform; rows that begin at any value)
+            typedef float four __attribute__((ext_vector_type(4), aligned(4)));
+            const four v = *reinterpret_cast<const four*>(row + i0);
+            x[s][0] = v.x; x[s][1] = v.y; x[s][2] = v.z; x[s][3] = v.w;
         } else {
 #pragma unroll
             for (int e = 0; e < 4; ++e) x[s][e] = i0 + e < V ? row[i0 + e] : -INFINITY;
