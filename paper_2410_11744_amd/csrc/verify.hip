@@ -102,11 +102,15 @@ __global__ __launch_bounds__(kBlock) void softmax_stats_kernel(
 constexpr int kStatThreads = 256;
 constexpr int kStatUnroll = 8;
 
+// NANS: what both hold without a maximum is kept (NaN among their values).  (No branch: with one a call takes 0.5 us longer.)
+template <bool NANS = false>
 __device__ __forceinline__ void merge_stat(float& m, float& s, float m2, float s2, float c)
 {
     const float M = fmaxf(m, m2);
-    if (M == -INFINITY) { s += s2; return; }                     // both empty (or NaN among their values)
-    s = s * __builtin_amdgcn_exp2f((m - M) * c) + s2 * __builtin_amdgcn_exp2f((m2 - M) * c);
+    const bool empty = M == -INFINITY;
+    if (!NANS && empty) return;
+    const float f = __builtin_amdgcn_exp2f((m - M) * c), f2 = __builtin_amdgcn_exp2f((m2 - M) * c);
+    s = s * (NANS && empty ? 1.0f : f) + s2 * (NANS && empty ? 1.0f : f2);
     m = M;
 }
 
@@ -302,14 +306,14 @@ __global__ __launch_bounds__(kStatThreads) void softmax_stats_stream_pieces_kern
         m = M;
     }
 #pragma unroll
-    for (int o = kWave / 2; o > 0; o >>= 1) merge_stat(m, s, __shfl_xor(m, o, kWave), __shfl_xor(s, o, kWave), c);
+    for (int o = kWave / 2; o > 0; o >>= 1) merge_stat<RAGGED>(m, s, __shfl_xor(m, o, kWave), __shfl_xor(s, o, kWave), c);
     const int wave = threadIdx.x / kWave;
     if ((threadIdx.x & (kWave - 1)) == 0) { red[2 * wave] = m; red[2 * wave + 1] = s; }
     __syncthreads();
     if (threadIdx.x == 0) {
         m = red[0]; s = red[1];
 #pragma unroll
-        for (int w = 1; w < kStatThreads / kWave; ++w) merge_stat(m, s, red[2 * w], red[2 * w + 1], c);
+        for (int w = 1; w < kStatThreads / kWave; ++w) merge_stat<RAGGED>(m, s, red[2 * w], red[2 * w + 1], c);
         *reinterpret_cast<float2*>(row_stats + 4 * (size_t)row + 2 * table) = make_float2(RAGGED ? m : m * inv_t, s);
         if (table == 0) accept_ratio[row] = (row == sa.node_off[seq]) ? 0.0f : -2.0f;   // -2: not tested by the walk
     }
