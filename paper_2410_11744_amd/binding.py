@@ -44,11 +44,12 @@ class _Tree(ctypes.Structure):
 
 
 _lib = None
+_torch = None       # the module, once the library is loaded (an import statement in every call is a microsecond of each)
 
 
 def load_library(path: Optional[str] = None) -> ctypes.CDLL:
     """Load libdyspec.so (building it first only when nothing is built)."""
-    global _lib
+    global _lib, _torch
     if _lib is not None and path is None:
         return _lib
     p = path or _build.LIB
@@ -57,7 +58,8 @@ def load_library(path: Optional[str] = None) -> ctypes.CDLL:
     # torch brings its own copy of the HIP runtime; it has to be the one in the process before
     # this library is mapped, or the two would run on separate runtimes and every pointer torch
     # hands over would be foreign to the kernels' launches
-    import torch  # noqa: F401
+    import torch
+    _torch = torch
     lib = ctypes.CDLL(p)
     V, I32, U64, SZ, F = ctypes.c_void_p, ctypes.c_int32, ctypes.c_uint64, ctypes.c_size_t, ctypes.c_float
     PB, PT = ctypes.POINTER(_Batch), ctypes.POINTER(_Tree)
@@ -151,8 +153,9 @@ class Batch:
             self.__dict__["_memo_store"] = memo
         return memo
 
-    def _c(self) -> _Batch:
-        memo = self._memo()
+    def _c(self, memo: Optional[dict] = None) -> _Batch:
+        if memo is None:
+            memo = self._memo()
         c = memo.get("c")
         if c is None:
             no = np.ascontiguousarray(self.node_offset, dtype=np.int32)
@@ -165,12 +168,15 @@ class Batch:
             memo["c"], memo["keep"] = c, (no, pl, kv)          # the struct points into these copies
         return c
 
+    def _mask_words(self, memo: dict) -> int:
+        words = memo.get("mask_words")
+        if words is None:
+            words = memo["mask_words"] = int(load_library().dyspec_mask_words(ctypes.byref(self._c(memo))))
+        return words
+
     @property
     def mask_words(self) -> int:
-        memo = self._memo()
-        if "mask_words" not in memo:
-            memo["mask_words"] = int(load_library().dyspec_mask_words(ctypes.byref(self._c())))
-        return memo["mask_words"]
+        return self._mask_words(self._memo())
 
 
 @dataclass
@@ -195,6 +201,15 @@ class Tree:
         rows = torch.empty((6, -(-total_nodes // 128) * 128), dtype=torch.int32, device=device)
         return Tree(*rows[:, :total_nodes].unbind(0))
 
+    @staticmethod
+    def _empty_c(total_nodes: int, device) -> "tuple[Tree, _Tree]":
+        """empty() on a GPU, and its pointers: no need to look at arrays just made."""
+        tree = Tree.empty(total_nodes, device)
+        if not tree.parent.is_cuda:
+            raise ValueError("device tensor required")
+        first, step = tree.parent.data_ptr(), -(-total_nodes // 128) * 512
+        return tree, _Tree(first, first + step, first + 2 * step, first + 3 * step, first + 4 * step, first + 5 * step)
+
 
 _dtypes: dict = {}
 
@@ -217,10 +232,10 @@ def _ptr(t, want: Optional[str] = None) -> int:
 
 
 def _stream(stream=None) -> int:
-    import torch
     if stream is not None:
         return int(stream.cuda_stream)
-    return int(torch._C._cuda_getCurrentRawStream(torch.cuda.current_device()))
+    torch = _torch or __import__("torch")
+    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
 
 
 def _temps(x, n_seq: int):
@@ -251,21 +266,22 @@ class BuiltTrees:
 def build_tree(draft_logits, batch: Batch, draft_temp, seed: int, stream=None, use_workspace: bool = True) -> BuiltTrees:
     """dyspec_build_tree: greedy token-tree construction (Algorithm 1) + ancestor mask.
     use_workspace=False passes no workspace (the slower form that recomputes row sums)."""
-    import torch
     lib = load_library()
+    torch = _torch
     dev = draft_logits.device
-    total, V = batch.total_nodes, int(draft_logits.shape[1])
+    total, n_seq, V = batch.total_nodes, batch.n_seq, int(draft_logits.shape[1])
     if draft_logits.shape[0] != total:
         raise ValueError("draft_logits needs one row per tree node")
-    tree = Tree.empty(total, dev)
+    memo = batch._memo()
+    cb = batch._c(memo)
+    tree, ct = Tree._empty_c(total, dev)
     est = torch.empty(total, dtype=torch.float32, device=dev)
-    mask = torch.empty((total, batch.mask_words), dtype=torch.int64, device=dev)
-    nb = torch.empty(batch.n_seq, dtype=torch.int32, device=dev)
-    cb, ct = batch._c(), tree._c()
-    tarr, tptr = _temps(draft_temp, batch.n_seq)
+    mask = torch.empty((total, batch._mask_words(memo)), dtype=torch.int64, device=dev)
+    nb = torch.empty(n_seq, dtype=torch.int32, device=dev)
+    tarr, tptr = _temps(draft_temp, n_seq)
     ws, ws_bytes = None, 0
     if use_workspace:
-        memo, wkey = batch._memo(), ("ws_build", V)
+        wkey = ("ws_build", V)
         if wkey not in memo:
             memo[wkey] = int(lib.dyspec_workspace_bytes(WS_BUILD_TREE, ctypes.byref(cb), V, 0, 0, 0))
         ws_bytes = memo[wkey]
@@ -320,16 +336,16 @@ class ReorderedTrees:
 
 def dfs_reorder(tree: Tree, batch: Batch, stream=None) -> ReorderedTrees:
     """dyspec_dfs_reorder: rename every tree's nodes in depth-first order (block-sparsity friendly)."""
-    import torch
     lib = load_library()
+    torch = _torch
     dev = tree.parent.device
-    total = batch.total_nodes
-    out = Tree.empty(total, dev)
+    total, memo = batch.total_nodes, batch._memo()
+    cb, ci = batch._c(memo), tree._c()
+    out, co = Tree._empty_c(total, dev)
     order = torch.empty(total, dtype=torch.int32, device=dev)
-    mask = torch.empty((total, batch.mask_words), dtype=torch.int64, device=dev)
-    cb, ci, co = batch._c(), tree._c(), out._c()
-    _check(lib.dyspec_dfs_reorder(ctypes.byref(cb), ctypes.byref(ci), ctypes.byref(co), _ptr(order, "int32"),
-                                  _ptr(mask, "int64"), _stream(stream)), "dyspec_dfs_reorder")
+    mask = torch.empty((total, batch._mask_words(memo)), dtype=torch.int64, device=dev)
+    _check(lib.dyspec_dfs_reorder(ctypes.byref(cb), ctypes.byref(ci), ctypes.byref(co), order.data_ptr(),
+                                  mask.data_ptr(), _stream(stream)), "dyspec_dfs_reorder")
     return ReorderedTrees(out, order, mask)
 
 
@@ -395,27 +411,32 @@ def tree_attn_call(q, k_prefix, v_prefix, k_tree, v_tree, anc_mask, batch: Batch
                    out=None, dtype: Optional[int] = None, stream=None, use_workspace: bool = True,
                    static_scratch: bool = False) -> PreparedCall:
     """tree_attn's call, prepared: nothing is launched until the returned object is called."""
-    import torch
     lib = load_library()
+    torch = _torch
     total, Hq, d = q.shape
-    Hkv = int(k_tree.shape[1])
+    kt_shape, q_dtype = k_tree.shape, q.dtype
+    Hkv = int(kt_shape[1])
     if dtype is None:
-        dtype = {torch.float32: F32, torch.bfloat16: BF16}[q.dtype]
-    if total != batch.total_nodes or k_tree.shape[0] != total or v_tree.shape != k_tree.shape:
+        dtype = BF16 if q_dtype is torch.bfloat16 else {torch.float32: F32}[q_dtype]
+    if total != batch.total_nodes or kt_shape[0] != total or v_tree.shape != kt_shape:
         raise ValueError("q / k_tree / v_tree need one row per tree node")
-    if batch.total_prefix > 0 and (k_prefix.shape[0] < batch.total_prefix or k_prefix.shape[1] != Hkv
-                                   or k_prefix.shape[2] != d or v_prefix.shape != k_prefix.shape):
-        raise ValueError("prefix K/V shape does not match the batch")
-    if anc_mask.shape[0] != total or anc_mask.shape[1] != batch.mask_words:
+    prefix = batch.total_prefix
+    if prefix > 0:
+        kp_shape = k_prefix.shape
+        if kp_shape[0] < prefix or kp_shape[1] != Hkv or kp_shape[2] != d or v_prefix.shape != kp_shape:
+            raise ValueError("prefix K/V shape does not match the batch")
+    memo = batch._memo()
+    mask_shape = anc_mask.shape
+    if mask_shape[0] != total or mask_shape[1] != batch._mask_words(memo):
         raise ValueError("ancestor mask shape does not match the batch")
     for t in (k_prefix, v_prefix, k_tree, v_tree):
-        if t is not None and t.dtype != q.dtype:
+        if t is not None and t.dtype != q_dtype:
             raise ValueError("q, k, v must share a dtype")
     if out is None:
         if static_scratch:
             raise ValueError("static_scratch=True needs the caller's `out` tensor")
         out = torch.empty_like(q)
-    cb = batch._c()
+    cb = batch._c(memo)
     keep = (q, k_prefix, v_prefix, k_tree, v_tree, anc_mask, out, batch, cb)
     if static_scratch:
         args = (_ptr(q), _ptr(k_prefix), _ptr(v_prefix), _ptr(k_tree), _ptr(v_tree), _ptr(anc_mask, "int64"),
@@ -423,7 +444,7 @@ def tree_attn_call(q, k_prefix, v_prefix, k_tree, v_tree, anc_mask, batch: Batch
         return PreparedCall(lib.dyspec_tree_attn_static_scratch, args, keep, "dyspec_tree_attn_static_scratch", out)
     ws, ws_bytes = None, 0
     if use_workspace and dtype == BF16:
-        memo, wkey = batch._memo(), ("ws_attn", int(Hq), Hkv, int(d))
+        wkey = ("ws_attn", int(Hq), Hkv, int(d))
         if wkey not in memo:
             memo[wkey] = int(lib.dyspec_workspace_bytes(WS_TREE_ATTN, ctypes.byref(cb), 0, int(Hq), Hkv, int(d)))
         ws_bytes = memo[wkey]
@@ -510,20 +531,20 @@ def verify(draft_logits, target_logits, batch: Batch, tree: Tree, draft_temp, ta
 def verify_call(draft_logits, target_logits, batch: Batch, tree: Tree, draft_temp, target_temp, seed: int,
                 emit_bonus: bool = True, out: Optional[VerifyOutput] = None, stream=None) -> PreparedCall:
     """verify's call, prepared: nothing is launched until the returned object is called."""
-    import torch
     lib = load_library()
-    total, V = batch.total_nodes, int(draft_logits.shape[1])
-    if draft_logits.shape[0] != total or target_logits.shape != draft_logits.shape:
+    total, n_seq, shape, dtype = batch.total_nodes, batch.n_seq, draft_logits.shape, draft_logits.dtype
+    V = int(shape[1])
+    if shape[0] != total or target_logits.shape != shape:
         raise ValueError("logit tables need one row per tree node")
-    if draft_logits.dtype != target_logits.dtype or draft_logits.dtype not in (torch.float32, torch.bfloat16):
+    bf16 = dtype is _torch.bfloat16
+    if target_logits.dtype != dtype or not (bf16 or dtype is _torch.float32):
         raise ValueError("logit tables must both be float32 or both be bfloat16")
-    bf16 = draft_logits.dtype == torch.bfloat16
     entry = lib.dyspec_verify_bf16 if bf16 else lib.dyspec_verify
     if out is None:
         out = VerifyOutput.empty(batch, draft_logits.device)
     cb, ct = batch._c(), tree._c()
-    da, dp = _temps(draft_temp, batch.n_seq)
-    ta, tp = _temps(target_temp, batch.n_seq)
+    da, dp = _temps(draft_temp, n_seq)
+    ta, tp = _temps(target_temp, n_seq)
     args = (_ptr(draft_logits), _ptr(target_logits), V, ctypes.byref(cb), ctypes.byref(ct), dp, tp,
             ctypes.c_uint64(seed), int(bool(emit_bonus)), _ptr(out.row_stats), _ptr(out.accept_ratio),
             _ptr(out.accepted_nodes), _ptr(out.n_accepted), _ptr(out.final_token), _ptr(out.min_margin), None, 0,
