@@ -12,8 +12,8 @@
 // depend on its row, its path key and the child's rank only, not on when the node is popped, so
 // they are made ahead by other waves of the workgroup; draft_row_sums_kernel (one workgroup per row, all
 // rows at once) has stored every row's maximum and group totals before.  Without a workspace the builder (build_tree_kernel)
-// recomputes the sums of the parent's row for every draw; both ways take the same decisions
-// and build the same tree.
+// recomputes the sums of the parent's row for every draw.  Both ways make the same draws to the rounding of their sums, and build the
+// same tree where no decision is closer than that; one call builds the same tree every time.
 #include <algorithm>
 #include <cstddef>
 
@@ -21,6 +21,7 @@
 #include "lane_ops.h"
 #include "row_copies.h"
 #include "row_workspace.h"
+#include "run_draw.h"
 #include "wave_draw.h"
 
 namespace dyspec {
@@ -465,35 +466,13 @@ __device__ __forceinline__ void draw_for_node(MadeDraw& d, uint32_t place, uint3
     if (rank > 0 && (rank & (kWave - 1)) == 0) make_names(names, seed, key_word, node, rank);     // (the draw before has not left this one's uniform)
     const bool named = names.node == node && names.first == (rank & ~(kWave - 1));                 // uniform
     const double u = (double)(named ? readlane_f32(names.u, rank & (kWave - 1)) : *lds_at<float>(place + kUAt));
-    // ---- the run: the lane of the crossing, then one of its four totals (every lane walks its own)
-    const double t01 = h.tot[0] + h.tot[1], four = t01 + (h.tot[2] + h.tot[3]);
-    const double cum = wave_scan_dpp(four);
-    const double W = readlane_f64(cum, 63);
-    if (!(W > 0.0)) {                               // nothing left to sample under the node
+    const RunSums sums = sum_runs(h.tot);
+    if (!(sums.W > 0.0)) {                          // nothing left to sample under the node
         hand_over();
         return;
     }
-    const double target = u * W;
-    const int gl = pick_lane(ballot(four > 0.0) & ballot(cum > target), ballot(four > 0.0));
-    const double start = scan_at(cum, gl - 1);
-    double run_start = start;
-    int k = -1;
-    {
-        double run = start;
-        int last = 0;
-        double last_start = start;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            const double after = run + h.tot[e];
-            if (h.tot[e] > 0.0) { last = e; last_start = run; }
-            if (k < 0 && h.tot[e] > 0.0 && after > target) { k = e; run_start = run; }
-            run = after;
-        }
-        if (k < 0) { k = last; run_start = last_start; }            // rounding at the top
-    }
-    k = __builtin_amdgcn_readlane(k, gl);
-    run_start = readlane_f64(run_start, gl);
-    const int run0 = (4 * gl + k) * kRun;
+    const PickedRun run = pick_run(h.tot, sums, u);
+    const int run0 = (4 * run.lane + run.k) * kRun;
     const int tok0 = run0 + 2 * lane;               // this lane's two tokens of the run
     // (past the end of the row a token that is there is read: with the loads in a branch of their own they are waited for in it)
     float2 x;
@@ -538,31 +517,25 @@ __device__ __forceinline__ void draw_for_node(MadeDraw& d, uint32_t place, uint3
     exp_nonpos_xn<2>(z, w);
     if (out & 1u) w[0] = 0.0;
     if (out & 2u) w[1] = 0.0;
-    const double mine = w[0] + w[1];
-    const double inc = wave_scan_dpp(mine);
-    const u64 live = ballot(mine > 0.0);
-    if (!live) {                                    // (the run's total says otherwise: not while totals and logits belong together)
+    const TokenSums tokens = sum_tokens(w);
+    if (!tokens.live) {                             // (the run's total says otherwise: not while totals and logits belong together)
         hand_over();
         return;
     }
-    const int ol = pick_lane(live & ballot(run_start + inc > target), live);
-    const double mid = run_start + scan_at(inc, ol - 1) + w[0];     // (of interest in lane ol)
-    const int second = (w[0] > 0.0 && (mid > target || !(w[1] > 0.0))) ? 0 : 1;
-    const int e = __builtin_amdgcn_readlane(second, ol);
-    const int y = run0 + 2 * ol + e;
-    const double wy = readlane_f64(e ? w[1] : w[0], ol);
+    const PickedToken t = pick_token(w, tokens, run);
+    const int y = run0 + 2 * t.lane + t.second;
     if (lane == ((rank + 1) & (kWave - 1))) *lds_at<float>(place + kUAt) = next_u;
-    d.R = wy / W;
+    d.R = t.wy / sums.W;
     d.child = join_key(child);
     d.child_u = child_u;
     d.word = kAnswer | ((uint32_t)rank << 15) | (uint32_t)y;
     hand_over();
     // what is left of the run
-    const double left = wave_sum_dpp(lane == ol ? (e ? w[0] : w[1]) : mine);
-    const bool here = lane == gl;
+    const double left = run_left(w, tokens, t);
+    const bool here = lane == run.lane;
 #pragma unroll
-    for (int q = 0; q < 4; ++q) h.tot[q] = here && q == k ? left : h.tot[q];       // (selects: a store to tot[k] puts the array in scratch memory)
-    if (here) ws_totals(ws, ws_row)[4 * lane + k] = left;
+    for (int q = 0; q < 4; ++q) h.tot[q] = here && q == run.k ? left : h.tot[q];       // (selects: a store to tot[k] puts the array in scratch memory)
+    if (here) ws_totals(ws, ws_row)[4 * lane + run.k] = left;
     if (lane == (rank & 63)) {
         drawn[rank] = (unsigned short)y;
         if (rank < kWave) h.drawn = y;
@@ -672,7 +645,7 @@ __device__ __attribute__((noinline, aligned(64))) void draw_for_nodes(uint32_t l
 // waited too long leaves), its other word (wave 1: draws taken, or that the tree is complete), the count of draws that can be read (helper;
 // written when they are there).  A helper waits for a claim, for room in the ring, and for the end, each a bounded number of looks.
 // Only a helper that is there is claimed: nobody waits for a workgroup that has no CU, and a tree without its helpers is built by its own waves.
-// (A draw is the same whoever makes it, to the rounding of the sums behind it.)
+// At which rank a helper takes over depends on the clock; a draw has the same bits whoever makes it (run_draw.h).
 //
 // Measured, with the pass over the rows, 512 rows of 32000 tokens, four tables, without helpers, with them and with their draws popped
 // many at a time (pop_nodes): 961, 470, 582, 553 -> 334, 320, 332, 319 -> 332, 201, 225, 211 us; all draws from
@@ -703,9 +676,10 @@ struct HelpLds {
     static constexpr uint32_t room = 8;                                            // draws that may be made (kStopped: no more)
     static constexpr uint32_t fred = 16;
     static constexpr uint32_t ring = fred + 4 * (kBuildThreads / kWave);
-    static constexpr uint32_t row = ring + kMailRing * kHelpPlace;
+    static constexpr uint32_t totals = ring + kMailRing * kHelpPlace;
+    static constexpr uint32_t row = totals + 8 * kSums;
 };
-static_assert(HelpLds::row % 16 == 0, "");
+static_assert(HelpLds::totals % 16 == 0 && HelpLds::row % 16 == 0, "");
 template <typename T> __device__ __forceinline__ T agent_load(const T* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
 template <typename T> __device__ __forceinline__ void agent_store(T* p, T v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
 __device__ __forceinline__ void memory_done() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
@@ -716,19 +690,18 @@ __device__ __forceinline__ u64* mail_key(double* mail) { return reinterpret_cast
 __device__ __forceinline__ uint32_t* mail_count(double* mail) { return reinterpret_cast<uint32_t*>(mail + 2); }
 
 // A helper's first wave: draws rank 0 .. N - 2 of the row in LDS, as far as there is room, and leaves them in the ring in LDS.
-__device__ __attribute__((noinline, aligned(64))) void make_draws(uint32_t lds_, double inv_temp, double m, int V_, int N_, uint64_t seed_, u64 key_)
+__device__ __attribute__((noinline, aligned(64))) void make_draws(uint32_t lds_, double inv_temp, double m, int N_, uint64_t seed_, u64 key_)
 {
     const uint32_t lds = uniform(lds_), ring = lds + HelpLds::ring;
-    const int V = uniform(V_), N = uniform(N_);
+    const int N = uniform(N_);
     const u64 seed = uniform((u64)seed_);
     const uint2 key = split_key(uniform(key_));
-    WaveRow row;
-    row.leaf = lds_at<double>(lds + HelpLds::row);
-    row.logits = lds_at<float>(lds + HelpLds::row + 8 * row_leaves(V));
+    RunRow row;
+    row.logits = lds_at<float>(lds + HelpLds::row);
     row.inv_temp = uniform(inv_temp);
     row.m = uniform(m);
     const int lane = threadIdx.x & 63;
-    open_wave_row(row, V);
+    open_run_row(row, lds_at<double>(lds + HelpLds::totals));
     float us = 0.f;                                 // the uniforms of 64 ranks
     for (int rank = 0; rank < N - 1; ++rank) {
         if ((rank & 3) == 0) {
@@ -740,14 +713,14 @@ __device__ __attribute__((noinline, aligned(64))) void make_draws(uint32_t lds_,
                 __builtin_amdgcn_s_sleep(2);
             }
         }
-        Drawn d;
-        const bool drawn = draw_wave_row(row, (double)readlane_f32(us, rank & 63), &d);
-        if (lane == 0) {
-            const uint32_t place = ring + kHelpPlace * (uint32_t)(rank & (kMailRing - 1));
-            *lds_at<doublex2>(place) = drawn ? doublex2{ d.wy, d.W } : doublex2{ -1.0, 1.0 };
-            *lds_at<uint32_t>(place + 16) = (uint32_t)(drawn ? d.y : 0);
-            lds_set(lds_at<uint32_t>(lds + HelpLds::made), (uint32_t)rank + 1u);
-        }
+        // (all lanes write what one would: with a branch on the lane, or one that the compiler joins with it, the whole loop is run under masks)
+        Drawn d = { 0, -1.0, 1.0 };
+        uint32_t drawn = draw_run_row(row, (double)readlane_f32(us, rank & 63), &d) ? 1u : 0u;
+        asm("" : "+s"(drawn));
+        const uint32_t place = ring + kHelpPlace * (uint32_t)(rank & (kMailRing - 1));
+        *lds_at<doublex2>(place) = doublex2{ d.wy, d.W };
+        *lds_at<uint32_t>(place + 16) = (uint32_t)d.y;
+        lds_set(lds_at<uint32_t>(lds + HelpLds::made), (uint32_t)rank + 1u);
         if (!drawn) return;
     }
 }
@@ -825,9 +798,9 @@ __device__ __attribute__((noinline)) void help_build(uint32_t lds_, const float*
         node = uniform(*lds_at<int>(lds + HelpLds::node));
         if (node < 0 || node >= N) return;
     }
-    const double m = load_row_lds<kBuildThreads, VEC>(draft_logits + (size_t)(base + node) * V, V, inv_temp, lds_at<double>(lds + HelpLds::row),
-                                                      lds_at<float>(lds + HelpLds::row + 8 * row_leaves(V)), (float*)lds_at<float>(lds + HelpLds::fred));
-    if (wave == 0) make_draws(lds, inv_temp, m, V, N, seed_, mine > 0 ? agent_load(mail_key(mail)) : join_key(root_key(uniform(seq_))));
+    const double m = load_run_row<kBuildThreads, VEC>(draft_logits + (size_t)(base + node) * V, V, inv_temp, lds_at<double>(lds + HelpLds::totals),
+                                                      lds_at<float>(lds + HelpLds::row), (float*)lds_at<float>(lds + HelpLds::fred));
+    if (wave == 0) make_draws(lds, inv_temp, m, N, seed_, mine > 0 ? agent_load(mail_key(mail)) : join_key(root_key(uniform(seq_))));
     else if (wave == 1) ship_draws(lds, ws, mail, base + node);
 }
 
@@ -945,8 +918,6 @@ __device__ __forceinline__ double largest_of_rings(double x)
 // 657 us before there were rings, 691 with the stores and moves under `lane == 0`, 644 now.  (As a function that is called, it saved and restored 35
 // scalar registers and 2 vector registers in memory: 0.3 to 0.5 us of every tree, 11.9 us at the least.)
 constexpr int kRelisted = 16;           // found one after the other
-constexpr int kDppWaveShl1 = 0x130;     // lane i: lane i + 1's
-constexpr int kDppWaveShr1 = 0x138;     // lane i: lane i - 1's
 template <int CTRL> __device__ __forceinline__ int dpp_or_own(int x) { return __builtin_amdgcn_update_dpp(x, x, CTRL, 0xf, 0xf, false); }
 template <int CTRL> __device__ __forceinline__ double dpp_or_own(double x)
 {
@@ -1529,7 +1500,7 @@ hipError_t launch_build_tree(const float* draft_logits, int V, const SeqArgs& sa
         for (int s = 0; s < sa.n_seq; ++s) widest = max(widest, sa.node_off[s + 1] - sa.node_off[s]);
         const bool helped = widest >= kHelpedRows && sa.n_seq * (1 + kRings) <= kHelpedBlocks;
         const int root_ring = !helped && widest >= kRingRows && build_lds_bytes(V, widest, true) <= kLdsPerWorkgroup;
-        const size_t lds_bytes = helped ? std::max((size_t)BuildLds::row(widest) + kRings * kRing * kPlace, HelpLds::row + row_lds_bytes(V))
+        const size_t lds_bytes = helped ? std::max((size_t)BuildLds::row(widest) + kRings * kRing * kPlace, HelpLds::row + run_row_lds_bytes(V))
                                         : build_lds_bytes(V, widest, root_ring);
         const int grid = sa.n_seq * (helped ? 1 + kRings : 1);
         const hipError_t ea = prepare_build_tree();

@@ -45,6 +45,8 @@ constexpr int kDppHalfMirror = 0x141;   // lane i of a group of 8 <-> lane 7-i
 constexpr int kDppMirror = 0x140;       // lane i of a row of 16 <-> lane 15-i
 constexpr int kDppBcast15 = 0x142;      // lane 15 of a row to the next row
 constexpr int kDppBcast31 = 0x143;      // lane 31 to rows 2 and 3
+constexpr int kDppWaveShl1 = 0x130;     // lane i: lane i + 1's
+constexpr int kDppWaveShr1 = 0x138;     // lane i: lane i - 1's
 template <int CTRL, int ROW_MASK = 0xf>
 __device__ __forceinline__ int dpp_or_zero(int x)   // the picked lane's x; 0 where there is none or the row is masked off
 {

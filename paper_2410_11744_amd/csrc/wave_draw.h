@@ -50,16 +50,11 @@ __device__ __forceinline__ double scan32_dpp(double x)
 // the lane's value at position i of a scan, 0 for i = -1
 __device__ __forceinline__ double scan_at(double x, int i) { const double v = readlane_f64(x, i & 63); return i < 0 ? 0.0 : v; }
 
-// Brings a row into LDS with NT threads: logits, leaf sums; the row maximum over T is returned to
-// every thread.  `fred`: NT / 64 floats.  Ends with a barrier.
-template <int NT, bool VEC>
-__device__ __forceinline__ double load_row_lds(const float* __restrict__ row, int V, double inv_temp, lds_t<double>* leaf, lds_t<float>* logits, float* fred)
+// A row in sweeps of 4 tokens per thread of NT (-inf: past the end).
+template <int NT, bool VEC, int SW>
+__device__ __forceinline__ void load_row_sweeps(const float* __restrict__ row, int V, float (&x)[SW][4])
 {
-    constexpr int SW = DYSPEC_MAX_VOCAB / (4 * NT);         // sweeps of 4 tokens per thread
-    const int tid = threadIdx.x, lane = tid & 63;
-    const int Vl = row_logits(V), Vg = row_leaves(V) * kLeafTokens;
-    float x[SW][4];
-    float mx = -INFINITY;
+    const int tid = threadIdx.x;
 #pragma unroll
     for (int s = 0; s < SW; ++s) {
         const int i0 = 4 * (s * NT + tid);
@@ -75,6 +70,19 @@ __device__ __forceinline__ double load_row_lds(const float* __restrict__ row, in
             for (int e = 0; e < 4; ++e) x[s][e] = i0 + e < V ? row[i0 + e] : -INFINITY;
         }
     }
+}
+
+// Brings a row into LDS with NT threads: logits, leaf sums; the row maximum over T is returned to
+// every thread.  `fred`: NT / 64 floats.  Ends with a barrier.
+template <int NT, bool VEC>
+__device__ __forceinline__ double load_row_lds(const float* __restrict__ row, int V, double inv_temp, lds_t<double>* leaf, lds_t<float>* logits, float* fred)
+{
+    constexpr int SW = DYSPEC_MAX_VOCAB / (4 * NT);         // sweeps of 4 tokens per thread
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int Vl = row_logits(V), Vg = row_leaves(V) * kLeafTokens;
+    float x[SW][4];
+    load_row_sweeps<NT, VEC>(row, V, x);
+    float mx = -INFINITY;
 #pragma unroll
     for (int s = 0; s < SW; ++s) {
         mx = fmaxf(mx, fmaxf(fmaxf(x[s][0], x[s][1]), fmaxf(x[s][2], x[s][3])));
