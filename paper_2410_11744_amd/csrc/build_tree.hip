@@ -638,7 +638,7 @@ __device__ __attribute__((noinline, aligned(64))) void draw_for_nodes(uint32_t l
 // A draw from global memory takes a wave 2.1 us, one from a row in LDS 0.6, and the tree's workgroup has room for the root's
 // row at most.  So a node that is popped kClaimRank times gets a helper, as long as there is one, the root at its first pop: a workgroup
 // that brings the node's row into its LDS, makes the node's draws from rank 0 on (they depend on the row and the path key alone)
-// and leaves them in a ring in memory.  Wave 1 of the tree's workgroup brings them to a ring in LDS, and from a rank
+// and leaves them in a ring in memory (row_workspace.h).  Wave 1 of the tree's workgroup brings them to a ring in LDS, and from a rank
 // that the helper has reached by then on (kOwnDraws) control takes the node's draws from there, as it takes the root's where there are no helpers.
 //
 // Words in memory, all accesses relaxed and device-scope: the mailbox's state (the helper comes: kHere; wave 1 claims it; one that has
@@ -725,10 +725,10 @@ __device__ __attribute__((noinline, aligned(64))) void make_draws(uint32_t lds_,
     }
 }
 // Its second wave: brings them to memory, where wave 1 of the tree's workgroup reads them.
-__device__ __attribute__((noinline)) void ship_draws(uint32_t lds_, double* ws_, double* mail_, int row_)
+__device__ __attribute__((noinline)) void ship_draws(uint32_t lds_, double* mail_, double* ring_)
 {
     const uint32_t lds = uniform(lds_);
-    double *const mail = uniform(mail_), *const ring = ws_mail_ring(uniform(ws_), uniform(row_));
+    double *const mail = uniform(mail_), *const ring = uniform(ring_);
     const int lane = threadIdx.x & 63;
     int shipped = 0;
     for (int polls = 0; polls < kHelperPolls; ++polls) {
@@ -801,11 +801,11 @@ __device__ __attribute__((noinline)) void help_build(uint32_t lds_, const float*
     const double m = load_run_row<kBuildThreads, VEC>(draft_logits + (size_t)(base + node) * V, V, inv_temp, lds_at<double>(lds + HelpLds::totals),
                                                       lds_at<float>(lds + HelpLds::row), (float*)lds_at<float>(lds + HelpLds::fred));
     if (wave == 0) make_draws(lds, inv_temp, m, N, seed_, mine > 0 ? agent_load(mail_key(mail)) : join_key(root_key(uniform(seq_))));
-    else if (wave == 1) ship_draws(lds, ws, mail, base + node);
+    else if (wave == 1) ship_draws(lds, mail, ws_mail_ring(ws, base, N, mine));
 }
 
 // Wave 1 of a tree with helpers: fills the rings in LDS from the helpers'.  Lane 8 k + j has place j of ring k.
-__device__ __attribute__((noinline, aligned(64))) void bring_draws(uint32_t lds_, uint32_t rings_, double* ws_, int base_, uint64_t seed_)
+__device__ __attribute__((noinline, aligned(64))) void bring_draws(uint32_t lds_, uint32_t rings_, double* ws_, int base_, int N_, uint64_t seed_)
 {
     const uint32_t lds = uniform(lds_), rings = uniform(rings_);
     const int base = uniform(base_);
@@ -813,10 +813,10 @@ __device__ __attribute__((noinline, aligned(64))) void bring_draws(uint32_t lds_
     double* const ws = uniform(ws_);
     const int lane = threadIdx.x & 63, k = lane / kRing, j = lane % kRing;
     double* const mail = ws_mail(ws, base + k);
+    const double* const ring = ws_mail_ring(ws, base, uniform(N_), k);
     const bool first = j == 0;
     uint32_t asked = 0, claimed = 0;                // rings that have a node, and whose helper has been told
     u64 here = 0, key = 0;
-    const double* ring = nullptr;
     int put = -1, told = 0, count = 0;              // the draw last put into the place, what the helper knows to be taken, what it has told of
     while (uniform(lds_now(lds_at<uint32_t>(lds + BuildLds::news))) != kStop) {
         const uint32_t claims = uniform(lds_now(lds_at<uint32_t>(lds + BuildLds::claims)));
@@ -853,7 +853,6 @@ __device__ __attribute__((noinline, aligned(64))) void bring_draws(uint32_t lds_
             if (mine) {
                 node = *lds_at<int>(lds + BuildLds::hot + 4 * k);
                 key = *lds_at<u64>(lds + BuildLds::nodes + kNode * (uint32_t)node + kKeyAt);
-                ring = ws_mail_ring(ws, base + node);
                 if (first) agent_store(mail_key(mail), key);
             }
             memory_done();
@@ -1405,7 +1404,7 @@ __global__ __launch_bounds__(kBuildThreads) void build_tree_waves_kernel(
         }
     } else if (wave == 1) {
         if (!helped) __builtin_amdgcn_s_setprio(2);
-        if (helped) bring_draws(lds, rings, ws, base, seed);
+        if (helped) bring_draws(lds, rings, ws, base, N, seed);
         else if (root_ring && N > 1) draw_for_root(lds, row_at, inv_temp, m, V, N, seed, (uint32_t)seq);
     } else {
         draw_for_nodes<VEC>(lds, wave - 2, draft_logits, V, inv_temp, seed, ws, base, N);

@@ -18,8 +18,9 @@ constexpr int kDrawnOffset = kSums + 2;
 constexpr int kDrawnEntries = DYSPEC_MAX_BUILD_NODES + 1;
 constexpr int kMadeOffset = kDrawnOffset + (kDrawnEntries + 3) / 4;
 constexpr int kMadeDoubles = 3;
-// Draws of a node made by another workgroup: a ring in the row of the node, 16 bytes a draw, in the place of the tokens of ranks
-// kMailRanks and on (the node's own wave makes the first few draws of such a node only), and a mailbox in the row of the helper's number.
+// Draws of a node made by another workgroup (helper): a mailbox in the row of the helper's number, and a ring, 16 bytes a draw, from the back
+// of the tree: a node's children are later rows, so that one of the last rows has hardly a draw, and the places of its tokens of ranks
+// kMailRanks and on are free.  (In the node's own row they are not: a helper may come when the node's wave is past those ranks.)
 constexpr int kMailOffset = kMadeOffset + kMadeDoubles;
 constexpr int kMailDoubles = 3;
 constexpr int kMailRing = 64;
@@ -33,6 +34,7 @@ __host__ __device__ inline double* ws_rowmax(double* ws, int row) { return ws_to
 __host__ __device__ inline unsigned short* ws_drawn(double* ws, int row) { return reinterpret_cast<unsigned short*>(ws_totals(ws, row) + kDrawnOffset); }
 __host__ __device__ inline double* ws_made(double* ws, int row) { return ws_totals(ws, row) + kMadeOffset; }
 __host__ __device__ inline double* ws_mail(double* ws, int row) { return ws_totals(ws, row) + kMailOffset; }
-__host__ __device__ inline double* ws_mail_ring(double* ws, int row) { return ws_totals(ws, row) + kMailRingOffset; }
+// of helper k of the tree whose N rows begin at `base`
+__host__ __device__ inline double* ws_mail_ring(double* ws, int base, int N, int k) { return ws_totals(ws, base + N - 1 - k) + kMailRingOffset; }
 
 }  // namespace dyspec
