@@ -18,6 +18,7 @@
 #include <cstddef>
 
 #include "draft_row.h"
+#include "helper_rings.h"
 #include "lane_ops.h"
 #include "row_copies.h"
 #include "row_workspace.h"
@@ -26,7 +27,6 @@
 
 namespace dyspec {
 
-constexpr int kRing = 8, kRings = 8;        // places of a ring, rings (helpers) of a tree
 constexpr int kMaxSlots = 2 * DYSPEC_MAX_BUILD_NODES + 2;
 
 // Data-parallel part (the draft softmax of every node, Algorithm 1's model call output):
@@ -293,8 +293,8 @@ constexpr uint32_t kPlace = kNode - kWordAt;                     // a place in a
 struct BuildLds {
     static constexpr uint32_t ring = 0;                                            // places of the root's ring, draw r at r % kRing; with helpers the rings lie behind the nodes
     static constexpr uint32_t state = ring + kRing * kPlace;                       // of every ring (RingState)
-    static constexpr uint32_t here = state + 16 * kRings;                          // bit 8 k: helper k runs
-    static constexpr uint32_t hot = here + 8;                                      // per ring: its node
+    static constexpr uint32_t here = state + 16 * kRings;                          // bit k: helper k runs
+    static constexpr uint32_t hot = here + 4;                                      // per ring: its node
     static constexpr uint32_t from = hot + 4 * kRings;                             // per ring: the rank from which on it may be used
     static constexpr uint32_t claims = from + 4 * kRings;                           // bit k: ring k has a node
     static constexpr uint32_t bound = claims + 4;                                  // bit k: and its helper has been told
@@ -302,7 +302,7 @@ struct BuildLds {
     static constexpr uint32_t n_built = news + 4;
     static constexpr uint32_t fred = n_built + 4;
     static constexpr uint32_t gone = fred + 4 * (kBuildThreads / kWave);          // drawn tokens of the run a wave is drawing from
-    static_assert(state % 16 == 0 && here % 8 == 0, "");
+    static_assert(state % 16 == 0, "");
     static constexpr uint32_t nodes = (gone + kDrawWaves * (kRun / 8) + 15) / 16 * 16;
     __host__ __device__ static constexpr uint32_t row(int widest) { return nodes + kNode * widest; }
 };
@@ -845,7 +845,7 @@ __device__ __attribute__((noinline, aligned(64))) void bring_draws(uint32_t lds_
         count = max(count, (int)now);
         if (!all_here) {
             here |= ballot(first && state == kHere);
-            if (lane == 0) lds_set(lds_at<u64>(lds + BuildLds::here), here);
+            if (lane == 0) lds_set(lds_at<uint32_t>(lds + BuildLds::here), ring_bits(here));
         }
         if (claims != asked) {
             const bool mine = (claims & ~asked) >> k & 1u;
@@ -862,7 +862,7 @@ __device__ __attribute__((noinline, aligned(64))) void bring_draws(uint32_t lds_
                 __hip_atomic_compare_exchange_strong(mail_state(mail), &was, kClaimed | (uint32_t)node << 2, __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             }
             const u64 got = ballot(was == kHere);    // bit 8 k; (a helper that has left meanwhile has not been got)
-            for (uint32_t q = 0; q < kRings; ++q) claimed |= (uint32_t)(got >> (kRing * q) & 1u) << q;
+            claimed |= ring_bits(got);
             if (lane == 0) lds_set(lds_at<uint32_t>(lds + BuildLds::bound), claimed);
             asked = claims;
         }
@@ -1061,8 +1061,8 @@ __device__ __forceinline__ uint32_t ring_for(uint32_t lds_, uint32_t p_, uint32_
         const uint32_t from = uniform(*lds_at<uint32_t>(lds + BuildLds::from + 4 * c)), bound = uniform(lds_now(lds_at<uint32_t>(lds + BuildLds::bound)));
         return rank + 1u >= from && (bound >> c & 1u) ? c + 1u : 0u;
     }
-    const uint32_t c = p == 0 ? 0u : (uint32_t)__builtin_ctz(~(claims | 1u));
-    if (c < kRings && rank < (uint32_t)kMailRanks / 2 && n + kHelpedLeft < N && ((uniform(lds_now(lds_at<u64>(lds + BuildLds::here))) >> (8 * c)) & 1ull)) {
+    const uint32_t c = free_ring(uniform(lds_now(lds_at<uint32_t>(lds + BuildLds::here))), claims, p == 0);
+    if (c < kRings && rank < (uint32_t)kMailRanks / 2 && n + kHelpedLeft < N) {
         const uint32_t from = rank + 1u + (p == 0 ? kRootOwnDraws : kOwnDraws);
         *lds_at<uint32_t>(lds + BuildLds::state + 16 * c + kTakenAt) = from;
         *lds_at<uint32_t>(lds + BuildLds::from + 4 * c) = from;
@@ -1383,7 +1383,7 @@ __global__ __launch_bounds__(kBuildThreads) void build_tree_waves_kernel(
         *lds_at<double>(lds + BuildLds::state) = 1.0;
         *lds_at<uint32_t>(lds + BuildLds::state + 8) = 0u;
         *lds_at<uint32_t>(lds + BuildLds::state + kTakenAt) = 0u;
-        *lds_at<u64>(lds + BuildLds::here) = 0ull;
+        *lds_at<uint32_t>(lds + BuildLds::here) = 0u;
         *lds_at<uint32_t>(lds + BuildLds::claims) = 0u;
         *lds_at<uint32_t>(lds + BuildLds::bound) = 0u;
         *lds_at<uint32_t>(lds + BuildLds::news) = 1u << 31;
