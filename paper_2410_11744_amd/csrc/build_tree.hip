@@ -295,10 +295,9 @@ struct BuildLds {
     static constexpr uint32_t state = ring + kRing * kPlace;                       // of every ring (RingState)
     static constexpr uint32_t here = state + 16 * kRings;                          // bit k: helper k runs
     static constexpr uint32_t hot = here + 4;                                      // per ring: its node
-    static constexpr uint32_t from = hot + 4 * kRings;                             // per ring: the rank from which on it may be used
-    static constexpr uint32_t claims = from + 4 * kRings;                           // bit k: ring k has a node
-    static constexpr uint32_t bound = claims + 4;                                  // bit k: and its helper has been told
-    static constexpr uint32_t news = bound + 4;                                   // new node | popped node << 10 | kRequest if it was asked for another draw
+    static constexpr uint32_t claims = hot + 4 * kRings;                           // bit k: ring k has a node
+    static constexpr uint32_t caught_up = claims + 4;                              // bit k: and its helper has the draws that are taken next
+    static constexpr uint32_t news = caught_up + 4;                                   // new node | popped node << 10 | kRequest if it was asked for another draw
     static constexpr uint32_t n_built = news + 4;
     static constexpr uint32_t fred = n_built + 4;
     static constexpr uint32_t gone = fred + 4 * (kBuildThreads / kWave);          // drawn tokens of the run a wave is drawing from
@@ -638,8 +637,8 @@ __device__ __attribute__((noinline, aligned(64))) void draw_for_nodes(uint32_t l
 // A draw from global memory takes a wave 2.1 us, one from a row in LDS 0.6, and the tree's workgroup has room for the root's
 // row at most.  So a node that is popped kClaimRank times gets a helper, as long as there is one, the root at its first pop: a workgroup
 // that brings the node's row into its LDS, makes the node's draws from rank 0 on (they depend on the row and the path key alone)
-// and leaves them in a ring in memory (row_workspace.h).  Wave 1 of the tree's workgroup brings them to a ring in LDS, and from a rank
-// that the helper has reached by then on (kOwnDraws) control takes the node's draws from there, as it takes the root's where there are no helpers.
+// and leaves them in a ring in memory (row_workspace.h).  Wave 1 of the tree's workgroup brings them to a ring in LDS, and kOwnDraws after the claim, or
+// when the helper has caught up with the node's own wave (helper_rings.h), control takes the node's draws from there, as it takes the root's where there are no helpers.
 //
 // Words in memory, all accesses relaxed and device-scope: the mailbox's state (the helper comes: kHere; wave 1 claims it; one that has
 // waited too long leaves), its other word (wave 1: draws taken, or that the tree is complete), the count of draws that can be read (helper;
@@ -659,7 +658,7 @@ __device__ __attribute__((noinline, aligned(64))) void draw_for_nodes(uint32_t l
 // 1.07.  A claim at the first pop: 0.983 and 1.03, the worst of the former 1.08; at the third 0.989 and 1.00, 1.04.  Told apart by R[y] (below
 // 1/4, 1/8, 1/16 at rank 1): 0.995, the peaked ones no better.
 // kHelpedRows: below, a node has hardly the draws to pay for a row's loading (some 8 us before the first draw is there).
-constexpr int kClaimRank = 1, kOwnDraws = 4, kRootOwnDraws = 2;        // draws the node's own wave makes after the claim
+constexpr int kClaimRank = 1, kOwnDraws = 4, kRootOwnDraws = 2;        // draws the node's own wave makes after the claim, at least
 constexpr int kHelpedRows = 64;             // of the widest tree of a batch that has helpers,
 constexpr int kLeastHelped = 16;            // of any tree of it that has some (a mailbox each in its rows)
 constexpr int kHelpedLeft = 24;             // rows still to be built when a node is worth a helper
@@ -735,7 +734,7 @@ __device__ __attribute__((noinline)) void ship_draws(uint32_t lds_, double* mail
         const int made = (int)uniform(lds_now(lds_at<uint32_t>(lds + HelpLds::made)));
         const u64 words = agent_load(mail_words(mail));
         if (made > shipped) {
-            if (shipped + ((lane - shipped) & (kMailRing - 1)) < made) {
+            if (draw_of_place<kMailRing>(shipped, lane) < made) {
                 const uint32_t place = lds + HelpLds::ring + kHelpPlace * (uint32_t)lane;
                 const double wy = *lds_at<double>(place), W = *lds_at<double>(place + 8);
                 agent_store(ring + 2 * lane, wy / W);
@@ -747,7 +746,7 @@ __device__ __attribute__((noinline)) void ship_draws(uint32_t lds_, double* mail
         }
         const uint32_t taken = uniform((uint32_t)(words >> 32));
         if (taken & kStopped) break;
-        if (lane == 0) lds_set(lds_at<uint32_t>(lds + HelpLds::room), taken + kMailRing);
+        if (lane == 0) lds_set(lds_at<uint32_t>(lds + HelpLds::room), (uint32_t)draws_allowed<kMailRing>((int)taken));
         if (polls == kHelperPolls - 1) {            // (the root's helper, whose tree's workgroup may have no CU yet)
             uint32_t was = kHere;
             if (lane == 0) __hip_atomic_compare_exchange_strong(mail_state(mail), &was, 0u, __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -815,14 +814,14 @@ __device__ __attribute__((noinline, aligned(64))) void bring_draws(uint32_t lds_
     double* const mail = ws_mail(ws, base + k);
     const double* const ring = ws_mail_ring(ws, base, uniform(N_), k);
     const bool first = j == 0;
-    uint32_t asked = 0, claimed = 0;                // rings that have a node, and whose helper has been told
+    uint32_t asked = 0, claimed = 0, ready = 0;     // rings that have a node, whose helper has been told, whose helper has caught up
     u64 here = 0, key = 0;
     int put = -1, told = 0, count = 0;              // the draw last put into the place, what the helper knows to be taken, what it has told of
     while (uniform(lds_now(lds_at<uint32_t>(lds + BuildLds::news))) != kStop) {
         const uint32_t claims = uniform(lds_now(lds_at<uint32_t>(lds + BuildLds::claims)));
         const bool used = claimed >> k & 1u, all_here = here == 0x0101010101010101ull;
         const int taken = used ? (int)lds_now(lds_at<uint32_t>(lds + BuildLds::state + 16 * k + kTakenAt)) : 0;
-        const int rank = taken + ((j - taken) & (kRing - 1));        // the draw this place is for
+        const int rank = draw_of_place<kRing>(taken, j);
         const bool wanted = used && rank > put, get = wanted && rank < count;
         // (all of a look's loads are on their way together)
         const uint32_t state = all_here ? kHere : agent_load(mail_state(mail));
@@ -843,6 +842,10 @@ __device__ __attribute__((noinline, aligned(64))) void bring_draws(uint32_t lds_
             }
         }
         count = max(count, (int)now);
+        if (claimed != ready) {
+            ready |= ring_bits(ballot(used && first && helper_caught_up(count, taken)));
+            if (lane == 0) lds_set(lds_at<uint32_t>(lds + BuildLds::caught_up), ready);
+        }
         if (!all_here) {
             here |= ballot(first && state == kHere);
             if (lane == 0) lds_set(lds_at<uint32_t>(lds + BuildLds::here), ring_bits(here));
@@ -863,7 +866,6 @@ __device__ __attribute__((noinline, aligned(64))) void bring_draws(uint32_t lds_
             }
             const u64 got = ballot(was == kHere);    // bit 8 k; (a helper that has left meanwhile has not been got)
             claimed |= ring_bits(got);
-            if (lane == 0) lds_set(lds_at<uint32_t>(lds + BuildLds::bound), claimed);
             asked = claims;
         }
         if (used && first && taken > told) {
@@ -1057,15 +1059,15 @@ __device__ __forceinline__ uint32_t ring_for(uint32_t lds_, uint32_t p_, uint32_
     const uint32_t lane = threadIdx.x & 63, claims = uniform(*lds_at<uint32_t>(lds + BuildLds::claims));
     const u64 has = ballot(*lds_at<uint32_t>(lds + BuildLds::hot + 4 * (lane % kRings)) == p) & claims & ((1u << kRings) - 1u);
     if (has) {
-        const uint32_t c = (uint32_t)__builtin_ctzll(has);
-        const uint32_t from = uniform(*lds_at<uint32_t>(lds + BuildLds::from + 4 * c)), bound = uniform(lds_now(lds_at<uint32_t>(lds + BuildLds::bound)));
-        return rank + 1u >= from && (bound >> c & 1u) ? c + 1u : 0u;
+        const uint32_t c = (uint32_t)__builtin_ctzll(has), taken_at = lds + BuildLds::state + 16 * c + kTakenAt;
+        const uint32_t caught_up = uniform(lds_now(lds_at<uint32_t>(lds + BuildLds::caught_up)));
+        const HandOver h = hand_over(rank, uniform(*lds_at<uint32_t>(taken_at)), caught_up >> c & 1u);
+        if (h == kOwnDrawAndLater) lds_set(lds_at<uint32_t>(taken_at), rank + 2u);
+        return h == kFromRing ? c + 1u : 0u;
     }
     const uint32_t c = free_ring(uniform(lds_now(lds_at<uint32_t>(lds + BuildLds::here))), claims, p == 0);
-    if (c < kRings && rank < (uint32_t)kMailRanks / 2 && n + kHelpedLeft < N) {
-        const uint32_t from = rank + 1u + (p == 0 ? kRootOwnDraws : kOwnDraws);
-        *lds_at<uint32_t>(lds + BuildLds::state + 16 * c + kTakenAt) = from;
-        *lds_at<uint32_t>(lds + BuildLds::from + 4 * c) = from;
+    if (c < kRings && n + kHelpedLeft < N) {
+        *lds_at<uint32_t>(lds + BuildLds::state + 16 * c + kTakenAt) = rank + 1u + (p == 0 ? kRootOwnDraws : kOwnDraws);
         *lds_at<uint32_t>(lds + BuildLds::hot + 4 * c) = p;
         lds_set(lds_at<uint32_t>(lds + BuildLds::claims), claims | 1u << c);
     }
@@ -1385,7 +1387,7 @@ __global__ __launch_bounds__(kBuildThreads) void build_tree_waves_kernel(
         *lds_at<uint32_t>(lds + BuildLds::state + kTakenAt) = 0u;
         *lds_at<uint32_t>(lds + BuildLds::here) = 0u;
         *lds_at<uint32_t>(lds + BuildLds::claims) = 0u;
-        *lds_at<uint32_t>(lds + BuildLds::bound) = 0u;
+        *lds_at<uint32_t>(lds + BuildLds::caught_up) = 0u;
         *lds_at<uint32_t>(lds + BuildLds::news) = 1u << 31;
     }
     double m = 0.0;

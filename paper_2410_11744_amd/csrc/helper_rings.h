@@ -23,4 +23,22 @@ __host__ __device__ __forceinline__ unsigned free_ring(unsigned here, unsigned c
     return open ? (unsigned)__builtin_ctz(open) : (unsigned)kRings;
 }
 
+// A helper begins at rank 0 when it comes, the node's own wave goes on meanwhile.  So control takes draws from the ring only when
+// the helper has made the one that is taken next; until then every pop asks the own wave for the next draw, and moves `taken` behind it.
+// (A claim at rank 200 that moved the node to its ring four draws later made control wait for a helper that had 200 to make.)
+__host__ __device__ __forceinline__ bool helper_caught_up(int draws_told, int taken) { return draws_told > taken; }
+enum HandOver { kOwnDraw, kOwnDrawAndLater, kFromRing };
+// The node's draw of that rank is popped: the next one, rank + 1, is the own wave's (kOwnDrawAndLater: and `taken` is to be rank + 2), or the ring's.
+__host__ __device__ __forceinline__ HandOver hand_over(unsigned rank, unsigned taken, bool caught_up)
+{
+    return rank + 1u < taken ? kOwnDraw : caught_up ? kFromRing : kOwnDrawAndLater;
+}
+
+// Place j of a ring of SIZE: the draw that it is for when `first` is the lowest one of use.
+template <int SIZE>
+__host__ __device__ __forceinline__ int draw_of_place(int first, int j) { return first + ((j - first) & (SIZE - 1)); }
+// The helper may make draws below this: so none that is still of use is written over, in its LDS or in memory.
+template <int SIZE>
+__host__ __device__ __forceinline__ int draws_allowed(int taken) { return taken + SIZE; }
+
 }  // namespace dyspec

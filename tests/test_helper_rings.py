@@ -17,3 +17,9 @@ def check(tmp_path_factory):
 def test_a_helper_that_runs_is_used_whatever_the_others_do(check):
     r = subprocess.run([check, "free"], capture_output=True, text=True, timeout=60)
     assert r.returncode == 0, r.stdout
+
+
+@pytest.mark.parametrize("seed", [1, 100001])
+def test_a_nodes_draws_come_in_order_and_without_long_waits(check, seed):
+    r = subprocess.run([check, "draws", "300", str(seed)], capture_output=True, text=True, timeout=110)
+    assert r.returncode == 0, r.stdout
