@@ -131,8 +131,11 @@ dyspec_status dyspec_init(void);
  *                 rows at once before the serial expansion, and the tokens drawn from
  *                 the row so far; a draw then touches one run of the parent's row.
  *                 NULL or fewer bytes: the expansion makes a pass over the parent's whole
- *                 row at every draw instead (same arithmetic, same tree, several times
- *                 slower).
+ *                 row at every draw instead (several times slower; the same tree, unless a
+ *                 decision is closer than the rounding of the row's fp64 sums, about 1e-13:
+ *                 children with equal logits can be that close).
+ * A call builds the same tree every time.  (Some trees get more workgroups than one while others
+ * do not; which of them makes a draw does not show in it.)
  * vocab <= DYSPEC_MAX_VOCAB, N <= DYSPEC_MAX_BUILD_NODES (DYSPEC_BAD_SHAPE beyond).
  */
 dyspec_status dyspec_build_tree(const float* draft_logits, int32_t vocab,

@@ -247,7 +247,7 @@ __global__ __launch_bounds__(kBlock) void build_tree_kernel(
 // of a wave take effect in their order, so data written before a word are there for whoever has read the word.
 //
 // Every wait ends: control waits only for a requested draw, which the node's wave makes in finitely
-// many steps whatever else happens (an empty row is an answer as well); the drawing waves leave when
+// many steps whatever else happens (an empty row is an answer as well), or the node's helper, once it runs; the drawing waves leave when
 // control has set `news` to kStop, which it does after at most N - 1 pops.  (Were an answer to stay out all the
 // same, control gives up after kBuildPolls looks: the tree ends there, and n_built says so.)
 //
@@ -259,7 +259,7 @@ __global__ __launch_bounds__(kBlock) void build_tree_kernel(
 // 32000 tokens 1378 -> 508 us (with eight drawing waves on two SIMDs 562, on all four 543: a request waits for the draw its
 // wave is at), 128 rows 346 -> 134, 32 rows of 1000 tokens 92 -> 55; a single chain of 512 nodes 1413 -> 1130.  (All before
 // the sorted list of slots, see pop_nodes.)  Of one size the time depends on the table, that is, on how often nodes
-// are popped again: 200 to 333 us over tables of 512 rows of independent normal logits (before there were helpers, below, 470 to 960).
+// are popped again: 178 to 349 us over tables of 512 rows of independent normal logits (before there were helpers, below, 470 to 960).
 constexpr int kBuildThreads = 1024;
 constexpr int kDrawWaves = kBuildThreads / kWave - 2;
 static_assert(kRing * kRings == kWave, "a lane for every place");
@@ -634,30 +634,37 @@ __device__ __attribute__((noinline, aligned(64))) void draw_for_nodes(uint32_t l
 
 // ---- Helpers: workgroups on CUs of their own, each for one node that is drawn from again and again.
 //
-// A draw from global memory takes a wave 2.1 us, one from a row in LDS 0.6, and the tree's workgroup has room for the root's
-// row at most.  So a node that is popped kClaimRank times gets a helper, as long as there is one, the root at its first pop: a workgroup
-// that brings the node's row into its LDS, makes the node's draws from rank 0 on (they depend on the row and the path key alone)
-// and leaves them in a ring in memory (row_workspace.h).  Wave 1 of the tree's workgroup brings them to a ring in LDS, and kOwnDraws after the claim, or
-// when the helper has caught up with the node's own wave (helper_rings.h), control takes the node's draws from there, as it takes the root's where there are no helpers.
+// Rules.  A batch has helpers if its widest tree has kHelpedRows rows and kRings more workgroups a sequence leave each a CU of its own
+// (kHelpedBlocks), a tree of it from kLeastHelped rows on.  The root gets the first helper when it is popped, another node one from its pop
+// of rank kClaimRank on, while more than kHelpedLeft rows are to be built and a helper runs that no node has (free_ring).  kOwnDraws after
+// the claim at the earliest, and once the helper has caught up with the node's own wave (hand_over), the node's draws come from the helper.
+//
+// A draw from global memory takes a wave 2.1 us, one from a row in LDS 0.67, and the tree's workgroup has room for the root's row at most.
+// A helper brings the node's row into its LDS, makes the node's draws from rank 0 on (they depend on the row and the path key
+// alone) and leaves them in a ring in memory (row_workspace.h); wave 1 of the tree's workgroup brings them to a ring in LDS (helper_rings.h).
+// When a helper takes over depends on the clock; a draw has the same bits whoever makes it (run_draw.h).
 //
 // Words in memory, all accesses relaxed and device-scope: the mailbox's state (the helper comes: kHere; wave 1 claims it; one that has
 // waited too long leaves), its other word (wave 1: draws taken, or that the tree is complete), the count of draws that can be read (helper;
-// written when they are there).  A helper waits for a claim, for room in the ring, and for the end, each a bounded number of looks.
-// Only a helper that is there is claimed: nobody waits for a workgroup that has no CU, and a tree without its helpers is built by its own waves.
-// At which rank a helper takes over depends on the clock; a draw has the same bits whoever makes it (run_draw.h).
+// written when they are there).  Waits: for a claim a helper looks a bounded number of times.  Once it is claimed it stays until wave 1 says that the
+// tree is complete, which it does when control ends, after a bounded number of looks of its own (kBuildPolls).  Only a helper that runs is
+// claimed: nobody waits for a workgroup that has no CU, and a tree without its helpers is built by its own waves.
 //
-// Measured, with the pass over the rows, 512 rows of 32000 tokens, four tables, without helpers, with them and with their draws popped
+// Measured, with the pass over the rows: 512 rows of 32000 tokens, four tables, without helpers, with them and with their draws popped
 // many at a time (pop_nodes): 961, 470, 582, 553 -> 334, 320, 332, 319 -> 332, 201, 225, 211 us; all draws from
-// the root 381 -> 360, from another node 1091 -> 371; 1024 rows of 32768 tokens 1876 -> 597 -> 550 (the root's row never fitted there), 64 rows
-// 124 -> 80, 128 rows 222, 134, 177 -> 128, 110, 123 -> 118, 88, 107; a chain 559 -> 554 -> 550.  What is left is, where one
-// node has all the draws, its helper's draw, 0.63 us, and where slots of single draws come between, their pop, 0.5 us.
-// (These with a claim at rank 3 and eight more draws of the node's own wave.)
-// kClaimRank, kOwnDraws: at the node's second pop and four draws, as a helper has its first draw 8 us after it is told: those four tables 329, 179, 198,
+// the root 381 -> 360, from another node 1091 -> 371; 1024 rows of 32768 tokens 1876 -> 597 -> 550, 64 rows 124 -> 80, 128 rows
+// 222, 134, 177 -> 128, 110, 123 -> 118, 88, 107.  (These with a claim at rank 3, eight more draws of the node's own wave, and draws of 0.63 us
+// that had other bits than the own wave's.)  Now, three tables of 512 rows 349, 178, 205 us, two of 128 rows 117 and 81, all draws from
+// one node 390, 1024 rows of 32768 tokens 580.  What is left is, where one node has all the draws, its helper's draw, and where slots of
+// single draws come between, their pop, 0.5 us.
+// kClaimRank, kOwnDraws: at the node's second pop and four draws, as a helper has its first draw 8 us after it is told: the four tables 329, 179, 198,
 // 209 us, 128 rows 111, 83, 86.  Of 190 shapes of 64 to 512 rows (1000 to 32000 tokens, deviation 2 and 3, Zipf) the times are 0.985 of those
 // with rank 3 and eight draws, the best 0.83, the worst 1.03; peaked rows (deviation 10), whose nodes are hardly popped three times, 1.01, the worst
 // 1.07.  A claim at the first pop: 0.983 and 1.03, the worst of the former 1.08; at the third 0.989 and 1.00, 1.04.  Told apart by R[y] (below
 // 1/4, 1/8, 1/16 at rank 1): 0.995, the peaked ones no better.
 // kHelpedRows: below, a node has hardly the draws to pay for a row's loading (some 8 us before the first draw is there).
+// kHelpedBlocks: 28 sequences of 64 rows hold 252 CUs.  Such a call takes 145 us by itself (197 without helpers), beside another like it 223 for both (219),
+// beside four verifications of 512 rows on another stream 253 (216); 28 sequences of 200 rows 330 (545), 577 for two (638), 417 (566).
 constexpr int kClaimRank = 1, kOwnDraws = 4, kRootOwnDraws = 2;        // draws the node's own wave makes after the claim, at least
 constexpr int kHelpedRows = 64;             // of the widest tree of a batch that has helpers,
 constexpr int kLeastHelped = 16;            // of any tree of it that has some (a mailbox each in its rows)
@@ -1457,8 +1464,8 @@ __global__ __launch_bounds__(kBuildThreads) void build_tree_waves_kernel(
     if (tid == 0) n_built[seq] = ended < 0 ? -1 : n;
 }
 
-// The root's row is kept in LDS where it fits beside the node state (32000 tokens: up to 556 rows,
-// 32768: up to 489) and is drawn from often enough to pay for its loading (2 rows of 32000 tokens 26.0 us with it, 17.9
+// The root's row is kept in LDS in batches without helpers, where it fits beside the node state (32000 tokens: up to 564 rows,
+// 32768: up to 498) and is drawn from often enough to pay for its loading (2 rows of 32000 tokens 26.0 us with it, 17.9
 // without; 8 rows 30.3 and 30.0; 16 rows 35.8 and 45.5); else the root's draws are made like every other node's.
 constexpr int kRingRows = 10;
 static size_t build_lds_bytes(int V, int widest, bool root_ring) { return BuildLds::row(widest) + (root_ring ? row_lds_bytes(V) : 0); }
