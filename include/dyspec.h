@@ -134,8 +134,9 @@ dyspec_status dyspec_init(void);
  *                 row at every draw instead (several times slower; the same tree, unless a
  *                 decision is closer than the rounding of the row's fp64 sums, about 1e-13:
  *                 children with equal logits can be that close).
- * A call builds the same tree every time.  (Some trees get more workgroups than one while others
- * do not; which of them makes a draw does not show in it.)
+ * A call builds the same tree every time, whatever runs beside it.  In other batches (of more
+ * sequences, or with a wider tree) the root's row may be summed in another order: the same tree
+ * but for decisions that close.
  * vocab <= DYSPEC_MAX_VOCAB, N <= DYSPEC_MAX_BUILD_NODES (DYSPEC_BAD_SHAPE beyond).
  */
 dyspec_status dyspec_build_tree(const float* draft_logits, int32_t vocab,

@@ -1,8 +1,8 @@
 """A node's draws have the same bits whoever makes them: a tree must not depend on when its helpers (csrc/build_tree.hip) came.
 
 Tables rounded to bf16 are full of children of one node with equal logits, whose slots are equal but for the roundings of the sums
-behind them.  The same sequence in a batch of 29 has no helpers; where the root's row does not fit beside the tree's state in LDS,
-all its draws are made from memory, by the sums that helpers have to make as well."""
+behind them.  The same sequence in a batch of 29 has no helpers; where the root's row does not fit beside the tree's state in LDS
+(499 rows of 32768 tokens and more), all its draws are made from memory, by the sums that helpers have to make as well."""
 import pytest
 
 pytestmark = pytest.mark.gpu
